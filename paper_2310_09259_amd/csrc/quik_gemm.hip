@@ -564,306 +564,6 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_kernel(GemmArgs a) {
         }
 }
 
-// Small-T variant (T <= 32*TM): the layer is bound by streaming the packed weights, not by the
-// matrix cores, so the point is many bytes in flight per CU.  A workgroup owns a (32*TM) x (32*TN)
-// output tile and its four waves split K: every wave streams its own quarter of the weight rows
-// (and of the activations) through a private global->LDS ring, with no workgroup barrier in the main
-// loop (a wave waits only for its own DMA).  The four partial INT32 accumulators are summed exactly
-// through LDS; wave 0 then dequantizes, adds the fp16 outlier product (operands read straight from
-// global memory: they are tiny) and stores.
-template <int BITS, int TM, int TN, int BKB, int NST, int MODE>
-__global__ __launch_bounds__(256) void gemm_skinny(GemmArgs a) {
-    constexpr bool RAW = MODE != 0;
-    constexpr bool ASYM = (BITS == 4) && (MODE != 1);
-    constexpr int CPR = BKB / 16, RPI = 64 / CPR;        // 16-byte pieces per stage row, rows per DMA instr
-    constexpr int BM = 32 * TM, BN = 32 * TN;
-    constexpr int A_INSTR = BM / RPI, B_INSTR = BN / RPI; // per wave (each wave loads its own tiles)
-    constexpr int LPS = A_INSTR + B_INSTR;
-    constexpr int KSUB = BKB / 32;
-    constexpr int SHIFT = (BITS == 4) ? (ASYM ? 4 : 8) : 0;
-    constexpr int A_BYTES = BM * BKB, B_BYTES = BN * BKB, ST_BYTES = A_BYTES + B_BYTES;
-    constexpr int NF = TM + TN;
-    constexpr int HALVES = (BITS == 4) ? 2 : 1;
-    constexpr int RING = NST * ST_BYTES;                  // per wave
-    constexpr int RED_BYTES = 2 * TM * TN * 16 * 64 * 4;  // one wave's INT32 accumulators + fp32 outlier partials
-    constexpr int LDS_BYTES = (4 * RING > 3 * RED_BYTES) ? 4 * RING : 3 * RED_BYTES;
-    static_assert((NST - 1) * LPS < 64, "vmcnt range");
-
-    __shared__ __align__(1024) uint8_t lds[LDS_BYTES];
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l32 = lane & 31, g = lane >> 5;
-
-    const int tiles_m = (a.T + BM - 1) / BM;
-    const int t0 = (blockIdx.x % tiles_m) * BM, n0 = (blockIdx.x / tiles_m) * BN;
-
-    const int row_bytes = a.K_b * BITS / 8;
-    const int int_bytes = (row_bytes + 15) & ~15;      // up to the 16-byte piece that holds the last packed byte
-    const int nk = a.fp_only ? 0 : (row_bytes + BKB - 1) / BKB;
-    // this wave's K range, in stages
-    const int s_begin = (int)((long)nk * wave / 4), s_end = (int)((long)nk * (wave + 1) / 4);
-
-    const v4i rA = make_rsrc((const uint8_t*)a.xq + (size_t)t0 * a.ldq, (size_t)(a.T - t0) * a.ldq);
-    const v4i rB = make_rsrc((const uint8_t*)a.w_q + (size_t)n0 * a.ldw, (size_t)(a.N - n0) * a.ldw);
-
-    uint8_t* ring = lds + wave * RING;
-    const uint32_t ring_addr = lds_addr(ring);
-    const int lrow = lane / CPR, lslot = lane % CPR;
-
-    auto issue = [&](int s) {            // stage s of this wave's range (or beyond: all lanes out of range)
-        const uint32_t sb = (uint32_t)((s - s_begin) % NST) * ST_BYTES;
-        const int koff = s * BKB;
-        const bool live = s < s_end;
-#pragma unroll
-        for (int i = 0; i < A_INSTR; ++i) {
-            int row = i * RPI + lrow;
-            int c = (lslot ^ swz<BKB>(row)) * 16;
-            uint32_t vo = (live && koff + c < int_bytes) ? (uint32_t)(row * a.ldq + koff + c) : kOob;
-            dma16(rA, ring_addr + sb + i * 1024, vo, 0);
-        }
-#pragma unroll
-        for (int i = 0; i < B_INSTR; ++i) {
-            int row = i * RPI + lrow;
-            int c = (lslot ^ swz<BKB>(row)) * 16;
-            uint32_t vo = (live && koff + c < int_bytes) ? (uint32_t)(row * a.ldw + koff + c) : kOob;
-            dma16(rB, ring_addr + sb + A_BYTES + i * 1024, vo, 0);
-        }
-    };
-
-    uint32_t rd[NF][KSUB];
-#pragma unroll
-    for (int f = 0; f < NF; ++f) {
-        int r = (f < TM) ? (f * 32 + l32) : ((f - TM) * 32 + l32);
-        uint32_t base = (f < TM ? 0 : A_BYTES) + r * BKB;
-#pragma unroll
-        for (int ks = 0; ks < KSUB; ++ks) rd[f][ks] = base + (((ks * 2 + g) ^ swz<BKB>(r)) << 4);
-    }
-
-    v16i acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
-
-    // ---- everything the epilogue needs is requested before the weight stream starts, so none of it
-    // is waited for at the end: per-row parameters (to LDS), per-column parameters and this wave's
-    // share of the fp16 outlier operands (registers).  The outlier product is split over the four
-    // waves like K: wave w takes every fourth 16-column step.
-    constexpr int PF = 4;                                 // prefetched outlier steps per wave (n_out <= 256)
-    __shared__ float prm_sa[BM], prm_sh[BM];
-    __shared__ int prm_ct[BM];
-    float c_sw[TN], c_wr[TN], c_bv[TN];
-    int c_nc[TN];
-    uint4 pfa[PF][TM], pfb[PF][TN];
-    const int fsteps = (a.n_out + 15) >> 4;               // 16-column steps of the outlier product
-    if constexpr (!RAW) {
-        if (tid < BM) {
-            const int t = t0 + tid;
-            const bool ok = t < a.T;
-            const float sc = ok ? a.scale[t] : 0.0f;
-            prm_sa[tid] = sc;
-            prm_sh[tid] = (ok ? a.zero[t] : 0.0f) + (float)(1 << (BITS - 1)) * sc;
-            int cs = 0;
-            if constexpr (ASYM) cs = (ok && !a.fp_only) ? a.code_sum[t] : 0;
-            prm_ct[tid] = -(1 << SHIFT) * 8 * cs;
-        }
-        const __half* __restrict__ wsc = static_cast<const __half*>(a.w_scale);
-        const __half* __restrict__ bias = static_cast<const __half*>(a.bias);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int n = min(n0 + j * 32 + l32, a.N - 1);
-            c_sw[j] = __half2float(wsc[n]) * (1.0f / (float)(1 << SHIFT));
-            c_wr[j] = a.w_reduced[n];
-            c_bv[j] = bias ? __half2float(bias[n]) : 0.0f;
-            c_nc[j] = 0;
-            if constexpr (ASYM) c_nc[j] = a.fp_only ? 0 : -(1 << SHIFT) * 8 * a.w_code_sum[n];
-            if (a.fp_only) { c_sw[j] = 0.0f; c_wr[j] = 0.0f; c_bv[j] = 0.0f; }
-        }
-        const __half* __restrict__ xo = static_cast<const __half*>(a.x_out);
-        const __half* __restrict__ wo = static_cast<const __half*>(a.w_out);
-#pragma unroll
-        for (int q = 0; q < PF; ++q) {
-            const int kk = (wave + 4 * q) * 16 + g * 8;   // first of this lane's 8 outlier columns
-            const bool live = (wave + 4 * q) < fsteps && kk < a.n_out;
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                const int t = min(t0 + i * 32 + l32, a.T - 1);
-                pfa[q][i] = live ? *reinterpret_cast<const uint4*>(xo + (size_t)t * a.ldo + kk) : make_uint4(0, 0, 0, 0);
-            }
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int n = min(n0 + j * 32 + l32, a.N - 1);
-                pfb[q][j] = live ? *reinterpret_cast<const uint4*>(wo + (size_t)n * a.ldwo + kk) : make_uint4(0, 0, 0, 0);
-            }
-        }
-    }
-
-#pragma unroll
-    for (int s = 0; s < NST - 1; ++s) issue(s_begin + s);
-
-    for (int s = s_begin; s < s_end; ++s) {
-        issue(s + NST - 1);
-        wait_vm<(NST - 1) * LPS>();                       // stage s has landed (this wave's own loads)
-        const uint8_t* st = ring + ((s - s_begin) % NST) * ST_BYTES;
-#pragma unroll
-        for (int ks = 0; ks < KSUB; ++ks) {
-            v4i ua[TM][HALVES], ub[TN][HALVES];
-#pragma unroll
-            for (int f = 0; f < NF; ++f) {
-                const uint4 w = *reinterpret_cast<const uint4*>(st + rd[f][ks]);
-                v4i* u = (f < TM) ? ua[f] : ub[f - TM];
-                if constexpr (BITS == 4) {
-                    // register slots 0/2 hold the even k of a word, slots 1/3 the odd k
-                    constexpr uint32_t M = 0xF0F0F0F0u;
-                    auto hi = [](uint32_t x) { return (int)(x & M); };
-                    auto lo = [](uint32_t x) {
-                        return ASYM ? (int)((x ^ 0x08080808u) & 0x0F0F0F0Fu) : (int)((x << 4) & M);
-                    };
-                    if (f < TM) {                         // activations: even k in the high nibble
-                        u[0] = v4i{hi(w.x), lo(w.x), hi(w.y), lo(w.y)};
-                        u[1] = v4i{hi(w.z), lo(w.z), hi(w.w), lo(w.w)};
-                    } else {                              // weights: even k in the low nibble
-                        u[0] = v4i{lo(w.x), hi(w.x), lo(w.y), hi(w.y)};
-                        u[1] = v4i{lo(w.z), hi(w.z), lo(w.w), hi(w.w)};
-                    }
-                } else {
-                    u[0] = v4i{(int)w.x, (int)w.y, (int)w.z, (int)w.w};
-                }
-            }
-#pragma unroll
-            for (int h = 0; h < HALVES; ++h)
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ua[i][h], ub[j][h], acc[i][j], 0, 0, 0);
-        }
-        // the buffer read here is refilled NST-1 iterations later by this same wave: LDS reads above
-        // have returned (their data fed the MFMAs) before that DMA is issued
-    }
-    wait_vm<0>();
-
-    // ---- this wave's share of the fp16 outlier product, on fresh fp32 accumulators
-    v16f cf[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) cf[i][j][r] = 0.0f;
-    if constexpr (!RAW) {
-#pragma unroll
-        for (int q = 0; q < PF; ++q)
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    cf[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, pfa[q][i]),
-                                                                     __builtin_bit_cast(v8h, pfb[q][j]), cf[i][j], 0, 0, 0);
-        // more than 16 * 4 * PF outlier columns: the rest straight from memory
-        const __half* __restrict__ xo = static_cast<const __half*>(a.x_out);
-        const __half* __restrict__ wo = static_cast<const __half*>(a.w_out);
-        for (int st = wave + 4 * PF; st < fsteps; st += 4) {
-            const int kk = st * 16 + g * 8;
-            v8h fa[TM], fb[TN];
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                const int t = min(t0 + i * 32 + l32, a.T - 1);
-                const uint4 w = (kk < a.n_out) ? *reinterpret_cast<const uint4*>(xo + (size_t)t * a.ldo + kk) : make_uint4(0, 0, 0, 0);
-                fa[i] = __builtin_bit_cast(v8h, w);
-            }
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int n = min(n0 + j * 32 + l32, a.N - 1);
-                const uint4 w = (kk < a.n_out) ? *reinterpret_cast<const uint4*>(wo + (size_t)n * a.ldwo + kk) : make_uint4(0, 0, 0, 0);
-                fb[j] = __builtin_bit_cast(v8h, w);
-            }
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    cf[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[i], fb[j], cf[i][j], 0, 0, 0);
-        }
-    }
-    __syncthreads();                                      // rings are dead: reuse LDS for the reduction
-
-    // ---- sum the four partial results: waves 1..3 publish, wave 0 adds (INT32 exactly; the fp32
-    // outlier partials in wave order)
-    int* red = reinterpret_cast<int*>(lds);
-    float* redf = reinterpret_cast<float*>(lds) + 3 * TM * TN * 16 * 64;
-    if (wave > 0) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int slot = (((wave - 1) * TM * TN + i * TN + j) * 16 + r) * 64 + lane;
-                    red[slot] = acc[i][j][r];
-                    if constexpr (!RAW) redf[slot] = cf[i][j][r];
-                }
-    }
-    __syncthreads();
-    if (wave > 0) return;
-#pragma unroll
-    for (int w = 0; w < 3; ++w)
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int slot = ((w * TM * TN + i * TN + j) * 16 + r) * 64 + lane;
-                    acc[i][j][r] += red[slot];
-                    if constexpr (!RAW) cf[i][j][r] += redf[slot];
-                }
-
-    if constexpr (RAW) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                int n = n0 + j * 32 + l32;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    int t = t0 + i * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
-                    if (t < a.T && n < a.N) {
-                        int v = acc[i][j][r] >> SHIFT;
-                        if constexpr (ASYM) v -= 8 * (a.code_sum[t] + a.w_code_sum[n]);
-                        a.acc[(size_t)t * a.ldacc + n] = v;
-                    }
-                }
-            }
-        return;
-    } else {
-        // ---- epilogue on wave 0: dequantize (as in gemm_kernel), add the outlier product, store
-        __half* __restrict__ y = static_cast<__half*>(a.y);
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int n = n0 + j * 32 + l32;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int lr = i * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
-                    const int t = t0 + lr;
-                    int ai = acc[i][j][r];
-                    if constexpr (ASYM) ai = ai + prm_ct[lr] + c_nc[j];
-                    const float v = __builtin_fmaf((float)ai, prm_sa[lr] * c_sw[j], __builtin_fmaf(prm_sh[lr], c_wr[j], c_bv[j])) +
-                                    cf[i][j][r];
-                    if (t < a.T && n < a.N) {
-                        if (a.fp_only) reinterpret_cast<float*>(a.y)[(size_t)t * a.ldy + n] = v;
-                        else y[(size_t)t * a.ldy + n] = __float2half(v);
-                    }
-                }
-            }
-    }
-}
-
-
 template <int BITS, int WBITS, int BM, int BN, int WM, int WN, int BKB, int NST, int OCC, int GM, int MODE>
 hipError_t launch_cfg(const GemmArgs& a, hipStream_t stream) {
     int tiles = ((a.T + BM - 1) / BM) * ((a.N + BN - 1) / BN);
@@ -872,21 +572,10 @@ hipError_t launch_cfg(const GemmArgs& a, hipStream_t stream) {
     return hipGetLastError();
 }
 
-template <int BITS, int TM, int TN, int BKB, int NST, int MODE>
-hipError_t launch_skinny(const GemmArgs& a, hipStream_t stream) {
-    int tiles = ((a.T + 32 * TM - 1) / (32 * TM)) * ((a.N + 32 * TN - 1) / (32 * TN));
-    hipLaunchKernelGGL((gemm_skinny<BITS, TM, TN, BKB, NST, MODE>), dim3(tiles), dim3(256), 0, stream, a);
-    return hipGetLastError();
-}
-
 template <int BITS, int WBITS, int MODE>
 hipError_t dispatch(const GemmArgs& a, hipStream_t stream) {
-    // Few tokens: weight streaming dominates.  Up to 32 tokens the K-split kernel (same operand
-    // widths only); up to 128 tokens small tiles with a deeper stage ring so that enough workgroups
-    // and bytes are in flight.
-    if constexpr (BITS == WBITS) {
-        if (a.T <= 32) return launch_skinny<BITS, 1, 1, 128, 2, MODE>(a, stream);
-    }
+    // Few tokens: weight streaming dominates.  Up to 128 tokens small tiles with a deeper stage ring so that
+    // enough workgroups and bytes are in flight.
     if (a.T <= 64) return launch_cfg<BITS, WBITS, 64, 64, 2, 2, 128, 4, 2, 0, MODE>(a, stream);
     if (a.T <= 128) return launch_cfg<BITS, WBITS, 128, 64, 2, 2, 128, 2, 2, 0, MODE>(a, stream);
     // 128-byte stage rows (a full cache line per row per stage), two stage buffers.
@@ -993,15 +682,17 @@ int choose_gemm_stream(int T, int N, int K_b, int cus, StreamPlan* plan) {
     const long tiles = (long)plan->tiles_m * plan->tn;
     const long r = (tiles + cus - 1) / cus;
     const double blocks = (double)(r * plan->base + (r * plan->rem + plan->tn - 1) / plan->tn);
-    return (K_b >= 2048 && plan->base >= 5 && 0.94 * blocks <= tiles_estimate(T, N, cus)) ? 1 : 2;
+    return (T > kRowsTokens && K_b >= 2048 && plan->base >= 5 && 0.94 * blocks <= tiles_estimate(T, N, cus)) ? 1 : 2;
 }
 
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t stream) {
-    if (a.bits == 4 && !a.fp_only && g_gemm_path != 2) {
+    const int cus = compute_units(), path = g_gemm_path;
+    if (a.bits == 4 && !a.fp_only && (path == 1 || (path == 0 && a.T > kRowsTokens))) {
         StreamPlan plan;
-        const int c = choose_gemm_stream(a.T, a.N, a.K_b, compute_units(), &plan);
-        if (c == 1 || (c == 2 && g_gemm_path == 1)) return launch_gemm_stream(a, plan, stream);
+        const int c = choose_gemm_stream(a.T, a.N, a.K_b, cus, &plan);
+        if (c == 1 || (c == 2 && path == 1)) return launch_gemm_stream(a, plan, stream);
     }
+    if (a.T <= kRowsTokens) return launch_gemm_rows(a, cus, stream);
     return launch_gemm_tiles(a, stream);
 }
 

@@ -52,6 +52,14 @@ __device__ __forceinline__ void dma16(v4i rsrc, uint32_t lds_base, uint32_t voff
                  : "s"(lds_base), "v"(voff), "s"(rsrc), "s"(soff)
                  : "memory", "m0");
 }
+// dma16 for data that is read once (weights of a few-token layer): non-temporal, so that its lines do not
+// displace what is read again
+__device__ __forceinline__ void dma16_once(v4i rsrc, uint32_t lds_base, uint32_t voff) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds"
+                 :
+                 : "s"(lds_base), "v"(voff), "s"(rsrc)
+                 : "memory", "m0");
+}
 __device__ __forceinline__ uint32_t lds_addr(const void* p) { return (uint32_t)(uintptr_t)(lds_ptr)(p); }
 
 // XOR swizzle of the 16-byte slot index inside a stage row of BKB bytes.

@@ -182,6 +182,9 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t stream);
 hipError_t launch_gemm_tiles(const GemmArgs& a, hipStream_t stream);
 // equal operand widths, 256 x 128 tiles: the per-tile kernel on 16 x 16 matrix instructions (quik_gemm_tiles16.hip)
 hipError_t launch_gemm_tiles16(const GemmArgs& a, hipStream_t stream);
+// T <= kRowsTokens, any operand widths: weights streamed into registers, waves split K (quik_gemm_rows.hip)
+constexpr int kRowsTokens = 32;
+hipError_t launch_gemm_rows(const GemmArgs& a, int cus, hipStream_t stream);
 hipError_t launch_weight_reduce(const WeightReduceArgs& a, hipStream_t stream);
 bool plan_gemm_stream(int T, int N, int K_b, int cus, StreamPlan* p);
 int choose_gemm_stream(int T, int N, int K_b, int cus, StreamPlan* p);   // 0 cannot, 1 chosen, 2 possible but not chosen

@@ -1,0 +1,42 @@
+"""The few-token GEMM (T <= 32) at the edges of its dispatch and tiles, against the oracle: INT32 accumulators
+bit-exact, fp16 output within 5e-3 (run with -m gpu on an MI355X)."""
+import numpy as np
+import pytest
+
+from paper_2310_09259_amd import synth
+from tests.util import output_within_tolerance, to_dev, upload
+
+pytestmark = pytest.mark.gpu
+
+# N, K, n_out.  With 256 compute units: one 16-channel block per CU at most (four waves; eight where a row has
+# sixteen 128-byte lines), pairs of blocks just above that, single blocks where pairs would leave the busiest CU
+# with more; a last line with one 16-byte piece, none and a short fp16 part, ragged N.
+SHAPES = [
+    (37, 264, 0), (200, 4384, 288), (4096, 296, 24), (4104, 520, 40), (8200, 280, 8),
+]
+
+
+@pytest.mark.parametrize("T", [1, 15, 16, 17, 32])
+@pytest.mark.parametrize("N,K,n_out", SHAPES)
+@pytest.mark.parametrize("bits,w_bits", [(4, 4), (8, 8), (8, 4)])
+def test_few_token_layer(oracle, T, N, K, n_out, bits, w_bits):
+    from paper_2310_09259_amd import api
+    shp = synth.LayerShape("few", T, K, N, n_out, bits, seed=900 + T + N + K, w_bits=0 if w_bits == bits else w_bits)
+    inp = synth.make_inputs(shp)
+    d = upload(inp)
+    b = np.random.default_rng(T).standard_normal(N).astype(np.float16)
+    ref = oracle.linear(inp.x, inp.outlier_idx, bits, inp.w_packed, inp.w_scale, inp.w_out, bias=b, w_bits=w_bits)
+    w_red = api.quik_weight_reduce(d["w_q"], d["w_scale"], shp.K_b, w_bits)
+    xq, scale, zero, x_out, side = api.quik_quantize(d["x"], d["idx"], bits)
+    if w_bits == bits:
+        y = api.quik_linear(d["x"], d["idx"], bits, d["w_q"], d["w_scale"], w_red, d["w_out"], bias=to_dev(b))
+        accs = [api.quik_debug_int_gemm(xq, d["w_q"], shp.K_b, bits)]
+        if bits == 4:
+            accs.append(api.quik_debug_int_gemm(xq, d["w_q"], shp.K_b, 4, workspace=side, w_reduced=w_red))
+    else:
+        y = api.quik_linear_w4a8(d["x"], d["idx"], d["w_q"], d["w_scale"], w_red, d["w_out"], bias=to_dev(b))
+        accs = [api.quik_int_gemm_w4a8(xq, d["w_q"], shp.K_b)]
+    for acc in accs:
+        assert np.array_equal(acc.cpu().numpy(), ref.acc)
+    ok, worst = output_within_tolerance(y.cpu().numpy(), ref.y)
+    assert ok, f"fp16 output outside 5e-3 (worst error / tolerance = {worst:.2f})"
