@@ -29,7 +29,7 @@
 // uses v_mfma_f32_32x32x16_f16, whose accumulator has the same layout, so the
 // dequantized tile is simply the C operand of the outlier stages.
 //
-// Mixed widths (4-bit weights under 8-bit activations): see MIXED in gemm_kernel.
+// This kernel takes equal operand widths; 4-bit weights under 8-bit activations: see quik_gemm_tiles16.hip.
 //
 // Pipeline.  A workgroup of four or eight waves owns a BM x BN output tile.  Operand panels
 // are copied global -> LDS without passing through registers (buffer_load ... lds,
@@ -66,8 +66,7 @@ using namespace gemm_dev;
 // stage, NST stage buffers, GM = m-tiles per group of the tile order (0: plain column sweep).
 // MODE 0: fused epilogue (asymmetric widening for 4 bits); MODE 1: write raw INT32 accumulators,
 // symmetric widening; MODE 2: raw accumulators, asymmetric widening plus correction terms.
-// BITS: activation bits; WBITS: weight bits (equal, or 4-bit weights under 8-bit activations).
-template <int BITS, int WBITS, int BM, int BN, int WM, int WN, int BKB, int NST, int OCC, int GM, int MODE>
+template <int BITS, int BM, int BN, int WM, int WN, int BKB, int NST, int OCC, int GM, int MODE>
 __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_kernel(GemmArgs a) {
     constexpr bool RAW = MODE != 0;
     constexpr bool ASYM = (BITS == 4) && (MODE != 1);
@@ -77,12 +76,6 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_kernel(GemmArgs a) {
     // allocation left part of the SIMD's file free).
     static_assert(WM * WN * OCC == 8, "two waves per SIMD");
     asm volatile("" ::: "v255");
-    // Mixed layers: a stage still covers BKB activation bytes = BKB k, which is only BKB/2 packed
-    // weight bytes.  The weight nibbles are widened to 16x int8 (even / odd k of a word in two
-    // registers); the int8 activations are brought into the same k order with two byte permutes
-    // per 8 elements.  Accumulators are exactly 16x the integer dot product.
-    constexpr bool MIXED = (BITS == 8 && WBITS == 4);
-    static_assert(WBITS == BITS || MIXED, "weights: same width as the activations, or 4 under 8");
     constexpr int NWAVES = WM * WN, NT = NWAVES * 64;
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
     constexpr int CPR = BKB / 16, RPI = 64 / CPR;
@@ -90,14 +83,8 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_kernel(GemmArgs a) {
     static_assert(A_INSTR >= 1 && B_INSTR >= 1, "tile too small for the wave count");
     constexpr int LPS = A_INSTR + B_INSTR;
     constexpr int KSUB = BKB / 32;
-    constexpr int SHIFT = (BITS == 4) ? (ASYM ? 4 : 8) : (MIXED ? 4 : 0);
+    constexpr int SHIFT = (BITS == 4) ? (ASYM ? 4 : 8) : 0;
     constexpr int A_BYTES = BM * BKB, B_BYTES = BN * BKB, ST_BYTES = A_BYTES + B_BYTES;
-    // mixed int stages: weight rows of BKW bytes, RPW rows per DMA instruction, WI instructions
-    // per wave; the remaining B_INSTR - WI slots of a stage are issued as empty (out-of-range)
-    // loads so that every stage counts the same number of DMA instructions
-    constexpr int BKW = BKB / 2, CPW = BKW / 16, RPW = 64 / CPW;
-    constexpr int WI = MIXED ? BN / RPW / NWAVES : B_INSTR;
-    static_assert(!MIXED || (WI >= 1 && BKB == 128), "mixed layers: tile too small for the wave count");
     constexpr int NF = TM + TN;
     constexpr int HALVES = (BITS == 4) ? 2 : 1;          // MFMAs per output tile per sub-step
     constexpr int SLOTS = TM * TN * HALVES;
@@ -172,33 +159,12 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_kernel(GemmArgs a) {
     }
     const uint32_t m0A = lds_base + wave_u * A_INSTR * 1024;
     const uint32_t m0B = lds_base + A_BYTES + wave_u * B_INSTR * 1024;
-    // mixed int stages: geometry of the half-width weight rows
-    uint32_t voW[WI];
-    int chW[WI];
-    if constexpr (MIXED) {
-#pragma unroll
-        for (int i = 0; i < WI; ++i) {
-            int row = (wave_u * WI + i) * RPW + lane / CPW;
-            int c = ((lane % CPW) ^ swz<BKW>(row)) * 16;
-            chW[i] = c;
-            voW[i] = (uint32_t)(row * a.ldw + c);
-        }
-    }
-    const uint32_t m0W = lds_base + A_BYTES + wave_u * WI * 1024;
-    // where a mixed stage's empty loads land: this wave's 1 KB of the unused half of the B region
-    const uint32_t m0D = lds_base + A_BYTES + BN * BKW + wave_u * 1024;
-    static_assert(!MIXED || NWAVES * 1024 <= BN * BKW, "no room for the empty loads");
-
     // DMA instruction d of a full (unguarded) int stage
     auto issue_one = [&](int s, int d) {
         const uint32_t sb = (uint32_t)(s % NST) * ST_BYTES;
         const uint32_t so = (uint32_t)s * BKB;
         if (d < A_INSTR) {
             dma16(rA, m0A + sb + d * 1024, voA[d < A_INSTR ? d : 0], so);
-        } else if constexpr (MIXED) {
-            const int j = d - A_INSTR;
-            if (j < WI) dma16(rB, m0W + sb + j * 1024, voW[j < WI ? j : 0], (uint32_t)s * BKW);
-            else dma16(rB, m0D + sb, kOob, 0);
         } else {
             dma16(rB, m0B + sb + (d - A_INSTR) * 1024, voB[d >= A_INSTR ? d - A_INSTR : 0], so);
         }
@@ -210,29 +176,18 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_kernel(GemmArgs a) {
         const int koff = (fp ? s - nk_int : s) * BKB;
         // integer stages stop at the 16-byte piece that holds a row's last packed byte: what lies beyond may
         // be anything in the weight matrix
-        const int lima = s < nk ? (fp ? fp_bytes : int_bytes) : 0;
-        const int limb = s < nk ? (fp ? fp_bytes : (MIXED ? (((a.K_b / 2) + 15) & ~15) : int_bytes)) : 0;
+        const int lim = s < nk ? (fp ? fp_bytes : int_bytes) : 0;
         const int lda = fp ? lda_fp : a.ldq, ldb = fp ? ldb_fp : a.ldw;
         const v4i ra_ = fp ? rAf : rA;
         const v4i rb_ = fp ? rBf : rB;
 #pragma unroll
         for (int i = 0; i < A_INSTR; ++i) {
-            uint32_t vo = (koff + chA[i] < lima) ? (uint32_t)(rwA[i] * lda + koff + chA[i]) : kOob;
+            uint32_t vo = (koff + chA[i] < lim) ? (uint32_t)(rwA[i] * lda + koff + chA[i]) : kOob;
             dma16(ra_, m0A + sb + i * 1024, vo, 0);
-        }
-        if (MIXED && !fp) {
-            const int koffw = s * BKW;
-#pragma unroll
-            for (int i = 0; i < B_INSTR; ++i) {
-                uint32_t vo = kOob;
-                if (i < WI && koffw + chW[i < WI ? i : 0] < limb) vo = voW[i < WI ? i : 0] + (uint32_t)koffw;
-                dma16(rb_, (i < WI ? m0W + i * 1024 : m0D) + sb, vo, 0);
-            }
-            return;
         }
 #pragma unroll
         for (int i = 0; i < B_INSTR; ++i) {
-            uint32_t vo = (koff + chB[i] < limb) ? (uint32_t)(rwB[i] * ldb + koff + chB[i]) : kOob;
+            uint32_t vo = (koff + chB[i] < lim) ? (uint32_t)(rwB[i] * ldb + koff + chB[i]) : kOob;
             dma16(rb_, m0B + sb + i * 1024, vo, 0);
         }
     };
@@ -296,30 +251,8 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_kernel(GemmArgs a) {
     uint4 R[RD][NF];
     v4i U[2][NF][HALVES];
 
-    // mixed int stages: 8 bytes (16 nibbles = this lane's k-group) of a half-width weight row
-    uint32_t rdw[MIXED ? TN : 1][KSUB];
-    if constexpr (MIXED) {
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int r = wn * TN * 32 + j * 32 + l32;
-#pragma unroll
-            for (int ks = 0; ks < KSUB; ++ks) rdw[j][ks] = A_BYTES + r * BKW + ((ks ^ swz<BKW>(r)) << 4) + g * 8;
-        }
-    }
     auto read_frag = [&](int set, int f, const uint8_t* stage, int ks) {
         R[set][f] = *reinterpret_cast<const uint4*>(stage + rd[f][ks]);
-    };
-    // fragment f of sub-step ks of a stage that is an int stage (wide == false) or an fp16 stage
-    auto read_any = [&](int set, int f, const uint8_t* stage, int ks, bool wide) {
-        if constexpr (MIXED) {
-            if (f >= TM && !wide) {
-                const uint2 v = *reinterpret_cast<const uint2*>(stage + rdw[f >= TM ? f - TM : 0][ks]);
-                R[set][f].x = v.x;
-                R[set][f].y = v.y;
-                return;
-            }
-        }
-        read_frag(set, f, stage, ks);
     };
     auto widen_word = [&](int set, int rset, int w) {
         const int f = w >> 2, k = w & 3;
@@ -338,17 +271,6 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_kernel(GemmArgs a) {
             }
             U[set][f][k >> 1][(k & 1) * 2] = (int)(act ? hi : lo);
             U[set][f][k >> 1][(k & 1) * 2 + 1] = (int)(act ? lo : hi);
-        } else if constexpr (MIXED) {
-            if (f < TM) {
-                // int8 activations k0..k15 -> [even k of the low 8 | odd | even of the high 8 | odd]
-                const uint32_t lo = (k < 2) ? R[rset][f].x : R[rset][f].z, hi = (k < 2) ? R[rset][f].y : R[rset][f].w;
-                U[set][f][0][k] = (int)__builtin_amdgcn_perm(hi, lo, (k & 1) ? 0x07050301u : 0x06040200u);
-            } else {
-                // packed weights: word k/2 holds 8 nibbles; even k (low nibbles) / odd k (high), 16x
-                constexpr uint32_t M = 0xF0F0F0F0u;
-                const uint32_t wv = (k < 2) ? R[rset][f].x : R[rset][f].y;
-                U[set][f][0][k] = (int)((k & 1) ? (wv & M) : ((wv << 4) & M));
-            }
         } else {
             U[set][f][0][k] = (int)x;
         }
@@ -397,7 +319,6 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_kernel(GemmArgs a) {
         const int ts = (ks + LA < KSUB) ? s : s + 1, tks = (ks + LA) % KSUB;
         const uint8_t* tgt = lds + (ts % NST) * ST_BYTES;
         const int rnext = (ks + 1) % RD, rload = (ks + LA) % RD;   // static: KSUB is a multiple of RD
-        const bool wide = ts >= nk_int;                             // the look-ahead reaches the fp16 part
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int m = 0; m < SLOTS; ++m) {
@@ -412,9 +333,9 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_kernel(GemmArgs a) {
 #pragma unroll
             for (int w = 0; w < WORDS; ++w)
                 if (w * SLOTS / WORDS == m) widen_word(par ^ 1, rnext, w);
-            if (m < NF) read_any(rload, m, tgt, tks, wide);
+            if (m < NF) read_frag(rload, m, tgt, tks);
             if (SLOTS < NF && m == SLOTS - 1)
-                for (int f = SLOTS; f < NF; ++f) read_any(rload, f, tgt, tks, wide);
+                for (int f = SLOTS; f < NF; ++f) read_frag(rload, f, tgt, tks);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
@@ -424,7 +345,7 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_kernel(GemmArgs a) {
 #pragma unroll
     for (int q = 0; q < LA; ++q)
 #pragma unroll
-        for (int f = 0; f < NF; ++f) read_any(q, f, lds, q, nk_int == 0);
+        for (int f = 0; f < NF; ++f) read_frag(q, f, lds, q);
 #pragma unroll
     for (int w = 0; w < WORDS; ++w) widen_word(0, 0, w);
 
@@ -564,45 +485,96 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_kernel(GemmArgs a) {
         }
 }
 
-template <int BITS, int WBITS, int BM, int BN, int WM, int WN, int BKB, int NST, int OCC, int GM, int MODE>
+template <int BITS, int BM, int BN, int WM, int WN, int BKB, int NST, int OCC, int GM, int MODE>
 hipError_t launch_cfg(const GemmArgs& a, hipStream_t stream) {
     int tiles = ((a.T + BM - 1) / BM) * ((a.N + BN - 1) / BN);
-    hipLaunchKernelGGL((gemm_kernel<BITS, WBITS, BM, BN, WM, WN, BKB, NST, OCC, GM, MODE>), dim3(tiles),
+    hipLaunchKernelGGL((gemm_kernel<BITS, BM, BN, WM, WN, BKB, NST, OCC, GM, MODE>), dim3(tiles),
                        dim3(WM * WN * 64), 0, stream, a);
     return hipGetLastError();
 }
 
-template <int BITS, int WBITS, int MODE>
-hipError_t dispatch(const GemmArgs& a, hipStream_t stream) {
-    // Few tokens: weight streaming dominates.  Up to 128 tokens small tiles with a deeper stage ring so that
-    // enough workgroups and bytes are in flight.
-    if (a.T <= 64) return launch_cfg<BITS, WBITS, 64, 64, 2, 2, 128, 4, 2, 0, MODE>(a, stream);
-    if (a.T <= 128) return launch_cfg<BITS, WBITS, 128, 64, 2, 2, 128, 2, 2, 0, MODE>(a, stream);
-    // 128-byte stage rows (a full cache line per row per stage), two stage buffers.
-    // Large problems: 256 x 128 tiles shared by eight waves (one workgroup per CU) move 25 % fewer
-    // operand bytes per MFMA through L1/LDS than two independent 128 x 128 workgroups.  They need
-    // at least one tile per CU to pay off; otherwise 128 x 128 tiles with two workgroups per CU.
-    const long big_tiles = (long)((a.T + 255) / 256) * ((a.N + 127) / 128);
-    if (big_tiles < 256) return launch_cfg<BITS, WBITS, 128, 128, 2, 2, 128, 2, 2, 8, MODE>(a, stream);
-    if constexpr (BITS == WBITS) {   // every MODE: the accumulator hook runs the tiles of the fused call
-        // One workgroup per CU, so a launch runs in ceil(tiles / 256) rounds.  Tiles of 1.5x the area
-        // (64 x 96 or 96 x 64 per wave: 17 % fewer LDS fragment reads and widening operations per
-        // MFMA, a third fewer per-tile prologues and epilogues) take 1.42x as long per round
-        // (measured); they win whenever they save enough rounds.
-        auto rounds = [&](int bm, int bn) { return (((long)(a.T + bm - 1) / bm) * ((a.N + bn - 1) / bn) + 255) / 256; };
-        const double cost_a = (double)rounds(256, 128);
-        const double cost_b = 1.42 * (double)rounds(256, 192);
-        const double cost_c = 1.42 * (double)rounds(192, 256);
-        if (cost_b < cost_a && cost_b <= cost_c) return launch_cfg<BITS, WBITS, 256, 192, 4, 2, 128, 2, 1, 4, MODE>(a, stream);
-        if (cost_c < cost_a) return launch_cfg<BITS, WBITS, 192, 256, 2, 4, 128, 2, 1, 4, MODE>(a, stream);
+// The rules look at T, N, K_b and the widths alone, so the accumulator hook (every MODE) runs the tiles of the
+// fused call.  One workgroup of eight waves per CU unless said otherwise: a launch takes ceil(tiles / cus) rounds.
+inline long tiles_of(const GemmArgs& a, int bm, int bn) { return (long)((a.T + bm - 1) / bm) * ((a.N + bn - 1) / bn); }
+inline long rounds_of(const GemmArgs& a, int bm, int bn, int cus) { return (tiles_of(a, bm, bn) + cus - 1) / cus; }
+
+template <int MODE>
+hipError_t dispatch_4bit(const GemmArgs& a, int cus, hipStream_t stream) {
+    if (a.T <= 128 || tiles_of(a, 256, 128) < cus) {
+        // Fewer than one 256 x 128 tile per CU: the smallest tile that still goes through in one round, so that
+        // all CUs have work.  Weights from HBM, us, at 64 x 32 / 64 x 64 / 128 x 64 / 128 x 128 (the last two of
+        // gemm_kernel before: 128 x 64 up to 128 tokens, then 128 x 128):
+        //   K=4096  N=4096  T=128:  9.5 / 10.8 / 14.7 / 17.4 (was 14.0);  T=192 (384 tiles of 64 x 32): 18.5 / 11.0 / 15.0 / 19.0
+        //   K=11008 N=4096  T=128: 15.7 / 20.7 / 29.2 / 42.5 (was 38.2);  T=192: 28.7 / 20.7 / 29.2 / 42.5
+        //   K=5120  N=15360 T=128:  -   /  -   / 18.9 / 26.4 (was 22.8);  K=4096 N=4096 T=512: - / - / 15.3 / 17.6
+        // The four K groups of 64 x 32 cost two barriers and a pass through LDS at the end: at K = 1024 it takes
+        // 7.2 where 64 x 64 takes 6.5, at K = 2048 7.8 against 8.0.  64 x 64 on four waves, two workgroups per CU,
+        // beats its 16 x 16 form with two K groups up to K = 8192 or so (10.8 : 11.1) and by 15 % above one tile per CU.
+        if (tiles_of(a, 64, 32) <= cus && a.K_b >= 1792) return launch_gemm_tiles16(a, kTile64x32, stream);
+        if (a.T <= 64 || tiles_of(a, 64, 64) <= cus) return launch_cfg<4, 64, 64, 2, 2, 128, 4, 2, 0, MODE>(a, stream);
+        if (tiles_of(a, 128, 64) <= cus) return launch_gemm_tiles16(a, kTile128x64, stream);
+        return launch_cfg<4, 128, 128, 2, 2, 128, 2, 2, 8, MODE>(a, stream);
     }
-    // Equal widths run this tile on the 16 x 16 matrix instructions (quik_gemm_tiles16.hip), under which the
-    // chip keeps its clock: 2 - 6 % faster here with 4-bit operands, where two waves share every SIMD, 10 %
-    // with 8-bit ones (full bytes cost the 32 x 32 form most clock).  The smaller tiles
-    // above mostly run one wave per SIMD, which the 16 x 16 form's doubled instruction count slows down
-    // (128 tokens of the 13B QKV shape: +7 %), and the larger ones do not fit the register file in that form.
-    if constexpr (BITS == WBITS) return launch_gemm_tiles16(a, stream);
-    else return launch_cfg<BITS, WBITS, 256, 128, 4, 2, 128, 2, 1, 4, MODE>(a, stream);
+    // Tiles of 1.5x the area (64 x 96 or 96 x 64 per wave: 17 % fewer LDS fragment reads and widening
+    // operations per MFMA, a third fewer per-tile prologues and epilogues) take 1.42x as long per round
+    // (measured); they win whenever they save enough rounds.
+    const double cost_a = (double)rounds_of(a, 256, 128, cus);
+    const double cost_b = 1.42 * (double)rounds_of(a, 256, 192, cus);
+    const double cost_c = 1.42 * (double)rounds_of(a, 192, 256, cus);
+    if (cost_b < cost_a && cost_b <= cost_c) return launch_cfg<4, 256, 192, 4, 2, 128, 2, 1, 4, MODE>(a, stream);
+    if (cost_c < cost_a) return launch_cfg<4, 192, 256, 2, 4, 128, 2, 1, 4, MODE>(a, stream);
+    // 256 x 128 runs on the 16 x 16 matrix instructions, under which the chip keeps its clock: 2 - 6 % faster.
+    // The larger tiles do not fit the register file in that form.
+    return launch_gemm_tiles16(a, kTile256x128, stream);
+}
+
+// 8-bit activations: the tile with the least rounds * (fixed + per_stage * stages), a stage being 128 k.  The two
+// figures of a tile are a line through its measured time per round (us, weights from HBM, N = 4096 .. 28672):
+//   integer stages              4      6     14     30     84
+//   W8A8  64 x 32             5.5    5.8    7.0   10.2   18.5 - 22.8
+//         64 x 64             6.1    5.9    8.0   13.4   26 - 30
+//         two of 64 x 64      4.8    4.1    6.5   11.3      -         (per 256 tiles)
+//         128 x 64            8.9    8.9   11.4   18.6   32.2
+//         128 x 128          10.1   10.0   15.1   26.5   44 - 57
+//         256 x 128          15     14.5   21.3   34.2   88          256 x 192 (gemm_kernel): 50.8 at 30
+//   W4A8  64 x 32             5.9    6.3    8.0   10.7   17.5 - 20.7
+//         64 x 64             6.7    6.5    8.9   12.8   22 - 27
+//         two of 64 x 64      5.2    4.9    7.1   11.0      -
+//         128 x 64            9.5    9.0   12.0   17.7   33 - 37
+//         128 x 128          13.8   12.3   17.2   26.6   54
+//         256 x 128          15.8   15.6   22.0   36     79
+// What that changed (before: 64 x 64, 128 x 64, 128 x 128 on 32 x 32 matrix instructions with two or four stages,
+// 256 x 128 with two): W8A8 K=11008 N=4096 T=64 39.4 -> 23.3, T=128 68.5 -> 22.8, T=300 75.0 -> 32.2, T=2048 101 -> 88;
+// K=5000 N=4090 T=777 40.7 -> 29.8; W4A8 K=11008 N=4096 T=64 56.3 -> 21.1, T=128 55.1 -> 20.7, T=333 63.8 -> 33.9,
+// T=1024 66.4 -> 56.5.
+struct TileCost { int tile, bm, bn; double fixed, per_stage; };
+constexpr TileCost kCost8[] = {{kTile64x32, 64, 32, 5.2, 0.17},    {kTile64x64, 64, 64, 5.2, 0.28},
+                               {kTile64x64Pair, 64, 64, 3.0, 0.33}, {kTile128x64, 128, 64, 7.6, 0.31},
+                               {kTile128x128, 128, 128, 6.5, 0.58}, {kTile256x128, 256, 128, 9.5, 0.92},
+                               {-1, 256, 192, 13.5, 1.25},          {-2, 192, 256, 13.5, 1.25}};
+constexpr TileCost kCost8w4[] = {{kTile64x32, 64, 32, 5.4, 0.17},    {kTile64x64, 64, 64, 5.8, 0.24},
+                                 {kTile64x64Pair, 64, 64, 3.0, 0.30}, {kTile128x64, 128, 64, 8.0, 0.31},
+                                 {kTile128x128, 128, 128, 9.8, 0.55}, {kTile256x128, 256, 128, 11.5, 0.82}};
+
+template <int MODE>
+hipError_t dispatch_8bit(const GemmArgs& a, int cus, hipStream_t stream) {
+    const int stages = (a.K_b + 127) / 128;
+    const bool mixed = a.w_bits == 4;
+    const TileCost* list = mixed ? kCost8w4 : kCost8;
+    const int count = mixed ? (int)(sizeof(kCost8w4) / sizeof(TileCost)) : (int)(sizeof(kCost8) / sizeof(TileCost));
+    int best = 0;
+    double least = 0.0;
+    for (int i = 0; i < count; ++i) {
+        const long rounds = rounds_of(a, list[i].bm, list[i].bn, cus);
+        // (a four-wave workgroup alone on its CU has nothing to overlap with: 6.2 us at 8 stages, 15.4 at 30)
+        const double per_stage = (list[i].tile == kTile64x64Pair && rounds == 1) ? 0.42 : list[i].per_stage;
+        const double c = (double)rounds * (list[i].fixed + per_stage * stages);
+        if (i == 0 || c < least) { best = i; least = c; }
+    }
+    const int tile = list[best].tile;
+    if (tile == -1) return launch_cfg<8, 256, 192, 4, 2, 128, 2, 1, 4, MODE>(a, stream);
+    if (tile == -2) return launch_cfg<8, 192, 256, 2, 4, 128, 2, 1, 4, MODE>(a, stream);
+    return launch_gemm_tiles16(a, tile, stream);
 }
 
 // one wave per output channel; lanes stride over the packed row
@@ -693,18 +665,18 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t stream) {
         if (c == 1 || (c == 2 && path == 1)) return launch_gemm_stream(a, plan, stream);
     }
     if (a.T <= kRowsTokens) return launch_gemm_rows(a, cus, stream);
-    return launch_gemm_tiles(a, stream);
+    return launch_gemm_tiles(a, cus, stream);
 }
 
 // one workgroup per output tile (every shape the persistent kernel does not take)
-hipError_t launch_gemm_tiles(const GemmArgs& a, hipStream_t stream) {
+hipError_t launch_gemm_tiles(const GemmArgs& a, int cus, hipStream_t stream) {
     const bool raw = a.y == nullptr;
+    if (cus < 1) cus = 256;              // the count could not be read: any value gives a working choice
     if (a.bits == 4) {
-        if (!raw) return dispatch<4, 4, 0>(a, stream);
-        return (a.code_sum && a.w_code_sum) ? dispatch<4, 4, 2>(a, stream) : dispatch<4, 4, 1>(a, stream);
+        if (!raw) return dispatch_4bit<0>(a, cus, stream);
+        return (a.code_sum && a.w_code_sum) ? dispatch_4bit<2>(a, cus, stream) : dispatch_4bit<1>(a, cus, stream);
     }
-    if (a.w_bits == 4) return raw ? dispatch<8, 4, 1>(a, stream) : dispatch<8, 4, 0>(a, stream);
-    return raw ? dispatch<8, 8, 1>(a, stream) : dispatch<8, 8, 0>(a, stream);
+    return raw ? dispatch_8bit<1>(a, cus, stream) : dispatch_8bit<0>(a, cus, stream);
 }
 
 hipError_t launch_weight_reduce(const WeightReduceArgs& a, hipStream_t stream) {

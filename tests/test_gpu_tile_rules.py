@@ -1,0 +1,47 @@
+"""Every tile that the per-tile GEMM's rules can choose between one tile and one round, at its edges, against the
+oracle: INT32 accumulators bit-exact, fp16 output within 5e-3 (run with -m gpu on an MI355X)."""
+import numpy as np
+import pytest
+
+from paper_2310_09259_amd import synth
+from tests.util import output_within_tolerance, to_dev, upload
+
+pytestmark = pytest.mark.gpu
+
+# T, N, K, n_out.  With 256 compute units the tiles are, for 4 / 8 / 4-under-8 bits (P: two workgroups per CU):
+SHAPES = [
+    (33, 70, 2056, 72),       # 64 x 32 for all; eight and sixteen integer stages, the last not full, two outlier stages
+    (65, 35, 48, 0),          # 64 x 64 / P / P: one stage, no outlier columns
+    (129, 2040, 1880, 24),    # 64 x 32 for all, ragged in both directions, one short outlier stage
+    (100, 8150, 520, 40),     # 64 x 64 / P / P
+    (100, 8150, 5200, 40),    # 64 x 64 for all
+    (130, 8190, 4432, 80),    # 128 x 64 for all
+    (130, 8190, 648, 136),    # 128 x 64 / 128 x 128 / P
+    (250, 16300, 264, 8),     # 128 x 128 for all
+    (500, 16000, 304, 48),    # 256 x 128 under 8-bit activations
+]
+
+
+@pytest.mark.parametrize("T,N,K,n_out", SHAPES)
+@pytest.mark.parametrize("bits,w_bits", [(4, 4), (8, 8), (8, 4)])
+def test_tile_of_the_rules(oracle, T, N, K, n_out, bits, w_bits):
+    from paper_2310_09259_amd import api
+    shp = synth.LayerShape("tile", T, K, N, n_out, bits, seed=700 + T + N + K, w_bits=0 if w_bits == bits else w_bits)
+    inp = synth.make_inputs(shp)
+    d = upload(inp)
+    b = np.random.default_rng(T).standard_normal(N).astype(np.float16)
+    ref = oracle.linear(inp.x, inp.outlier_idx, bits, inp.w_packed, inp.w_scale, inp.w_out, bias=b, w_bits=w_bits)
+    w_red = api.quik_weight_reduce(d["w_q"], d["w_scale"], shp.K_b, w_bits)
+    xq, scale, zero, x_out, side = api.quik_quantize(d["x"], d["idx"], bits)
+    if w_bits == bits:
+        y = api.quik_linear(d["x"], d["idx"], bits, d["w_q"], d["w_scale"], w_red, d["w_out"], bias=to_dev(b))
+        accs = [api.quik_debug_int_gemm(xq, d["w_q"], shp.K_b, bits)]
+        if bits == 4:
+            accs.append(api.quik_debug_int_gemm(xq, d["w_q"], shp.K_b, 4, workspace=side, w_reduced=w_red))
+    else:
+        y = api.quik_linear_w4a8(d["x"], d["idx"], d["w_q"], d["w_scale"], w_red, d["w_out"], bias=to_dev(b))
+        accs = [api.quik_int_gemm_w4a8(xq, d["w_q"], shp.K_b)]
+    for acc in accs:
+        assert np.array_equal(acc.cpu().numpy(), ref.acc)
+    ok, worst = output_within_tolerance(y.cpu().numpy(), ref.y)
+    assert ok, f"fp16 output outside 5e-3 (worst error / tolerance = {worst:.2f})"
