@@ -502,17 +502,20 @@ template <int MODE>
 hipError_t dispatch_4bit(const GemmArgs& a, int cus, hipStream_t stream) {
     if (a.T <= 128 || tiles_of(a, 256, 128) < cus) {
         // Fewer than one 256 x 128 tile per CU: the smallest tile that still goes through in one round, so that
-        // all CUs have work.  Weights from HBM, us, at 64 x 32 / 64 x 64 / 128 x 64 / 128 x 128 (the last two of
-        // gemm_kernel before: 128 x 64 up to 128 tokens, then 128 x 128):
-        //   K=4096  N=4096  T=128:  9.5 / 10.8 / 14.7 / 17.4 (was 14.0);  T=192 (384 tiles of 64 x 32): 18.5 / 11.0 / 15.0 / 19.0
-        //   K=11008 N=4096  T=128: 15.7 / 20.7 / 29.2 / 42.5 (was 38.2);  T=192: 28.7 / 20.7 / 29.2 / 42.5
-        //   K=5120  N=15360 T=128:  -   /  -   / 18.9 / 26.4 (was 22.8);  K=4096 N=4096 T=512: - / - / 15.3 / 17.6
+        // all CUs have work.  64 x 64 runs two workgroups of four waves per CU.  us at 64 x 32 / 64 x 64 / 128 x 64 /
+        // 128 x 128, weights from HBM (in brackets from the last-level cache); before, 128 x 64 served 65 to 128
+        // tokens and 128 x 128 more:
+        //   K=4096  N=4096  T=128:  9.5 / 10.8 / 14.0 / 17.4 (9.9 / 11.0 / 13.1 / 17.2);  T=192: 18.5 / 11.0 / 15.9 / 19.0
+        //                   T=333: 26.8 / 13.7 / 15.7 / 18.8 (26.1 / 13.3 / 13.4 / 17.3);  T=512: ( - / 13.6 / 13.5 / 17.5)
+        //   K=11008 N=4096  T=128: 15.7 / 20.7 / 38.2 / 42.5;  T=333: 41.3 / 27.7 / 37.6 / 42.4
+        //   K=4096  N=11008 T=128: 29.0 / 16.9 / 18.8 / 21.7 (26.5 / 13.5 / 13.9 / 17.8)
+        //   K=5120  N=15360 T=128: (37.9 / 16.2 / 17.6 / 21.1)
         // The four K groups of 64 x 32 cost two barriers and a pass through LDS at the end: at K = 1024 it takes
-        // 7.2 where 64 x 64 takes 6.5, at K = 2048 7.8 against 8.0.  64 x 64 on four waves, two workgroups per CU,
-        // beats its 16 x 16 form with two K groups up to K = 8192 or so (10.8 : 11.1) and by 15 % above one tile per CU.
+        // 7.2 where 64 x 64 takes 6.5, at K = 2048 7.8 against 8.0.  Beyond two 64 x 64 tiles per CU, 128 x 64 has
+        // the edge only while weights are cached (T=66 K=4240 N=28296: 19.9 : 21.3, from HBM 28.9 : 27.9).
         if (tiles_of(a, 64, 32) <= cus && a.K_b >= 1792) return launch_gemm_tiles16(a, kTile64x32, stream);
-        if (a.T <= 64 || tiles_of(a, 64, 64) <= cus) return launch_cfg<4, 64, 64, 2, 2, 128, 4, 2, 0, MODE>(a, stream);
-        if (tiles_of(a, 128, 64) <= cus) return launch_gemm_tiles16(a, kTile128x64, stream);
+        if (a.T <= 64 || tiles_of(a, 64, 64) <= 2L * cus) return launch_cfg<4, 64, 64, 2, 2, 128, 4, 2, 0, MODE>(a, stream);
+        if (a.T <= 128) return launch_cfg<4, 128, 64, 2, 2, 128, 2, 2, 0, MODE>(a, stream);
         return launch_cfg<4, 128, 128, 2, 2, 128, 2, 2, 8, MODE>(a, stream);
     }
     // Tiles of 1.5x the area (64 x 96 or 96 x 64 per wave: 17 % fewer LDS fragment reads and widening

@@ -663,7 +663,7 @@ hipError_t launch_tile(const GemmArgs& a, int tile, hipStream_t stream) {
         else break;
     case kTile128x64:
         if constexpr (BITS == 8) return launch_cfg<BITS, WBITS, 128, 64, 2, 2, 2, 3, 8, MODE>(a, stream);
-        else return launch_cfg<BITS, WBITS, 128, 64, 4, 2, 1, 4, 8, MODE>(a, stream);   // 18.9 : 20.2 at K = 5120
+        else break;
     case kTile128x128:
         if constexpr (MIXED) return launch_cfg<BITS, WBITS, 128, 128, 2, 2, 2, 2, 8, MODE>(a, stream);
         else if constexpr (BITS == 8) return launch_cfg<BITS, WBITS, 128, 128, 4, 2, 1, 4, 8, MODE>(a, stream);

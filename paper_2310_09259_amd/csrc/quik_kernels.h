@@ -180,8 +180,8 @@ __host__ __device__ inline void stream_panel(const StreamPlan& p, int nt, int* b
 hipError_t launch_quantize(const QuantizeArgs& a, hipStream_t stream);
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t stream);
 hipError_t launch_gemm_tiles(const GemmArgs& a, int cus, hipStream_t stream);
-// one workgroup per tile on 16 x 16 matrix instructions (quik_gemm_tiles16.hip); 64 x 64 and 128 x 128 with 8-bit
-// activations only
+// one workgroup per tile on 16 x 16 matrix instructions (quik_gemm_tiles16.hip); those between 64 x 32 and
+// 256 x 128 with 8-bit activations only
 enum { kTile64x32, kTile64x64, kTile64x64Pair, kTile128x64, kTile128x128, kTile256x128 };
 hipError_t launch_gemm_tiles16(const GemmArgs& a, int tile, hipStream_t stream);
 // T <= kRowsTokens, any operand widths: weights streamed into registers, waves split K (quik_gemm_rows.hip)

@@ -11,12 +11,13 @@ pytestmark = pytest.mark.gpu
 # T, N, K, n_out.  With 256 compute units the tiles are, for 4 / 8 / 4-under-8 bits (P: two workgroups per CU):
 SHAPES = [
     (33, 70, 2056, 72),       # 64 x 32 for all; eight and sixteen integer stages, the last not full, two outlier stages
-    (65, 35, 48, 0),          # 64 x 64 / P / P: one stage, no outlier columns
+    (65, 35, 48, 0),          # P for all: one stage, no outlier columns
     (129, 2040, 1880, 24),    # 64 x 32 for all, ragged in both directions, one short outlier stage
-    (100, 8150, 520, 40),     # 64 x 64 / P / P
-    (100, 8150, 5200, 40),    # 64 x 64 for all
-    (130, 8190, 4432, 80),    # 128 x 64 for all
-    (130, 8190, 648, 136),    # 128 x 64 / 128 x 128 / P
+    (100, 8150, 520, 40),     # P for all (4 bits: 64 x 64 on 32 x 32 instructions)
+    (100, 8150, 5200, 40),    # P / 64 x 64 / 64 x 64
+    (130, 8190, 4432, 80),    # P / 128 x 64 / 128 x 64
+    (130, 8190, 648, 136),    # P for all
+    (128, 16400, 264, 8),     # 128 x 64 for 4 bits
     (250, 16300, 264, 8),     # 128 x 128 for all
     (500, 16000, 304, 48),    # 256 x 128 under 8-bit activations
 ]
