@@ -227,6 +227,17 @@ int quik_int_gemm(const void *xq, int ldq, const void *w_q, int ldw,
 int quik_debug_gemm_plan(int T, int N, int K_b, int cus, int *plan);
 
 /*
+ * Test hook (host only): the kernel that the GEMM entry points run for a [T, N] output with K_b base columns
+ * of `bits`-bit activations and `w_bits`-bit weights (equal, or 4 under 8) on a GPU with `cus` compute
+ * units, in automatic mode.  Returns 1 for the few-token kernel (gemm_rows_kernel), 2 for the per-tile kernel on
+ * 32 x 32 matrix instructions (gemm_kernel), 3 for the one on 16 x 16 (gemm_tiles16_kernel), 4 for the persistent
+ * one (gemm_stream_kernel), and writes to form[0..3] (HOST pointer): token rows and output channels of a
+ * workgroup's tile (persistent: of the narrower tiles), its waves, and the groups of waves that split K.
+ * QUIK_EINVAL / QUIK_ENULL on invalid input.
+ */
+int quik_debug_gemm_form(int T, int N, int K_b, int bits, int w_bits, int cus, int *form);
+
+/*
  * Test hook (host only): the k-th output tile (k = 0, 1, ...) that resident workgroup
  * `workgroup` (0 .. plan[4]-1) of the persistent kernel computes for the shape of
  * quik_debug_gemm_plan: tile[0] = first token row, tile[1] = first output channel,

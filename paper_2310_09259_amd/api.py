@@ -44,6 +44,8 @@ def load() -> C.CDLL:
         lib.quik_workspace_regions.argtypes = [i, i, i, i, i, vp, vp]
         lib.quik_debug_gemm_plan.restype = i
         lib.quik_debug_gemm_plan.argtypes = [i, i, i, i, vp]
+        lib.quik_debug_gemm_form.restype = i
+        lib.quik_debug_gemm_form.argtypes = [i, i, i, i, i, i, vp]
         lib.quik_debug_gemm_tile.restype = i
         lib.quik_debug_gemm_tile.argtypes = [i, i, i, i, i, i, vp]
         lib.quik_debug_set_gemm_path.restype = i
@@ -193,6 +195,16 @@ def quik_debug_gemm_plan(T: int, N: int, K_b: int, cus: int):
     if rc < 0:
         _check(rc, "quik_debug_gemm_plan")
     return (rc, tuple(plan)) if rc > 0 else None
+
+
+def quik_debug_gemm_form(T: int, N: int, K_b: int, bits: int, w_bits: int, cus: int):
+    """Host-only: (kernel, (rows, cols, waves, k_groups)) of the INT GEMM for this shape on `cus` compute units;
+    kernel 1 = gemm_rows_kernel, 2 = gemm_kernel, 3 = gemm_tiles16_kernel, 4 = gemm_stream_kernel."""
+    form = (C.c_int * 4)()
+    rc = load().quik_debug_gemm_form(T, N, K_b, bits, w_bits, cus, C.cast(form, C.c_void_p))
+    if rc < 0:
+        _check(rc, "quik_debug_gemm_form")
+    return rc, tuple(form)
 
 
 def quik_debug_set_gemm_path(mode: int):

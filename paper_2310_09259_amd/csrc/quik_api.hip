@@ -133,6 +133,15 @@ int quik_debug_gemm_plan(int T, int N, int K_b, int cus, int* plan) {
     return c;
 }
 
+int quik_debug_gemm_form(int T, int N, int K_b, int bits, int w_bits, int cus, int* form) {
+    if ((bits != 4 && bits != 8) || (w_bits != bits && !(bits == 8 && w_bits == 4))) return QUIK_EINVAL;
+    if (T <= 0 || N <= 0 || K_b <= 0 || K_b >= kMaxKb || (K_b * w_bits) % 8 || cus <= 0) return QUIK_EINVAL;
+    if (!form) return QUIK_ENULL;
+    const quik::GemmForm f = quik::choose_gemm_form(T, N, K_b, bits, w_bits, cus);
+    form[0] = f.rows; form[1] = f.cols; form[2] = f.waves; form[3] = f.k_groups;
+    return f.family;
+}
+
 int quik_debug_gemm_tile(int T, int N, int K_b, int cus, int workgroup, int k, int* tile) {
     if (T <= 0 || N <= 0 || K_b <= 0 || (K_b & 1) || K_b >= kMaxKb || cus <= 0 || workgroup < 0 || k < 0) return QUIK_EINVAL;
     if (!tile) return QUIK_ENULL;

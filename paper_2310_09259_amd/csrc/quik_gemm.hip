@@ -495,12 +495,11 @@ hipError_t launch_cfg(const GemmArgs& a, hipStream_t stream) {
 
 // The rules look at T, N, K_b and the widths alone, so the accumulator hook (every MODE) runs the tiles of the
 // fused call.  One workgroup of eight waves per CU unless said otherwise: a launch takes ceil(tiles / cus) rounds.
-inline long tiles_of(const GemmArgs& a, int bm, int bn) { return (long)((a.T + bm - 1) / bm) * ((a.N + bn - 1) / bn); }
-inline long rounds_of(const GemmArgs& a, int bm, int bn, int cus) { return (tiles_of(a, bm, bn) + cus - 1) / cus; }
+inline long tiles_of(int T, int N, int bm, int bn) { return (long)((T + bm - 1) / bm) * ((N + bn - 1) / bn); }
+inline long rounds_of(int T, int N, int bm, int bn, int cus) { return (tiles_of(T, N, bm, bn) + cus - 1) / cus; }
 
-template <int MODE>
-hipError_t dispatch_4bit(const GemmArgs& a, int cus, hipStream_t stream) {
-    if (a.T <= 128 || tiles_of(a, 256, 128) < cus) {
+int choose_tile_4bit(int T, int N, int K_b, int cus) {
+    if (T <= 128 || tiles_of(T, N, 256, 128) < cus) {
         // Fewer than one 256 x 128 tile per CU: the smallest tile that still goes through in one round, so that
         // all CUs have work.  64 x 64 runs two workgroups of four waves per CU.  us at 64 x 32 / 64 x 64 / 128 x 64 /
         // 128 x 128, weights from HBM (in brackets from the last-level cache); before, 128 x 64 served 65 to 128
@@ -513,22 +512,21 @@ hipError_t dispatch_4bit(const GemmArgs& a, int cus, hipStream_t stream) {
         // The four K groups of 64 x 32 cost two barriers and a pass through LDS at the end: at K = 1024 it takes
         // 7.2 where 64 x 64 takes 6.5, at K = 2048 7.8 against 8.0.  Beyond two 64 x 64 tiles per CU, 128 x 64 has
         // the edge only while weights are cached (T=66 K=4240 N=28296: 19.9 : 21.3, from HBM 28.9 : 27.9).
-        if (tiles_of(a, 64, 32) <= cus && a.K_b >= 1792) return launch_gemm_tiles16(a, kTile64x32, stream);
-        if (a.T <= 64 || tiles_of(a, 64, 64) <= 2L * cus) return launch_cfg<4, 64, 64, 2, 2, 128, 4, 2, 0, MODE>(a, stream);
-        if (a.T <= 128) return launch_cfg<4, 128, 64, 2, 2, 128, 2, 2, 0, MODE>(a, stream);
-        return launch_cfg<4, 128, 128, 2, 2, 128, 2, 2, 8, MODE>(a, stream);
+        if (tiles_of(T, N, 64, 32) <= cus && K_b >= 1792) return kTile64x32;
+        if (T <= 64 || tiles_of(T, N, 64, 64) <= 2L * cus) return kTile64x64Pair32;
+        return T <= 128 ? kTile128x64Pair32 : kTile128x128Pair32;
     }
     // Tiles of 1.5x the area (64 x 96 or 96 x 64 per wave: 17 % fewer LDS fragment reads and widening
     // operations per MFMA, a third fewer per-tile prologues and epilogues) take 1.42x as long per round
     // (measured); they win whenever they save enough rounds.
-    const double cost_a = (double)rounds_of(a, 256, 128, cus);
-    const double cost_b = 1.42 * (double)rounds_of(a, 256, 192, cus);
-    const double cost_c = 1.42 * (double)rounds_of(a, 192, 256, cus);
-    if (cost_b < cost_a && cost_b <= cost_c) return launch_cfg<4, 256, 192, 4, 2, 128, 2, 1, 4, MODE>(a, stream);
-    if (cost_c < cost_a) return launch_cfg<4, 192, 256, 2, 4, 128, 2, 1, 4, MODE>(a, stream);
+    const double cost_a = (double)rounds_of(T, N, 256, 128, cus);
+    const double cost_b = 1.42 * (double)rounds_of(T, N, 256, 192, cus);
+    const double cost_c = 1.42 * (double)rounds_of(T, N, 192, 256, cus);
+    if (cost_b < cost_a && cost_b <= cost_c) return kTile256x192;
+    if (cost_c < cost_a) return kTile192x256;
     // 256 x 128 runs on the 16 x 16 matrix instructions, under which the chip keeps its clock: 2 - 6 % faster.
     // The larger tiles do not fit the register file in that form.
-    return launch_gemm_tiles16(a, kTile256x128, stream);
+    return kTile256x128;
 }
 
 // 8-bit activations: the tile with the least rounds * (fixed + per_stage * stages), a stage being 128 k.  The two
@@ -554,30 +552,48 @@ struct TileCost { int tile, bm, bn; double fixed, per_stage; };
 constexpr TileCost kCost8[] = {{kTile64x32, 64, 32, 5.2, 0.17},    {kTile64x64, 64, 64, 5.2, 0.28},
                                {kTile64x64Pair, 64, 64, 3.0, 0.33}, {kTile128x64, 128, 64, 7.6, 0.31},
                                {kTile128x128, 128, 128, 6.5, 0.58}, {kTile256x128, 256, 128, 9.5, 0.92},
-                               {-1, 256, 192, 13.5, 1.25},          {-2, 192, 256, 13.5, 1.25}};
+                               {kTile256x192, 256, 192, 13.5, 1.25}, {kTile192x256, 192, 256, 13.5, 1.25}};
 constexpr TileCost kCost8w4[] = {{kTile64x32, 64, 32, 5.4, 0.17},    {kTile64x64, 64, 64, 5.8, 0.24},
                                  {kTile64x64Pair, 64, 64, 3.0, 0.30}, {kTile128x64, 128, 64, 8.0, 0.31},
                                  {kTile128x128, 128, 128, 9.8, 0.55}, {kTile256x128, 256, 128, 11.5, 0.82}};
 
-template <int MODE>
-hipError_t dispatch_8bit(const GemmArgs& a, int cus, hipStream_t stream) {
-    const int stages = (a.K_b + 127) / 128;
-    const bool mixed = a.w_bits == 4;
+int choose_tile_8bit(int T, int N, int K_b, bool mixed, int cus) {
+    const int stages = (K_b + 127) / 128;
     const TileCost* list = mixed ? kCost8w4 : kCost8;
     const int count = mixed ? (int)(sizeof(kCost8w4) / sizeof(TileCost)) : (int)(sizeof(kCost8) / sizeof(TileCost));
     int best = 0;
     double least = 0.0;
     for (int i = 0; i < count; ++i) {
-        const long rounds = rounds_of(a, list[i].bm, list[i].bn, cus);
+        const long rounds = rounds_of(T, N, list[i].bm, list[i].bn, cus);
         // (a four-wave workgroup alone on its CU has nothing to overlap with: 6.2 us at 8 stages, 15.4 at 30)
         const double per_stage = (list[i].tile == kTile64x64Pair && rounds == 1) ? 0.42 : list[i].per_stage;
         const double c = (double)rounds * (list[i].fixed + per_stage * stages);
         if (i == 0 || c < least) { best = i; least = c; }
     }
-    const int tile = list[best].tile;
-    if (tile == -1) return launch_cfg<8, 256, 192, 4, 2, 128, 2, 1, 4, MODE>(a, stream);
-    if (tile == -2) return launch_cfg<8, 192, 256, 2, 4, 128, 2, 1, 4, MODE>(a, stream);
-    return launch_gemm_tiles16(a, tile, stream);
+    return list[best].tile;
+}
+
+int choose_tile(int T, int N, int K_b, int bits, bool mixed, int cus) {
+    return bits == 4 ? choose_tile_4bit(T, N, K_b, cus) : choose_tile_8bit(T, N, K_b, mixed, cus);
+}
+
+template <int BITS, int MODE>
+hipError_t launch_tile(const GemmArgs& a, int tile, hipStream_t stream) {
+    switch (tile) {
+    case kTile64x64Pair32:
+        if constexpr (BITS == 4) return launch_cfg<4, 64, 64, 2, 2, 128, 4, 2, 0, MODE>(a, stream);
+        else break;
+    case kTile128x64Pair32:
+        if constexpr (BITS == 4) return launch_cfg<4, 128, 64, 2, 2, 128, 2, 2, 0, MODE>(a, stream);
+        else break;
+    case kTile128x128Pair32:
+        if constexpr (BITS == 4) return launch_cfg<4, 128, 128, 2, 2, 128, 2, 2, 8, MODE>(a, stream);
+        else break;
+    case kTile256x192: return launch_cfg<BITS, 256, 192, 4, 2, 128, 2, 1, 4, MODE>(a, stream);
+    case kTile192x256: return launch_cfg<BITS, 192, 256, 2, 4, 128, 2, 1, 4, MODE>(a, stream);
+    default: return launch_gemm_tiles16(a, tile, stream);
+    }
+    return hipErrorInvalidValue;
 }
 
 // one wave per output channel; lanes stride over the packed row
@@ -675,11 +691,31 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t stream) {
 hipError_t launch_gemm_tiles(const GemmArgs& a, int cus, hipStream_t stream) {
     const bool raw = a.y == nullptr;
     if (cus < 1) cus = 256;              // the count could not be read: any value gives a working choice
-    if (a.bits == 4) {
-        if (!raw) return dispatch_4bit<0>(a, cus, stream);
-        return (a.code_sum && a.w_code_sum) ? dispatch_4bit<2>(a, cus, stream) : dispatch_4bit<1>(a, cus, stream);
+    const int tile = choose_tile(a.T, a.N, a.K_b, a.bits, a.bits == 8 && a.w_bits == 4, cus);
+    if (a.bits == 8) return raw ? launch_tile<8, 1>(a, tile, stream) : launch_tile<8, 0>(a, tile, stream);
+    if (!raw) return launch_tile<4, 0>(a, tile, stream);
+    return (a.code_sum && a.w_code_sum) ? launch_tile<4, 2>(a, tile, stream) : launch_tile<4, 1>(a, tile, stream);
+}
+
+GemmForm choose_gemm_form(int T, int N, int K_b, int bits, int w_bits, int cus) {
+    const bool mixed = bits == 8 && w_bits == 4;
+    StreamPlan plan;
+    if (bits == 4 && T > kRowsTokens && choose_gemm_stream(T, N, K_b, cus, &plan) == 1)
+        return GemmForm{4, kStreamRows, plan.base * 32, 8, 1};
+    if (T <= kRowsTokens) return choose_rows_form(T, N, K_b, bits, w_bits, cus);
+    switch (choose_tile(T, N, K_b, bits, mixed, cus)) {
+    case kTile64x32: return GemmForm{3, 64, 32, 8, 4};
+    case kTile64x64: return GemmForm{3, 64, 64, 8, 2};
+    case kTile64x64Pair: return GemmForm{3, 64, 64, 4, 1};
+    case kTile128x64: return GemmForm{3, 128, 64, 8, 2};
+    case kTile128x128: return GemmForm{3, 128, 128, 8, mixed ? 2 : 1};
+    case kTile256x128: return GemmForm{3, 256, 128, 8, 1};
+    case kTile64x64Pair32: return GemmForm{2, 64, 64, 4, 1};
+    case kTile128x64Pair32: return GemmForm{2, 128, 64, 4, 1};
+    case kTile128x128Pair32: return GemmForm{2, 128, 128, 4, 1};
+    case kTile256x192: return GemmForm{2, 256, 192, 8, 1};
+    default: return GemmForm{2, 192, 256, 8, 1};
     }
-    return raw ? dispatch_8bit<1>(a, cus, stream) : dispatch_8bit<0>(a, cus, stream);
 }
 
 hipError_t launch_weight_reduce(const WeightReduceArgs& a, hipStream_t stream) {

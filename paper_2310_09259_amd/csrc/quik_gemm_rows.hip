@@ -290,17 +290,24 @@ hipError_t launch_cfg(const GemmArgs& a, int nw, hipStream_t stream) {
 //    busiest CU with less to do (N = 11008, 8-bit: 11.0 against 12.2; not with 8-bit activations under 4-bit
 //    weights, whose activation traffic is twice as heavy).  Two stages there: what a third brings in bytes in
 //    flight it costs in resident workgroups (10.1 against 10.3).
-template <int XB, int WB, int TB, int MODE>
-hipError_t launch(const GemmArgs& a, int cus, hipStream_t stream) {
-    constexpr bool MIXED = XB == 8 && WB == 4;
-    const int blocks = (a.N + 15) / 16, lines = (a.K_b * WB / 8 + kLine - 1) / kLine;
+struct RowsForm { int cb, nst, waves; };
+RowsForm rows_form(int N, int K_b, bool mixed, int w_bits, int tb, int cus) {
+    const int blocks = (N + 15) / 16, lines = (K_b * w_bits / 8 + kLine - 1) / kLine;
     auto busiest = [&](int cb) { return (blocks + cb * cus - 1) / (cb * cus) * cb; };
     if (blocks <= cus) {
-        if (TB == 1 && lines >= 16) return launch_cfg<XB, WB, TB, 1, TB == 1 ? 3 : 2, MODE>(a, 8, stream);
-        return launch_cfg<XB, WB, TB, 1, (TB == 2 && MIXED) ? 2 : 3, MODE>(a, 4, stream);
+        if (tb == 1 && lines >= 16) return {1, 3, 8};
+        return {1, (tb == 2 && mixed) ? 2 : 3, 4};
     }
-    if (!MIXED && blocks <= 4 * cus && busiest(1) < busiest(2)) return launch_cfg<XB, WB, TB, 1, 2, MODE>(a, 4, stream);
-    return launch_cfg<XB, WB, TB, 2, 2, MODE>(a, 4, stream);
+    if (!mixed && blocks <= 4 * cus && busiest(1) < busiest(2)) return {1, 2, 4};
+    return {2, 2, 4};
+}
+
+template <int XB, int WB, int TB, int MODE>
+hipError_t launch(const GemmArgs& a, int cus, hipStream_t stream) {
+    const RowsForm f = rows_form(a.N, a.K_b, XB != WB, WB, TB, cus);
+    if (f.cb == 2) return launch_cfg<XB, WB, TB, 2, 2, MODE>(a, f.waves, stream);
+    if (f.nst == 2) return launch_cfg<XB, WB, TB, 1, 2, MODE>(a, f.waves, stream);
+    return launch_cfg<XB, WB, TB, 1, (XB != WB && TB == 2) ? 2 : 3, MODE>(a, f.waves, stream);
 }
 
 template <int XB, int WB, int MODE>
@@ -309,6 +316,12 @@ hipError_t dispatch(const GemmArgs& a, int cus, hipStream_t stream) {
 }
 
 }  // namespace
+
+GemmForm choose_rows_form(int T, int N, int K_b, int bits, int w_bits, int cus) {
+    const int tb = T <= 16 ? 1 : 2;
+    const RowsForm f = rows_form(N, K_b, bits == 8 && w_bits == 4, w_bits, tb, cus);
+    return GemmForm{1, tb * 16, f.cb * 16, f.waves, f.waves};
+}
 
 hipError_t launch_gemm_rows(const GemmArgs& a, int cus, hipStream_t stream) {
     const bool raw = a.y == nullptr;

@@ -182,11 +182,20 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t stream);
 hipError_t launch_gemm_tiles(const GemmArgs& a, int cus, hipStream_t stream);
 // one workgroup per tile on 16 x 16 matrix instructions (quik_gemm_tiles16.hip); those between 64 x 32 and
 // 256 x 128 with 8-bit activations only
-enum { kTile64x32, kTile64x64, kTile64x64Pair, kTile128x64, kTile128x128, kTile256x128 };
+enum { kTile64x32, kTile64x64, kTile64x64Pair, kTile128x64, kTile128x128, kTile256x128,
+       // on 32 x 32 instructions (gemm_kernel): 64 x 64 to 128 x 128 in workgroups of four waves, two per CU
+       kTile64x64Pair32, kTile128x64Pair32, kTile128x128Pair32, kTile256x192, kTile192x256 };
 hipError_t launch_gemm_tiles16(const GemmArgs& a, int tile, hipStream_t stream);
-// T <= kRowsTokens, any operand widths: weights streamed into registers, waves split K (quik_gemm_rows.hip)
+// T <= kRowsTokens, any operand widths: weights streamed through LDS rings of single waves that split K
+// (quik_gemm_rows.hip)
 constexpr int kRowsTokens = 32;
 hipError_t launch_gemm_rows(const GemmArgs& a, int cus, hipStream_t stream);
+// What the rules choose for a shape on `cus` compute units (host only; launch_gemm launches exactly this).
+// family: 1 gemm_rows_kernel, 2 gemm_kernel, 3 gemm_tiles16_kernel, 4 gemm_stream_kernel (tile: its 256 rows and
+// narrower tile width); rows x cols of output per workgroup, waves per workgroup, groups of waves that split K
+struct GemmForm { int family, rows, cols, waves, k_groups; };
+GemmForm choose_gemm_form(int T, int N, int K_b, int bits, int w_bits, int cus);
+GemmForm choose_rows_form(int T, int N, int K_b, int bits, int w_bits, int cus);
 hipError_t launch_weight_reduce(const WeightReduceArgs& a, hipStream_t stream);
 bool plan_gemm_stream(int T, int N, int K_b, int cus, StreamPlan* p);
 int choose_gemm_stream(int T, int N, int K_b, int cus, StreamPlan* p);   // 0 cannot, 1 chosen, 2 possible but not chosen

@@ -117,7 +117,7 @@ INT_GEMM_SHAPES = [
     (16, 512, 480, 8), (150, 140, 1000, 8), (257, 129, 4864, 8),
     # enough 256 x 128 tiles to take the eight-wave configuration, ragged in T and N, K tail
     (520, 11000, 480, 4), (770, 5500, 224, 8),
-    # the 1.5x-area tiles (256 x 192 for the shape above, 192 x 256 for this one): the accumulator hook
+    # the 1.5x-area tiles (256 x 192 for the 4-bit shape above, 192 x 256 for this one): the accumulator hook
     # takes the tile choice of the fused call in every mode
     (576, 16640, 224, 4),
     # one round of 256 x 128 tiles: the 16 x 16 per-tile kernel, both widths, K tail
@@ -214,7 +214,8 @@ LINEAR_SHAPES = [
     # eight-wave 256 x 128 tile configuration (>= 256 such tiles), ragged T and N
     synth.LayerShape("big_tiles_ragged", 520, 512, 11000, 32, 4, seed=38),
     synth.LayerShape("big_tiles_w8a8", 770, 256, 5500, 24, 8, seed=39),
-    # 1.5x-area tiles: 256 x 192 is picked for the two shapes above; 192 x 256 for these
+    # 1.5x-area tiles: 256 x 192 is picked for the 4-bit shape above (its 8-bit neighbour stays on 256 x 128);
+    # 192 x 256 for these
     synth.LayerShape("tiles_192x256", 576, 256, 16640, 32, 4, seed=49),
     synth.LayerShape("tiles_192x256_w8a8_ragged", 570, 256, 16630, 24, 8, seed=50),
     # exactly one round of 256 x 128 tiles beats the larger tiles: the per-tile kernel on the 16 x 16 matrix
