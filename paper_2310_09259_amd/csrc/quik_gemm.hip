@@ -29,7 +29,7 @@
 // uses v_mfma_f32_32x32x16_f16, whose accumulator has the same layout, so the
 // dequantized tile is simply the C operand of the outlier stages.
 //
-// This kernel takes equal operand widths; 4-bit weights under 8-bit activations: see quik_gemm_tiles16.hip.
+// Mixed widths (4-bit weights under 8-bit activations): see MIXED in gemm_kernel.
 //
 // Pipeline.  A workgroup of four or eight waves owns a BM x BN output tile.  Operand panels
 // are copied global -> LDS without passing through registers (buffer_load ... lds,
@@ -66,7 +66,8 @@ using namespace gemm_dev;
 // stage, NST stage buffers, GM = m-tiles per group of the tile order (0: plain column sweep).
 // MODE 0: fused epilogue (asymmetric widening for 4 bits); MODE 1: write raw INT32 accumulators,
 // symmetric widening; MODE 2: raw accumulators, asymmetric widening plus correction terms.
-template <int BITS, int BM, int BN, int WM, int WN, int BKB, int NST, int OCC, int GM, int MODE>
+// BITS: activation bits; WBITS: weight bits (equal, or 4-bit weights under 8-bit activations).
+template <int BITS, int WBITS, int BM, int BN, int WM, int WN, int BKB, int NST, int OCC, int GM, int MODE>
 __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_kernel(GemmArgs a) {
     constexpr bool RAW = MODE != 0;
     constexpr bool ASYM = (BITS == 4) && (MODE != 1);
@@ -76,6 +77,12 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_kernel(GemmArgs a) {
     // allocation left part of the SIMD's file free).
     static_assert(WM * WN * OCC == 8, "two waves per SIMD");
     asm volatile("" ::: "v255");
+    // Mixed layers: a stage still covers BKB activation bytes = BKB k, which is only BKB/2 packed
+    // weight bytes.  The weight nibbles are widened to 16x int8 (even / odd k of a word in two
+    // registers); the int8 activations are brought into the same k order with two byte permutes
+    // per 8 elements.  Accumulators are exactly 16x the integer dot product.
+    constexpr bool MIXED = (BITS == 8 && WBITS == 4);
+    static_assert(WBITS == BITS || MIXED, "weights: same width as the activations, or 4 under 8");
     constexpr int NWAVES = WM * WN, NT = NWAVES * 64;
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
     constexpr int CPR = BKB / 16, RPI = 64 / CPR;
@@ -83,8 +90,14 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_kernel(GemmArgs a) {
     static_assert(A_INSTR >= 1 && B_INSTR >= 1, "tile too small for the wave count");
     constexpr int LPS = A_INSTR + B_INSTR;
     constexpr int KSUB = BKB / 32;
-    constexpr int SHIFT = (BITS == 4) ? (ASYM ? 4 : 8) : 0;
+    constexpr int SHIFT = (BITS == 4) ? (ASYM ? 4 : 8) : (MIXED ? 4 : 0);
     constexpr int A_BYTES = BM * BKB, B_BYTES = BN * BKB, ST_BYTES = A_BYTES + B_BYTES;
+    // mixed int stages: weight rows of BKW bytes, RPW rows per DMA instruction, WI instructions
+    // per wave; the remaining B_INSTR - WI slots of a stage are issued as empty (out-of-range)
+    // loads so that every stage counts the same number of DMA instructions
+    constexpr int BKW = BKB / 2, CPW = BKW / 16, RPW = 64 / CPW;
+    constexpr int WI = MIXED ? BN / RPW / NWAVES : B_INSTR;
+    static_assert(!MIXED || (WI >= 1 && BKB == 128), "mixed layers: tile too small for the wave count");
     constexpr int NF = TM + TN;
     constexpr int HALVES = (BITS == 4) ? 2 : 1;          // MFMAs per output tile per sub-step
     constexpr int SLOTS = TM * TN * HALVES;
@@ -159,12 +172,33 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_kernel(GemmArgs a) {
     }
     const uint32_t m0A = lds_base + wave_u * A_INSTR * 1024;
     const uint32_t m0B = lds_base + A_BYTES + wave_u * B_INSTR * 1024;
+    // mixed int stages: geometry of the half-width weight rows
+    uint32_t voW[WI];
+    int chW[WI];
+    if constexpr (MIXED) {
+#pragma unroll
+        for (int i = 0; i < WI; ++i) {
+            int row = (wave_u * WI + i) * RPW + lane / CPW;
+            int c = ((lane % CPW) ^ swz<BKW>(row)) * 16;
+            chW[i] = c;
+            voW[i] = (uint32_t)(row * a.ldw + c);
+        }
+    }
+    const uint32_t m0W = lds_base + A_BYTES + wave_u * WI * 1024;
+    // where a mixed stage's empty loads land: this wave's 1 KB of the unused half of the B region
+    const uint32_t m0D = lds_base + A_BYTES + BN * BKW + wave_u * 1024;
+    static_assert(!MIXED || NWAVES * 1024 <= BN * BKW, "no room for the empty loads");
+
     // DMA instruction d of a full (unguarded) int stage
     auto issue_one = [&](int s, int d) {
         const uint32_t sb = (uint32_t)(s % NST) * ST_BYTES;
         const uint32_t so = (uint32_t)s * BKB;
         if (d < A_INSTR) {
             dma16(rA, m0A + sb + d * 1024, voA[d < A_INSTR ? d : 0], so);
+        } else if constexpr (MIXED) {
+            const int j = d - A_INSTR;
+            if (j < WI) dma16(rB, m0W + sb + j * 1024, voW[j < WI ? j : 0], (uint32_t)s * BKW);
+            else dma16(rB, m0D + sb, kOob, 0);
         } else {
             dma16(rB, m0B + sb + (d - A_INSTR) * 1024, voB[d >= A_INSTR ? d - A_INSTR : 0], so);
         }
@@ -176,18 +210,29 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_kernel(GemmArgs a) {
         const int koff = (fp ? s - nk_int : s) * BKB;
         // integer stages stop at the 16-byte piece that holds a row's last packed byte: what lies beyond may
         // be anything in the weight matrix
-        const int lim = s < nk ? (fp ? fp_bytes : int_bytes) : 0;
+        const int lima = s < nk ? (fp ? fp_bytes : int_bytes) : 0;
+        const int limb = s < nk ? (fp ? fp_bytes : (MIXED ? (((a.K_b / 2) + 15) & ~15) : int_bytes)) : 0;
         const int lda = fp ? lda_fp : a.ldq, ldb = fp ? ldb_fp : a.ldw;
         const v4i ra_ = fp ? rAf : rA;
         const v4i rb_ = fp ? rBf : rB;
 #pragma unroll
         for (int i = 0; i < A_INSTR; ++i) {
-            uint32_t vo = (koff + chA[i] < lim) ? (uint32_t)(rwA[i] * lda + koff + chA[i]) : kOob;
+            uint32_t vo = (koff + chA[i] < lima) ? (uint32_t)(rwA[i] * lda + koff + chA[i]) : kOob;
             dma16(ra_, m0A + sb + i * 1024, vo, 0);
+        }
+        if (MIXED && !fp) {
+            const int koffw = s * BKW;
+#pragma unroll
+            for (int i = 0; i < B_INSTR; ++i) {
+                uint32_t vo = kOob;
+                if (i < WI && koffw + chW[i < WI ? i : 0] < limb) vo = voW[i < WI ? i : 0] + (uint32_t)koffw;
+                dma16(rb_, (i < WI ? m0W + i * 1024 : m0D) + sb, vo, 0);
+            }
+            return;
         }
 #pragma unroll
         for (int i = 0; i < B_INSTR; ++i) {
-            uint32_t vo = (koff + chB[i] < lim) ? (uint32_t)(rwB[i] * ldb + koff + chB[i]) : kOob;
+            uint32_t vo = (koff + chB[i] < limb) ? (uint32_t)(rwB[i] * ldb + koff + chB[i]) : kOob;
             dma16(rb_, m0B + sb + i * 1024, vo, 0);
         }
     };
@@ -251,8 +296,30 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_kernel(GemmArgs a) {
     uint4 R[RD][NF];
     v4i U[2][NF][HALVES];
 
+    // mixed int stages: 8 bytes (16 nibbles = this lane's k-group) of a half-width weight row
+    uint32_t rdw[MIXED ? TN : 1][KSUB];
+    if constexpr (MIXED) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int r = wn * TN * 32 + j * 32 + l32;
+#pragma unroll
+            for (int ks = 0; ks < KSUB; ++ks) rdw[j][ks] = A_BYTES + r * BKW + ((ks ^ swz<BKW>(r)) << 4) + g * 8;
+        }
+    }
     auto read_frag = [&](int set, int f, const uint8_t* stage, int ks) {
         R[set][f] = *reinterpret_cast<const uint4*>(stage + rd[f][ks]);
+    };
+    // fragment f of sub-step ks of a stage that is an int stage (wide == false) or an fp16 stage
+    auto read_any = [&](int set, int f, const uint8_t* stage, int ks, bool wide) {
+        if constexpr (MIXED) {
+            if (f >= TM && !wide) {
+                const uint2 v = *reinterpret_cast<const uint2*>(stage + rdw[f >= TM ? f - TM : 0][ks]);
+                R[set][f].x = v.x;
+                R[set][f].y = v.y;
+                return;
+            }
+        }
+        read_frag(set, f, stage, ks);
     };
     auto widen_word = [&](int set, int rset, int w) {
         const int f = w >> 2, k = w & 3;
@@ -271,6 +338,17 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_kernel(GemmArgs a) {
             }
             U[set][f][k >> 1][(k & 1) * 2] = (int)(act ? hi : lo);
             U[set][f][k >> 1][(k & 1) * 2 + 1] = (int)(act ? lo : hi);
+        } else if constexpr (MIXED) {
+            if (f < TM) {
+                // int8 activations k0..k15 -> [even k of the low 8 | odd | even of the high 8 | odd]
+                const uint32_t lo = (k < 2) ? R[rset][f].x : R[rset][f].z, hi = (k < 2) ? R[rset][f].y : R[rset][f].w;
+                U[set][f][0][k] = (int)__builtin_amdgcn_perm(hi, lo, (k & 1) ? 0x07050301u : 0x06040200u);
+            } else {
+                // packed weights: word k/2 holds 8 nibbles; even k (low nibbles) / odd k (high), 16x
+                constexpr uint32_t M = 0xF0F0F0F0u;
+                const uint32_t wv = (k < 2) ? R[rset][f].x : R[rset][f].y;
+                U[set][f][0][k] = (int)((k & 1) ? (wv & M) : ((wv << 4) & M));
+            }
         } else {
             U[set][f][0][k] = (int)x;
         }
@@ -319,6 +397,7 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_kernel(GemmArgs a) {
         const int ts = (ks + LA < KSUB) ? s : s + 1, tks = (ks + LA) % KSUB;
         const uint8_t* tgt = lds + (ts % NST) * ST_BYTES;
         const int rnext = (ks + 1) % RD, rload = (ks + LA) % RD;   // static: KSUB is a multiple of RD
+        const bool wide = ts >= nk_int;                             // the look-ahead reaches the fp16 part
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int m = 0; m < SLOTS; ++m) {
@@ -333,9 +412,9 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_kernel(GemmArgs a) {
 #pragma unroll
             for (int w = 0; w < WORDS; ++w)
                 if (w * SLOTS / WORDS == m) widen_word(par ^ 1, rnext, w);
-            if (m < NF) read_frag(rload, m, tgt, tks);
+            if (m < NF) read_any(rload, m, tgt, tks, wide);
             if (SLOTS < NF && m == SLOTS - 1)
-                for (int f = SLOTS; f < NF; ++f) read_frag(rload, f, tgt, tks);
+                for (int f = SLOTS; f < NF; ++f) read_any(rload, f, tgt, tks, wide);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
@@ -345,7 +424,7 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_kernel(GemmArgs a) {
 #pragma unroll
     for (int q = 0; q < LA; ++q)
 #pragma unroll
-        for (int f = 0; f < NF; ++f) read_frag(q, f, lds, q);
+        for (int f = 0; f < NF; ++f) read_any(q, f, lds, q, nk_int == 0);
 #pragma unroll
     for (int w = 0; w < WORDS; ++w) widen_word(0, 0, w);
 
@@ -485,10 +564,10 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_kernel(GemmArgs a) {
         }
 }
 
-template <int BITS, int BM, int BN, int WM, int WN, int BKB, int NST, int OCC, int GM, int MODE>
+template <int BITS, int WBITS, int BM, int BN, int WM, int WN, int BKB, int NST, int OCC, int GM, int MODE>
 hipError_t launch_cfg(const GemmArgs& a, hipStream_t stream) {
     int tiles = ((a.T + BM - 1) / BM) * ((a.N + BN - 1) / BN);
-    hipLaunchKernelGGL((gemm_kernel<BITS, BM, BN, WM, WN, BKB, NST, OCC, GM, MODE>), dim3(tiles),
+    hipLaunchKernelGGL((gemm_kernel<BITS, WBITS, BM, BN, WM, WN, BKB, NST, OCC, GM, MODE>), dim3(tiles),
                        dim3(WM * WN * 64), 0, stream, a);
     return hipGetLastError();
 }
@@ -529,8 +608,13 @@ int choose_tile_4bit(int T, int N, int K_b, int cus) {
     return kTile256x128;
 }
 
-// 8-bit activations: the tile with the least rounds * (fixed + per_stage * stages), a stage being 128 k.  The two
-// figures of a tile are a line through its measured time per round (us, weights from HBM, N = 4096 .. 28672):
+// 8-bit activations: the tile whose launch is estimated to be the shortest.  One workgroup of eight waves per CU:
+// rounds * (fixed + per_stage * stages), a stage being 128 k.  Workgroups of four waves go two to a CU
+// (pair_fixed > 0): up to one per CU they take the same line; when some CUs hold two, pair_fixed + (pair_per_stage +
+// pair_more * share of CUs that do) * stages, the launch lasting as long as such a CU but slowed by how many there
+// are; every further two per CU that again, and a remainder `rest` of what it would take by itself, as the CUs have
+// drifted apart by then.
+// Measured lines behind it (us; integer stages; both from HBM unless said otherwise, N = 4096 .. 28672):
 //   integer stages              4      6     14     30     84
 //   W8A8  64 x 32             5.5    5.8    7.0   10.2   18.5 - 22.8
 //         64 x 64             6.1    5.9    8.0   13.4   26 - 30
@@ -544,18 +628,51 @@ int choose_tile_4bit(int T, int N, int K_b, int cus) {
 //         128 x 64            9.5    9.0   12.0   17.7   33 - 37
 //         128 x 128          13.8   12.3   17.2   26.6   54
 //         256 x 128          15.8   15.6   22.0   36     79
-// What that changed (before: 64 x 64, 128 x 64, 128 x 128 on 32 x 32 matrix instructions with two or four stages,
-// 256 x 128 with two): W8A8 K=11008 N=4096 T=64 39.4 -> 23.3, T=128 68.5 -> 22.8, T=300 75.0 -> 32.2, T=2048 101 -> 88;
-// K=5000 N=4090 T=777 40.7 -> 29.8; W4A8 K=11008 N=4096 T=64 56.3 -> 21.1, T=128 55.1 -> 20.7, T=333 63.8 -> 33.9,
-// T=1024 66.4 -> 56.5.
-struct TileCost { int tile, bm, bn; double fixed, per_stage; };
-constexpr TileCost kCost8[] = {{kTile64x32, 64, 32, 5.2, 0.17},    {kTile64x64, 64, 64, 5.2, 0.28},
-                               {kTile64x64Pair, 64, 64, 3.0, 0.33}, {kTile128x64, 128, 64, 7.6, 0.31},
-                               {kTile128x128, 128, 128, 6.5, 0.58}, {kTile256x128, 256, 128, 9.5, 0.92},
-                               {kTile256x192, 256, 192, 13.5, 1.25}, {kTile192x256, 192, 256, 13.5, 1.25}};
-constexpr TileCost kCost8w4[] = {{kTile64x32, 64, 32, 5.4, 0.17},    {kTile64x64, 64, 64, 5.8, 0.24},
-                                 {kTile64x64Pair, 64, 64, 3.0, 0.30}, {kTile128x64, 128, 64, 8.0, 0.31},
-                                 {kTile128x128, 128, 128, 9.8, 0.55}, {kTile256x128, 256, 128, 11.5, 0.82}};
+//   128 x 128 in pairs (gemm_kernel; weights cached / from HBM), tiles on 256 CUs:
+//   W8A8  256        10.0/11.7   10.7/13.2   14.3/19.6   27.7/32.9
+//         272        12.6/13.2   13.9/14.8   20.4/21.4   30.0/35.0       (256 x 128: 13.7/14.2, 15.2/16.0, 20.9/22.1, 32.1/36.6)
+//         500        13.9/15.7   16.1/18.4   24.0/28.6   39.8/49.2       (256 x 128: 14.7/15.8, 16.2/17.7, 23.4/25.0, 36.1/40.7)
+//   W4A8  256        11.4/12.2   12.4/13.5   16.5/18.7   27.6/29.8
+//         272        14.0/14.2   15.6/15.5   20.7/21.5   33.9/32.6       (256 x 128: 14.7/14.8, 16.4/16.5, 22.5/22.9, 36.4/36.6)
+//         500        15.0/16.3   17.1/18.9   24.7/27.1   41.0/43.1       (256 x 128: 16.0/15.7, 17.3/17.7, 24.2/24.9, 39.4/40.1)
+// The figures of the table are fitted, with cached weights and from HBM alike, to what loses least against the best
+// tile over 900 shapes with every tile measured (T 33 .. 4096, K 512 .. 11008, N 512 .. 28672): they rank the tiles of
+// a shape rather than predict its time.  Against the fastest tile the choice costs 0.9 % (W8A8) and 0.4 % (W4A8) in the
+// mean.  With lines through the times from HBM alone and without the workgroups of four waves on 32 x 32 instructions,
+// shapes like these took (cached / from HBM): W4A8 T=384 K=1024 N=24000 31.4/32.0 (now 26.4/30.4), T=120 K=1008 N=16448
+// 13.5/14.2 (10.1/13.2), T=512 K=4096 N=8704 36.4/36.7 (34.8/33.0), T=508 K=592 N=5260 14.0/14.5 (11.1/11.6); W8A8
+// T=947 K=1520 N=4232 18.8/21.6 (18.3/19.8), T=333 K=960 N=11008 13.9/14.6 (12.6/13.7).  Where the two states disagree
+// the fit takes the middle: W8A8 T=200 K=960 N=21100 18.2/20.6 (17.6/22.0).
+struct TileCost { int tile, bm, bn; double fixed, per_stage, pair_fixed, pair_per_stage, pair_more, rest; };
+constexpr TileCost kCost8[] = {{kTile64x32, 64, 32, 5.44, 0.126, 0, 0, 0, 0},
+                               {kTile64x64, 64, 64, 5.79, 0.218, 0, 0, 0, 0},
+                               {kTile64x64Pair, 64, 64, 3.87, 0.311, 4.51, 0.605, 0, 0.71},
+                               {kTile64x64Pair32, 64, 64, 2.61, 0.493, 3.54, 0.631, 0.117, 0.79},
+                               {kTile128x64, 128, 64, 6.71, 0.281, 0, 0, 0, 0},
+                               {kTile128x128Pair32, 128, 128, 7.17, 0.778, 6.51, 0.913, 0.405, 0.93},
+                               {kTile128x128, 128, 128, 6.95, 0.415, 0, 0, 0, 0},
+                               {kTile256x128, 256, 128, 9.89, 0.65, 0, 0, 0, 0},
+                               {kTile256x192, 256, 192, 11.0, 0.897, 0, 0, 0, 0},
+                               {kTile192x256, 192, 256, 11.0, 0.897, 0, 0, 0, 0}};
+constexpr TileCost kCost8w4[] = {{kTile64x32, 64, 32, 6.12, 0.118, 0, 0, 0, 0},
+                                 {kTile64x64, 64, 64, 6.6, 0.203, 0, 0, 0, 0},
+                                 {kTile64x64Pair, 64, 64, 4.07, 0.406, 5.17, 0.485, 0, 0.88},
+                                 {kTile128x64Pair32, 128, 64, 6.12, 0.569, 5.67, 0.692, 0.106, 0.99},
+                                 {kTile128x64, 128, 64, 8.11, 0.288, 0, 0, 0, 0},
+                                 {kTile128x128Pair32, 128, 128, 7.5, 0.736, 9.6, 0.649, 0.322, 0.743},
+                                 {kTile128x128, 128, 128, 10.52, 0.487, 0, 0, 0, 0},
+                                 {kTile256x128, 256, 128, 10.33, 0.82, 0, 0, 0, 0}};
+
+double launch_cost(const TileCost& t, long tiles, int cus, int stages) {
+    const double alone = t.fixed + t.per_stage * stages;
+    if (t.pair_fixed == 0) return (double)((tiles + cus - 1) / cus) * alone;
+    auto up_to_two = [&](long n) {
+        return n <= cus ? alone : t.pair_fixed + (t.pair_per_stage + t.pair_more * (double)(n - cus) / cus) * stages;
+    };
+    if (tiles <= 2L * cus) return up_to_two(tiles);
+    const long full = tiles / (2L * cus), left = tiles % (2L * cus);
+    return (double)full * up_to_two(2L * cus) + (left ? t.rest * up_to_two(left) : 0.0);
+}
 
 int choose_tile_8bit(int T, int N, int K_b, bool mixed, int cus) {
     const int stages = (K_b + 127) / 128;
@@ -564,10 +681,7 @@ int choose_tile_8bit(int T, int N, int K_b, bool mixed, int cus) {
     int best = 0;
     double least = 0.0;
     for (int i = 0; i < count; ++i) {
-        const long rounds = rounds_of(T, N, list[i].bm, list[i].bn, cus);
-        // (a four-wave workgroup alone on its CU has nothing to overlap with: 6.2 us at 8 stages, 15.4 at 30)
-        const double per_stage = (list[i].tile == kTile64x64Pair && rounds == 1) ? 0.42 : list[i].per_stage;
-        const double c = (double)rounds * (list[i].fixed + per_stage * stages);
+        const double c = launch_cost(list[i], tiles_of(T, N, list[i].bm, list[i].bn), cus, stages);
         if (i == 0 || c < least) { best = i; least = c; }
     }
     return list[best].tile;
@@ -577,20 +691,22 @@ int choose_tile(int T, int N, int K_b, int bits, bool mixed, int cus) {
     return bits == 4 ? choose_tile_4bit(T, N, K_b, cus) : choose_tile_8bit(T, N, K_b, mixed, cus);
 }
 
-template <int BITS, int MODE>
+template <int BITS, int WBITS, int MODE>
 hipError_t launch_tile(const GemmArgs& a, int tile, hipStream_t stream) {
     switch (tile) {
     case kTile64x64Pair32:
-        if constexpr (BITS == 4) return launch_cfg<4, 64, 64, 2, 2, 128, 4, 2, 0, MODE>(a, stream);
+        if constexpr (BITS == WBITS) return launch_cfg<BITS, WBITS, 64, 64, 2, 2, 128, 4, 2, 0, MODE>(a, stream);
         else break;
     case kTile128x64Pair32:
-        if constexpr (BITS == 4) return launch_cfg<4, 128, 64, 2, 2, 128, 2, 2, 0, MODE>(a, stream);
+        if constexpr (WBITS == 4) return launch_cfg<BITS, WBITS, 128, 64, 2, 2, 128, 2, 2, 0, MODE>(a, stream);
         else break;
-    case kTile128x128Pair32:
-        if constexpr (BITS == 4) return launch_cfg<4, 128, 128, 2, 2, 128, 2, 2, 8, MODE>(a, stream);
+    case kTile128x128Pair32: return launch_cfg<BITS, WBITS, 128, 128, 2, 2, 128, 2, 2, 8, MODE>(a, stream);
+    case kTile256x192:
+        if constexpr (BITS == WBITS) return launch_cfg<BITS, WBITS, 256, 192, 4, 2, 128, 2, 1, 4, MODE>(a, stream);
         else break;
-    case kTile256x192: return launch_cfg<BITS, 256, 192, 4, 2, 128, 2, 1, 4, MODE>(a, stream);
-    case kTile192x256: return launch_cfg<BITS, 192, 256, 2, 4, 128, 2, 1, 4, MODE>(a, stream);
+    case kTile192x256:
+        if constexpr (BITS == WBITS) return launch_cfg<BITS, WBITS, 192, 256, 2, 4, 128, 2, 1, 4, MODE>(a, stream);
+        else break;
     default: return launch_gemm_tiles16(a, tile, stream);
     }
     return hipErrorInvalidValue;
@@ -691,10 +807,12 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t stream) {
 hipError_t launch_gemm_tiles(const GemmArgs& a, int cus, hipStream_t stream) {
     const bool raw = a.y == nullptr;
     if (cus < 1) cus = 256;              // the count could not be read: any value gives a working choice
-    const int tile = choose_tile(a.T, a.N, a.K_b, a.bits, a.bits == 8 && a.w_bits == 4, cus);
-    if (a.bits == 8) return raw ? launch_tile<8, 1>(a, tile, stream) : launch_tile<8, 0>(a, tile, stream);
-    if (!raw) return launch_tile<4, 0>(a, tile, stream);
-    return (a.code_sum && a.w_code_sum) ? launch_tile<4, 2>(a, tile, stream) : launch_tile<4, 1>(a, tile, stream);
+    const bool mixed = a.bits == 8 && a.w_bits == 4;
+    const int tile = choose_tile(a.T, a.N, a.K_b, a.bits, mixed, cus);
+    if (mixed) return raw ? launch_tile<8, 4, 1>(a, tile, stream) : launch_tile<8, 4, 0>(a, tile, stream);
+    if (a.bits == 8) return raw ? launch_tile<8, 8, 1>(a, tile, stream) : launch_tile<8, 8, 0>(a, tile, stream);
+    if (!raw) return launch_tile<4, 4, 0>(a, tile, stream);
+    return (a.code_sum && a.w_code_sum) ? launch_tile<4, 4, 2>(a, tile, stream) : launch_tile<4, 4, 1>(a, tile, stream);
 }
 
 GemmForm choose_gemm_form(int T, int N, int K_b, int bits, int w_bits, int cus) {

@@ -27,15 +27,18 @@ def form(T, N, K_b, bits, w_bits):
 
 TILE_RULES = {                         # shapes of tests/test_gpu_tile_rules.py: 4-bit, 8-bit, 4-bit weights under 8
     (33, 70, 2056, 72): (T64x32, T64x32, T64x32),
-    (65, 35, 48, 0): (S64x64, T64x64_PAIR, T64x64_PAIR),
+    (65, 35, 48, 0): (S64x64, S64x64, T64x64_PAIR),
     (129, 2040, 1880, 24): (T64x32, T64x32, T64x32),
-    (100, 8150, 520, 40): (S64x64, T64x64_PAIR, T64x64_PAIR),
+    (100, 8150, 520, 40): (S64x64, S64x64, T64x64_PAIR),
     (100, 8150, 5200, 40): (S64x64, T64x64, T64x64),
     (130, 8190, 4432, 80): (S64x64, T128x64, T128x64),
-    (130, 8190, 648, 136): (S64x64, T64x64_PAIR, T64x64_PAIR),
-    (128, 16400, 264, 8): (S128x64, T128x128, T64x64_PAIR),
-    (250, 16300, 264, 8): (S128x128, T128x128, T128x128_K2),
-    (500, 16000, 304, 48): (S128x128, T256x128, T256x128),
+    (130, 8190, 648, 136): (S64x64, S64x64, T64x64_PAIR),
+    (128, 16400, 264, 8): (S128x64, T128x128, S128x64),
+    (250, 16300, 264, 8): (S128x128, T128x128, S128x64),
+    (500, 16000, 304, 48): (S128x128, S128x128, S128x128),
+    (120, 9904, 1032, 128): (S64x64, S64x64, T64x64_PAIR),
+    (120, 16472, 1240, 72): (S128x64, T128x128, S128x64),
+    (300, 11080, 1240, 40): (S128x128, S128x128, S128x128),
 }
 
 
@@ -43,6 +46,22 @@ def test_tile_rule_shapes_run_the_tiles_they_name():
     assert set(test_gpu_tile_rules.SHAPES) == set(TILE_RULES)
     for (T, N, K, n_out), want in TILE_RULES.items():
         assert tuple(form(T, N, K - n_out, *w) for w in WIDTHS) == want, (T, N, K, n_out)
+
+
+# The band in which workgroups of four waves, two per CU, are ahead (T, K, N, n_out, w_bits; a 256 x 128 or 128 x 128
+# tile per CU took these while the pairs were gone, 5 - 30 % slower)
+PAIRS = [
+    (512, 4096, 8704, 256, 4), (384, 1024, 24000, 256, 4), (947, 1520, 4232, 256, 4), (333, 1520, 11008, 256, 4),
+    (466, 5008, 10880, 328, 4), (1143, 5568, 3648, 712, 4), (1348, 1600, 3264, 256, 4), (120, 1008, 16448, 128, 4),
+    (508, 592, 5260, 144, 4), (947, 1520, 4232, 256, 8), (333, 960, 11008, 128, 8), (510, 672, 8384, 168, 8),
+    (512, 1536, 8704, 256, 8),
+]
+
+
+def test_few_more_than_one_large_tile_per_cu_run_in_pairs():
+    for T, K, N, n_out, w_bits in PAIRS:
+        kernel, (rows_, cols, waves, groups) = form(T, N, K - n_out, 8, w_bits)
+        assert (kernel, waves, groups) == (2, 4, 1), (T, K, N, n_out, w_bits)
 
 
 FEW_TOKENS = {                         # shapes of tests/test_gpu_few_tokens.py: channels and waves up to 16 / to 32 tokens
@@ -65,9 +84,9 @@ def test_few_token_shapes_run_the_forms_they_name():
 
 
 LINEAR = {                             # layers of tests/test_gpu_parity.py that are there for their tile
-    "big_tiles_ragged": S256x192, "big_tiles_w8a8": T256x128, "tiles_192x256": S192x256,
-    "tiles_192x256_w8a8_ragged": S192x256, "tiles16_256x128_ragged": T256x128, "tiles16_256x128_w8a8_ragged": T256x128,
-    "t32_ragged_n": rows(32, 16, 4), "t5_w8a8": rows(16, 16, 4), "t100": S64x64, "t60_w8a8": T64x64_PAIR,
+    "big_tiles_ragged": S256x192, "big_tiles_w8a8": S128x128, "tiles_192x256": S192x256,
+    "tiles_192x256_w8a8_ragged": S192x256, "tiles16_256x128_ragged": T256x128, "tiles16_256x128_w8a8_ragged": S128x128,
+    "t32_ragged_n": rows(32, 16, 4), "t5_w8a8": rows(16, 16, 4), "t100": S64x64, "t60_w8a8": S64x64,
 }
 
 

@@ -120,7 +120,7 @@ INT_GEMM_SHAPES = [
     # the 1.5x-area tiles (256 x 192 for the 4-bit shape above, 192 x 256 for this one): the accumulator hook
     # takes the tile choice of the fused call in every mode
     (576, 16640, 224, 4),
-    # one round of 256 x 128 tiles: the 16 x 16 per-tile kernel, both widths, K tail
+    # one round of 256 x 128 tiles: the 16 x 16 per-tile kernel (8 bits: 128 x 128 tiles in pairs), K tail
     (1000, 8190, 368, 4), (1000, 8190, 232, 8),
     # small-T paths: K-split kernel (T <= 32; K shorter than four stages, ragged N), 64 x 64 and
     # 128 x 64 tile configurations
@@ -214,12 +214,12 @@ LINEAR_SHAPES = [
     # eight-wave 256 x 128 tile configuration (>= 256 such tiles), ragged T and N
     synth.LayerShape("big_tiles_ragged", 520, 512, 11000, 32, 4, seed=38),
     synth.LayerShape("big_tiles_w8a8", 770, 256, 5500, 24, 8, seed=39),
-    # 1.5x-area tiles: 256 x 192 is picked for the 4-bit shape above (its 8-bit neighbour stays on 256 x 128);
-    # 192 x 256 for these
+    # 1.5x-area tiles: 256 x 192 is picked for the 4-bit shape above (its 8-bit neighbour runs 128 x 128 tiles, two
+    # per CU); 192 x 256 for these
     synth.LayerShape("tiles_192x256", 576, 256, 16640, 32, 4, seed=49),
     synth.LayerShape("tiles_192x256_w8a8_ragged", 570, 256, 16630, 24, 8, seed=50),
     # exactly one round of 256 x 128 tiles beats the larger tiles: the per-tile kernel on the 16 x 16 matrix
-    # instructions (4-bit and 8-bit forms), ragged T, N and K
+    # instructions (the 8-bit layer, with two stages, runs 128 x 128 tiles on 32 x 32 ones), ragged T, N and K
     synth.LayerShape("tiles16_256x128_ragged", 1000, 392, 8184, 24, 4, seed=55),
     synth.LayerShape("tiles16_256x128_w8a8_ragged", 1000, 280, 8184, 40, 8, seed=56),
     # small-T paths

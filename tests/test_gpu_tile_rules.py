@@ -8,18 +8,22 @@ from tests.util import output_within_tolerance, to_dev, upload
 
 pytestmark = pytest.mark.gpu
 
-# T, N, K, n_out.  With 256 compute units the tiles are, for 4 / 8 / 4-under-8 bits (P: two workgroups per CU):
+# T, N, K, n_out.  The tiles they run on 256 compute units, for 4 / 8 / 4-under-8 bits, are asserted in
+# test_gemm_forms.py (S: 32 x 32 matrix instructions, T: 16 x 16, P: two workgroups per CU):
 SHAPES = [
-    (33, 70, 2056, 72),       # 64 x 32 for all; eight and sixteen integer stages, the last not full, two outlier stages
-    (65, 35, 48, 0),          # P for all: one stage, no outlier columns
-    (129, 2040, 1880, 24),    # 64 x 32 for all, ragged in both directions, one short outlier stage
-    (100, 8150, 520, 40),     # P for all (4 bits: 64 x 64 on 32 x 32 instructions)
-    (100, 8150, 5200, 40),    # P / 64 x 64 / 64 x 64
-    (130, 8190, 4432, 80),    # P / 128 x 64 / 128 x 64
-    (130, 8190, 648, 136),    # P for all
-    (128, 16400, 264, 8),     # 128 x 64 for 4 bits
-    (250, 16300, 264, 8),     # 128 x 128 for all
-    (500, 16000, 304, 48),    # 256 x 128 under 8-bit activations
+    (33, 70, 2056, 72),       # T 64 x 32 for all; eight and sixteen integer stages, the last not full, two outlier stages
+    (65, 35, 48, 0),          # S / S / T 64 x 64 P: one stage, no outlier columns
+    (129, 2040, 1880, 24),    # T 64 x 32 for all, ragged in both directions, one short outlier stage
+    (100, 8150, 520, 40),     # S / S / T 64 x 64 P
+    (100, 8150, 5200, 40),    # S 64 x 64 P / T 64 x 64 / T 64 x 64
+    (130, 8190, 4432, 80),    # S 64 x 64 P / T 128 x 64 / T 128 x 64
+    (130, 8190, 648, 136),    # S / S / T 64 x 64 P
+    (128, 16400, 264, 8),     # S 128 x 64 P / T 128 x 128 / S 128 x 64 P
+    (250, 16300, 264, 8),     # S 128 x 128 P / T 128 x 128 / S 128 x 64 P
+    (500, 16000, 304, 48),    # S 128 x 128 P for all
+    (120, 9904, 1032, 128),   # S / S / T 64 x 64 P: whole 16-byte output pieces, more stages than the ring has
+    (120, 16472, 1240, 72),   # S 128 x 64 P / T 128 x 128 / S 128 x 64 P: the same
+    (300, 11080, 1240, 40),   # S 128 x 128 P for all: the same
 ]
 
 
