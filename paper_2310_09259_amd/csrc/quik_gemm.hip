@@ -792,6 +792,16 @@ int choose_gemm_stream(int T, int N, int K_b, int cus, StreamPlan* plan) {
     return (T > kRowsTokens && K_b >= 2048 && plan->base >= 5 && 0.94 * blocks <= tiles_estimate(T, N, cus)) ? 1 : 2;
 }
 
+// Few tokens go to gemm_rows_kernel, except 17 to 32 tokens of W4A8 layers with more than one pair of 16-channel blocks
+// per CU: two activation lines per weight line and 32 rows of them fill the rings so far that a CU holds one
+// workgroup, and its rounds do not overlap.  us, weights cached / from HBM, this kernel against 64 x 64 tiles, T = 32:
+// N = 8192, K = 1280 5.5/5.7 : 8.3/8.3;  N = 14464, K = 768 8.5/9.1 : 7.2/7.8, K = 4352 14.6/15.1 : 13.3/13.9;
+// N = 27520, K = 768 15.2/16.8 : 8.7/9.5, K = 4352 27.2/27.9 : 19.2/23.1.
+static bool rows_take(int T, int N, int bits, int w_bits, int cus) {
+    if (T <= 16) return true;
+    return T <= kRowsTokens && !(bits == 8 && w_bits == 4 && N > 32L * (cus < 1 ? 256 : cus));
+}
+
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t stream) {
     const int cus = compute_units(), path = g_gemm_path;
     if (a.bits == 4 && !a.fp_only && (path == 1 || (path == 0 && a.T > kRowsTokens))) {
@@ -799,7 +809,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t stream) {
         const int c = choose_gemm_stream(a.T, a.N, a.K_b, cus, &plan);
         if (c == 1 || (c == 2 && path == 1)) return launch_gemm_stream(a, plan, stream);
     }
-    if (a.T <= kRowsTokens) return launch_gemm_rows(a, cus, stream);
+    if (rows_take(a.T, a.N, a.bits, a.w_bits, cus)) return launch_gemm_rows(a, cus, stream);
     return launch_gemm_tiles(a, cus, stream);
 }
 
@@ -820,7 +830,7 @@ GemmForm choose_gemm_form(int T, int N, int K_b, int bits, int w_bits, int cus) 
     StreamPlan plan;
     if (bits == 4 && T > kRowsTokens && choose_gemm_stream(T, N, K_b, cus, &plan) == 1)
         return GemmForm{4, kStreamRows, plan.base * 32, 8, 1};
-    if (T <= kRowsTokens) return choose_rows_form(T, N, K_b, bits, w_bits, cus);
+    if (rows_take(T, N, bits, w_bits, cus)) return choose_rows_form(T, N, K_b, bits, w_bits, cus);
     switch (choose_tile(T, N, K_b, bits, mixed, cus)) {
     case kTile64x32: return GemmForm{3, 64, 32, 8, 4};
     case kTile64x64: return GemmForm{3, 64, 64, 8, 2};

@@ -69,7 +69,7 @@ FEW_TOKENS = {                         # shapes of tests/test_gpu_few_tokens.py:
     (200, 4384, 288): [((16, 8), (16, 4))] * 3,
     (4096, 296, 24): [((16, 4), (16, 4))] * 3,
     (4104, 520, 40): [((32, 4), (32, 4))] * 3,
-    (8200, 280, 8): [((16, 4), (16, 4)), ((16, 4), (16, 4)), ((32, 4), (32, 4))],
+    (8200, 280, 8): [((16, 4), (16, 4)), ((16, 4), (16, 4)), ((32, 4), T64x64_PAIR)],
 }
 
 
@@ -80,7 +80,16 @@ def test_few_token_shapes_run_the_forms_they_name():
             for T in (1, 16):
                 assert form(T, N, K - n_out, *w) == rows(16, *upto16), (T, N, K, w)
             for T in (17, 32):
-                assert form(T, N, K - n_out, *w) == rows(32, *upto32), (T, N, K, w)
+                want_form = upto32 if upto32 == T64x64_PAIR else rows(32, *upto32)
+                assert form(T, N, K - n_out, *w) == want_form, (T, N, K, w)
+
+
+def test_wide_w4a8_layers_of_17_to_32_tokens_run_tiles():
+    for T in (17, 32):
+        assert form(T, 8192, 1024, 8, 4) == rows(32, 32, 4)
+        for N, K_b in ((8200, 272), (14464, 832), (18496, 384), (27526, 2032), (24412, 648), (27520, 10752)):
+            assert form(T, N, K_b, 8, 4)[0] == 3, (T, N, K_b)
+            assert form(T, N, K_b, 8, 8)[0] == form(T, N, K_b, 4, 4)[0] == form(16, N, K_b, 8, 4)[0] == 1, (T, N, K_b)
 
 
 LINEAR = {                             # layers of tests/test_gpu_parity.py that are there for their tile

@@ -10,7 +10,8 @@ pytestmark = pytest.mark.gpu
 
 # N, K, n_out.  With 256 compute units: one 16-channel block per CU at most (four waves; eight where a row has
 # sixteen 128-byte lines), pairs of blocks just above that, single blocks where pairs would leave the busiest CU
-# with more; a last line with one 16-byte piece, none and a short fp16 part, ragged N.
+# with more (4-bit weights under 8-bit activations: 64 x 64 tiles from 17 tokens on); a last line with one 16-byte
+# piece, none and a short fp16 part, ragged N.
 SHAPES = [
     (37, 264, 0), (200, 4384, 288), (4096, 296, 24), (4104, 520, 40), (8200, 280, 8),
 ]
