@@ -8,8 +8,8 @@
 //    streams the same number of bytes and the outlier weights ride in the same pipeline.  No barrier until the
 //    waves add up their partial sums (INT32 exactly, the fp32 partials in wave order) through LDS.
 //  - A wave copies its lines global -> LDS (16 bytes per lane, eight whole lines per instruction) into a private
-//    ring of NST stages, the weights with the non-temporal hint: they are read once, and without it their lines
-//    evict the activations and wait for the evictions.  A copy-only loop over 47 MB of such rows in HBM takes 8.3 us
+//    ring of NST stages, the weights mostly with the non-temporal hint (see `once` below): they are read once, and
+//    without it their lines evict the activations and wait for the evictions.  A copy-only loop over 47 MB of such rows in HBM takes 8.3 us
 //    with the hint (5.7 TB/s, launch included), 9.9 us without, 9.3 us into registers instead of LDS, and 10.8 us
 //    into registers in the matrix instruction's lane order (lane = row: four lines per quad of lanes).
 //  - The activations of the same k (at most 32 rows, resident in every L2) come through the same ring.
@@ -38,8 +38,9 @@ constexpr int kLine = 128;                               // bytes of a row per s
 
 // XB / WB: activation / weight bits (4 + 4, 8 + 8, or 8 + 4).  TB: 16-token blocks.  CB: 16-channel blocks per
 // workgroup.  NST: stages of a wave's ring.  MODE as in quik_gemm.hip: 0 fused epilogue, 1 raw INT32 accumulators
-// with the symmetric widening, 2 raw accumulators with the single-AND widening and its correction.
-template <int XB, int WB, int TB, int CB, int NST, int MODE>
+// with the symmetric widening, 2 raw accumulators with the single-AND widening and its correction.  ONCE: weights
+// are copied with the hint that their lines are read once.
+template <int XB, int WB, int TB, int CB, int NST, int MODE, bool ONCE>
 __global__ __launch_bounds__(kMaxWaves * 64) void gemm_rows_kernel(GemmArgs a) {
     constexpr bool RAW = MODE != 0;
     constexpr bool ASYM = XB == 4 && MODE != 1;
@@ -112,7 +113,9 @@ __global__ __launch_bounds__(kMaxWaves * 64) void gemm_rows_kernel(GemmArgs a) {
 #pragma unroll
         for (int i = 0; i < CB * 2; ++i) {
             const int row = i * 8 + lrow, c = k + (((lane & 7) ^ swz<kLine>(row)) << 4);
-            dma16_once(rb, dst + i * 1024, c < blim ? (uint32_t)(row * ldb + c) : kOob);
+            const uint32_t vo = c < blim ? (uint32_t)(row * ldb + c) : kOob;
+            if constexpr (ONCE) dma16_once(rb, dst + i * 1024, vo);
+            else dma16(rb, dst + i * 1024, vo, 0);
         }
 #pragma unroll
         for (int p = 0; p < AX; ++p)
@@ -266,19 +269,43 @@ __global__ __launch_bounds__(kMaxWaves * 64) void gemm_rows_kernel(GemmArgs a) {
     }
 }
 
-template <int XB, int WB, int TB, int CB, int NST, int MODE>
-hipError_t launch_cfg(const GemmArgs& a, int nw, hipStream_t stream) {
+template <int XB, int WB, int TB, int CB, int NST, int MODE, bool ONCE>
+hipError_t launch_kernel(const GemmArgs& a, int nw, hipStream_t stream) {
     constexpr int AX = (XB == 8 && WB == 4) ? 2 : 1;
     const int ring = nw * NST * (CB + TB * AX) * 16 * kLine, red = nw * TB * CB * 64 * 16 * (MODE == 0 ? 2 : 1);
     const int lds = ring > red ? ring : red;
-    const void* fn = reinterpret_cast<const void*>(&gemm_rows_kernel<XB, WB, TB, CB, NST, MODE>);
+    const void* fn = reinterpret_cast<const void*>(&gemm_rows_kernel<XB, WB, TB, CB, NST, MODE, ONCE>);
     if (lds > 65536) {
         const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
     }
     const int groups = (a.N + CB * 16 - 1) / (CB * 16);
-    hipLaunchKernelGGL((gemm_rows_kernel<XB, WB, TB, CB, NST, MODE>), dim3(groups), dim3(nw * 64), lds, stream, a);
+    hipLaunchKernelGGL((gemm_rows_kernel<XB, WB, TB, CB, NST, MODE, ONCE>), dim3(groups), dim3(nw * 64), lds, stream, a);
     return hipGetLastError();
+}
+
+// Whether weights carry the read-once hint.  Rows that are not whole 128-byte lines share lines, and the second reader
+// of a shared line should find it in a cache; the hint lets go of it.  Beyond what the L2s (8 x 4 MB) can hold beside
+// the rest that costs as much from HBM as the hint brings there, or more.  GEMM, us, weights cached / from HBM, with and
+// without the hint:
+//   whole lines   K = 5120, N = 15360, T = 1 9.2/10.2 : 10.3/11.3;  K = 10624, N = 7488, 8-bit, T = 10 15.1/16.1 : 15.0/18.1
+//   shared lines  92 MB (K = 6368, N = 13952, 8-bit, T = 19) 26.9/28.3 : 18.8/26.3;  107 MB (K = 4512, N = 22350, 8-bit,
+//                 T = 1) 23.7/25.6 : 18.7/21.7;  30 MB (K = 5328, N = 10048, W4A8, T = 13) 13.8/14.8 : 9.4/14.8;
+//                 26 MB (K = 6336, N = 3968, 8-bit, T = 3) 7.9/8.2 : 5.9/8.7;  15 MB (K = 1888, N = 11076, T = 3) 6.3/6.7 : 5.4/7.3
+// Where the rule keeps the hint, a layer that is called by itself over and over, so that its weights stay in the L2s
+// (or, from 17 tokens on, 80 MB and more in the last-level cache), would be faster without it: K = 4096, N = 11008, T = 24
+// 9.9/10.2 : 7.9/10.8;  K = 8192, N = 28672, T = 24 27.3/28.1 : 25.1/29.7.  In a model the weights come from HBM.
+bool once(const GemmArgs& a) {
+    return a.ldw % kLine == 0 || (size_t)a.N * ((size_t)a.ldw + 2 * (size_t)a.n_out) <= (24u << 20);
+}
+
+// (the accumulator hook writes the same integers either way and has one form)
+template <int XB, int WB, int TB, int CB, int NST, int MODE>
+hipError_t launch_cfg(const GemmArgs& a, int nw, hipStream_t stream) {
+    if constexpr (MODE == 0) {
+        if (!once(a)) return launch_kernel<XB, WB, TB, CB, NST, MODE, false>(a, nw, stream);
+    }
+    return launch_kernel<XB, WB, TB, CB, NST, MODE, true>(a, nw, stream);
 }
 
 // How a launch is cut.  Measured per launch in us (weights from HBM), best against the runner-up:

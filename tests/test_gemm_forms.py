@@ -84,6 +84,11 @@ def test_few_token_shapes_run_the_forms_they_name():
                 assert form(T, N, K - n_out, *w) == want_form, (T, N, K, w)
 
 
+def test_layers_without_the_read_once_hint_run_the_few_token_kernel():
+    for w in WIDTHS:
+        assert form(3, 6500, 8000, *w) == rows(16, 32, 4) and form(20, 6500, 8000, *w) == rows(32, 32, 4), w
+
+
 def test_wide_w4a8_layers_of_17_to_32_tokens_run_tiles():
     for T in (17, 32):
         assert form(T, 8192, 1024, 8, 4) == rows(32, 32, 4)

@@ -21,6 +21,19 @@ SHAPES = [
 @pytest.mark.parametrize("N,K,n_out", SHAPES)
 @pytest.mark.parametrize("bits,w_bits", [(4, 4), (8, 8), (8, 4)])
 def test_few_token_layer(oracle, T, N, K, n_out, bits, w_bits):
+    _layer(oracle, T, N, K, n_out, bits, w_bits)
+
+
+@pytest.mark.parametrize("T", [3, 20])
+@pytest.mark.parametrize("bits,w_bits", [(4, 4), (8, 8), (8, 4)])
+def test_few_token_layer_whose_weights_are_copied_without_the_read_once_hint(oracle, T, bits, w_bits):
+    N, K, n_out = 6500, 8008, 8                      # more than 24 MB, rows that are not whole 128-byte lines
+    ldw = (K - n_out) * w_bits // 8
+    assert ldw % 128 != 0 and ldw % 16 == 0 and N * ldw > 24 << 20
+    _layer(oracle, T, N, K, n_out, bits, w_bits)
+
+
+def _layer(oracle, T, N, K, n_out, bits, w_bits):
     from paper_2310_09259_amd import api
     shp = synth.LayerShape("few", T, K, N, n_out, bits, seed=900 + T + N + K, w_bits=0 if w_bits == bits else w_bits)
     inp = synth.make_inputs(shp)
