@@ -33,15 +33,17 @@ using namespace gemm_dev;
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-constexpr int kMaxWaves = 16;
 constexpr int kLine = 128;                               // bytes of a row per stage
+// More threads than any launch has: the bound makes the compiler keep to 128 registers (four waves per SIMD), which
+// a bound on the waves alone does not where LDS allows fewer.
+constexpr int kBoundThreads = 1024;
 
 // XB / WB: activation / weight bits (4 + 4, 8 + 8, or 8 + 4).  TB: 16-token blocks.  CB: 16-channel blocks per
-// workgroup.  NST: stages of a wave's ring.  MODE as in quik_gemm.hip: 0 fused epilogue, 1 raw INT32 accumulators
+// workgroup.  NW: waves.  NST: stages of a wave's ring.  MODE as in quik_gemm.hip: 0 fused epilogue, 1 raw INT32 accumulators
 // with the symmetric widening, 2 raw accumulators with the single-AND widening and its correction.  ONCE: weights
 // are copied with the hint that their lines are read once.
-template <int XB, int WB, int TB, int CB, int NST, int MODE, bool ONCE>
-__global__ __launch_bounds__(kMaxWaves * 64) void gemm_rows_kernel(GemmArgs a) {
+template <int XB, int WB, int TB, int CB, int NW, int NST, int MODE, bool ONCE>
+__global__ __launch_bounds__(kBoundThreads) void gemm_rows_kernel(GemmArgs a) {
     constexpr bool RAW = MODE != 0;
     constexpr bool ASYM = XB == 4 && MODE != 1;
     constexpr bool MIXED = XB == 8 && WB == 4;
@@ -56,12 +58,14 @@ __global__ __launch_bounds__(kMaxWaves * 64) void gemm_rows_kernel(GemmArgs a) {
     // quik_gemm.hip)
     asm volatile("" ::: "v127");
 
-    extern __shared__ __align__(1024) uint8_t lds[];     // rings; then the partial sums
+    // rings; then the partial sums.  Static: dynamic LDS beyond 64 KB needs a host call per launch
+    constexpr int RING = NW * NST * ST_BYTES, RED = NW * TB * CB * 1024 * (RAW ? 1 : 2);
+    __shared__ __align__(1024) uint8_t lds[RING > RED ? RING : RED];
     __shared__ float prm_sa[TB * 16], prm_sh[TB * 16];
     __shared__ int prm_ct[TB * 16];
 
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, g = lane >> 4;
     const int n0 = xcd_contiguous_id(blockIdx.x, gridDim.x) * (CB * 16);
 
@@ -70,7 +74,7 @@ __global__ __launch_bounds__(kMaxWaves * 64) void gemm_rows_kernel(GemmArgs a) {
     const int fplim = RAW ? 0 : a.n_out * 2;
     const int nint = a.fp_only ? 0 : (wlim + kLine - 1) / kLine;
     const int lines = nint + (fplim + kLine - 1) / kLine;
-    const int first = (int)((long)lines * wave / nw), last = (int)((long)lines * (wave + 1) / nw);
+    const int first = (int)((long)lines * wave / NW), last = (int)((long)lines * (wave + 1) / NW);
 
     const v4i rA = make_rsrc(a.xq, (size_t)a.T * a.ldq);
     const v4i rB = make_rsrc((const uint8_t*)a.w_q + (size_t)n0 * a.ldw, (size_t)(a.N - n0) * a.ldw);
@@ -226,7 +230,7 @@ __global__ __launch_bounds__(kMaxWaves * 64) void gemm_rows_kernel(GemmArgs a) {
     }
     __syncthreads();                                     // every ring is dead
     int4* red = reinterpret_cast<int4*>(lds);
-    float4* redf = reinterpret_cast<float4*>(lds) + nw * TB * CB * 64;
+    float4* redf = reinterpret_cast<float4*>(lds) + NW * TB * CB * 64;
 #pragma unroll
     for (int t = 0; t < TB; ++t)
 #pragma unroll
@@ -240,7 +244,7 @@ __global__ __launch_bounds__(kMaxWaves * 64) void gemm_rows_kernel(GemmArgs a) {
     int sum[4] = {0, 0, 0, 0};
     float sumf[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll 4
-    for (int w = 0; w < nw; ++w) {
+    for (int w = 0; w < NW; ++w) {
         const int e = (w * TB * CB + wave) * 64 + lane;
         const int4 v = red[e];
         sum[0] += v.x; sum[1] += v.y; sum[2] += v.z; sum[3] += v.w;
@@ -269,21 +273,6 @@ __global__ __launch_bounds__(kMaxWaves * 64) void gemm_rows_kernel(GemmArgs a) {
     }
 }
 
-template <int XB, int WB, int TB, int CB, int NST, int MODE, bool ONCE>
-hipError_t launch_kernel(const GemmArgs& a, int nw, hipStream_t stream) {
-    constexpr int AX = (XB == 8 && WB == 4) ? 2 : 1;
-    const int ring = nw * NST * (CB + TB * AX) * 16 * kLine, red = nw * TB * CB * 64 * 16 * (MODE == 0 ? 2 : 1);
-    const int lds = ring > red ? ring : red;
-    const void* fn = reinterpret_cast<const void*>(&gemm_rows_kernel<XB, WB, TB, CB, NST, MODE, ONCE>);
-    if (lds > 65536) {
-        const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (e != hipSuccess) return e;
-    }
-    const int groups = (a.N + CB * 16 - 1) / (CB * 16);
-    hipLaunchKernelGGL((gemm_rows_kernel<XB, WB, TB, CB, NST, MODE, ONCE>), dim3(groups), dim3(nw * 64), lds, stream, a);
-    return hipGetLastError();
-}
-
 // Whether weights carry the read-once hint.  Rows that are not whole 128-byte lines share lines, and the second reader
 // of a shared line should find it in a cache; the hint lets go of it.  Beyond what the L2s (8 x 4 MB) can hold beside
 // the rest that costs as much from HBM as the hint brings there, or more.  GEMM, us, weights cached / from HBM, with and
@@ -300,12 +289,17 @@ bool once(const GemmArgs& a) {
 }
 
 // (the accumulator hook writes the same integers either way and has one form)
-template <int XB, int WB, int TB, int CB, int NST, int MODE>
-hipError_t launch_cfg(const GemmArgs& a, int nw, hipStream_t stream) {
+template <int XB, int WB, int TB, int CB, int NW, int NST, int MODE>
+hipError_t launch_cfg(const GemmArgs& a, hipStream_t stream) {
+    const dim3 groups((a.N + CB * 16 - 1) / (CB * 16)), threads(NW * 64);
     if constexpr (MODE == 0) {
-        if (!once(a)) return launch_kernel<XB, WB, TB, CB, NST, MODE, false>(a, nw, stream);
+        if (!once(a)) {
+            hipLaunchKernelGGL((gemm_rows_kernel<XB, WB, TB, CB, NW, NST, 0, false>), groups, threads, 0, stream, a);
+            return hipGetLastError();
+        }
     }
-    return launch_kernel<XB, WB, TB, CB, NST, MODE, true>(a, nw, stream);
+    hipLaunchKernelGGL((gemm_rows_kernel<XB, WB, TB, CB, NW, NST, MODE, true>), groups, threads, 0, stream, a);
+    return hipGetLastError();
 }
 
 // How a launch is cut.  Measured per launch in us (weights from HBM), best against the runner-up:
@@ -332,9 +326,13 @@ RowsForm rows_form(int N, int K_b, bool mixed, int w_bits, int tb, int cus) {
 template <int XB, int WB, int TB, int MODE>
 hipError_t launch(const GemmArgs& a, int cus, hipStream_t stream) {
     const RowsForm f = rows_form(a.N, a.K_b, XB != WB, WB, TB, cus);
-    if (f.cb == 2) return launch_cfg<XB, WB, TB, 2, 2, MODE>(a, f.waves, stream);
-    if (f.nst == 2) return launch_cfg<XB, WB, TB, 1, 2, MODE>(a, f.waves, stream);
-    return launch_cfg<XB, WB, TB, 1, (XB != WB && TB == 2) ? 2 : 3, MODE>(a, f.waves, stream);
+    if (f.cb == 2) return launch_cfg<XB, WB, TB, 2, 4, 2, MODE>(a, stream);
+    if constexpr (TB == 1) {
+        if (f.waves == 8) return launch_cfg<XB, WB, 1, 1, 8, 3, MODE>(a, stream);
+    }
+    if (f.nst == 2) return launch_cfg<XB, WB, TB, 1, 4, 2, MODE>(a, stream);
+    if constexpr (XB == WB || TB == 1) return launch_cfg<XB, WB, TB, 1, 4, 3, MODE>(a, stream);
+    else return hipErrorInvalidValue;        // (rows_form gives two stages there)
 }
 
 template <int XB, int WB, int MODE>

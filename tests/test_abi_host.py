@@ -31,6 +31,12 @@ def test_every_declared_symbol_is_exported(lib):
         assert hasattr(lib, n), n
 
 
+def test_a_launch_needs_no_other_runtime_call(lib):
+    """Kernels hold their LDS statically: no attribute is set from the host on the way to a launch."""
+    assert b"hipLaunchKernel" in open(LIB, "rb").read()
+    assert b"hipFuncSetAttribute" not in open(LIB, "rb").read()
+
+
 def test_sizes_and_strings(lib):
     assert lib.quik_version() >= 1
     assert lib.quik_packed_row_bytes(480, 4) == 240

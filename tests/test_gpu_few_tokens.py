@@ -33,6 +33,34 @@ def test_few_token_layer_whose_weights_are_copied_without_the_read_once_hint(ora
     _layer(oracle, T, N, K, n_out, bits, w_bits)
 
 
+@pytest.mark.parametrize("bits,w_bits", [(4, 4), (8, 8), (8, 4)])
+def test_few_token_layer_replays_from_a_graph(bits, w_bits):
+    """The form with the largest LDS rings (eight waves), captured on first use; eager work between the replays."""
+    import torch
+    from paper_2310_09259_amd import api
+    shp = synth.LayerShape("few_graph", 7, 4384, 200, 288, bits, seed=77, w_bits=0 if w_bits == bits else w_bits)
+    d = upload(synth.make_inputs(shp))
+    w_red = api.quik_weight_reduce(d["w_q"], d["w_scale"], shp.K_b, w_bits)
+    y = torch.zeros((shp.T, shp.N), dtype=torch.float16, device="cuda")
+    ws = torch.empty(api.quik_workspace_bytes(shp.T, shp.K, shp.N, shp.n_out, bits), dtype=torch.uint8, device="cuda")
+    kept = {"out": y, "workspace": ws}
+
+    def layer(x, **kw):
+        if w_bits == bits:
+            return api.quik_linear(x, d["idx"], bits, d["w_q"], d["w_scale"], w_red, d["w_out"], **kw)
+        return api.quik_linear_w4a8(x, d["idx"], d["w_q"], d["w_scale"], w_red, d["w_out"], **kw)
+
+    x = d["x"].clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        layer(x, **kept)
+    for rep in range(3):
+        x.copy_(torch.roll(d["x"], rep, 0))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y.view(torch.int16), layer(x).view(torch.int16)), rep
+
+
 def _layer(oracle, T, N, K, n_out, bits, w_bits):
     from paper_2310_09259_amd import api
     shp = synth.LayerShape("few", T, K, N, n_out, bits, seed=900 + T + N + K, w_bits=0 if w_bits == bits else w_bits)
