@@ -382,7 +382,7 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_kernel(GemmArgs a) {
 
     // stage barrier of iteration s: stage s+1 has landed for everybody, and nobody reads stage s any more
     auto stage_barrier = [&]() {
-        wait_vm<(NST - 2) * LPS>();
+        wait_stage<(NST - 2) * LPS>();
         __syncthreads();
     };
 
@@ -419,7 +419,7 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_kernel(GemmArgs a) {
         }
     };
 
-    wait_vm<(NST - 1) * LPS>();          // stage 0 landed
+    wait_stage<(NST - 1) * LPS>();          // stage 0 landed
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < LA; ++q)

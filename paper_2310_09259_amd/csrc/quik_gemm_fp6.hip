@@ -230,7 +230,7 @@ __global__ __launch_bounds__(WM * WN * 64, (WM * WN == 8) ? 1 : 2) void gemm_fp6
     // stage s + NST right away, one DMA instruction per matrix instruction.  PLAIN: stage s + NST is an
     // FP6 stage; AHEAD: stage s + 1 is one.
     auto step = [&](int s, int set, bool plain, bool ahead) __attribute__((always_inline)) {
-        wait_vm<(NST - 2) * LPS>();
+        wait_stage<(NST - 2) * LPS>();
         __syncthreads();
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -248,7 +248,7 @@ __global__ __launch_bounds__(WM * WN * 64, (WM * WN == 8) ? 1 : 2) void gemm_fp6
     };
     static_assert(TM * TN >= NF && TM * TN >= LPS, "a stage has fewer matrix instructions than reads or copies to place");
 
-    wait_vm<(NST - 1) * LPS>();            // stage 0 landed
+    wait_stage<(NST - 1) * LPS>();            // stage 0 landed
     __syncthreads();
     if (nk_int > 0) {
 #pragma unroll
@@ -312,7 +312,7 @@ __global__ __launch_bounds__(WM * WN * 64, (WM * WN == 8) ? 1 : 2) void gemm_fp6
     // fp16 outlier stages: 16 columns each, one matrix step, same protocol as the FP6 stages (fragments
     // of stage s + 1 are read while the matrix instructions of stage s run; one barrier per stage)
     auto wide_step = [&](int s, int set) __attribute__((always_inline)) {
-        wait_vm<(NST - 2) * LPS>();
+        wait_stage<(NST - 2) * LPS>();
         __syncthreads();
         __builtin_amdgcn_sched_barrier(0);
         const uint8_t* nxt = lds + ((s + 1) % NST) * ST_BYTES;
@@ -327,7 +327,7 @@ __global__ __launch_bounds__(WM * WN * 64, (WM * WN == 8) ? 1 : 2) void gemm_fp6
         }
     };
     if (s < nk) {
-        wait_vm<(NST - 1) * LPS>();        // first fp16 stage landed
+        wait_stage<(NST - 1) * LPS>();        // first fp16 stage landed
         __syncthreads();
         const uint8_t* st = lds + (s % NST) * ST_BYTES;
 #pragma unroll

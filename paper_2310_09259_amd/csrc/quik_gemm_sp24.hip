@@ -260,7 +260,7 @@ __global__ __launch_bounds__(WM * WN * 64, (WM * WN == 8) ? 1 : 2) void gemm_sp2
     // requested one fragment per slot.
     auto step = [&](int s, int set, bool bar, bool plain, bool next1, bool next2) __attribute__((always_inline)) {
         if (bar) {
-            wait_vm<WAIT_BAR>();
+            wait_stage<WAIT_BAR>();
             __syncthreads();
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -282,7 +282,7 @@ __global__ __launch_bounds__(WM * WN * 64, (WM * WN == 8) ? 1 : 2) void gemm_sp2
         }
     };
 
-    wait_vm<(NST - 2) * LPS>();            // stages 0 and 1 landed
+    wait_stage<(NST - 2) * LPS>();            // stages 0 and 1 landed
     __syncthreads();
     if (nk_int > 0) {
 #pragma unroll
@@ -367,7 +367,7 @@ __global__ __launch_bounds__(WM * WN * 64, (WM * WN == 8) ? 1 : 2) void gemm_sp2
     // instructions of stage s issue, and stage s's buffer (read during stage s - 1, before this barrier)
     // is refilled
     auto wide_step = [&](int s, int set) __attribute__((always_inline)) {
-        wait_vm<WAIT_BAR>();
+        wait_stage<WAIT_BAR>();
         __syncthreads();
         __builtin_amdgcn_sched_barrier(0);
         const uint8_t* nxt = lds + ((s + 1) % NST) * ST_BYTES;
@@ -388,7 +388,7 @@ __global__ __launch_bounds__(WM * WN * 64, (WM * WN == 8) ? 1 : 2) void gemm_sp2
     if (s < nk) {
         // the first fp16 stage has landed (at most KS + 1 stages behind the last barrier's stage); the wait
         // and barrier matter only if there was no integer stage
-        wait_vm<WAIT_BAR>();
+        wait_stage<WAIT_BAR>();
         __syncthreads();
         const uint8_t* st = lds + (s % NST) * ST_BYTES;
 #pragma unroll

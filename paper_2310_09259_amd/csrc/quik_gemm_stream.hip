@@ -320,7 +320,7 @@ __global__ __launch_bounds__(NT, 1) void gemm_stream_kernel(GemmArgs a, StreamPl
     prep_copy(rf, cur_t0, cur_n0, cur_nc, false, 1, true);
 #pragma unroll
     for (int d = 0; d < LPS; ++d) issue_copy(rf, 1, d);
-    wait_vm<LPS>();                                       // stage 0 has landed
+    wait_stage<LPS>();                                       // stage 0 has landed
     __syncthreads();
     {
         int cb0, tna;
@@ -404,7 +404,7 @@ __global__ __launch_bounds__(NT, 1) void gemm_stream_kernel(GemmArgs a, StreamPl
                     const int par = ks & 1;                           // raw set of this sub-step; the other holds the next one
                     const int tks = (ks + 2) % KSUB;
                     if (ks == 2) {
-                        wait_vm<0>();
+                        wait_stage<0>();
                         __syncthreads();          // stage s + 1 has landed for everybody; nobody reads this stage's slot any more
                         prep_refill(rf, s);
                         if (s == nk_int - 2) {
@@ -547,7 +547,7 @@ __global__ __launch_bounds__(NT, 1) void gemm_stream_kernel(GemmArgs a, StreamPl
                 auto fp_stage = [&](auto last_c, int f, int slot_) QUIK_INLINE {
                     constexpr bool LAST = decltype(last_c)::value != 0;
                     fp_mfmas(ic<0>{}, slot_, true);
-                    wait_vm<0>();
+                    wait_stage<0>();
                     __syncthreads();
                     prep_refill(rf, nk_int + f);
                     __builtin_amdgcn_sched_barrier(0);

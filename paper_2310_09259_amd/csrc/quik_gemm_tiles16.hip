@@ -275,7 +275,7 @@ __global__ __launch_bounds__(WM * WN * KS * 64, 8 / (WM * WN * KS)) void gemm_ti
 
     // stage barrier of iteration s: stage s+1 has landed for everybody, and nobody reads stage s any more
     auto stage_barrier = [&]() {
-        wait_vm<(NST - 2) * LPS>();
+        wait_stage<(NST - 2) * LPS>();
         __syncthreads();
     };
 
@@ -393,7 +393,7 @@ __global__ __launch_bounds__(WM * WN * KS * 64, 8 / (WM * WN * KS)) void gemm_ti
             }
         };
 
-        wait_vm<(NST - 1) * LPS>();          // stage 0 landed
+        wait_stage<(NST - 1) * LPS>();          // stage 0 landed
         __syncthreads();
     #pragma unroll
         for (int q = 0; q < LA; ++q)
@@ -442,7 +442,7 @@ __global__ __launch_bounds__(WM * WN * KS * 64, 8 / (WM * WN * KS)) void gemm_ti
             if (wide) read_fp(1, s_ + 1);
             else read_int8(1, s_ + 1);
         };
-        wait_vm<(NST - 1) * LPS>();          // stage 0 landed
+        wait_stage<(NST - 1) * LPS>();          // stage 0 landed
         __syncthreads();
         if (MIXED && li == 0) {               // the outlier hook: fp16 rows from the start
             read_fp(0, 0);
@@ -461,7 +461,7 @@ __global__ __launch_bounds__(WM * WN * KS * 64, 8 / (WM * WN * KS)) void gemm_ti
     constexpr int SUMS = IB * JB * (RAW ? 1024 : 2048);
     static_assert((KS - 1) * NWAVES * SUMS <= KS * NST * ST_BYTES, "stage rings too small for the partial sums");
     if constexpr (RAW) {
-        wait_vm<0>();                      // drain the look-ahead DMA before the wave ends
+        wait_stage<0>();                      // drain the look-ahead DMA before the wave ends
         if constexpr (KS > 1) {
             __syncthreads();               // nobody reads or fills a ring any more
             if (kg) {
@@ -548,7 +548,7 @@ __global__ __launch_bounds__(WM * WN * KS * 64, 8 / (WM * WN * KS)) void gemm_ti
         if (s + 1 < nk) read_fp(1, s + 1);
     }
 
-    wait_vm<0>();                          // drain the look-ahead DMA before the wave ends
+    wait_stage<0>();                          // drain the look-ahead DMA before the wave ends
     if constexpr (KS > 1) {
         __syncthreads();                   // nobody reads or fills a ring any more
         if (kg) {
