@@ -48,6 +48,42 @@ def test_tile_rule_shapes_run_the_tiles_they_name():
         assert tuple(form(T, N, K - n_out, *w) for w in WIDTHS) == want, (T, N, K, n_out)
 
 
+DEEP = [T64x32, T64x32, T64x32, T64x64, T64x64, T128x64, T128x64, T128x128, T128x128_K2, T256x128, T256x128, T256x128,
+        S256x192, S128x128, S128x128, S128x64]
+
+
+def test_deep_tile_shapes_run_the_tiles_they_name_and_wrap_their_rings():
+    assert len(test_gpu_tile_rules.DEEP) == len(DEEP)
+    for (T, N, K, n_out, bits, w_bits), want in zip(test_gpu_tile_rules.DEEP, DEEP):
+        assert form(T, N, K - n_out, bits, w_bits) == want, (T, N, K, n_out, bits, w_bits)
+        stages = -(-(K - n_out) * bits // 1024)            # 128 activation bytes each
+        assert stages >= 8 and (want[1][3] == 1 or stages % want[1][3]), (T, N, K, stages)
+
+
+REPEATS = {                            # layers that test_gpu_parity.py repeats with more workgroups than CUs
+    "rep2_64x64": S64x64, "rep2_128x64": S128x64, "rep2_128x128": S128x128, "rep2_64x64_w8a8": S64x64,
+    "rep2_128x128_w8a8": S128x128, "rep2_128x64_w4a8": S128x64, "rep2_128x128_w4a8": S128x128,
+    "rep2_pair_w8a8": T64x64_PAIR, "rep2_pair_w4a8": T64x64_PAIR, "rep2_rows": (1, (16, 16, 4, 4)),
+    "rep2_rows_pairs": (1, (32, 32, 4, 4)), "rep2_rows_w8a8": (1, (16, 16, 4, 4)), "rep2_rows_w4a8": (1, (16, 32, 4, 4)),
+}
+
+
+def test_repeated_layers_have_more_workgroups_than_compute_units():
+    shapes = {s.name: s for s in test_gpu_parity.REPEAT_SHAPES if s.name.startswith("rep2_")}
+    assert set(shapes) == set(REPEATS)
+    for name, s in shapes.items():
+        kernel, tile = form(s.T, s.N, s.K_b, s.bits, s.weight_bits)
+        assert (kernel, tile) == REPEATS[name], name
+        assert -(-s.T // tile[0]) * -(-s.N // tile[1]) > CUS and tile[2] == 4, name
+
+
+def test_canary_layers_run_the_k_groups_they_name():
+    shapes = {s.name: s for s in test_gpu_parity.CANARY_SHAPES}
+    for name, want in (("canary_k_groups", T64x32), ("canary_k_groups_w8a8", T128x64)):
+        s = shapes[name]
+        assert form(s.T, s.N, s.K_b, s.bits, s.bits) == want, name
+
+
 # The band in which workgroups of four waves, two per CU, are ahead (T, K, N, n_out, w_bits; a 256 x 128 or 128 x 128
 # tile per CU took these while the pairs were gone, 5 - 30 % slower)
 PAIRS = [

@@ -122,8 +122,7 @@ INT_GEMM_SHAPES = [
     (576, 16640, 224, 4),
     # one round of 256 x 128 tiles: the 16 x 16 per-tile kernel (8 bits: 128 x 128 tiles in pairs), K tail
     (1000, 8190, 368, 4), (1000, 8190, 232, 8),
-    # small-T paths: K-split kernel (T <= 32; K shorter than four stages, ragged N), 64 x 64 and
-    # 128 x 64 tile configurations
+    # small-T paths: few-token kernel (T <= 32; K shorter than four stages, ragged N) and 64 x 64 tiles
     (32, 100, 160, 4), (7, 333, 2432, 4), (20, 95, 4864, 8), (50, 200, 992, 4), (64, 130, 480, 8),
     (100, 300, 480, 4), (128, 70, 1000, 8),
 ]
@@ -411,12 +410,14 @@ def test_persistent_kernel_output_matches_oracle(api, oracle, persistent_path, s
 
 
 CANARY_SHAPES = [
-    synth.LayerShape("canary_small_t", 20, 1024, 200, 64, 4, seed=91),        # K-split kernel
+    synth.LayerShape("canary_small_t", 20, 1024, 200, 64, 4, seed=91),        # few-token kernel
     synth.LayerShape("canary_tiles", 300, 1096, 333, 32, 4, seed=92),         # per-tile kernel, ragged everything
     synth.LayerShape("canary_w8a8", 130, 1000, 140, 24, 8, seed=93),
     synth.LayerShape("canary_persistent", 1030, 1104, 9990, 40, 4, seed=94),  # persistent kernel
     synth.LayerShape("canary_tiles16", 1000, 392, 8190, 24, 4, seed=95),      # 16 x 16 per-tile kernel
     synth.LayerShape("canary_tiles16_w8a8", 1000, 280, 8190, 40, 8, seed=96),
+    synth.LayerShape("canary_k_groups", 130, 2056, 2044, 72, 4, seed=97),     # 16 x 16 per-tile kernel, four K groups
+    synth.LayerShape("canary_k_groups_w8a8", 66, 2264, 8444, 104, 8, seed=98),   # two K groups
 ]
 
 
@@ -598,20 +599,20 @@ def test_vector_store_path_with_a_ragged_last_piece(api, oracle):
 
 
 def _random_shape(seed):
-    """A seeded random layer shape: ragged sizes, every tile configuration reachable."""
+    """A seeded random layer shape: ragged sizes, from few-token layers to several large tiles per CU."""
     rng = np.random.default_rng(9000 + seed)
     kind = seed % 4
     K = int(rng.integers(1, 160)) * 8 if kind != 3 else int(rng.integers(1, 40)) * 8
     n_out = int(rng.integers(0, max(1, min(K // 8, 40)))) * 8
     if n_out >= K:
         n_out = K - 8
-    if kind == 0:      # few tokens: K-split kernel and small tiles
+    if kind == 0:      # few tokens: few-token kernel and small tiles
         T, N = int(rng.integers(1, 130)), int(rng.integers(1, 700))
-    elif kind == 1:    # 128 x 128 tiles
+    elif kind == 1:    # up to one 256 x 128 tile per CU
         T, N = int(rng.integers(129, 700)), int(rng.integers(1, 900))
     elif kind == 2:    # mixed
         T, N = int(rng.integers(1, 400)), int(rng.integers(1, 2000))
-    else:              # at least 256 tiles of 256 x 128: eight-wave configurations, shallow K
+    else:              # at least 256 tiles of 256 x 128, shallow K
         T, N = int(rng.integers(513, 1100)), int(rng.integers(11000, 17000))
     mode = ("w4a4", "w8a8", "w4a8")[int(rng.integers(0, 3))]
     return T, K, N, n_out, mode
@@ -650,14 +651,31 @@ def test_random_shapes_match_oracle(api, oracle, seed):
 
 # Kernel forms that run more than one workgroup per CU (the forms in which a register allocation that ends
 # on a partial share of the SIMD's file has produced wrong bytes now and then): every one of them many times
-# in a row on shapes with several workgroups per CU; the first result is checked against the oracle, every
-# later one must equal it bit for bit.
+# in a row on shapes with more workgroups than CUs; the first result is checked against the oracle, every
+# later one must equal it bit for bit.  The forms are asserted in test_gemm_forms.py; the first five shapes, from
+# before its rules, run one workgroup per CU of the forms named there.
 REPEAT_SHAPES = [
     synth.LayerShape("rep_64x64", 60, 1024, 3000, 64, 4, seed=101),           # 64 x 64 tiles, deep ring
-    synth.LayerShape("rep_128x64", 120, 1024, 3000, 64, 4, seed=102),         # 128 x 64 tiles
-    synth.LayerShape("rep_128x128", 700, 1024, 2900, 64, 4, seed=103),        # 128 x 128 tiles, two per CU
-    synth.LayerShape("rep_128x128_w8a8", 700, 1024, 2900, 64, 8, seed=104),
-    synth.LayerShape("rep_ksplit", 24, 2048, 4000, 64, 4, seed=105),          # K-split kernel
+    synth.LayerShape("rep_128x64", 120, 1024, 3000, 64, 4, seed=102),         # 64 x 64 tiles
+    synth.LayerShape("rep_128x128", 700, 1024, 2900, 64, 4, seed=103),        # 64 x 64 tiles, two per CU
+    synth.LayerShape("rep_128x128_w8a8", 700, 1024, 2900, 64, 8, seed=104),   # 128 x 128 tiles of eight waves
+    synth.LayerShape("rep_ksplit", 24, 2048, 4000, 64, 4, seed=105),          # few-token kernel
+    # more workgroups than CUs: gemm_kernel's tiles of four waves ...
+    synth.LayerShape("rep2_64x64", 130, 544, 8000, 64, 4, seed=106),
+    synth.LayerShape("rep2_128x64", 128, 304, 20000, 64, 4, seed=107),
+    synth.LayerShape("rep2_128x128", 260, 304, 16000, 64, 4, seed=108),
+    synth.LayerShape("rep2_64x64_w8a8", 130, 576, 8190, 64, 8, seed=109),
+    synth.LayerShape("rep2_128x128_w8a8", 500, 320, 16000, 64, 8, seed=110),
+    synth.LayerShape("rep2_128x64_w4a8", 250, 320, 16300, 64, 8, seed=111, w_bits=4),
+    synth.LayerShape("rep2_128x128_w4a8", 500, 320, 16000, 64, 8, seed=112, w_bits=4),
+    # ... gemm_tiles16_kernel's ...
+    synth.LayerShape("rep2_pair_w8a8", 33, 1272, 26320, 64, 8, seed=113),
+    synth.LayerShape("rep2_pair_w4a8", 130, 576, 8190, 64, 8, seed=114, w_bits=4),
+    # ... and the few-token kernel's single channel blocks and pairs of blocks
+    synth.LayerShape("rep2_rows", 10, 544, 8200, 64, 4, seed=115),
+    synth.LayerShape("rep2_rows_pairs", 24, 544, 16384, 64, 4, seed=116),
+    synth.LayerShape("rep2_rows_w8a8", 10, 544, 8200, 64, 8, seed=117),
+    synth.LayerShape("rep2_rows_w4a8", 10, 544, 16400, 64, 8, seed=118, w_bits=4),
 ]
 
 
@@ -665,15 +683,20 @@ REPEAT_SHAPES = [
 def test_repeated_calls_of_multi_workgroup_forms_are_bit_identical(api, oracle, shp):
     inp = synth.make_inputs(shp)
     d = upload(inp)
-    ref = oracle.linear(inp.x, inp.outlier_idx, shp.bits, inp.w_packed, inp.w_scale, inp.w_out)
-    w_red = api.quik_weight_reduce(d["w_q"], d["w_scale"], shp.K_b, shp.bits)
+    w_bits = shp.weight_bits
+    mixed = w_bits != shp.bits
+    ref = oracle.linear(inp.x, inp.outlier_idx, shp.bits, inp.w_packed, inp.w_scale, inp.w_out, w_bits=w_bits)
+    w_red = api.quik_weight_reduce(d["w_q"], d["w_scale"], shp.K_b, w_bits)
     first = {}
     for rep in range(8):
-        got = {"layer": api.quik_linear(d["x"], d["idx"], shp.bits, d["w_q"], d["w_scale"], w_red, d["w_out"])}
-        for version in (1, 2):                                     # the unfused kernels
-            got[f"ablation_v{version}"], _ = api.quik_linear_ablation(version, d["x"], d["idx"], shp.bits, d["w_q"],
-                                                                      d["w_scale"], w_red, d["w_out"])
-        got["w_reduced"] = api.quik_weight_reduce(d["w_q"], d["w_scale"], shp.K_b, shp.bits)
+        if mixed:
+            got = {"layer": api.quik_linear_w4a8(d["x"], d["idx"], d["w_q"], d["w_scale"], w_red, d["w_out"])}
+        else:
+            got = {"layer": api.quik_linear(d["x"], d["idx"], shp.bits, d["w_q"], d["w_scale"], w_red, d["w_out"])}
+            for version in (1, 2):                                 # the unfused kernels
+                got[f"ablation_v{version}"], _ = api.quik_linear_ablation(version, d["x"], d["idx"], shp.bits, d["w_q"],
+                                                                          d["w_scale"], w_red, d["w_out"])
+        got["w_reduced"] = api.quik_weight_reduce(d["w_q"], d["w_scale"], shp.K_b, w_bits)
         if shp.bits == 4:
             got["w6"] = api.quik_weight_pack_fp6(d["w_q"], shp.K_b)
             got["xq6"] = api.quik_quantize_fp6(d["x"], d["idx"])[0]
@@ -682,7 +705,7 @@ def test_repeated_calls_of_multi_workgroup_forms_are_bit_identical(api, oracle, 
         got = {k: v.cpu().numpy().view(np.uint8) for k, v in got.items()}
         if rep == 0:
             first = got
-            for name in ("layer", "ablation_v1", "ablation_v2"):
+            for name in ("layer",) if mixed else ("layer", "ablation_v1", "ablation_v2"):
                 ok, worst = output_within_tolerance(got[name].view(np.float16), ref.y)
                 assert ok, (name, worst)
         else:

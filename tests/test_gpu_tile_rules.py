@@ -27,9 +27,32 @@ SHAPES = [
 ]
 
 
+# T, N, K, n_out, bits, w_bits: enough integer stages for the ring to wrap inside the unguarded loop (an odd number
+# with K groups, so that the groups differ), ragged T and last stage, several outlier stages; N whole 16-byte output
+# pieces or not.  The tiles are asserted in test_gemm_forms.py.
+DEEP = [
+    (33, 72, 2256, 72, 8, 8), (33, 72, 2256, 72, 8, 4), (129, 2044, 2256, 72, 4, 4),          # T 64 x 32, four groups
+    (100, 8152, 5288, 136, 8, 8), (100, 8152, 5288, 136, 8, 4),                               # T 64 x 64, two groups
+    (130, 8192, 4368, 152, 8, 8), (66, 8442, 2264, 104, 8, 4),                                # T 128 x 64, two groups
+    (73, 18504, 1240, 72, 8, 8), (73, 18010, 3104, 272, 8, 4),                                # T 128 x 128, one / two groups
+    (201, 18406, 1432, 136, 8, 8), (389, 14616, 1176, 136, 8, 4), (389, 14614, 1176, 136, 8, 4),   # T 256 x 128
+    (387, 16440, 1112, 80, 8, 8),                                                             # S 256 x 192
+    (300, 11082, 1368, 168, 8, 8), (300, 11082, 1368, 168, 8, 4), (120, 16470, 1368, 168, 8, 4),   # S in pairs
+]
+
+
+@pytest.mark.parametrize("T,N,K,n_out,bits,w_bits", DEEP)
+def test_tile_with_many_stages(oracle, T, N, K, n_out, bits, w_bits):
+    _layer(oracle, T, N, K, n_out, bits, w_bits)
+
+
 @pytest.mark.parametrize("T,N,K,n_out", SHAPES)
 @pytest.mark.parametrize("bits,w_bits", [(4, 4), (8, 8), (8, 4)])
 def test_tile_of_the_rules(oracle, T, N, K, n_out, bits, w_bits):
+    _layer(oracle, T, N, K, n_out, bits, w_bits)
+
+
+def _layer(oracle, T, N, K, n_out, bits, w_bits):
     from paper_2310_09259_amd import api
     shp = synth.LayerShape("tile", T, K, N, n_out, bits, seed=700 + T + N + K, w_bits=0 if w_bits == bits else w_bits)
     inp = synth.make_inputs(shp)
