@@ -495,9 +495,13 @@ def main():
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     plan = api.quik_debug_gemm_plan(T, N, K_b, cus) if (bits == 4 and not mixed) else None
     persistent = plan is not None and args.gemm_path != "tiles" and (plan[0] == 1 or args.gemm_path == "persistent")
-    # per-tile family: gemm_tiles16_kernel runs the 256 x 128 tiles of equal operand widths, gemm_kernel the
-    # other tiles, gemm_rows_kernel up to 32 tokens (the dispatch in quik_gemm.hip decides)
-    gemm_kernel_name = "gemm_stream_kernel" if persistent else "gemm_kernel|gemm_tiles16_kernel"
+    family, _ = api.quik_debug_gemm_form(T, N, K_b, bits, shp.weight_bits, cus)
+    if persistent:
+        gemm_kernel_name = "gemm_stream_kernel"
+    elif family == 4:                    # --gemm-path tiles keeps the persistent kernel from its shapes
+        gemm_kernel_name = "gemm_kernel|gemm_tiles16_kernel"
+    else:
+        gemm_kernel_name = {1: "gemm_rows_kernel", 2: "gemm_kernel", 3: "gemm_tiles16_kernel"}[family]
     tops = ops_layer / (ms_step * 1e-3) / 1e12
     gemm_tops = ops_int / (ms_gemm * 1e-3) / 1e12
     out = {

@@ -253,8 +253,10 @@ int quik_debug_gemm_tile(int T, int N, int K_b, int cus, int workgroup, int k, i
 /*
  * Test hook: which kernel family the 4-bit GEMM entry points use from now on, in
  * this process: 0 = automatic (the default), 1 = the persistent kernel wherever
- * quik_debug_gemm_plan returns 1 or 2, 2 = the per-tile kernels always.  Results
- * are the same either way.  Not synchronised with calls in flight on other
+ * quik_debug_gemm_plan returns 1 or 2, 2 = never the persistent kernel.  The INT32
+ * accumulators are the same either way; the fp16 output too, except where a kernel
+ * splits K over waves (the few-token kernel, 64-row tiles of 32 channels): there the
+ * fp32 sums of the outlier product are taken in another order.  Not synchronised with calls in flight on other
  * threads.  Returns QUIK_OK or QUIK_EINVAL.
  */
 int quik_debug_set_gemm_path(int mode);
@@ -350,7 +352,8 @@ int quik_linear_w4a8(const void *x, int T, int K, int ldx,
 /*
  * QUIK-4B with the integer product on the FP6 matrix pipe of gfx950 (a higher-rate, still exact,
  * form of Algorithm 1's "INTmatmul" for 4-bit weights and activations; same arithmetic and same
- * results as the bits = 4 entry points above).  The signed codes -8 .. 7 are stored as the 6-bit
+ * integers as the bits = 4 entry points above, and the same fp16 output where those do not split K
+ * over waves: see quik_debug_set_gemm_path).  The signed codes -8 .. 7 are stored as the 6-bit
  * float format E3M2 (1 sign bit, 3 exponent bits with bias 3, 2 mantissa bits), in which they
  * are exact; products are integers of magnitude <= 64 and a dot product over K_b < 131072
  * columns stays below 2^24, so the fp32 accumulators of the matrix instruction hold the

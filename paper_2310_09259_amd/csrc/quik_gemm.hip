@@ -112,7 +112,7 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_kernel(GemmArgs a) {
     __shared__ __align__(1024) uint8_t lds[NST * ST_BYTES];
     __shared__ __align__(16) float lds_sa[BM];
     __shared__ __align__(16) float lds_sh[BM];
-    __shared__ __align__(16) int lds_ct[BM];             // 8 * (per-token correction sum)
+    __shared__ __align__(16) int lds_ct[BM];             // -128 * (per-token correction sum)
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
@@ -459,8 +459,9 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void gemm_kernel(GemmArgs a) {
             }
         return;
     }
-    // Dequantization.  The accumulator is 2^SHIFT times the integer dot product, its conversion to binary32
-    // is exact (at most 24 significant bits), and 2^-SHIFT rides on the weight scale.
+    // Dequantization.  The accumulator is 2^SHIFT times the integer dot product and 2^-SHIFT rides on the weight
+    // scale.  The conversion to binary32 is exact with 4-bit activations (at most 24 significant bits); sums over
+    // 8-bit ones can be longer and are rounded once (relative error 2^-24).
     v16f cf[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -590,7 +591,8 @@ int choose_tile_4bit(int T, int N, int K_b, int cus) {
         //   K=5120  N=15360 T=128: (37.9 / 16.2 / 17.6 / 21.1)
         // The four K groups of 64 x 32 cost two barriers and a pass through LDS at the end: at K = 1024 it takes
         // 7.2 where 64 x 64 takes 6.5, at K = 2048 7.8 against 8.0.  Beyond two 64 x 64 tiles per CU, 128 x 64 has
-        // the edge only while weights are cached (T=66 K=4240 N=28296: 19.9 : 21.3, from HBM 28.9 : 27.9).
+        // the edge over 128 x 128 only while weights are cached (T=66 K=4240 N=28296: 19.9 : 21.3, from HBM 28.9 : 27.9;
+        // T=128 K=8192 N=28672 from HBM 43.1 : 40.0).
         if (tiles_of(T, N, 64, 32) <= cus && K_b >= 1792) return kTile64x32;
         if (T <= 64 || tiles_of(T, N, 64, 64) <= 2L * cus) return kTile64x64Pair32;
         return T <= 128 ? kTile128x64Pair32 : kTile128x128Pair32;
@@ -767,7 +769,8 @@ static int compute_units() {
 
 // Estimated time of the per-tile kernels' launch for a 4-bit [T, N] output on `cus` compute units, in the
 // unit of plan_gemm_stream's estimate (one 32-channel block of a 256-row tile through the K loop): the
-// rounds and relative round times of dispatch() below.
+// rounds and relative round times of choose_tile_4bit.  (It knows the 256-row tiles only; the persistent kernel, whose
+// own tiles have 256 rows, is not compared with the smaller ones.)
 static double tiles_estimate(int T, int N, int cus) {
     auto rounds = [&](int bm, int bn) { return (double)((((long)(T + bm - 1) / bm) * ((N + bn - 1) / bn) + cus - 1) / cus); };
     const double a = 4.0 * rounds(256, 128), b = 4.0 * 1.42 * rounds(256, 192), c = 4.0 * 1.42 * rounds(192, 256);

@@ -71,9 +71,9 @@ template <int N> __device__ __forceinline__ void wait_vm() {   // s_waitcnt vmcn
     __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 // Wait of a barrier behind which stage buffers are refilled: at most N of this wave's copies outstanding, and every LDS
-// read of it returned.  The reads have to be named here.  The compiler adds a wait for them to __syncthreads(), but
-// takes it out again in a loop that no read is in flight into, although one is around its back edge; a refill by a
-// wave ahead then overtook the reads of one behind (copies past the end bring zeros at once).  Explicit waits stay.
+// read of it returned.  The reads have to be named here: the wait for them that the compiler adds to __syncthreads() is
+// missing in loops that no read is in flight into, although one is around the back edge, and a refill by a wave ahead
+// then overtook the reads of one behind (copies past the end bring zeros at once).
 template <int N> __device__ __forceinline__ void wait_stage() {   // s_waitcnt vmcnt(N) lgkmcnt(0)
     __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | ((N >> 4) << 14));
 }

@@ -4,7 +4,8 @@
 //
 // Same data path, operand formats, widenings, stage ring and epilogue arithmetic as gemm_kernel in quik_gemm.hip
 // (see the header of that file), for 4 + 4 or 8 + 8 bits and for 4-bit weights under 8-bit activations; the
-// integer sums are the same, without K groups (KS below) the output is too.  What differs is the matrix
+// integer sums are the same, without K groups (KS below) the output is too (with them the fp32 sums of the outlier
+// product are taken in KS parts and added after dequantization).  What differs is the matrix
 // instruction: v_mfma_i32_16x16x64_i8 for the integer product and v_mfma_f32_16x16x32_f16 for the outlier
 // product.  On MI355X the chip holds its full clock under these, where it lowers it under the 32 x 32 forms on
 // the same operand bytes.
@@ -70,10 +71,9 @@ __global__ __launch_bounds__(WM * WN * KS * 64, 8 / (WM * WN * KS)) void gemm_ti
     constexpr int NF = IB + JB;                          // fragments per sub-step
     constexpr int SLOTS = IB * JB;                       // MFMAs per sub-step
     constexpr int WORDS = NF * 2;                        // packed words per sub-step and lane
-    // LDS reads run LA sub-steps ahead of their MFMAs, issued from MFMA slot RO of a sub-step on
+    // LDS reads run LA sub-steps ahead of their MFMAs
     constexpr int LA = 2, RD = 2;
     constexpr int BAR_KS = KSUB - LA;                    // stage barrier sits before this sub-step
-    constexpr int RO = 0;
     static_assert(KSUB == 4 && NST >= 2 && BKB == 128, "written for 128-byte stage rows");
 
     __shared__ __align__(1024) uint8_t lds[KS * NST * ST_BYTES];
@@ -386,9 +386,9 @@ __global__ __launch_bounds__(WM * WN * KS * 64, 8 / (WM * WN * KS)) void gemm_ti
     #pragma unroll
                 for (int w = 0; w < WORDS; ++w)
                     if (w * SLOTS / WORDS == m) widen_word(par ^ 1, rnext, w);
-                if (m >= RO && m - RO < NF) read_frag(rload, m - RO, tgt, tks);
-                if (SLOTS - RO < NF && m == SLOTS - 1)
-                    for (int f = SLOTS - RO; f < NF; ++f) read_frag(rload, f, tgt, tks);
+                if (m < NF) read_frag(rload, m, tgt, tks);
+                if (SLOTS < NF && m == SLOTS - 1)
+                    for (int f = SLOTS; f < NF; ++f) read_frag(rload, f, tgt, tks);
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
@@ -494,8 +494,9 @@ __global__ __launch_bounds__(WM * WN * KS * 64, 8 / (WM * WN * KS)) void gemm_ti
             }
         return;
     }
-    // Dequantization.  The accumulator is 2^SHIFT times the integer dot product, its conversion to binary32 is
-    // exact (at most 24 significant bits), and 2^-SHIFT rides on the weight scale.
+    // Dequantization.  The accumulator is 2^SHIFT times the integer dot product and 2^-SHIFT rides on the weight
+    // scale.  The conversion to binary32 is exact with 4-bit activations (at most 24 significant bits); sums over
+    // 8-bit ones can be longer and are rounded once (relative error 2^-24).
     v4f cf[IB][JB];
     auto dequantize = [&](bool add) {
 #pragma unroll

@@ -186,7 +186,7 @@ enum { kTile64x32, kTile64x64, kTile64x64Pair, kTile128x64, kTile128x128, kTile2
        // on 32 x 32 instructions (gemm_kernel): 64 x 64 to 128 x 128 in workgroups of four waves, two per CU
        kTile64x64Pair32, kTile128x64Pair32, kTile128x128Pair32, kTile256x192, kTile192x256 };
 hipError_t launch_gemm_tiles16(const GemmArgs& a, int tile, hipStream_t stream);
-// T <= kRowsTokens, any operand widths: weights streamed through LDS rings of single waves that split K
+// up to kRowsTokens tokens (rows_take in quik_gemm.hip), any operand widths: weights streamed through LDS rings of single waves that split K
 // (quik_gemm_rows.hip)
 constexpr int kRowsTokens = 32;
 hipError_t launch_gemm_rows(const GemmArgs& a, int cus, hipStream_t stream);
