@@ -798,8 +798,8 @@ int choose_gemm_stream(int T, int N, int K_b, int cus, StreamPlan* plan) {
 // Few tokens go to gemm_rows_kernel, except 17 to 32 tokens of W4A8 layers with more than one pair of 16-channel blocks
 // per CU: two activation lines per weight line and 32 rows of them fill the rings so far that a CU holds one
 // workgroup, and its rounds do not overlap.  us, weights cached / from HBM, this kernel against 64 x 64 tiles, T = 32:
-// N = 8192, K = 1280 5.5/5.7 : 8.3/8.3;  N = 14464, K = 768 8.5/9.1 : 7.2/7.8, K = 4352 14.6/15.1 : 13.3/13.9;
-// N = 27520, K = 768 15.2/16.8 : 8.7/9.5, K = 4352 27.2/27.9 : 19.2/23.1.
+// N = 8192, K = 1280 5.2/5.2 : 8.3/8.3;  N = 14464, K = 768 8.5/9.1 : 7.2/7.6, K = 4352 14.6/15.1 : 13.2/13.9;
+// N = 27520, K = 768 15.2/16.8 : 8.8/9.6, K = 4352 27.2/27.9 : 19.3/23.2.
 static bool rows_take(int T, int N, int bits, int w_bits, int cus) {
     if (T <= 16) return true;
     return T <= kRowsTokens && !(bits == 8 && w_bits == 4 && N > 32L * (cus < 1 ? 256 : cus));

@@ -277,13 +277,13 @@ __global__ __launch_bounds__(kBoundThreads) void gemm_rows_kernel(GemmArgs a) {
 // of a shared line should find it in a cache; the hint lets go of it.  Beyond what the L2s (8 x 4 MB) can hold beside
 // the rest that costs as much from HBM as the hint brings there, or more.  GEMM, us, weights cached / from HBM, with and
 // without the hint:
-//   whole lines   K = 5120, N = 15360, T = 1 9.2/10.2 : 10.3/11.3;  K = 10624, N = 7488, 8-bit, T = 10 15.1/16.1 : 15.0/18.1
-//   shared lines  92 MB (K = 6368, N = 13952, 8-bit, T = 19) 26.9/28.3 : 18.8/26.3;  107 MB (K = 4512, N = 22350, 8-bit,
-//                 T = 1) 23.7/25.6 : 18.7/21.7;  30 MB (K = 5328, N = 10048, W4A8, T = 13) 13.8/14.8 : 9.4/14.8;
-//                 26 MB (K = 6336, N = 3968, 8-bit, T = 3) 7.9/8.2 : 5.9/8.7;  15 MB (K = 1888, N = 11076, T = 3) 6.3/6.7 : 5.4/7.3
+//   whole lines   K = 5120, N = 15360, T = 1 7.9/9.9 : 9.8/10.8;  K = 10624, N = 7488, 8-bit, T = 10 14.8/15.6 : 15.1/17.4
+//   shared lines  92 MB (K = 6368, N = 13952, 8-bit, T = 19) 26.7/28.2 : 18.2/25.6;  107 MB (K = 4512, N = 22350, 8-bit,
+//                 T = 1) 23.3/25.3 : 18.3/21.0;  30 MB (K = 5328, N = 10048, W4A8, T = 13) 13.6/14.5 : 8.6/14.1;
+//                 26 MB (K = 6336, N = 3968, 8-bit, T = 3) 7.6/7.9 : 5.6/8.1;  15 MB (K = 1888, N = 11076, T = 3) 6.2/6.4 : 5.1/6.7
 // Where the rule keeps the hint, a layer that is called by itself over and over, so that its weights stay in the L2s
 // (or, from 17 tokens on, 80 MB and more in the last-level cache), would be faster without it: K = 4096, N = 11008, T = 24
-// 9.9/10.2 : 7.9/10.8;  K = 8192, N = 28672, T = 24 27.3/28.1 : 25.1/29.7.  In a model the weights come from HBM.
+// 9.6/9.8 : 7.6/10.0;  K = 8192, N = 28672, T = 24 26.9/27.8 : 24.3/28.8.  In a model the weights come from HBM.
 bool once(const GemmArgs& a) {
     return a.ldw % kLine == 0 || (size_t)a.N * ((size_t)a.ldw + 2 * (size_t)a.n_out) <= (24u << 20);
 }
@@ -304,13 +304,13 @@ hipError_t launch_cfg(const GemmArgs& a, hipStream_t stream) {
 
 // How a launch is cut.  Measured per launch in us (weights from HBM), best against the runner-up:
 //  - up to one 16-channel block per CU, blocks stay single and eight waves split K where a row has the lines for
-//    it (K = 11008, N = 4096, 16 tokens: 8.0 against 9.9 with pairs and four waves; 8-bit 11.4 against 14.6),
-//    four with 17 - 32 tokens, whose activations fill the ring (9.4 against 11.4);
+//    it (K = 11008, N = 4096, 16 tokens: 7.7 against 9.4 with pairs and four waves; 8-bit 11.3 against 14.4),
+//    four with 17 - 32 tokens, whose activations fill the ring (8.4 against 8.9);
 //  - beyond that pairs of blocks and four waves: half the activation traffic per weight byte (K = 5120,
-//    N = 15360, 16 tokens: 10.9 against 12.0; N = 28672: 23.7 against 25.1), except where single blocks leave the
-//    busiest CU with less to do (N = 11008, 8-bit: 11.0 against 12.2; not with 8-bit activations under 4-bit
-//    weights, whose activation traffic is twice as heavy).  Two stages there: what a third brings in bytes in
-//    flight it costs in resident workgroups (10.1 against 10.3).
+//    N = 15360, 16 tokens: 10.7 against 12.0; N = 28672, K = 8192, 8 tokens: 23.7 against 24.9), except where single
+//    blocks leave the busiest CU with less to do (K = 4096, N = 11008, 8-bit: 12.5 against 13.0; not with 8-bit
+//    activations under 4-bit weights, whose activation traffic is twice as heavy).  Two stages there: what a third
+//    brings in bytes in flight it costs in resident workgroups (N = 15360, one token: 9.9 against 10.1).
 struct RowsForm { int cb, nst, waves; };
 RowsForm rows_form(int N, int K_b, bool mixed, int w_bits, int tb, int cus) {
     const int blocks = (N + 15) / 16, lines = (K_b * w_bits / 8 + kLine - 1) / kLine;

@@ -161,8 +161,8 @@ FULL_SIZE = ["llama7b_up", "llama7b_down", "llama13b_qkv_t128", "llama13b_qkv_t1
 def test_full_size_workloads_on_sampled_tokens_fp6(api, oracle, name):
     """The 4-bit benchmark workloads at full size on the FP6 path, in the launch configuration
     bench.py times: quantization checked in full (panels, scale, zero, outlier block), the output on
-    sampled token rows, and the whole output against the int8-MFMA path's (bit-identical where that
-    path runs its large-tile kernel, i.e. above 32 tokens)."""
+    sampled token rows, and the whole output against the int8-MFMA path's (bit-identical: that path does
+    not split K over waves on these shapes)."""
     import torch
     shp = synth.CONFIGS[name]
     inp = synth.make_inputs(shp)
