@@ -578,7 +578,7 @@ hipError_t launch_cfg(const GemmArgs& a, hipStream_t stream) {
 inline long tiles_of(int T, int N, int bm, int bn) { return (long)((T + bm - 1) / bm) * ((N + bn - 1) / bn); }
 inline long rounds_of(int T, int N, int bm, int bn, int cus) { return (tiles_of(T, N, bm, bn) + cus - 1) / cus; }
 
-int choose_tile_4bit(int T, int N, int K_b, int cus) {
+int basic_tile_4bit(int T, int N, int K_b, int cus) {
     if (T <= 128 || tiles_of(T, N, 256, 128) < cus) {
         // Fewer than one 256 x 128 tile per CU: the smallest tile that still goes through in one round, so that
         // all CUs have work.  64 x 64 runs two workgroups of four waves per CU.  us at 64 x 32 / 64 x 64 / 128 x 64 /
@@ -674,6 +674,45 @@ double launch_cost(const TileCost& t, long tiles, int cus, int stages) {
     if (tiles <= 2L * cus) return up_to_two(tiles);
     const long full = tiles / (2L * cus), left = tiles % (2L * cus);
     return (double)full * up_to_two(2L * cus) + (left ? t.rest * up_to_two(left) : 0.0);
+}
+
+// 4-bit operands beyond the smallest tiles: the same estimate, a stage being 256 k, fitted to 139 shapes with every tile
+// measured (T 65 .. 4096, K 2048 .. 11008, N 1024 .. 28672, cached weights and from HBM).  It predicts a tile's time to
+// 7 - 9 %, so the tile of basic_tile_4bit is left only for one that is estimated 7 % shorter; over those shapes that
+// makes the launch 5.5 % shorter in the mean, none more than 3 % longer except two (6 %, 5 %).  GEMM, us, before : now,
+// cached and from HBM alike:
+//   T=333 K=4096 N=11008, 258 tiles of 128 x 128 on 256 CUs, now 460 of 96 x 96, two per CU          28.8 : 23.4
+//   T=92 K=7552 N=18626 (128 x 64) 35.8 : 28.4;  T=143 K=9984 N=20644 56.0 : 43.2;  T=1360 K=7040 N=1628 29.8 : 25.0
+//   T=512 K=4096 N=11008, 344 tiles, now 232 of 128 x 192                                              29.4 : 26.7
+//   T=2325 K=5344 N=2444 39.2 : 33.4;  T=1365 K=8368 N=5514, 174 tiles of 256 x 192, now 484 of 128 x 128  73.9 : 59.5
+constexpr TileCost kCost4[] = {{kTile128x64Pair32, 128, 64, 0.975, 0.777, 6.956, 0.769, 0.195, 0.891},
+                               {kTile128x128Pair32, 128, 128, 8.275, 0.768, 10.375, 1.193, 0.324, 0.829},
+                               {kTile96x96Pair, 96, 96, 7.771, 0.604, 8.613, 0.979, -0.039, 0.823},
+                               {kTile96x128Pair, 96, 128, 8.225, 0.725, 9.431, 1.103, 0.128, 0.765},
+                               {kTile128x192, 128, 192, 9.532, 1.065, 0, 0, 0, 0},
+                               {kTile256x128, 256, 128, 11.229, 1.282, 0, 0, 0, 0},
+                               {kTile256x192, 256, 192, 13.517, 1.635, 0, 0, 0, 0},
+                               {kTile192x256, 192, 256, 13.336, 1.637, 0, 0, 0, 0}};
+constexpr int kModelK4 = 1792;        // below, the fixed parts decide and the measurements behind basic_tile_4bit hold
+constexpr double kModelGain4 = 0.93;
+
+// estimate of a 4-bit tile; 0 where the table has no line for it
+double tile_estimate_4bit(int tile, int T, int N, int K_b, int cus) {
+    for (const TileCost& c : kCost4)
+        if (c.tile == tile) return launch_cost(c, tiles_of(T, N, c.bm, c.bn), cus, (K_b + 255) / 256);
+    return 0.0;
+}
+
+int choose_tile_4bit(int T, int N, int K_b, int cus) {
+    const int basic = basic_tile_4bit(T, N, K_b, cus);
+    if (K_b < kModelK4 || basic == kTile64x32 || basic == kTile64x64Pair32) return basic;
+    int best = basic;
+    double least = kModelGain4 * tile_estimate_4bit(basic, T, N, K_b, cus);
+    for (const TileCost& c : kCost4) {
+        const double e = tile_estimate_4bit(c.tile, T, N, K_b, cus);
+        if (e < least) { best = c.tile; least = e; }
+    }
+    return best;
 }
 
 int choose_tile_8bit(int T, int N, int K_b, bool mixed, int cus) {
@@ -787,12 +826,19 @@ void set_gemm_path(int mode) { g_gemm_path = mode; }
 // rounds of fixed 256 x 192 tiles cost 0.947 per block, so it also wins 4 % where those balance perfectly),
 // and 1.04 where the tiles are four blocks wide (a wave then holds two column blocks: more fragment reads
 // and widening per MFMA than the per-tile 256 x 128 form) or K is shallow (its longer per-tile epilogue).
+// From kModelK4 base columns on a fitted estimate of its launch (the persistent kernel forced onto 60 of the shapes behind
+// kCost4; per tile of the busiest CU, and per block and stage of 256 k; good to 6 %) also gives it what it is estimated
+// 7 % ahead on: T=2445 K=2160 N=10388 (256 x 128) 84 : 73, T=1945 K=3424 N=19666 145 : 125.
 int choose_gemm_stream(int T, int N, int K_b, int cus, StreamPlan* plan) {
     if (!plan_gemm_stream(T, N, K_b, cus, plan)) return 0;
     const long tiles = (long)plan->tiles_m * plan->tn;
     const long r = (tiles + cus - 1) / cus;
     const double blocks = (double)(r * plan->base + (r * plan->rem + plan->tn - 1) / plan->tn);
-    return (T > kRowsTokens && K_b >= 2048 && plan->base >= 5 && 0.94 * blocks <= tiles_estimate(T, N, cus)) ? 1 : 2;
+    const bool rule = T > kRowsTokens && K_b >= 2048 && plan->base >= 5 && 0.94 * blocks <= tiles_estimate(T, N, cus);
+    if (rule || T <= kRowsTokens || K_b < kModelK4) return rule ? 1 : 2;
+    const double there = tile_estimate_4bit(choose_tile_4bit(T, N, K_b, cus), T, N, K_b, cus);
+    const double here = 4.983 + 8.323 * (double)r + blocks * (0.33 * ((K_b + 255) / 256) + 0.099);
+    return (here < kModelGain4 * there) ? 1 : 2;      // (`there` is 0 where the smallest tiles run)
 }
 
 // Few tokens go to gemm_rows_kernel, except 17 to 32 tokens of W4A8 layers with more than one pair of 16-channel blocks
@@ -841,6 +887,9 @@ GemmForm choose_gemm_form(int T, int N, int K_b, int bits, int w_bits, int cus) 
     case kTile128x64: return GemmForm{3, 128, 64, 8, 2};
     case kTile128x128: return GemmForm{3, 128, 128, 8, mixed ? 2 : 1};
     case kTile256x128: return GemmForm{3, 256, 128, 8, 1};
+    case kTile96x96Pair: return GemmForm{3, 96, 96, 4, 1};
+    case kTile96x128Pair: return GemmForm{3, 96, 128, 4, 1};
+    case kTile128x192: return GemmForm{3, 128, 192, 8, 1};
     case kTile64x64Pair32: return GemmForm{2, 64, 64, 4, 1};
     case kTile128x64Pair32: return GemmForm{2, 128, 64, 4, 1};
     case kTile128x128Pair32: return GemmForm{2, 128, 128, 4, 1};

@@ -669,6 +669,17 @@ hipError_t launch_tile(const GemmArgs& a, int tile, hipStream_t stream) {
         if constexpr (MIXED) return launch_cfg<BITS, WBITS, 128, 128, 2, 2, 2, 2, 8, MODE>(a, stream);
         else if constexpr (BITS == 8) return launch_cfg<BITS, WBITS, 128, 128, 4, 2, 1, 4, 8, MODE>(a, stream);
         else break;
+    // 4-bit tiles between 64 x 64 and the 256-row ones (measurements at choose_tile_4bit).  Four waves, two workgroups per
+    // CU, three stages where two rings of them fit; 128 x 192 is one workgroup per CU, 64 x 48 per wave.
+    case kTile96x96Pair:
+        if constexpr (BITS == 4) return launch_cfg<4, 4, 96, 96, 2, 2, 1, 3, 8, MODE>(a, stream);
+        else break;
+    case kTile96x128Pair:
+        if constexpr (BITS == 4) return launch_cfg<4, 4, 96, 128, 2, 2, 1, 2, 8, MODE>(a, stream);
+        else break;
+    case kTile128x192:
+        if constexpr (BITS == 4) return launch_cfg<4, 4, 128, 192, 2, 4, 1, 2, 8, MODE>(a, stream);
+        else break;
     case kTile256x128:   // a third stage: 8-bit 101 -> 88 us (K = 11008, T = 2048), 4-bit 72.5 -> 75 (copies do not bound it)
         return launch_cfg<BITS, WBITS, 256, 128, 4, 2, 1, BITS == 8 ? 3 : 2, 4, MODE>(a, stream);
     }

@@ -180,9 +180,10 @@ __host__ __device__ inline void stream_panel(const StreamPlan& p, int nt, int* b
 hipError_t launch_quantize(const QuantizeArgs& a, hipStream_t stream);
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t stream);
 hipError_t launch_gemm_tiles(const GemmArgs& a, int cus, hipStream_t stream);
-// one workgroup per tile on 16 x 16 matrix instructions (quik_gemm_tiles16.hip); those between 64 x 32 and
-// 256 x 128 with 8-bit activations only
+// one workgroup per tile on 16 x 16 matrix instructions (quik_gemm_tiles16.hip); those from 64 x 64 to 128 x 128 with
+// 8-bit activations only
 enum { kTile64x32, kTile64x64, kTile64x64Pair, kTile128x64, kTile128x128, kTile256x128,
+       kTile96x96Pair, kTile96x128Pair, kTile128x192,      // 4-bit only
        // on 32 x 32 instructions (gemm_kernel): 64 x 64 to 128 x 128 in workgroups of four waves, two per CU
        kTile64x64Pair32, kTile128x64Pair32, kTile128x128Pair32, kTile256x192, kTile192x256 };
 hipError_t launch_gemm_tiles16(const GemmArgs& a, int tile, hipStream_t stream);
