@@ -238,6 +238,13 @@ int quik_debug_gemm_plan(int T, int N, int K_b, int cus, int *plan);
 int quik_debug_gemm_form(int T, int N, int K_b, int bits, int w_bits, int cus, int *form);
 
 /*
+ * Test hook (host only): the output tile of quik_gemm_dequant_fp6 / quik_int_gemm_fp6 for these sizes on a GPU with
+ * `cus` compute units; form[0], form[1] (HOST pointer): token rows and output channels.  Returns QUIK_OK, or
+ * QUIK_EINVAL / QUIK_ENULL on invalid input.
+ */
+int quik_debug_fp6_form(int T, int N, int K_b, int cus, int *form);
+
+/*
  * Test hook (host only): the k-th output tile (k = 0, 1, ...) that resident workgroup
  * `workgroup` (0 .. plan[4]-1) of the persistent kernel computes for the shape of
  * quik_debug_gemm_plan: tile[0] = first token row, tile[1] = first output channel,

@@ -142,6 +142,13 @@ int quik_debug_gemm_form(int T, int N, int K_b, int bits, int w_bits, int cus, i
     return f.family;
 }
 
+int quik_debug_fp6_form(int T, int N, int K_b, int cus, int* form) {
+    if (T <= 0 || N <= 0 || K_b <= 0 || K_b >= kMaxKb || cus <= 0) return QUIK_EINVAL;
+    if (!form) return QUIK_ENULL;
+    quik::fp6_form(T, N, K_b, cus, &form[0], &form[1]);
+    return QUIK_OK;
+}
+
 int quik_debug_gemm_tile(int T, int N, int K_b, int cus, int workgroup, int k, int* tile) {
     if (T <= 0 || N <= 0 || K_b <= 0 || (K_b & 1) || K_b >= kMaxKb || cus <= 0 || workgroup < 0 || k < 0) return QUIK_EINVAL;
     if (!tile) return QUIK_ENULL;

@@ -794,7 +794,7 @@ __global__ __launch_bounds__(kThreads) void weight_reduce_kernel(WeightReduceArg
 }  // namespace
 
 // compute units of the current device (looked up once per device)
-static int compute_units() {
+int compute_units() {
     static int cached[64] = {};
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;

@@ -2,24 +2,32 @@
 // (Algorithm 1 of arXiv 2310.09259: "INTmatmul", "Dequantization", "FPmatmul", final add; the
 // epilogue fusion of Section 3.4).  The signed 4-bit codes travel as E3M2 patterns (see
 // quik_fp6_device.h: exact, and the fp32 accumulators hold the exact integer dot products), so the
-// K loop is DMA -> LDS -> registers -> v_mfma_f32_32x32x64_f8f6f4 with no widening work at all, at
+// K loop is DMA -> LDS -> registers -> v_mfma_f32_16x16x128_f8f6f4 with no widening work at all, at
 // twice the int8 rate of the matrix pipe.
 //
-// A workgroup of WM x WN waves owns a BM x BN output tile.  A stage is 64 columns = one matrix step = one
-// 48-byte block per operand row; the operands are stored stage by stage (quik_fp6_device.h), so the
-// tile's rows of a stage are one contiguous run of BM * 48 (BN * 48) bytes that 16-byte-per-lane DMA
-// instructions copy global -> LDS as it is.  The K loop needs many bytes in flight per CU (completion is
-// in order, so every request waits like the slowest before it), but not as many as the LDS could hold: a
-// ring of six stages for the 256 x 192 tile (108 KB in flight) runs 5 % faster than one of seven.  Lane (row l%32, half g = l/32) reads,
-// per stage, 16 bytes (dwords 0..3 of its group) and 8 bytes (dwords 4, 5); 48-byte rows need no
-// swizzle (twelve dwords per row walk all 64 banks in sixteen rows).  One workgroup barrier per stage;
-// right after it the buffer that was read during the previous stage is refilled, the DMA
-// instructions spread between the matrix instructions.  The fp16 outlier columns run through the same
-// ring as stages of 16 columns (32-byte rows, 32 rows per DMA instruction, pieces exchanged in every
-// second group of eight rows), with the dequantized integer part as the C operand of
-// v_mfma_f32_32x32x16_f16, whose accumulator layout is the same.  Rows beyond T / N are out of range
-// for the per-stage buffer descriptors and arrive as zeros (the E3M2 pattern of 0); columns beyond K_b
-// are zero padding.
+// A workgroup of WM x WN waves owns a BM x BN output tile.  The operands are stored panel by panel of 64
+// columns (quik_fp6_device.h), so a tile's rows of a panel are one contiguous run of BM * 48 (BN * 48) bytes
+// that 16-byte-per-lane copies bring global -> LDS as it is, into one slot of a ring.  A step of the K loop is
+// two panels = one matrix instruction per 16 x 16 block and wave.
+//
+// What bounds it: the supply of operand bytes (at 70B sizes the loop takes 0.9 us a step with them and 0.6 with
+// copies that fetch nothing; the matrix instructions alone 0.5).  What it needs for that:
+//  - whole lines per copy.  Splitting a panel's 16-byte and 8-byte parts into planes of LDS, for reads without bank
+//    conflicts, made the copies touch every line twice: 256 x 192, K = 4096, N = 11008, T = 2048 72.6 us against 71.2,
+//    70B 256 x 256 580 against 528;
+//  - large tiles: 256 x 256 fetches 48 KB for 2 x 256 x 256 x 128 operations, 256 x 192 42 KB for three quarters of them;
+//  - copies in flight: two block rows before the end of a step all its fragments have been read, so the one barrier
+//    of a step sits there, frees the step's own slots and leaves all slots but four flying.  With the barrier at the
+//    step's start (two slots landed but not yet read) 70B took 668 us instead of 580.
+// The 16 x 16 x 128 instruction sustains 7.1 POP/s on operands like these, the 32 x 32 x 64 one 6.4 (the chip lowers its
+// clock).  GEMM, us, 32 x 32 x 64 kernel with a step of one panel : this one, same box: 7B up-projection, 2048 tokens
+// 81.5 : 70;  70B, 4096 tokens 656 : 525;  13B QKV, 1024 tokens 75 : 49;  7B down-projection 66.6 : 59;  T = 333,
+// N = 11008, K = 4096 27.9 : 21;  T = 16, K = N = 4096 16.8 : 11.9.
+//
+// The fp16 outlier columns run as stages of 32 columns (64-byte rows) through slots of their own over the same
+// memory, copied while the tile is dequantized, with the dequantized integer part as the C operand of
+// v_mfma_f32_16x16x32_f16, whose accumulator layout is the same.  Rows beyond T / N are out of range
+// for the panel descriptors and arrive as zeros (the E3M2 pattern of 0); columns beyond K_b are zero padding.
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 #include <stdint.h>
@@ -34,363 +42,336 @@ namespace {
 
 using namespace gemm_dev;
 
+typedef float v4f __attribute__((ext_vector_type(4)));
 typedef int v8i __attribute__((ext_vector_type(8)));
 
-__device__ __forceinline__ int swz_f(int r) { return (r >> 3) & 1; }   // fp16 stages: 32-byte rows, two pieces
+// place of a 16-byte piece in a 64-byte stage row: an LDS instruction serves lanes 0 - 3, 12 - 15, 20 - 27 together (and so
+// on); with this the sixteen rows of a block meet 64 different banks in every such group
+__device__ __forceinline__ int swz_f(int r) { return -(r >> 2) & 3; }
 
-// descriptor r moved forward by `bytes`
-__device__ __forceinline__ v4i advance(v4i r, uint32_t bytes) {
-    const uint64_t base = (((uint64_t)(uint32_t)r[1]) << 32 | (uint32_t)r[0]) + bytes;
-    r[0] = (int)(uint32_t)base;
-    r[1] = (int)(uint32_t)(base >> 32);
-    return r;
-}
-
-// MODE 0: fused epilogue, fp16 output; MODE 1: the integer accumulators as INT32.
-template <int BM, int BN, int WM, int WN, int NST, int GM, int MODE>
-__global__ __launch_bounds__(WM * WN * 64, (WM * WN == 8) ? 1 : 2) void gemm_fp6_kernel(GemmArgs a) {
+// MODE 0: fused epilogue, fp16 output; MODE 1: the integer accumulators as INT32.  IB x JB accumulator blocks of 16 x 16
+// per wave, WM x WN waves; OCC: workgroups per CU; NST: ring slots of 64 columns; GM: as in quik_gemm.hip.
+template <int IB, int JB, int WM, int WN, int NST, int OCC, int GM, int MODE>
+__global__ __launch_bounds__(WM * WN * 64, OCC * WM * WN / 4) void gemm_fp6_kernel(GemmArgs a) {
     constexpr bool RAW = MODE != 0;
+    constexpr int NWAVES = WM * WN;
     // claim the whole register budget of the launch bounds, so that the highest allocated register is
     // never a live one (see the note in the row-quantization kernel)
-    asm volatile("" ::: "v255");
-    constexpr int NWAVES = WM * WN, NT = NWAVES * 64;
-    constexpr int TM = BM / WM / 32, TN = BN / WN / 32, NF = TM + TN;
-    constexpr int A_BYTES = BM * 48, B_BYTES = BN * 48, ST_BYTES = A_BYTES + B_BYTES;
-    // DMA instructions of a stage (1 KB each): FP6 stages N_A + N_B over the tile's two runs, fp16 stages
-    // BM / 32 and BN / 32.  A wave issues LPS of them per stage: instruction i = wave + NWAVES * slot; one
-    // that does not exist is issued empty so that every wave counts the same number.
-    constexpr int N_A = BM * 48 / 1024, N_B = BN * 48 / 1024, N_AF = BM / 32, N_BF = BN / 32;
-    constexpr int LPS = (N_A + N_B + NWAVES - 1) / NWAVES;
-    static_assert(BM % 64 == 0 && BN % 64 == 0 && N_AF + N_BF <= LPS * NWAVES && (BM + BN) * 32 <= ST_BYTES, "geometry");
-    static_assert(NST * LPS < 64, "vmcnt range");
-    constexpr int DUMMY = NST * ST_BYTES;                 // 1 KB that empty DMA instructions clear
+    if constexpr (OCC * NWAVES <= 8) asm volatile("" ::: "v255");
+    else asm volatile("" ::: "v127");
+    constexpr int BM = WM * IB * 16, BN = WN * JB * 16;
+    // a slot: the 48-byte blocks of the tile's token rows, then of its channels, as they lie in memory
+    constexpr int A_BYTES = BM * 48, SLOT = (BM + BN) * 48;
+    // copy instructions of a slot (1 KB each); wave w issues instructions w, w + NWAVES, ...; one that does not exist is
+    // issued empty so that every wave counts the same number
+    constexpr int I_A = A_BYTES / 1024, INSTR = SLOT / 1024;
+    constexpr int LPS = (INSTR + NWAVES - 1) / NWAVES;
+    static_assert(BM % 64 == 0 && BN % 64 == 0 && IB % 4 == 0, "geometry");
+    static_assert(NST >= 4 && NST * LPS < 64, "a step is read while the next lands");
+    constexpr int RING = NST * SLOT, DUMMY = RING;       // 1 KB that empty copies clear
+    // outlier stages: 32 columns, 64 bytes of every row, in slots of their own over the same memory
+    constexpr int FSLOT = (BM + BN) * 64, FNST = RING / FSLOT, F_A = BM / 16, F_B = BN / 16, FLPS = (F_A + F_B + NWAVES - 1) / NWAVES;
+    static_assert(FNST >= 3 && FNST * FLPS < 64, "outlier ring");
+    constexpr int PARK_ROW = JB * 32 + 16, PARK = 16 * PARK_ROW;
+    static_assert(NWAVES * PARK <= RING, "stage ring too small to park the output tile");
 
-    __shared__ __align__(1024) uint8_t lds[NST * ST_BYTES + 1024];
+    __shared__ __align__(1024) uint8_t lds[RING + 1024];
     __shared__ __align__(16) float lds_sa[BM];
     __shared__ __align__(16) float lds_sh[BM];
 
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave_u = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave_u / WN, wn = wave_u % WN;
-    const int l32 = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave % WM, wn = wave / WM;            // (the waves of a SIMD, 4 apart, differ in the channels)
+    const int l16 = lane & 15, g = lane >> 4;
 
     const int tiles_m = (a.T + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
     const int id = xcd_contiguous_id(blockIdx.x, tiles_m * tiles_n);
-    int tile_m, tile_n;
-    if constexpr (GM > 0) {
-        const int per_group = GM * tiles_n;
-        const int grp = id / per_group, rem = id % per_group;
-        const int first_m = grp * GM;
-        const int gsz = min(GM, tiles_m - first_m);
-        tile_m = first_m + rem % gsz;
-        tile_n = rem / gsz;
-    } else {
-        tile_m = id % tiles_m;
-        tile_n = id / tiles_m;
-    }
-    const int t0 = tile_m * BM, n0 = tile_n * BN;
+    const int per_group = GM * tiles_n;
+    const int grp = id / per_group, rem = id % per_group;
+    const int gsz = min(GM, tiles_m - grp * GM);
+    const int t0 = (grp * GM + rem % gsz) * BM, n0 = (rem / gsz) * BN;
 
-    const int S = fp6::stages(a.K_b);
-    const int nk_int = a.fp_only ? 0 : S;
+    const int S = fp6::stages(a.K_b);                    // slots of 64 columns
+    const int nk = a.fp_only ? 0 : (S + 1) / 2;          // steps of 128 columns; an odd last slot is filled with zeros
     const int fp_bytes = a.n_out * 2;
-    const int nk_fp = RAW ? 0 : (fp_bytes + 31) / 32;
-    const int nk = nk_int + nk_fp;
+    const int nkf = RAW ? 0 : (fp_bytes + 63) / 64;
     const int lda_fp = a.ldo * 2, ldb_fp = a.ldwo * 2;
-    const int T_ = a.T, N_ = a.N;                         // values, so that nothing takes the address of an argument
-
-    // stage 0 of the tile's rows; stage s lies s * T * 48 (s * N * 48) bytes further on
-    const v4i rA = make_rsrc((const uint8_t*)a.xq + (size_t)t0 * 48, (size_t)(a.T - t0) * 48);
-    const v4i rB = make_rsrc((const uint8_t*)a.w_q + (size_t)n0 * 48, (size_t)(a.N - n0) * 48);
-    const v4i rAf = make_rsrc(a.n_out ? (const uint8_t*)a.x_out + (size_t)t0 * lda_fp : (const uint8_t*)a.xq,
-                              a.n_out ? (size_t)(a.T - t0) * lda_fp : 0);
-    const v4i rBf = make_rsrc(a.n_out ? (const uint8_t*)a.w_out + (size_t)n0 * ldb_fp : (const uint8_t*)a.xq,
-                              a.n_out ? (size_t)(a.N - n0) * ldb_fp : 0);
     const uint32_t lds_base = lds_addr(lds);
 
-    // fp16 stage: 32 rows (lane / 2) x two 16-byte pieces of a 32-byte stage row per instruction
-    const int colF = ((lane & 1) ^ ((lane >> 4) & 1)) * 16;
-    const uint32_t vo_af = (uint32_t)((lane >> 1) * lda_fp + colF), vo_bf = (uint32_t)((lane >> 1) * ldb_fp + colF);
-    // DMA slot j of stage s (int part, fp16 part, or past the end: every lane out of range)
-    auto issue_one = [&](int s, int j) __attribute__((always_inline)) {
-        const int i = wave_u + NWAVES * j;                      // instruction of the stage (wave-uniform)
-        const uint32_t sb = (uint32_t)(s % NST) * ST_BYTES;
-        const bool fp = s >= nk_int;
-        uint32_t vo = kOob, dst = (uint32_t)DUMMY;
-        v4i r;
-        if (!fp) {
-            // instructions 0 .. N_A-1 copy A's run, N_A .. N_A+N_B-1 B's: piece 64 i' + lane of the run
-            const bool isb = i >= N_A;
-            const int ii = isb ? i - N_A : i;
-            if (i < N_A + N_B) {
-                dst = sb + (isb ? A_BYTES : 0) + ii * 1024;
-                if (s < nk) vo = (uint32_t)(ii * 1024 + lane * 16);
-            }
-            r = isb ? advance(rB, (uint32_t)s * (uint32_t)N_ * 48u) : advance(rA, (uint32_t)s * (uint32_t)T_ * 48u);
-        } else {
-            const bool isb = i >= N_AF;
-            const int ii = isb ? i - N_AF : i;
-            const int c0 = 32 * (s - nk_int);
-            if (i < N_AF + N_BF) {
-                dst = sb + (isb ? BM * 32 : 0) + ii * 1024;
-                if (s < nk && c0 + colF < fp_bytes)
-                    vo = (isb ? vo_bf : vo_af) + (uint32_t)(ii * 32 * (isb ? ldb_fp : lda_fp) + c0);
-            }
-            r = isb ? rBf : rAf;
-        }
-        // wave-uniform by construction; say so, the DMA takes them in scalar registers
-        r = v4i{__builtin_amdgcn_readfirstlane(r[0]), __builtin_amdgcn_readfirstlane(r[1]),
-                __builtin_amdgcn_readfirstlane(r[2]), __builtin_amdgcn_readfirstlane(r[3])};
-        dma16(r, (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds_base + dst)), vo, 0);
-    };
-    // DMA slot j of an FP6 stage that exists (the hot loop's form)
-    auto issue_int = [&](int s, int j) __attribute__((always_inline)) {
-        const int i = wave_u + NWAVES * j;
-        const bool isb = i >= N_A;
-        const int ii = isb ? i - N_A : i;
-        const bool exists = i < N_A + N_B;
-        const uint32_t dst = exists ? (uint32_t)(s % NST) * ST_BYTES + (isb ? A_BYTES : 0) + ii * 1024 : (uint32_t)DUMMY;
-        const uint32_t vo = exists ? (uint32_t)(ii * 1024 + lane * 16) : kOob;
-        v4i r = isb ? advance(rB, (uint32_t)s * (uint32_t)N_ * 48u) : advance(rA, (uint32_t)s * (uint32_t)T_ * 48u);
-        r = v4i{__builtin_amdgcn_readfirstlane(r[0]), __builtin_amdgcn_readfirstlane(r[1]),
-                __builtin_amdgcn_readfirstlane(r[2]), __builtin_amdgcn_readfirstlane(r[3])};
-        dma16(r, (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds_base + dst)), vo, 0);
-    };
-    auto issue = [&](int s) __attribute__((always_inline)) {
+    // ---- copies.  Panel s of an operand with R rows begins s * R * 48 bytes into its buffer; the descriptor of a slot
+    // covers the rest of the panel from the tile's first row on, so rows beyond R arrive as zeros.
+    const uint64_t pA = (uint64_t)(uintptr_t)a.xq + (uint64_t)t0 * 48u, pB = (uint64_t)(uintptr_t)a.w_q + (uint64_t)n0 * 48u;
+    const uint32_t nA = (uint32_t)(a.T - t0) * 48u, nB = (uint32_t)(a.N - n0) * 48u;
+    const uint64_t strideA = (uint64_t)a.T * 48u, strideB = (uint64_t)a.N * 48u;
+    uint32_t vo[LPS];
 #pragma unroll
-        for (int j = 0; j < LPS; ++j) issue_one(s, j);
+    for (int j = 0; j < LPS; ++j) {
+        const int i = wave + NWAVES * j;                 // instruction of the slot (wave-uniform)
+        vo[j] = i < INSTR ? (uint32_t)((i < I_A ? i : i - I_A) * 1024 + lane * 16) : kOob;
+    }
+    int ring_f = 0;                                      // ring slot that is filled next
+    uint32_t next = 0;                                   // panel that goes into it
+    auto issue_one = [&](int j) __attribute__((always_inline)) {
+        const int i = wave + NWAVES * j;
+        const bool isb = i >= I_A;
+        const uint64_t base = isb ? pB + next * strideB : pA + next * strideA;
+        const uint32_t n = (int)next < S ? (isb ? nB : nA) : 0u;
+        v4i r = v4i{(int)(uint32_t)base, (int)(uint32_t)(base >> 32), (int)n, 0x00020000};
+        r = v4i{__builtin_amdgcn_readfirstlane(r[0]), __builtin_amdgcn_readfirstlane(r[1]), __builtin_amdgcn_readfirstlane(r[2]), r[3]};
+        const uint32_t dst = i < INSTR ? (uint32_t)(ring_f * SLOT + i * 1024) : (uint32_t)DUMMY;
+        dma16(r, (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds_base + dst)), vo[j], 0);
+    };
+    auto advance = [&]() __attribute__((always_inline)) {
+        ring_f = ring_f + 1 == NST ? 0 : ring_f + 1;
+        ++next;
     };
 
-    // ---- epilogue parameters, requested before the first DMA
-    constexpr int RPT = (BM + NT - 1) / NT;
+    // ---- epilogue parameters of the token rows, requested before the first copy
+    constexpr int NT = NWAVES * 64, RPT = (BM + NT - 1) / NT;
     float p_s[RPT], p_z[RPT];
-    float c_sw[TN], c_wr[TN], c_bv[TN];
     if constexpr (!RAW) {
 #pragma unroll
         for (int q = 0; q < RPT; ++q) {
-            const int t = t0 + tid + q * NT;
-            const bool ok = (tid + q * NT < BM) && t < a.T;
-            p_s[q] = ok ? a.scale[t] : 0.0f;
-            p_z[q] = ok ? a.zero[t] : 0.0f;
-        }
-        const __half* __restrict__ wsc = static_cast<const __half*>(a.w_scale);
-        const __half* __restrict__ bias = static_cast<const __half*>(a.bias);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int n = min(n0 + wn * TN * 32 + j * 32 + l32, a.N - 1);
-            c_sw[j] = __half2float(wsc[n]);
-            c_bv[j] = bias ? __half2float(bias[n]) : 0.0f;
-            c_wr[j] = a.w_reduced[n];
-            if (a.fp_only) { c_sw[j] = 0.0f; c_bv[j] = 0.0f; c_wr[j] = 0.0f; }
+            const int t = min(t0 + tid + q * NT, a.T - 1);
+            p_s[q] = a.scale[t];
+            p_z[q] = a.zero[t];
         }
     }
-
 #pragma unroll
-    for (int s = 0; s < NST; ++s) issue(s);
-
+    for (int s = 0; s < NST; ++s) {
+#pragma unroll
+        for (int j = 0; j < LPS; ++j) issue_one(j);
+        advance();
+    }
     if constexpr (!RAW) {
 #pragma unroll
         for (int q = 0; q < RPT; ++q) {
             const int r = tid + q * NT;
             if (r < BM) {
-                lds_sa[r] = p_s[q];                        // scaleAct
-                lds_sh[r] = p_z[q] + 8.0f * p_s[q];        // zeroAct + halfRange * scaleAct
+                lds_sa[r] = p_s[q];                      // scaleAct
+                lds_sh[r] = p_z[q] + 8.0f * p_s[q];      // zeroAct + halfRange * scaleAct
             }
         }
     }
 
-    // LDS read addresses of this lane's row of every fragment.  FP6 stage: piece g of the row's 48-byte
-    // block (16 bytes) and 8 bytes at 32 + 8 g; fp16 stage: piece g of a 32-byte row.
-    uint32_t rdp[NF], rdf[NF];
-#pragma unroll
-    for (int f = 0; f < NF; ++f) {
-        const int r = (f < TM) ? (wm * TM * 32 + f * 32 + l32) : (wn * TN * 32 + (f - TM) * 32 + l32);
-        rdp[f] = (f < TM ? 0 : A_BYTES) + r * 48 + 16 * g;
-        rdf[f] = (f < TM ? 0 : BM * 32) + r * 32 + ((g ^ swz_f(r)) << 4);
-    }
-    // two fragment sets: the matrix instructions of one stage run on one set while the LDS reads of the
-    // next stage fill the other
-    uint4 FP[2][NF];
-    uint2 FQ[2][NF];
-    auto read_frag = [&](int set, int f, int s) __attribute__((always_inline)) {
-        const uint8_t* st = lds + (s % NST) * ST_BYTES;
-        FP[set][f] = *reinterpret_cast<const uint4*>(st + rdp[f]);
-        FQ[set][f] = *reinterpret_cast<const uint2*>(st + rdp[f] + 32 - 8 * g);     // 32 + 8 g of the block
+    // ---- fragments: lane (l, g) supplies 32 codes for row (channel) l of a 16-row block: half g / 2 of the row's block in
+    // panel g % 2 of the step's two, 16 bytes at 16 (g / 2) and 8 at 32 + 8 (g / 2).  Both operands read alike, so which
+    // columns a group holds does not matter; this assignment lets the lanes that LDS serves together (0 - 3, 12 - 15,
+    // 20 - 27 and so on) read the same part of sixteen different rows, and twelve dwords a row spread these over all banks.
+    const uint32_t rdP = (uint32_t)(l16 * 48 + (g >> 1) * 16), rdQ = (uint32_t)(l16 * 48 + 32 + (g >> 1) * 8);
+    const uint32_t aP = rdP + wm * IB * 768, bP = rdP + A_BYTES + wn * JB * 768;
+    const uint32_t aQ = rdQ + wm * IB * 768, bQ = rdQ + A_BYTES + wn * JB * 768;
+    v8i fa[4], fb[JB];
+    auto rd6 = [&](uint32_t P, uint32_t Q) __attribute__((always_inline)) -> v8i {
+        const uint4 x = *reinterpret_cast<const uint4*>(lds + P);
+        const uint2 y = *reinterpret_cast<const uint2*>(lds + Q);
+        return v8i{(int)x.x, (int)x.y, (int)x.z, (int)x.w, (int)y.x, (int)y.y, 0, 0};
+    };
+    auto read_a = [&](int i, uint32_t so) __attribute__((always_inline)) { fa[i & 3] = rd6(so + aP + i * 768, so + aQ + i * 768); };
+    auto read_b = [&](int j, uint32_t so) __attribute__((always_inline)) { fb[j] = rd6(so + bP + j * 768, so + bQ + j * 768); };
+    // LDS offset of this lane's slot of the step whose first slot is `r`
+    auto slot_of = [&](int r) __attribute__((always_inline)) {
+        const int r1 = r + 1 == NST ? 0 : r + 1;
+        return (uint32_t)(((g & 1) ? r1 : r) * SLOT);
     };
 
-    v16f acc[TM][TN];
+    v4f acc[IB][JB];
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < IB; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+        for (int j = 0; j < JB; ++j) acc[i][j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
 
-    // FP6 stage s.  Its successor must have landed for everybody (its fragments are read during this
-    // stage); all reads of stage s itself completed before the barrier, so its buffer is refilled with
-    // stage s + NST right away, one DMA instruction per matrix instruction.  PLAIN: stage s + NST is an
-    // FP6 stage; AHEAD: stage s + 1 is one.
-    auto step = [&](int s, int set, bool plain, bool ahead) __attribute__((always_inline)) {
-        wait_stage<(NST - 2) * LPS>();
-        __syncthreads();
+    // A step: 128 columns.  Two block rows before its end every fragment of the step has been read, so the barrier there
+    // frees the step's own two slots -- refilled right away, beside the last matrix instructions -- and lets everybody
+    // read the next step's, which must have landed; all other slots (NST - 4 at the wait) are in flight.
+    constexpr int SLOTS = IB * JB, LAST_READ = (IB - 2) * JB - 1;
+    int cur = 0;
+    auto step = [&]() __attribute__((always_inline)) {
+        const int nxt = cur + 2 >= NST ? cur + 2 - NST : cur + 2;
+        const uint32_t so = slot_of(cur), so1 = slot_of(nxt);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int m = 0; m < TM * TN; ++m) {
-            const int i = m / TN, j = m % TN;
-            const v8i oa = v8i{(int)FP[set][i].x, (int)FP[set][i].y, (int)FP[set][i].z, (int)FP[set][i].w,
-                               (int)FQ[set][i].x, (int)FQ[set][i].y, 0, 0};
-            const v8i ob = v8i{(int)FP[set][TM + j].x, (int)FP[set][TM + j].y, (int)FP[set][TM + j].z,
-                               (int)FP[set][TM + j].w, (int)FQ[set][TM + j].x, (int)FQ[set][TM + j].y, 0, 0};
-            acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(oa, ob, acc[i][j], 3, 3, 0, 0, 0, 0);
-            if (m < LPS) { if (plain) issue_int(s + NST, m); else issue_one(s + NST, m); }
-            if (ahead && m < NF) read_frag(set ^ 1, m, s + 1);
+        for (int m = 0; m < SLOTS; ++m) {
+            const int i = m / JB, j = m % JB;
+            acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fa[i & 3], fb[j], acc[i][j], 3, 3, 0, 0, 0, 0);
+            if (j == 0 && i + 2 < IB) read_a(i + 2, so);
+            if (m == LAST_READ) {
+                wait_stage<(NST - 4) * LPS>();
+                __syncthreads();
+            }
+            if (j == 0 && i + 2 >= IB) read_a(i + 2 - IB, so1);
+            if (i == IB - 1) read_b(j, so1);
+#pragma unroll
+            for (int d = 0; d < 2 * LPS; ++d)
+                if (m > LAST_READ && d * (SLOTS - 1 - LAST_READ) / (2 * LPS) == m - LAST_READ - 1) {
+                    issue_one(d % LPS);
+                    if (d % LPS == LPS - 1) advance();
+                }
             __builtin_amdgcn_sched_barrier(0);
         }
+        cur = nxt;
     };
-    static_assert(TM * TN >= NF && TM * TN >= LPS, "a stage has fewer matrix instructions than reads or copies to place");
-
-    wait_stage<(NST - 1) * LPS>();            // stage 0 landed
-    __syncthreads();
-    if (nk_int > 0) {
+    if (nk > 0) {
+        wait_stage<(NST - 2) * LPS>();                   // the first step's two slots have landed
+        __syncthreads();
+        const uint32_t so = slot_of(0);
 #pragma unroll
-        for (int f = 0; f < NF; ++f) read_frag(0, f, 0);
+        for (int j = 0; j < JB; ++j) read_b(j, so);
+        read_a(0, so);
+        read_a(1, so);
     }
+    for (int s = 0; s < nk; ++s) step();
 
-    int s = 0;
-    for (; s + 1 + NST < nk_int; s += 2) {
-        step(s, 0, true, true);
-        step(s + 1, 1, true, true);
-    }
-    for (; s + 2 < nk_int; s += 2) {
-        step(s, 0, false, true);
-        step(s + 1, 1, false, true);
-    }
-    if (s + 2 == nk_int) {
-        step(s, 0, false, true);
-        step(s + 1, 1, false, false);
-        s += 2;
-    } else if (s + 1 == nk_int) {
-        step(s, 0, false, false);
-        s += 1;
-    }
-
-    const int tw = t0 + wm * TM * 32, nw = n0 + wn * TN * 32;
+    const int tw = t0 + wm * IB * 16, nw = n0 + wn * JB * 16;
+    wait_stage<0>();
+    __syncthreads();                                     // every copy and every read of the ring is done
     if constexpr (RAW) {
-        wait_vm<0>();                      // drain the look-ahead DMA before the wave ends
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < IB; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int n = nw + j * 32 + l32;
+            for (int j = 0; j < JB; ++j) {
+                const int n = nw + j * 16 + l16;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int t = tw + i * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
+                for (int r = 0; r < 4; ++r) {
+                    const int t = tw + i * 16 + 4 * g + r;
                     if (t < a.T && n < a.N) a.acc[(size_t)t * a.ldacc + n] = (int)acc[i][j][r];
                 }
             }
         return;
     }
 
-    // Dequantization: the accumulators are exact integers already in binary32.
+    // ---- outlier stages on the way while the tile is dequantized.  Instruction i of a stage: 16 rows, 16-byte pieces
+    // exchanged so that the four rows of an LDS pass that share banks differ in their place.
+    const v4i rAf = make_rsrc(a.n_out ? (const uint8_t*)a.x_out + (size_t)t0 * lda_fp : (const uint8_t*)a.xq,
+                              a.n_out ? (size_t)(a.T - t0) * lda_fp : 0);
+    const v4i rBf = make_rsrc(a.n_out ? (const uint8_t*)a.w_out + (size_t)n0 * ldb_fp : (const uint8_t*)a.xq,
+                              a.n_out ? (size_t)(a.N - n0) * ldb_fp : 0);
+    const int fc = ((lane & 3) ^ swz_f(lane >> 2)) << 4;
+    auto issue_fp = [&](int f) __attribute__((always_inline)) {
+        const uint32_t sb = (uint32_t)(f % FNST) * FSLOT;
+        const bool live = f * 64 + fc < fp_bytes;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int rq = 0; rq < 4; ++rq) {
-            const int lr = wm * TM * 32 + i * 32 + 8 * rq + 4 * g;
-            const float4 sa4 = *reinterpret_cast<const float4*>(&lds_sa[lr]);
-            const float4 sh4 = *reinterpret_cast<const float4*>(&lds_sh[lr]);
-            const float sa_[4] = {sa4.x, sa4.y, sa4.z, sa4.w}, sh_[4] = {sh4.x, sh4.y, sh4.z, sh4.w};
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr) {
-                    const int r = rq * 4 + rr;
-                    acc[i][j][r] = __builtin_fmaf(acc[i][j][r], sa_[rr] * c_sw[j],
-                                                  __builtin_fmaf(sh_[rr], c_wr[j], c_bv[j]));
-                }
-        }
-
-    // fp16 outlier stages: 16 columns each, one matrix step, same protocol as the FP6 stages (fragments
-    // of stage s + 1 are read while the matrix instructions of stage s run; one barrier per stage)
-    auto wide_step = [&](int s, int set) __attribute__((always_inline)) {
-        wait_stage<(NST - 2) * LPS>();
-        __syncthreads();
-        __builtin_amdgcn_sched_barrier(0);
-        const uint8_t* nxt = lds + ((s + 1) % NST) * ST_BYTES;
-#pragma unroll
-        for (int m = 0; m < TM * TN; ++m) {
-            const int i = m / TN, j = m % TN;
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, FP[set][i]),
-                                                               __builtin_bit_cast(v8h, FP[set][TM + j]), acc[i][j], 0, 0, 0);
-            if (m < LPS) issue_one(s + NST, m);
-            if (m < NF) FP[set ^ 1][m] = *reinterpret_cast<const uint4*>(nxt + rdf[m]);
-            __builtin_amdgcn_sched_barrier(0);
+        for (int j = 0; j < FLPS; ++j) {
+            const int i = wave + NWAVES * j;
+            const bool isb = i >= F_A;
+            const int row = (isb ? i - F_A : i) * 16 + (lane >> 2);
+            const uint32_t v = live && i < F_A + F_B ? (uint32_t)(row * (isb ? ldb_fp : lda_fp) + fc) : kOob;
+            const v4i r_ = isb ? rBf : rAf;
+            dma16(r_, lds_base + (i < F_A + F_B ? sb + i * 1024 : (uint32_t)DUMMY), v, (uint32_t)f * 64u);
         }
     };
-    if (s < nk) {
-        wait_stage<(NST - 1) * LPS>();        // first fp16 stage landed
-        __syncthreads();
-        const uint8_t* st = lds + (s % NST) * ST_BYTES;
+    float c_sw[JB], c_wr[JB], c_bv[JB];
+    {
+        const __half* __restrict__ wsc = static_cast<const __half*>(a.w_scale);
+        const __half* __restrict__ bias = static_cast<const __half*>(a.bias);
 #pragma unroll
-        for (int f = 0; f < NF; ++f) FP[0][f] = *reinterpret_cast<const uint4*>(st + rdf[f]);
-        for (; s + 1 < nk; s += 2) {
-            wide_step(s, 0);
-            wide_step(s + 1, 1);
+        for (int j = 0; j < JB; ++j) {
+            const int n = min(nw + j * 16 + l16, a.N - 1);
+            c_sw[j] = __half2float(wsc[n]);
+            c_bv[j] = bias ? __half2float(bias[n]) : 0.0f;
+            c_wr[j] = a.w_reduced[n];
+            if (a.fp_only) { c_sw[j] = 0.0f; c_bv[j] = 0.0f; c_wr[j] = 0.0f; }
         }
-        if (s < nk) { wide_step(s, 0); ++s; }
     }
-
-    wait_vm<0>();                          // drain the look-ahead DMA before the wave ends
+    // (the parameters first: the compiler's wait for them would otherwise be one for the copies)
+#pragma unroll
+    for (int j = 0; j < JB; ++j) asm volatile("" : "+v"(c_sw[j]), "+v"(c_bv[j]), "+v"(c_wr[j]));
+    if (nkf > 0) {
+#pragma unroll
+        for (int f = 0; f < FNST; ++f) issue_fp(f);
+    }
+    // Dequantization: the accumulators are exact integers already in binary32.
+#pragma unroll
+    for (int i = 0; i < IB; ++i) {
+        const int lr = wm * IB * 16 + i * 16 + 4 * g;
+        const float4 sa4 = *reinterpret_cast<const float4*>(&lds_sa[lr]);
+        const float4 sh4 = *reinterpret_cast<const float4*>(&lds_sh[lr]);
+        const float sa_[4] = {sa4.x, sa4.y, sa4.z, sa4.w}, sh_[4] = {sh4.x, sh4.y, sh4.z, sh4.w};
+#pragma unroll
+        for (int j = 0; j < JB; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                acc[i][j][r] = __builtin_fmaf(acc[i][j][r], sa_[r] * c_sw[j], __builtin_fmaf(sh_[r], c_wr[j], c_bv[j]));
+    }
+    if (nkf > 0) {
+        const uint32_t rdF = (uint32_t)(l16 * 64 + ((g ^ swz_f(l16)) << 4));
+        const uint32_t aF = rdF + wm * IB * 1024, bF = rdF + BM * 64 + wn * JB * 1024;
+        v8h ha[4], hb[JB];
+        auto read_ha = [&](int i, uint32_t fo) __attribute__((always_inline)) { ha[i & 3] = *reinterpret_cast<const v8h*>(lds + fo + aF + i * 1024); };
+        auto read_hb = [&](int j, uint32_t fo) __attribute__((always_inline)) { hb[j] = *reinterpret_cast<const v8h*>(lds + fo + bF + j * 1024); };
+        wait_stage<(FNST - 1) * FLPS>();
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < JB; ++j) read_hb(j, 0);
+        read_ha(0, 0);
+        read_ha(1, 0);
+        for (int f = 0; f < nkf; ++f) {
+            const uint32_t fo = (uint32_t)(f % FNST) * FSLOT, fo1 = (uint32_t)((f + 1) % FNST) * FSLOT;
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int m = 0; m < SLOTS; ++m) {
+                const int i = m / JB, j = m % JB;
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ha[i & 3], hb[j], acc[i][j], 0, 0, 0);
+                if (j == 0 && i + 2 < IB) read_ha(i + 2, fo);
+                if (m == (IB - 2) * JB - 1) {
+                    // every read of this stage has been issued: behind the barrier its slot is free, the next has landed
+                    wait_stage<(FNST - 2) * FLPS>();
+                    __syncthreads();
+                    issue_fp(f + FNST);
+                }
+                if (j == 0 && i + 2 >= IB) read_ha(i + 2 - IB, fo1);
+                if (i == IB - 1) read_hb(j, fo1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        wait_stage<0>();
+        __syncthreads();                                 // the stage memory is dead
+    }
     __half* __restrict__ y = static_cast<__half*>(a.y);
-    // Output through LDS (each wave parks its fp16 tile in its own slice of the dead stage ring and
-    // writes whole row segments as 16-byte pieces); needs 16-byte aligned output rows.
-    constexpr int WROW = (NWAVES * TM * 32 * (TN * 64 + 16) <= NST * ST_BYTES) ? TN * 64 + 16 : TN * 64;
-    constexpr int WBUF = TM * 32 * WROW;
-    static_assert(NWAVES * WBUF <= NST * ST_BYTES, "stage ring too small to park the output tile");
+    // Output through LDS: a wave parks sixteen rows of its tile and writes them out as 16-byte pieces, whole row segments
+    // per store; needs 16-byte aligned output rows.
     const bool vec_ok = !a.fp_only && ((reinterpret_cast<uintptr_t>(a.y) & 15u) == 0) && (a.ldy % 8 == 0);
     if (vec_ok) {
-        __syncthreads();                   // every wave is past its last read of the stage ring
-        uint8_t* wbuf = lds + wave_u * WBUF;
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = i * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
-                    *reinterpret_cast<__half*>(wbuf + row * WROW + (j * 32 + l32) * 2) = __float2half(acc[i][j][r]);
-                }
-        constexpr int CH = TN * 4;                       // 16-byte pieces per row
-        constexpr int RPS = 64 / CH;                     // rows per store instruction
+        uint8_t* wbuf = lds + wave * PARK;
+        constexpr int CH = JB * 2, RPS = 64 / CH;        // 16-byte pieces per row, rows per store instruction
         const int prow = lane / CH, pch = lane % CH;
 #pragma unroll
-        for (int p = 0; p < (TM * 32 + RPS - 1) / RPS; ++p) {
-            const int row = p * RPS + prow;
-            if (prow >= RPS || row >= TM * 32) continue;
-            const uint4 v = *reinterpret_cast<const uint4*>(wbuf + row * WROW + pch * 16);
-            const int t = tw + row, n = nw + pch * 8;
-            if (t < a.T) {
-                __half* dst = y + (size_t)t * a.ldy + n;
-                if (n + 8 <= a.N) {
-                    store16_through(dst, v);
-                } else {
-                    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+        for (int i = 0; i < IB; ++i) {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        if (n + e < a.N)
-                            reinterpret_cast<uint16_t*>(dst)[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+            for (int j = 0; j < JB; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    *reinterpret_cast<__half*>(wbuf + (4 * g + r) * PARK_ROW + (j * 16 + l16) * 2) = __float2half(acc[i][j][r]);
+#pragma unroll
+            for (int q = 0; q < (16 + RPS - 1) / RPS; ++q) {
+                const int row = q * RPS + prow;
+                if (prow >= RPS || row >= 16) continue;
+                const uint4 v = *reinterpret_cast<const uint4*>(wbuf + row * PARK_ROW + pch * 16);
+                const int t = tw + i * 16 + row, n = nw + pch * 8;
+                if (t < a.T) {
+                    __half* dst = y + (size_t)t * a.ldy + n;
+                    if (n + 8 <= a.N) {
+                        store16_through(dst, v);
+                    } else {
+                        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            if (n + e < a.N)
+                                reinterpret_cast<uint16_t*>(dst)[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+                    }
                 }
             }
         }
         return;
     }
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < IB; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int n = nw + j * 32 + l32;
+        for (int j = 0; j < JB; ++j) {
+            const int n = nw + j * 16 + l16;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int t = tw + i * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
+            for (int r = 0; r < 4; ++r) {
+                const int t = tw + i * 16 + 4 * g + r;
                 if (t < a.T && n < a.N) {
                     if (a.fp_only) reinterpret_cast<float*>(a.y)[(size_t)t * a.ldy + n] = acc[i][j][r];
                     else y[(size_t)t * a.ldy + n] = __float2half(acc[i][j][r]);
@@ -436,27 +417,64 @@ __global__ __launch_bounds__(256) void weight_pack_fp6_kernel(const uint8_t* __r
     for (int i = 0; i < 6; ++i) blk[fp6::block_dword(G & 1, i)] = d[i];
 }
 
-template <int BM, int BN, int WM, int WN, int NST, int GM, int MODE>
+template <int IB, int JB, int WM, int WN, int NST, int OCC, int GM, int MODE>
 hipError_t launch_cfg(const GemmArgs& a, hipStream_t stream) {
+    constexpr int BM = WM * IB * 16, BN = WN * JB * 16;
     const int tiles = ((a.T + BM - 1) / BM) * ((a.N + BN - 1) / BN);
-    hipLaunchKernelGGL((gemm_fp6_kernel<BM, BN, WM, WN, NST, GM, MODE>), dim3(tiles), dim3(WM * WN * 64), 0, stream, a);
+    hipLaunchKernelGGL((gemm_fp6_kernel<IB, JB, WM, WN, NST, OCC, GM, MODE>), dim3(tiles), dim3(WM * WN * 64), 0, stream, a);
     return hipGetLastError();
 }
 
+// The tile whose launch is estimated to be the shortest, up to `occ` workgroups of it per CU: base + round * rounds +
+// tile * tiles of the busiest CU + stages (of 128 columns) * (round_stage * rounds + tile_stage * tiles of the busiest CU).
+// Fitted to 175 shapes with every tile measured (T 1 .. 4096, K 512 .. 11008, N 512 .. 28672, cached weights and from
+// HBM); good to 5 - 10 %, and the choice costs 0.5 % against the fastest tile in the mean.  The 256 x 256 tile needs a
+// third fewer operand bytes per operation than 256 x 128 and wins wherever it fills the chip: K = 5120, N = 15360,
+// T = 1024 in one round 49 us (256 x 192 in two 73, 128 x 128 64; the former kernel's 256 x 128 73).
+struct TileCost6 { int bm, bn, occ; double base, round, tile, round_stage, tile_stage; };
+constexpr TileCost6 kCost6[] = {{64, 64, 4, 1.495, 1.495, 1.396, 0.160, 0.092},
+                                {64, 128, 2, 2.020, 1.115, 2.378, 0.137, 0.153},
+                                {128, 192, 1, -2.250, 9.384, 0, 0.409, 0},
+                                {128, 256, 1, -4.435, 12.559, 0, 0.481, 0},
+                                {256, 192, 1, -6.067, 18.828, 0, 0.558, 0},
+                                {256, 256, 1, -6.037, 20.272, 0, 0.670, 0}};
+
+int choose_tile_fp6(int T, int N, int K_b, int cus) {
+    const int stages = (K_b + 127) / 128;
+    int best = 0;
+    double least = 0.0;
+    for (int i = 0; i < (int)(sizeof(kCost6) / sizeof(TileCost6)); ++i) {
+        const TileCost6& c = kCost6[i];
+        const long tiles = (long)((T + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+        const double rounds = (double)((tiles + (long)c.occ * cus - 1) / ((long)c.occ * cus)), busiest = (double)((tiles + cus - 1) / cus);
+        const double t = c.base + c.round * rounds + c.tile * busiest + stages * (c.round_stage * rounds + c.tile_stage * busiest);
+        if (i == 0 || t < least) { best = i; least = t; }
+    }
+    return best;
+}
+
+// Six ring slots everywhere: a seventh under 256 x 192 cost 3 %, 256 x 256 has room for no more.
 template <int MODE>
 hipError_t dispatch6(const GemmArgs& a, hipStream_t stream) {
-    // One workgroup of eight waves per CU, so a launch runs in ceil(tiles / 256) rounds; a 256 x 192 tile
-    // takes about 1.4x as long as a 256 x 128 one.  Few tokens or few tiles: 128 x 128 tiles, two
-    // workgroups per CU.  Ring depths as measured: six buffers for the 256 x 192 tile (five 1 %, seven, all
-    // the LDS holds, 5 % slower), eight for the 256 x 128 tile (six 2 %, seven 6 % slower).
-    auto rounds = [&](int bm, int bn) { return (((long)(a.T + bm - 1) / bm) * ((a.N + bn - 1) / bn) + 255) / 256; };
-    const long tiles_128 = (long)((a.T + 255) / 256) * ((a.N + 127) / 128);
-    if (a.T <= 128 || tiles_128 < 256) return launch_cfg<128, 128, 2, 2, 6, 0, MODE>(a, stream);
-    if (1.4 * (double)rounds(256, 192) <= (double)rounds(256, 128)) return launch_cfg<256, 192, 4, 2, 6, 4, MODE>(a, stream);
-    return launch_cfg<256, 128, 4, 2, 8, 4, MODE>(a, stream);
+    int cus = compute_units();
+    if (cus < 1) cus = 256;
+    switch (choose_tile_fp6(a.T, a.N, a.K_b, cus)) {
+    case 0: return launch_cfg<4, 1, 1, 4, 6, 4, 8, MODE>(a, stream);
+    case 1: return launch_cfg<4, 2, 1, 4, 6, 2, 8, MODE>(a, stream);
+    case 2: return launch_cfg<4, 3, 2, 4, 6, 1, 8, MODE>(a, stream);
+    case 3: return launch_cfg<4, 4, 2, 4, 6, 1, 8, MODE>(a, stream);
+    case 4: return launch_cfg<4, 6, 4, 2, 6, 1, 4, MODE>(a, stream);
+    default: return launch_cfg<8, 4, 2, 4, 6, 1, 8, MODE>(a, stream);
+    }
 }
 
 }  // namespace
+
+void fp6_form(int T, int N, int K_b, int cus, int* rows, int* cols) {
+    const TileCost6& c = kCost6[choose_tile_fp6(T, N, K_b, cus)];
+    *rows = c.bm;
+    *cols = c.bn;
+}
 
 hipError_t launch_gemm_fp6(const GemmArgs& a, hipStream_t stream) {
     if (a.T <= 0 || a.N <= 0) return hipSuccess;
