@@ -434,6 +434,7 @@ hipError_t launch_cfg(const GemmArgs& a, hipStream_t stream) {
 struct TileCost6 { int bm, bn, occ; double base, round, tile, round_stage, tile_stage; };
 constexpr TileCost6 kCost6[] = {{64, 64, 4, 1.495, 1.495, 1.396, 0.160, 0.092},
                                 {64, 128, 2, 2.020, 1.115, 2.378, 0.137, 0.153},
+                                {128, 128, 2, 1.548, 1.632, 4.020, 0.099, 0.250},
                                 {128, 192, 1, -2.250, 9.384, 0, 0.409, 0},
                                 {128, 256, 1, -4.435, 12.559, 0, 0.481, 0},
                                 {256, 192, 1, -6.067, 18.828, 0, 0.558, 0},
@@ -461,9 +462,10 @@ hipError_t dispatch6(const GemmArgs& a, hipStream_t stream) {
     switch (choose_tile_fp6(a.T, a.N, a.K_b, cus)) {
     case 0: return launch_cfg<4, 1, 1, 4, 6, 4, 8, MODE>(a, stream);
     case 1: return launch_cfg<4, 2, 1, 4, 6, 2, 8, MODE>(a, stream);
-    case 2: return launch_cfg<4, 3, 2, 4, 6, 1, 8, MODE>(a, stream);
-    case 3: return launch_cfg<4, 4, 2, 4, 6, 1, 8, MODE>(a, stream);
-    case 4: return launch_cfg<4, 6, 4, 2, 6, 1, 4, MODE>(a, stream);
+    case 2: return launch_cfg<4, 4, 2, 2, 6, 2, 8, MODE>(a, stream);
+    case 3: return launch_cfg<4, 3, 2, 4, 6, 1, 8, MODE>(a, stream);
+    case 4: return launch_cfg<4, 4, 2, 4, 6, 1, 8, MODE>(a, stream);
+    case 5: return launch_cfg<4, 6, 4, 2, 6, 1, 4, MODE>(a, stream);
     default: return launch_cfg<8, 4, 2, 4, 6, 1, 8, MODE>(a, stream);
     }
 }

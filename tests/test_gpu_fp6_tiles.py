@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 SHAPES = {
     (12, 74, 184, 16): (64, 64), (70, 136, 2056, 264): (64, 64), (65, 64, 64, 0): (64, 64),
     (97, 8206, 96, 32): (64, 128), (130, 6000, 1104, 48): (64, 128),
-    (142, 11074, 112, 40): (128, 192), (300, 7000, 1000, 104): (128, 192),
+    (151, 10910, 176, 40): (128, 128), (300, 7000, 1000, 104): (128, 128),
+    (142, 11074, 112, 40): (128, 192), (340, 12000, 1000, 104): (128, 192),
     (709, 8110, 96, 32): (128, 256), (700, 8112, 776, 0): (128, 256),
     (666, 10926, 104, 40): (256, 192), (666, 10928, 904, 136): (256, 192),
     (803, 12438, 112, 40): (256, 256), (770, 14000, 904, 72): (256, 256),
