@@ -13,8 +13,10 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libquik.so")
+CALL_PATH = os.path.join(_HERE, "_quik_call.so")
 
 _lib = None
+_call = None          # native marshalling of the layer calls (csrc/quik_call.cpp), set by load()
 
 
 class QuikError(RuntimeError):
@@ -121,8 +123,37 @@ def load() -> C.CDLL:
         lib.quik_debug_copy_probe.argtypes = [vp, vp, C.c_size_t, vp]
         lib.quik_check_outlier_idx_host.restype = i
         lib.quik_check_outlier_idx_host.argtypes = [vp, i, i]
+        _load_call(lib)
         _lib = lib
     return _lib
+
+
+def _load_call(lib):
+    global _call
+    if not os.path.exists(CALL_PATH):
+        raise ImportError(
+            f"{CALL_PATH} is missing: build it with `python -m paper_2310_09259_amd.build` "
+            "(there is no fallback path)")
+    import importlib.machinery
+    import importlib.util
+    loader = importlib.machinery.ExtensionFileLoader("_quik_call", CALL_PATH)
+    call = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_quik_call", CALL_PATH, loader=loader))
+    call.bind(*(C.cast(fn, C.c_void_p).value
+                for fn in (lib.quik_linear, lib.quik_linear_w4a8, lib.quik_linear_fp6, lib.quik_linear_sp24,
+                           lib.quik_quantize, lib.quik_gemm_dequant)))
+    _call = call
+
+
+def _fast_linear(kind, where, x, outlier_idx, w, w_scale, w_reduced, w_out, bias, out, workspace):
+    """True if the native marshalling served the call; False: not an ordinary call, nothing was enqueued."""
+    if _call is None:
+        load()
+    rc = _call.linear(kind, x, outlier_idx, w, w_scale, w_reduced, w_out, bias, out, workspace)
+    if rc is None:
+        return False
+    if rc != 0:
+        raise QuikError(rc, where)
+    return True
 
 
 def _ptr(t):
@@ -237,6 +268,13 @@ def quik_quantize(x, outlier_idx, bits: int, out=None):
     """x fp16 [T,K] -> (xq uint8 [T,ldq], scale f32 [T], zero f32 [T], x_out f16 [T,n_out],
     workspace uint8 [quik_quantize_workspace_bytes]).  The workspace carries the side data that
     quik_gemm_dequant needs beside xq for bits = 4."""
+    if type(out) is tuple and len(out) == 5:
+        if _call is None:
+            load()
+        rc = _call.quantize(x, outlier_idx, bits, *out)
+        if rc is not None:
+            _check(rc, "quik_quantize")
+            return out
     x = _dev(x, torch.float16, "x")
     T, K = x.shape
     n_out = 0 if outlier_idx is None else int(outlier_idx.numel())
@@ -286,6 +324,13 @@ def _gemm_dequant_args(xq, scale, zero, x_out, K_b, bits, w_q, w_scale, w_reduce
 def quik_gemm_dequant(xq, scale, zero, x_out, K_b: int, bits: int, w_q, w_scale, w_reduced, w_out, bias=None,
                       out=None, workspace=None):
     """workspace: the one quik_quantize returned together with xq (needed for bits = 4)."""
+    if out is not None:
+        if _call is None:
+            load()
+        rc = _call.gemm_dequant(xq, scale, zero, x_out, K_b, bits, w_q, w_scale, w_reduced, w_out, bias, out, workspace)
+        if rc is not None:
+            _check(rc, "quik_gemm_dequant")
+            return out
     xq = _dev(xq, torch.uint8, "xq")
     w_q = _dev(w_q, torch.uint8, "w_q")
     T, N = xq.shape[0], w_q.shape[0]
@@ -339,6 +384,9 @@ def _linear_args(x, outlier_idx, bits, w_q, w_scale, w_reduced, w_out, bias, y, 
 
 def quik_linear(x, outlier_idx, bits: int, w_q, w_scale, w_reduced, w_out, bias=None, out=None, workspace=None):
     """Whole layer.  Returns y fp16 [T, N]."""
+    if (out is not None and workspace is not None and (bits == 4 or bits == 8) and
+            _fast_linear(bits, "quik_linear", x, outlier_idx, w_q, w_scale, w_reduced, w_out, bias, out, workspace)):
+        return out
     y, workspace = _linear_buffers(x, outlier_idx, bits, w_q, out, workspace)
     rc = load().quik_linear(*_linear_args(x, outlier_idx, bits, w_q, w_scale, w_reduced, w_out, bias, y, workspace))
     _check(rc, "quik_linear")
@@ -399,6 +447,9 @@ def quik_int_gemm_w4a8(xq, w_q, K_b: int):
 
 def quik_linear_w4a8(x, outlier_idx, w_q, w_scale, w_reduced, w_out, bias=None, out=None, workspace=None):
     """Whole layer with 8-bit activations and packed 4-bit weights.  Returns y fp16 [T, N]."""
+    if (out is not None and workspace is not None and
+            _fast_linear(84, "quik_linear_w4a8", x, outlier_idx, w_q, w_scale, w_reduced, w_out, bias, out, workspace)):
+        return out
     x = _dev(x, torch.float16, "x")
     w_q = _dev(w_q, torch.uint8, "w_q")
     T, K = x.shape
@@ -578,6 +629,9 @@ def _linear_fp6_buffers(x, outlier_idx, w6, out, workspace):
 
 def quik_linear_fp6(x, outlier_idx, w6, w_scale, w_reduced, w_out, bias=None, out=None, workspace=None):
     """Whole 4-bit layer on the FP6 matrix path.  Returns y fp16 [T, N]."""
+    if (out is not None and workspace is not None and
+            _fast_linear(6, "quik_linear_fp6", x, outlier_idx, w6, w_scale, w_reduced, w_out, bias, out, workspace)):
+        return out
     y, workspace = _linear_fp6_buffers(x, outlier_idx, w6, out, workspace)
     rc = load().quik_linear_fp6(*_linear_fp6_args(x, outlier_idx, w6, w_scale, w_reduced, w_out, bias, y, workspace))
     _check(rc, "quik_linear_fp6")
@@ -723,6 +777,9 @@ def _linear_sp24_buffers(x, outlier_idx, w24, w_scale, out, workspace):
 
 def quik_linear_sp24(x, outlier_idx, w24, w_scale, w_reduced, w_out, bias=None, out=None, workspace=None):
     """Whole 4-bit layer with 2:4-sparse weights.  Returns y fp16 [T, N]."""
+    if (out is not None and workspace is not None and
+            _fast_linear(24, "quik_linear_sp24", x, outlier_idx, w24, w_scale, w_reduced, w_out, bias, out, workspace)):
+        return out
     y, workspace = _linear_sp24_buffers(x, outlier_idx, w24, w_scale, out, workspace)
     rc = load().quik_linear_sp24(*_linear_sp24_args(x, outlier_idx, w24, w_scale, w_reduced, w_out, bias, y,
                                                     workspace))

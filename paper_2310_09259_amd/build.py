@@ -19,6 +19,8 @@ LIB = os.path.join(HERE, "libquik.so")
 SOURCES = ["quik_api.hip", "quik_quantize.hip", "quik_gemm.hip", "quik_gemm_rows.hip", "quik_gemm_tiles16.hip", "quik_gemm_stream.hip", "quik_gemm_fp6.hip", "quik_gemm_sp24.hip",
            "quik_unfused.hip", "quik_probe.hip"]
 
+CALL_SRC, CALL_LIB = os.path.join(CSRC, "quik_call.cpp"), os.path.join(HERE, "_quik_call.so")
+
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -64,8 +66,27 @@ def _compile(src: str, extra_flags, verbose: bool):
     return src, obj, proc
 
 
+def build_call(verbose: bool = False, incremental: bool = False) -> str:
+    """The Python binding's native marshalling (host code only, against the installed torch)."""
+    import sysconfig
+
+    import torch
+    if incremental and os.path.exists(CALL_LIB) and os.path.getmtime(CALL_LIB) > os.path.getmtime(CALL_SRC):
+        return CALL_LIB
+    t = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           "-isystem", os.path.join(t, "include"), "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], "-isystem", "/opt/rocm/include", CALL_SRC, "-o", CALL_LIB,
+           "-L" + os.path.join(t, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return CALL_LIB
+
+
 def build(verbose: bool = False, extra_flags=(), incremental: bool = False) -> str:
     os.makedirs(OBJ, exist_ok=True)
+    build_call(verbose, incremental)
     todo = []
     hdr_time = _newest_header()
     for s in SOURCES:
