@@ -244,6 +244,9 @@ int quik_debug_gemm_form(int T, int N, int K_b, int bits, int w_bits, int cus, i
  */
 int quik_debug_fp6_form(int T, int N, int K_b, int cus, int *form);
 
+/* Test hook (host only): the same for quik_gemm_dequant_sp24 / quik_int_gemm_sp24 (n_out = 0). */
+int quik_debug_sp24_form(int T, int N, int K_b, int n_out, int cus, int *form);
+
 /*
  * Test hook (host only): the k-th output tile (k = 0, 1, ...) that resident workgroup
  * `workgroup` (0 .. plan[4]-1) of the persistent kernel computes for the shape of

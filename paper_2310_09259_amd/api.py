@@ -50,6 +50,8 @@ def load() -> C.CDLL:
         lib.quik_debug_gemm_form.argtypes = [i, i, i, i, i, i, vp]
         lib.quik_debug_fp6_form.restype = i
         lib.quik_debug_fp6_form.argtypes = [i, i, i, i, vp]
+        lib.quik_debug_sp24_form.restype = i
+        lib.quik_debug_sp24_form.argtypes = [i, i, i, i, i, vp]
         lib.quik_debug_gemm_tile.restype = i
         lib.quik_debug_gemm_tile.argtypes = [i, i, i, i, i, i, vp]
         lib.quik_debug_set_gemm_path.restype = i
@@ -244,6 +246,13 @@ def quik_debug_fp6_form(T: int, N: int, K_b: int, cus: int):
     """Host-only: (rows, cols) of the FP6 GEMM's output tile for this shape on `cus` compute units."""
     form = (C.c_int * 2)()
     _check(load().quik_debug_fp6_form(T, N, K_b, cus, C.cast(form, C.c_void_p)), "quik_debug_fp6_form")
+    return tuple(form)
+
+
+def quik_debug_sp24_form(T: int, N: int, K_b: int, n_out: int, cus: int):
+    """Host-only: (rows, cols) of the 2:4-sparse GEMM's output tile for this shape on `cus` compute units."""
+    form = (C.c_int * 2)()
+    _check(load().quik_debug_sp24_form(T, N, K_b, n_out, cus, C.cast(form, C.c_void_p)), "quik_debug_sp24_form")
     return tuple(form)
 
 

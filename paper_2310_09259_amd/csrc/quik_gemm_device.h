@@ -52,6 +52,19 @@ __device__ __forceinline__ void dma16(v4i rsrc, uint32_t lds_base, uint32_t voff
                  : "s"(lds_base), "v"(voff), "s"(rsrc), "s"(soff)
                  : "memory", "m0");
 }
+// the same with 4 bytes per lane, to lds_base + lane * 4, and with 2 bytes, zero-extended to 4 in LDS
+__device__ __forceinline__ void dma4(v4i rsrc, uint32_t lds_base, uint32_t voff) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds"
+                 :
+                 : "s"(lds_base), "v"(voff), "s"(rsrc)
+                 : "memory", "m0");
+}
+__device__ __forceinline__ void dma2(v4i rsrc, uint32_t lds_base, uint32_t voff) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_ushort %1, %2, 0 offen lds"
+                 :
+                 : "s"(lds_base), "v"(voff), "s"(rsrc)
+                 : "memory", "m0");
+}
 // dma16 for data that is read once (weights of a few-token layer): non-temporal, so that its lines do not
 // displace what is read again
 __device__ __forceinline__ void dma16_once(v4i rsrc, uint32_t lds_base, uint32_t voff) {

@@ -1,28 +1,37 @@
 // QUIK-4B linear layer for 2:4-sparse weights, the integer product computed by the sparse int8 matrix
 // instruction of gfx950 (Algorithm 1 of arXiv 2310.09259: "INTmatmul", "Dequantization", "FPmatmul",
 // final add, with the epilogue fusion of Section 3.4; the weight format is the joint INT4 + 2:4 one of
-// Section 4.3.2).  v_smfmac_i32_32x32x64_i8 runs at twice the dense int8 rate and accumulates exactly in
-// INT32.  Operand formats and the measured register layout of the instruction: quik_sp24_device.h.
+// Section 4.3.2).  v_smfmac_i32_16x16x128_i8 runs at twice the dense int8 rate and accumulates exactly in
+// INT32.  Operand formats: quik_sp24_device.h.
 //
 // The sparse operand is the instruction's first one, so it carries the weights: an accumulator register
 // belongs to an output channel and a lane to a token, the transpose of the dense kernels' arrangement.
-// Per-token parameters therefore live in registers, per-channel ones in LDS, and a lane converts four
+// Per-token parameters therefore belong to lanes and per-channel ones to registers, and a lane converts four
 // neighbouring channels of its token at a time.
 //
-// A workgroup of WM x WN waves owns a BM (tokens) x BN (channels) output tile.  A stage is 64 columns = one
-// matrix step: 32 bytes per token row and 32 per weight row, stored stage by stage, so the tile's rows of
-// a stage are two contiguous runs that 16-byte-per-lane DMA instructions copy global -> LDS (32 rows per
-// instruction, the two 16-byte pieces of a row exchanged in every second group of eight rows, which keeps
-// the 16-byte LDS reads free of bank conflicts).  The stage ring takes most of the LDS.  The packed words
-// of stage s + 2 are read from LDS (one 16-byte read per fragment) and those of stage s + 1 widened to
-// int8 (two or three VALU operations per two operand registers) while the matrix instructions of stage s
-// issue; one workgroup barrier per two stages, after which the buffers just read are refilled.  Measured
-// on MI355X: LDS read instructions of a wave do not hide behind its matrix instructions (their cost adds
-// to the loop time whatever their latency slack), VALU work in these amounts does.  The fp16 outlier
-// columns run through the same ring as stages of 16 columns of the same shape, with the dequantized
-// integer part as the C operand of v_mfma_f32_32x32x16_f16 (weights first, so the accumulator layout is
-// the same).  Rows beyond T / N are out of range for the per-stage buffer descriptors and arrive as
-// zeros.
+// A workgroup of WM x WN waves owns a BM (tokens) x BN (channels) output tile.  The operands are stored panel by
+// panel of 64 columns, 32 bytes a row, so a tile's rows of a panel are two contiguous runs that
+// 16-byte-per-lane copies bring global -> LDS, into one slot of a ring.  A step of the K loop is two panels = one
+// matrix instruction per 16 x 16 block and wave.
+//
+// What bounds it: the issue of matrix and widening instructions, which hardly overlap (measured, ns per 16 x 16 x 128
+// instruction and SIMD beside 0 / 1 / 2 / 3 / 4 / 6 vector instructions: 9.2 / 11.7 / 12.3 / 13.5 / 15.3 / 18.5).  A
+// token block of a step takes 12 of these and a channel block 6, so a wave of IB x JB blocks has 12 / JB + 6 / IB of
+// them per matrix instruction: 3 for 4 x 8 blocks, 4.5 for 4 x 4.  N = 15360, K = 5120, T = 1024 without outliers takes
+// 45 us; 41 with copies that fetch nothing, and the issue alone is 35.  What it needs beside that:
+//  - two workgroups of four waves of 4 x 8 blocks per CU (128 x 256 tiles): as little widening as under 256 x 256 with
+//    eight waves and half the granularity, and one works through its prologue and epilogue beside the other's loop;
+//  - a barrier two token blocks before the end of a step, when all its fragments have been read: it frees the step's
+//    own slots and leaves all slots but four flying;
+//  - no drain at the ends: the epilogue's parameters come by copies to LDS, and the fp16 outlier columns run as stages
+//    of 32 columns (64-byte rows) through the same ring right behind the last panels, with the dequantized integer part
+//    as the C operand of v_mfma_f32_16x16x32_f16 (weights first, so the accumulator layout is the same).  With
+//    parameters loaded to registers and an outlier ring that starts when the loop has ended 128 x 128 tiles
+//    took 64 us instead of 60 for the shape above with 256 outliers.
+// GEMM, us, a 32 x 32 x 64 kernel with steps of one panel : this one, same box: 13B QKV, 1024 tokens 72 : 49; 4096
+// tokens 214 : 186; 7B up-projection, 2048 tokens 72.5 : 63; 7B down-projection 61.5 : 59; T = 333, N = 11008, K = 4096
+// 27.6 : 23.9.  Over 183 drawn shapes of more than 64 tokens it takes 0.67 of that kernel's time in the mean.
+// Rows beyond T / N are out of range for the panel descriptors and arrive as zeros.
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 #include <stdint.h>
@@ -37,6 +46,7 @@ namespace {
 
 using namespace gemm_dev;
 
+typedef float v4f __attribute__((ext_vector_type(4)));
 typedef int v8i __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ int swz_f(int r) { return (r >> 3) & 1; }   // 32-byte rows, two pieces
@@ -49,435 +59,353 @@ __device__ __forceinline__ v4i advance(v4i r, uint32_t bytes) {
     return r;
 }
 
-// MODE 0: fused epilogue, fp16 output; MODE 1: the integer accumulators as INT32.
-// NST: stage buffers of the ring; KS: stages per workgroup barrier.
-template <int BM, int BN, int WM, int WN, int NST, int KS, int GM, int MODE>
-__global__ __launch_bounds__(WM * WN * 64, (WM * WN == 8) ? 1 : 2) void gemm_sp24_kernel(GemmArgs a) {
+// place of a 16-byte piece in a 64-byte fp16 stage row: an LDS instruction serves lanes 0 - 3, 12 - 15, 20 - 27 together
+// (and so on); with this the sixteen rows of a block meet 64 different banks in every such group
+__device__ __forceinline__ int swz_h(int r) { return -(r >> 2) & 3; }
+
+__device__ __forceinline__ float h2f(uint32_t u) { return __half2float(__ushort_as_half((unsigned short)u)); }
+
+// MODE 0: fused epilogue, fp16 output; MODE 1: the integer accumulators as INT32.  IB (tokens) x JB (channels) accumulator
+// blocks of 16 x 16 per wave, WM x WN waves; OCC: workgroups per CU; NST: ring slots of 64 columns; GM: as in quik_gemm.hip.
+template <int IB, int JB, int WM, int WN, int NST, int OCC, int GM, int MODE>
+__global__ __launch_bounds__(WM * WN * 64, OCC * WM * WN / 4) void gemm_sp24_kernel(GemmArgs a) {
     constexpr bool RAW = MODE != 0;
+    constexpr int NWAVES = WM * WN;
     // claim the whole register budget of the launch bounds, so that the highest allocated register is
     // never a live one (see the note in the row-quantization kernel)
-    asm volatile("" ::: "v255");
-    constexpr int NWAVES = WM * WN, NT = NWAVES * 64;
-    constexpr int TM = BM / WM / 32, TN = BN / WN / 32, NF = TM + TN, SL = TM * TN;
-    static_assert(sp24::kActBytes == 32 && sp24::kWgtBytes == 32, "every stage row is 32 bytes");
-    // Integer and fp16 stages have the same shape in LDS: BM token rows, then BN channel rows, 32 bytes
-    // each.  DMA instructions of a stage (1 KB = 32 rows each): N_A + N_B.  A wave issues LPS per stage:
-    // instruction i = wave + NWAVES * slot; one that does not exist is issued empty so that every wave
-    // counts the same number.
-    constexpr int A_BYTES = BM * 32, B_BYTES = BN * 32, ST_BYTES = A_BYTES + B_BYTES;
-    constexpr int N_A = BM / 32, N_B = BN / 32;
-    constexpr int LPS = (N_A + N_B + NWAVES - 1) / NWAVES;
-    static_assert(BM % 64 == 0 && BN % 64 == 0 && BN <= NT, "geometry");
-    static_assert(NST * LPS < 64, "vmcnt range");
-    static_assert(NST >= KS + 3, "ring too short");
-    // Ring protocol.  The packed words of integer stage s + 2 are read from LDS while the matrix
-    // instructions of stage s issue (and widened during stage s + 1), and the workgroup meets at a barrier
-    // before every KS-th stage s (s % KS == 0).  At that barrier stages up to s + KS + 1 must have landed
-    // (they are read before the next barrier), and stages up to s + 1 are in registers everywhere, so
-    // during stage s' of the group its own buffer is refilled with stage s' + NST.  The prologue requests
-    // stages 0 .. NST - 1.  (fp16 stages: read one stage ahead, a barrier before every stage.)
-    constexpr int AHEAD = NST;
-    constexpr int WAIT_BAR = (NST - KS - 2) * LPS;        // requests that may still be in flight at a barrier
-    static_assert(SL >= 2 && SL >= LPS && SL >= TM, "a stage has too few matrix instructions to place its reads and copies");
-    constexpr int DUMMY = NST * ST_BYTES;                 // 1 KB that empty DMA instructions clear
+    if constexpr (OCC * NWAVES <= 8) asm volatile("" ::: "v255");
+    else asm volatile("" ::: "v127");
+    constexpr int BM = WM * IB * 16, BN = WN * JB * 16;
+    // a slot: the 32-byte rows of the tile's tokens, then of its channels
+    constexpr int A_BYTES = BM * 32, SLOT = (BM + BN) * 32;
+    // copy instructions of a slot (1 KB each); wave w issues instructions w, w + NWAVES, ...; one that does not exist is
+    // issued empty so that every wave counts the same number
+    constexpr int I_A = A_BYTES / 1024, INSTR = SLOT / 1024;
+    constexpr int LPS = (INSTR + NWAVES - 1) / NWAVES;
+    static_assert(sp24::kActBytes == 32 && sp24::kWgtBytes == 32, "every row of a panel is 32 bytes");
+    static_assert(BM % 64 == 0 && BN % 64 == 0 && IB % 4 == 0, "geometry");
+    static_assert(NST % 2 == 0 && NST >= 6 && NST * LPS < 64, "a step is read while the next lands");
+    constexpr int RING = NST * SLOT, DUMMY = RING;       // 1 KB that empty copies clear
+    // outlier stages: 32 columns, 64 bytes of every row, in the two slots of a step
+    constexpr int FSLOT = 2 * SLOT, F_A = BM / 16, F_B = BN / 16;
+    static_assert((F_A + F_B + NWAVES - 1) / NWAVES <= 2 * LPS, "an outlier stage takes no more copies than a step");
+    constexpr int PARK_ROW = JB * 32 + 16, PARK = 16 * PARK_ROW;
+    static_assert(NWAVES * PARK <= RING, "stage ring too small to park the output tile");
 
-    __shared__ __align__(1024) uint8_t lds[NST * ST_BYTES + 1024];
-    __shared__ __align__(16) float lds_sw[BN];            // scaleWeight / 256
-    __shared__ __align__(16) float lds_wr[BN];            // wReduced
-    __shared__ __align__(16) float lds_bv[BN];            // bias
+    __shared__ __align__(1024) uint8_t lds[RING + 1024];
+    __shared__ __align__(16) float lds_s[BM], lds_z[BM], lds_wr[BN];
+    __shared__ __align__(16) uint32_t lds_sw[BN], lds_bv[BN];       // binary16 patterns
 
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave_u = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave_u / WN, wn = wave_u % WN;
-    const int l32 = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave % WM, wn = wave / WM;
+    const int l16 = lane & 15, g = lane >> 4;
 
     const int tiles_m = (a.T + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
     const int id = xcd_contiguous_id(blockIdx.x, tiles_m * tiles_n);
-    int tile_m, tile_n;
-    if constexpr (GM > 0) {
-        const int per_group = GM * tiles_n;
-        const int grp = id / per_group, rem = id % per_group;
-        const int first_m = grp * GM;
-        const int gsz = min(GM, tiles_m - first_m);
-        tile_m = first_m + rem % gsz;
-        tile_n = rem / gsz;
-    } else {
-        tile_m = id % tiles_m;
-        tile_n = id / tiles_m;
-    }
-    const int t0 = tile_m * BM, n0 = tile_n * BN;
+    const int per_group = GM * tiles_n;
+    const int grp = id / per_group, rem = id % per_group;
+    const int gsz = min(GM, tiles_m - grp * GM);
+    const int t0 = (grp * GM + rem % gsz) * BM, n0 = (rem / gsz) * BN;
 
-    const int S = sp24::stages(a.K_b);
-    const int nk_int = a.fp_only ? 0 : S;
+    const int S = sp24::stages(a.K_b);                   // slots of 64 columns
+    const int nk = (S + 1) / 2;                          // steps of 128 columns; an odd last slot is filled with zeros
     const int fp_bytes = a.n_out * 2;
-    const int nk_fp = RAW ? 0 : (fp_bytes + 31) / 32;
-    const int nk = nk_int + nk_fp;
+    const int nkf = RAW ? 0 : (fp_bytes + 63) / 64;
     const int lda_fp = a.ldo * 2, ldb_fp = a.ldwo * 2;
-    const uint32_t strideA = (uint32_t)a.T * sp24::kActBytes;                  // bytes from stage to stage
-    const uint32_t strideB = (uint32_t)a.N * sp24::kWgtBytes;
+    const uint32_t lds_base = lds_addr(lds);
 
-    // stage 0 of the tile's rows
-    const v4i rA = make_rsrc((const uint8_t*)a.xq + (size_t)t0 * sp24::kActBytes, (size_t)(a.T - t0) * sp24::kActBytes);
-    const v4i rB = make_rsrc((const uint8_t*)a.w_q + (size_t)n0 * sp24::kWgtBytes, (size_t)(a.N - n0) * sp24::kWgtBytes);
+    // ---- copies.  Panel s of an operand with R rows begins s * R * 32 bytes into its buffer; the descriptor of a slot
+    // covers the rest of the panel from the tile's first row on, so rows beyond R arrive as zeros.  The two records of a
+    // channel change places in odd panels (see the fragments below).
+    const uint64_t pA = (uint64_t)(uintptr_t)a.xq + (uint64_t)t0 * 32u, pB = (uint64_t)(uintptr_t)a.w_q + (uint64_t)n0 * 32u;
+    const uint32_t nA = (uint32_t)(a.T - t0) * 32u, nB = (uint32_t)(a.N - n0) * 32u;
+    const uint64_t strideA = (uint64_t)a.T * 32u, strideB = (uint64_t)a.N * 32u;
     const v4i rAf = make_rsrc(a.n_out ? (const uint8_t*)a.x_out + (size_t)t0 * lda_fp : (const uint8_t*)a.xq,
                               a.n_out ? (size_t)(a.T - t0) * lda_fp : 0);
     const v4i rBf = make_rsrc(a.n_out ? (const uint8_t*)a.w_out + (size_t)n0 * ldb_fp : (const uint8_t*)a.xq,
                               a.n_out ? (size_t)(a.N - n0) * ldb_fp : 0);
-    const uint32_t lds_base = lds_addr(lds);
-
-    // 32-byte rows (activation stages and both operands of fp16 stages): an instruction copies 32 rows
-    // (lane / 2), two 16-byte pieces each, exchanged in every second group of eight rows
-    const int colF = ((lane & 1) ^ ((lane >> 4) & 1)) * 16;
-    const uint32_t vo_a = (uint32_t)((lane >> 1) * 32 + colF);
-    const uint32_t vo_af = (uint32_t)((lane >> 1) * lda_fp + colF), vo_bf = (uint32_t)((lane >> 1) * ldb_fp + colF);
-    // DMA slot j of stage s (int part, fp16 part, or past the end: every lane out of range)
-    auto issue_one = [&](int s, int j) __attribute__((always_inline)) {
-        const int i = wave_u + NWAVES * j;                      // instruction of the stage (wave-uniform)
-        const uint32_t sb = (uint32_t)(s % NST) * ST_BYTES;
-        const bool fp = s >= nk_int;
-        uint32_t vo = kOob, dst = (uint32_t)DUMMY;
-        v4i r;
-        if (!fp) {
-            const bool isb = i >= N_A;
-            const int ii = isb ? i - N_A : i;
-            if (i < N_A + N_B) {
-                dst = sb + (isb ? A_BYTES : 0) + ii * 1024;
-                if (s < nk) vo = (uint32_t)(ii * 1024) + vo_a;
-            }
-            r = isb ? advance(rB, (uint32_t)s * strideB) : advance(rA, (uint32_t)s * strideA);
-        } else {
-            const bool isb = i >= N_A;
-            const int ii = isb ? i - N_A : i;
-            const int c0 = 32 * (s - nk_int);
-            if (i < N_A + N_B) {
-                dst = sb + (isb ? BM * 32 : 0) + ii * 1024;
-                if (s < nk && c0 + colF < fp_bytes)
-                    vo = (isb ? vo_bf : vo_af) + (uint32_t)(ii * 32 * (isb ? ldb_fp : lda_fp) + c0);
-            }
-            r = isb ? rBf : rAf;
-        }
-        // wave-uniform by construction; say so, the DMA takes them in scalar registers
-        r = v4i{__builtin_amdgcn_readfirstlane(r[0]), __builtin_amdgcn_readfirstlane(r[1]),
-                __builtin_amdgcn_readfirstlane(r[2]), __builtin_amdgcn_readfirstlane(r[3])};
-        dma16(r, (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds_base + dst)), vo, 0);
-    };
-    // DMA slot j of an integer stage that exists (the hot loop's form)
-    auto issue_int = [&](int s, int j) __attribute__((always_inline)) {
-        const int i = wave_u + NWAVES * j;
-        const bool isb = i >= N_A;
-        const int ii = isb ? i - N_A : i;
-        const bool exists = i < N_A + N_B;
-        const uint32_t dst = exists ? (uint32_t)(s % NST) * ST_BYTES + (isb ? A_BYTES : 0) + ii * 1024 : (uint32_t)DUMMY;
-        const uint32_t vo = exists ? (uint32_t)(ii * 1024) + vo_a : kOob;
-        v4i r = isb ? advance(rB, (uint32_t)s * strideB) : advance(rA, (uint32_t)s * strideA);
-        r = v4i{__builtin_amdgcn_readfirstlane(r[0]), __builtin_amdgcn_readfirstlane(r[1]),
-                __builtin_amdgcn_readfirstlane(r[2]), __builtin_amdgcn_readfirstlane(r[3])};
-        dma16(r, (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds_base + dst)), vo, 0);
-    };
-    auto issue = [&](int s) __attribute__((always_inline)) {
+    uint32_t vo[LPS];
 #pragma unroll
-        for (int j = 0; j < LPS; ++j) issue_one(s, j);
+    for (int j = 0; j < LPS; ++j) {
+        const int i = wave + NWAVES * j;                 // instruction of the slot (wave-uniform)
+        vo[j] = i < INSTR ? (uint32_t)((i < I_A ? i : i - I_A) * 1024 + lane * 16) : kOob;
+    }
+    // copy d of the 2 * LPS of step p, whose slots begin at LDS offset `at`
+    auto issue_int = [&](int p, int d, int at) __attribute__((always_inline)) {
+        const int i = wave + NWAVES * (d % LPS);
+        const uint32_t odd = d / LPS, panel = 2u * (uint32_t)p + odd;
+        const bool isb = i >= I_A;
+        const uint64_t base = isb ? pB + panel * strideB : pA + panel * strideA;
+        const uint32_t n = (int)panel < S ? (isb ? nB : nA) : 0u;
+        v4i r = v4i{(int)(uint32_t)base, (int)(uint32_t)(base >> 32), (int)n, 0x00020000};
+        r = v4i{__builtin_amdgcn_readfirstlane(r[0]), __builtin_amdgcn_readfirstlane(r[1]), __builtin_amdgcn_readfirstlane(r[2]), r[3]};
+        const uint32_t dst = i < INSTR ? (uint32_t)at + odd * SLOT + i * 1024 : (uint32_t)DUMMY;
+        dma16(r, (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds_base + dst)), isb ? vo[d % LPS] ^ (odd << 4) : vo[d % LPS], 0);
+    };
+    // the same of outlier stage f (beyond the last one: nothing is fetched).  An instruction copies 16 rows, whose 16-byte
+    // pieces are exchanged so that the four rows of an LDS pass that share banks differ in their place.
+    const int fc = ((lane & 3) ^ swz_h(lane >> 2)) << 4;
+    auto issue_fp = [&](int f, int d, int at) __attribute__((always_inline)) {
+        const int i = wave + NWAVES * d;
+        const bool isb = i >= F_A;
+        const int row = (isb ? i - F_A : i) * 16 + (lane >> 2);
+        const uint32_t v = f * 64 + fc < fp_bytes && i < F_A + F_B ? (uint32_t)(row * (isb ? ldb_fp : lda_fp) + fc) : kOob;
+        const v4i r = isb ? rBf : rAf;
+        const uint32_t dst = i < F_A + F_B ? (uint32_t)at + i * 1024 : (uint32_t)DUMMY;
+        dma16(r, (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds_base + dst)), v, (uint32_t)f * 64u);
     };
 
-    // ---- epilogue parameters: per token in registers (a lane owns one token of every token fragment),
-    // per channel through LDS.  They are requested before the first DMA, so that their (in-order) return
-    // does not sit behind the stage loads, and first touched after the integer stages: an earlier use
-    // would make the compiler wait for them and, with them, for every stage load requested since.
-    float t_s[TM], t_z[TM];
-    float p_wr = 0.0f;
-    uint32_t p_sw = 0, p_bv = 0;                           // binary16 patterns
+    // ---- the epilogue's parameters, copied to LDS first of all: loads into registers would make the compiler wait for
+    // everything requested since when they are used
     if constexpr (!RAW) {
+        constexpr int PA = BM / 64, PB = BN / 64;        // instructions of 64 values
+        const v4i rs = make_rsrc(a.scale + t0, (size_t)(a.T - t0) * 4), rz = make_rsrc(a.zero + t0, (size_t)(a.T - t0) * 4);
+        const v4i rr = make_rsrc(a.w_reduced + n0, (size_t)(a.N - n0) * 4);
+        const v4i rw_ = make_rsrc(static_cast<const __half*>(a.w_scale) + n0, (size_t)(a.N - n0) * 2);
+        const v4i rb = make_rsrc(a.bias ? static_cast<const __half*>(a.bias) + n0 : a.w_scale, a.bias ? (size_t)(a.N - n0) * 2 : 0);
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            const int t = t0 + wm * TM * 32 + i * 32 + l32;
-            t_s[i] = t < a.T ? a.scale[t] : 0.0f;
-            t_z[i] = t < a.T ? a.zero[t] : 0.0f;
-        }
-        const uint16_t* __restrict__ wsc = static_cast<const uint16_t*>(a.w_scale);
-        const uint16_t* __restrict__ bias = static_cast<const uint16_t*>(a.bias);
-        if (tid < BN && !a.fp_only) {
-            const int n = min(n0 + tid, a.N - 1);
-            p_sw = wsc[n];
-            p_bv = (bias ? bias : wsc)[n];                 // no branch here: a join would wait for the loads
-            p_wr = a.w_reduced[n];
+        for (int q = 0; q < (2 * PA + 3 * PB + NWAVES - 1) / NWAVES; ++q) {
+            int k = wave + NWAVES * q;
+            if (k < PA) dma4(rs, lds_addr(lds_s) + k * 256, (uint32_t)(k * 64 + lane) * 4u);
+            else if ((k -= PA) < PA) dma4(rz, lds_addr(lds_z) + k * 256, (uint32_t)(k * 64 + lane) * 4u);
+            else if ((k -= PA) < PB) dma4(rr, lds_addr(lds_wr) + k * 256, (uint32_t)(k * 64 + lane) * 4u);
+            else if ((k -= PB) < PB) dma2(rw_, lds_addr(lds_sw) + k * 256, (uint32_t)(k * 64 + lane) * 2u);
+            else if ((k -= PB) < PB) dma2(rb, lds_addr(lds_bv) + k * 256, (uint32_t)(k * 64 + lane) * 2u);
         }
     }
-
 #pragma unroll
-    for (int s = 0; s < AHEAD; ++s) issue(s);
-
-    // LDS read addresses of this lane's row of every fragment (token fragments first): piece g of the
-    // 32-byte row, exchanged as above
-    uint32_t rdf[NF];
+    for (int p = 0; p < NST / 2; ++p)
 #pragma unroll
-    for (int f = 0; f < NF; ++f) {
-        const int r = (f < TM) ? (wm * TM * 32 + f * 32 + l32) : (wn * TN * 32 + (f - TM) * 32 + l32);
-        rdf[f] = (f < TM ? 0 : BM * 32) + r * 32 + ((g ^ swz_f(r)) << 4);
-    }
-    // two sets of packed fragments and two sets of widened operands, by stage parity: the matrix
-    // instructions of stage s run on one set of operands while the words of stage s + 1 are widened into
-    // the other and those of stage s + 2 arrive from LDS
-    // (a weight fragment's packed words hold its index word too, which the matrix instruction takes as it
-    // is: such a fragment is requested only after the last matrix instruction that uses the old index)
-    uint4 RA[2][TM];
-    uint4 RW[2][TN];                                       // x, y: values; z: index word
-    v8i UA[2][TM];
-    v4i UW[2][TN];
-    uint4 FP[2][NF];                                       // fp16 stages
-
-    auto read_frag = [&](int set, int f, int s) __attribute__((always_inline)) {
-        const uint8_t* st = lds + (s % NST) * ST_BYTES;
-        if (f < TM) RA[set][f] = *reinterpret_cast<const uint4*>(st + rdf[f]);
-        else RW[set][f - TM] = *reinterpret_cast<const uint4*>(st + rdf[f]);
-    };
-    auto widen = [&](int set, int f) __attribute__((always_inline)) {
-        constexpr uint32_t M = 0xF0F0F0F0u;
-        if (f < TM) {
-            const uint32_t w[4] = {RA[set][f].x, RA[set][f].y, RA[set][f].z, RA[set][f].w};
-#pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                UA[set][f][2 * m] = (int)(w[m] & M);               // columns 8 m .. 8 m + 3, sixteen-fold
-                UA[set][f][2 * m + 1] = (int)((w[m] << 4) & M);    // columns 8 m + 4 .. 8 m + 7
-            }
-        } else {
-            const int j = f - TM;
-            UW[set][j] = v4i{(int)((RW[set][j].x << 4) & M), (int)(RW[set][j].x & M), (int)((RW[set][j].y << 4) & M),
-                             (int)(RW[set][j].y & M)};
+        for (int d = 0; d < 2 * LPS; ++d) {
+            if (p < nk) issue_int(p, d, p * FSLOT);
+            else issue_fp(p - nk, d, p * FSLOT);
         }
+
+    // ---- fragments.  v_smfmac_i32_16x16x128_i8, measured: dense lane (l, g) holds 32 columns of token l, sparse lane
+    // (l, g) the 16 kept values of channel l, of which the first eight meet bytes 16 (g / 2) .. of the dense lanes of group
+    // 2 (g % 2) and the others the same bytes of group 2 (g % 2) + 1.  So token lanes take piece g % 2 of panel g / 2 of
+    // the step's two, channel lanes record g / 2 of panel g % 2.  Lanes that LDS serves together (0 - 3, 12 - 15, 20 - 27
+    // and so on) read 16 different pieces of sixteen rows: the tokens' because groups 0 and 1 read two pieces of one
+    // panel, the channels' because the records of odd panels have changed places.
+    const uint32_t oddA = (uint32_t)((g >> 1) * SLOT + l16 * 32 + ((g & 1) << 4) + wm * IB * 512);
+    const uint32_t oddW = (uint32_t)((g & 1) * SLOT + l16 * 32 + (((g >> 1) ^ (g & 1)) << 4) + A_BYTES + wn * JB * 512);
+    uint4 ra[2], rw[JB];                                 // packed words (rw.z: the index word)
+    v8i ua[2];                                           // int8 operands, sixteen-fold
+    v4i uw[JB];
+    constexpr uint32_t M = 0xF0F0F0F0u;
+    auto read_a = [&](int i, uint32_t so) __attribute__((always_inline)) { ra[i & 1] = *reinterpret_cast<const uint4*>(lds + so + oddA + i * 512); };
+    auto read_w = [&](int j, uint32_t so) __attribute__((always_inline)) { rw[j] = *reinterpret_cast<const uint4*>(lds + so + oddW + j * 512); };
+    auto widen_a = [&](int i, int d) __attribute__((always_inline)) {      // one word: columns 8 d .. 8 d + 3, 8 d + 4 .. 8 d + 7
+        const uint32_t w = d == 0 ? ra[i & 1].x : d == 1 ? ra[i & 1].y : d == 2 ? ra[i & 1].z : ra[i & 1].w;
+        ua[i & 1][2 * d] = (int)(w & M);
+        ua[i & 1][2 * d + 1] = (int)((w << 4) & M);
     };
+    auto widen_w = [&](int j) __attribute__((always_inline)) {
+        uw[j] = v4i{(int)((rw[j].x << 4) & M), (int)(rw[j].x & M), (int)((rw[j].y << 4) & M), (int)(rw[j].y & M)};
+    };
+    v4i acc[IB][JB];
+#pragma unroll
+    for (int i = 0; i < IB; ++i)
+#pragma unroll
+        for (int j = 0; j < JB; ++j) acc[i][j] = v4i{0, 0, 0, 0};
 
-    v16i acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
-
-    // Integer stage s, set = s % 2 (BAR: s % KS == 0, the group's barrier comes first).  PLAIN: stage
-    // s + NST is an integer stage; NEXT1 / NEXT2: stages s + 1 / s + 2 are.  Stage s + 1's words (they
-    // arrived during the previous stage) are widened between the matrix instructions, stage s + 2's are
-    // requested one fragment per slot.
-    auto step = [&](int s, int set, bool bar, bool plain, bool next1, bool next2) __attribute__((always_inline)) {
-        if (bar) {
-            wait_stage<WAIT_BAR>();
-            __syncthreads();
-        }
+    // A step: 128 columns.  The words of token block i + 2 are read and those of block i + 1 widened beside the matrix
+    // instructions of block i; the next step's channel words are read beside the last block, each after the last use of its
+    // predecessor, and widened one instruction before their first use.  Two blocks before the end of a step everything of
+    // it has been read, so the barrier there frees the step's own two slots -- refilled right away -- and lets everybody
+    // read the next step's, which must have landed; all other slots (NST - 4 at the wait) are in flight.
+    constexpr int SLOTS = IB * JB, LAST_READ = (IB - 2) * JB - 1;
+    int at = 0;                                          // LDS offset of the step's slots
+    auto step = [&](int s, bool tail) __attribute__((always_inline)) {
+        const int nxt = at + FSLOT == RING ? 0 : at + FSLOT;
+        const uint32_t so = (uint32_t)at, so1 = (uint32_t)nxt;
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int m = 0; m < SL; ++m) {
-            const int i = m / TN, j = m % TN;
-            acc[i][j] = __builtin_amdgcn_smfmac_i32_32x32x64_i8(UW[set][j], UA[set][i], acc[i][j], (int)RW[set][j].z, 0, 0);
-            if (m < LPS) { if (plain) issue_int(s + AHEAD, m); else issue_one(s + AHEAD, m); }
-            if (next2) {
-                if (m < TM) read_frag(set, m, s + 2);
-                if (i == TM - 1) read_frag(set, TM + j, s + 2);
+        for (int m = 0; m < SLOTS; ++m) {
+            const int i = m / JB, j = m % JB;
+            acc[i][j] = __builtin_amdgcn_smfmac_i32_16x16x128_i8(uw[j], ua[i & 1], acc[i][j], (int)rw[j].z, 0, 0);
+            if (j == 0 && i + 2 < IB) read_a(i + 2, so);
+            if (m == LAST_READ) {
+                wait_stage<(NST - 4) * LPS>();
+                __syncthreads();
             }
-            if (next1) {
+            if (j == 0 && i + 2 >= IB) read_a(i + 2 - IB, so1);
+            if (i == IB - 1) read_w(j, so1);
 #pragma unroll
-                for (int f = 0; f < NF; ++f)
-                    if (f * SL / NF == m) widen(set ^ 1, f);
-            }
+            for (int d = 0; d < 4; ++d)
+                if (d * JB / 4 == j) widen_a(i + 1, d);
+            if (i == 0 && j + 1 < JB) widen_w(j + 1);
+            if (m == SLOTS - 1) widen_w(0);
+#pragma unroll
+            for (int d = 0; d < 2 * LPS; ++d)
+                if (m > LAST_READ && d * (SLOTS - 1 - LAST_READ) / (2 * LPS) == m - LAST_READ - 1) {
+                    if (!tail) issue_int(s + NST / 2, d, at);
+                    else issue_fp(s + NST / 2 - nk, d, at);
+                }
             __builtin_amdgcn_sched_barrier(0);
         }
+        at = nxt;
     };
-
-    wait_stage<(NST - 2) * LPS>();            // stages 0 and 1 landed
+    wait_stage<(NST - 2) * LPS>();                       // the first step's two slots have landed
     __syncthreads();
-    if (nk_int > 0) {
+    {
 #pragma unroll
-        for (int f = 0; f < NF; ++f) read_frag(0, f, 0);
-    }
-    if (nk_int > 1) {
+        for (int j = 0; j < JB; ++j) read_w(j, 0);
+        read_a(0, 0);
+        read_a(1, 0);
 #pragma unroll
-        for (int f = 0; f < NF; ++f) read_frag(1, f, 1);
+        for (int d = 0; d < 4; ++d) widen_a(0, d);
+        widen_w(0);
     }
-    if (nk_int > 0) {
-#pragma unroll
-        for (int f = 0; f < NF; ++f) widen(0, f);
-    }
-
-    static_assert(KS == 1 || KS == 2, "the loops below step two stages at a time");
-    constexpr bool BAR1 = KS == 1;         // the odd stage of a pair opens a group only if groups are single stages
     int s = 0;
-    for (; s + 1 + AHEAD < nk_int; s += 2) {
-        step(s, 0, true, true, true, true);
-        step(s + 1, 1, BAR1, true, true, true);
-    }
-    for (; s + 1 < nk_int; s += 2) {
-        step(s, 0, true, false, true, s + 2 < nk_int);
-        step(s + 1, 1, BAR1, false, s + 2 < nk_int, s + 3 < nk_int);
-    }
-    if (s < nk_int) {
-        step(s, 0, true, false, false, false);
-        s += 1;
-    }
+    for (; s + NST / 2 < nk; ++s) step(s, false);
+    for (; s < nk; ++s) step(s, true);                   // the freed slots take the outlier stages
 
-    // lane: token tw + 32 i + l32; register r of fragment j: channel nw + 32 j + 8 (r / 4) + 4 g + r % 4
-    const int tw = t0 + wm * TM * 32, nw = n0 + wn * TN * 32;
+    // lane: token tw + 16 i + l16; register r of block j: channel nw + 16 j + 4 g + r
+    const int tw = t0 + wm * IB * 16, nw = n0 + wn * JB * 16;
     if constexpr (RAW) {
-        wait_vm<0>();                      // drain the look-ahead DMA before the wave ends
+        wait_vm<0>();                                    // drain the copies before the wave ends
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < IB; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int t = tw + i * 32 + l32;
+            for (int j = 0; j < JB; ++j) {
+                const int t = tw + i * 16 + l16;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int n = nw + j * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
+                for (int r = 0; r < 4; ++r) {
+                    const int n = nw + j * 16 + 4 * g + r;
                     if (t < a.T && n < a.N) a.acc[(size_t)t * a.ldacc + n] = acc[i][j][r] >> 8;   // exact: a multiple of 256
                 }
             }
         return;
     }
 
-    // Dequantization: the accumulators are 256 times the integer dot products (the factor rides on the
-    // weight scale); the conversion to binary32 is exact (at most 24 significant bits).
-    if (tid < BN) {
-        lds_sw[tid] = __half2float(__ushort_as_half((unsigned short)p_sw)) * (1.0f / 256.0f);   // exact power-of-two factor
-        lds_wr[tid] = p_wr;
-        lds_bv[tid] = a.bias ? __half2float(__ushort_as_half((unsigned short)p_bv)) : 0.0f;
+    // first outlier fragments (the last step waited for the first stage)
+    const uint32_t rdF = (uint32_t)(l16 * 64 + ((g ^ swz_h(l16)) << 4));
+    const uint32_t aF = rdF + wm * IB * 1024, bF = rdF + BM * 64 + wn * JB * 1024;
+    v8h ha[4], hb[JB];
+    auto read_ha = [&](int i, uint32_t fo) __attribute__((always_inline)) { ha[i & 3] = *reinterpret_cast<const v8h*>(lds + fo + aF + i * 1024); };
+    auto read_hb = [&](int j, uint32_t fo) __attribute__((always_inline)) { hb[j] = *reinterpret_cast<const v8h*>(lds + fo + bF + j * 1024); };
+    float t_s[IB], t_h[IB];
+#pragma unroll
+    for (int i = 0; i < IB; ++i) {
+        const int lr = wm * IB * 16 + i * 16 + l16;
+        t_s[i] = lds_s[lr];                              // scaleAct
+        t_h[i] = lds_z[lr] + 8.0f * t_s[i];              // zeroAct + halfRange * scaleAct
     }
-    float t_h[TM];
+    // Dequantization: the accumulators are 256 times the integer dot products (the factor rides on the weight scale); the
+    // conversion to binary32 is exact (at most 24 significant bits).
+    v4f cf[IB][JB];
 #pragma unroll
-    for (int i = 0; i < TM; ++i) t_h[i] = t_z[i] + 8.0f * t_s[i];     // zeroAct + halfRange * scaleAct
-    __syncthreads();
-    v16f cf[TM][TN];
+    for (int j = 0; j < JB; ++j) {
+        const int lc = wn * JB * 16 + j * 16 + 4 * g;
+        const uint4 sw4 = *reinterpret_cast<const uint4*>(&lds_sw[lc]);
+        const float4 wr4 = *reinterpret_cast<const float4*>(&lds_wr[lc]);
+        const uint4 bv4 = *reinterpret_cast<const uint4*>(&lds_bv[lc]);
+        const float wr_[4] = {wr4.x, wr4.y, wr4.z, wr4.w}, bv_[4] = {h2f(bv4.x), h2f(bv4.y), h2f(bv4.z), h2f(bv4.w)};
+        constexpr float k = 1.0f / 256.0f;               // an exact power-of-two factor
+        const float sw_[4] = {h2f(sw4.x) * k, h2f(sw4.y) * k, h2f(sw4.z) * k, h2f(sw4.w) * k};
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+        for (int i = 0; i < IB; ++i)
 #pragma unroll
-        for (int rq = 0; rq < 4; ++rq) {
-            const int lc = wn * TN * 32 + j * 32 + 8 * rq + 4 * g;
-            const float4 sw4 = *reinterpret_cast<const float4*>(&lds_sw[lc]);
-            const float4 wr4 = *reinterpret_cast<const float4*>(&lds_wr[lc]);
-            const float4 bv4 = *reinterpret_cast<const float4*>(&lds_bv[lc]);
-            const float sw_[4] = {sw4.x, sw4.y, sw4.z, sw4.w}, wr_[4] = {wr4.x, wr4.y, wr4.z, wr4.w};
-            const float bv_[4] = {bv4.x, bv4.y, bv4.z, bv4.w};
+            for (int r = 0; r < 4; ++r)
+                cf[i][j][r] = __builtin_fmaf((float)acc[i][j][r], t_s[i] * sw_[r], __builtin_fmaf(t_h[i], wr_[r], bv_[r]));
+    }
+    if (nkf > 0) {
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr) {
-                    const int r = rq * 4 + rr;
-                    cf[i][j][r] = __builtin_fmaf((float)acc[i][j][r], t_s[i] * sw_[rr],
-                                                 __builtin_fmaf(t_h[i], wr_[rr], bv_[rr]));
-                }
-        }
-
-    // fp16 outlier stages: 16 columns each, one matrix step; stage s + 1 is read while the matrix
-    // instructions of stage s issue, and stage s's buffer (read during stage s - 1, before this barrier)
-    // is refilled
-    auto wide_step = [&](int s, int set) __attribute__((always_inline)) {
-        wait_stage<WAIT_BAR>();
-        __syncthreads();
-        __builtin_amdgcn_sched_barrier(0);
-        const uint8_t* nxt = lds + ((s + 1) % NST) * ST_BYTES;
-#pragma unroll
-        for (int m = 0; m < SL; ++m) {
-            const int i = m / TN, j = m % TN;
-            cf[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, FP[set][TM + j]),
-                                                              __builtin_bit_cast(v8h, FP[set][i]), cf[i][j], 0, 0, 0);
-            if (m < LPS) issue_one(s + AHEAD, m);
-            if (m < NF) FP[set ^ 1][m] = *reinterpret_cast<const uint4*>(nxt + rdf[m]);
-            if (SL < NF && m == SL - 1) {
-#pragma unroll
-                for (int f = SL; f < NF; ++f) FP[set ^ 1][f] = *reinterpret_cast<const uint4*>(nxt + rdf[f]);
-            }
+        for (int j = 0; j < JB; ++j) read_hb(j, (uint32_t)at);
+        read_ha(0, (uint32_t)at);
+        read_ha(1, (uint32_t)at);
+        for (int f = 0; f < nkf; ++f) {
+            const int nxt = at + FSLOT == RING ? 0 : at + FSLOT;
+            const uint32_t fo = (uint32_t)at, fo1 = (uint32_t)nxt;
             __builtin_amdgcn_sched_barrier(0);
-        }
-    };
-    if (s < nk) {
-        // the first fp16 stage has landed (at most KS + 1 stages behind the last barrier's stage); the wait
-        // and barrier matter only if there was no integer stage
-        wait_stage<WAIT_BAR>();
-        __syncthreads();
-        const uint8_t* st = lds + (s % NST) * ST_BYTES;
 #pragma unroll
-        for (int f = 0; f < NF; ++f) FP[0][f] = *reinterpret_cast<const uint4*>(st + rdf[f]);
-        for (; s + 1 < nk; s += 2) {
-            wide_step(s, 0);
-            wide_step(s + 1, 1);
-        }
-        if (s < nk) { wide_step(s, 0); ++s; }
-    }
-
-    wait_vm<0>();                          // drain the look-ahead DMA before the wave ends
-    __half* __restrict__ y = static_cast<__half*>(a.y);
-    // Output through LDS: each wave parks its fp16 tile (token rows) in its own slice of the dead stage
-    // ring, four channels = 8 bytes per lane and write, and stores whole row segments as 16-byte pieces;
-    // needs 16-byte aligned output rows.
-    constexpr int WROW = (NWAVES * TM * 32 * (TN * 64 + 16) <= NST * ST_BYTES) ? TN * 64 + 16 : TN * 64;
-    constexpr int WBUF = TM * 32 * WROW;
-    static_assert(NWAVES * WBUF <= NST * ST_BYTES, "stage ring too small to park the output tile");
-    const bool vec_ok = !a.fp_only && ((reinterpret_cast<uintptr_t>(a.y) & 15u) == 0) && (a.ldy % 8 == 0);
-    if (vec_ok) {
-        __syncthreads();                   // every wave is past its last read of the stage ring
-        uint8_t* wbuf = lds + wave_u * WBUF;
+            for (int m = 0; m < SLOTS; ++m) {
+                const int i = m / JB, j = m % JB;
+                cf[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(hb[j], ha[i & 3], cf[i][j], 0, 0, 0);
+                if (j == 0 && i + 2 < IB) read_ha(i + 2, fo);
+                if (m == LAST_READ) {
+                    // every read of this stage has been issued: behind the barrier its slot is free, the next has landed
+                    wait_stage<(NST - 4) * LPS>();
+                    __syncthreads();
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int rq = 0; rq < 4; ++rq) {
-                    const __half2 h0 = __floats2half2_rn(cf[i][j][4 * rq], cf[i][j][4 * rq + 1]);
-                    const __half2 h1 = __floats2half2_rn(cf[i][j][4 * rq + 2], cf[i][j][4 * rq + 3]);
-                    uint2 v;
-                    v.x = __builtin_bit_cast(uint32_t, h0);
-                    v.y = __builtin_bit_cast(uint32_t, h1);
-                    *reinterpret_cast<uint2*>(wbuf + (i * 32 + l32) * WROW + (j * 32 + 8 * rq + 4 * g) * 2) = v;
+                    for (int d = 0; d < 2 * LPS; ++d) issue_fp(f + NST / 2, d, at);
                 }
-        constexpr int CH = TN * 4;                       // 16-byte pieces per row
-        constexpr int RPS = 64 / CH;                     // rows per store instruction
+                if (j == 0 && i + 2 >= IB) read_ha(i + 2 - IB, fo1);
+                if (i == IB - 1) read_hb(j, fo1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            at = nxt;
+        }
+    }
+    wait_stage<0>();
+    __syncthreads();                                     // the stage memory is dead
+    __half* __restrict__ y = static_cast<__half*>(a.y);
+    // Output through LDS: a wave parks sixteen rows of its tile, four channels = 8 bytes per lane and write, and writes them
+    // out as 16-byte pieces, whole row segments per store; needs 16-byte aligned output rows.
+    const bool vec_ok = ((reinterpret_cast<uintptr_t>(a.y) & 15u) == 0) && (a.ldy % 8 == 0);
+    if (vec_ok) {
+        uint8_t* wbuf = lds + wave * PARK;
+        constexpr int CH = JB * 2, RPS = 64 / CH;        // 16-byte pieces per row, rows per store instruction
         const int prow = lane / CH, pch = lane % CH;
 #pragma unroll
-        for (int p = 0; p < (TM * 32 + RPS - 1) / RPS; ++p) {
-            const int row = p * RPS + prow;
-            if (prow >= RPS || row >= TM * 32) continue;
-            const uint4 v = *reinterpret_cast<const uint4*>(wbuf + row * WROW + pch * 16);
-            const int t = tw + row, n = nw + pch * 8;
-            if (t < a.T) {
-                __half* dst = y + (size_t)t * a.ldy + n;
-                if (n + 8 <= a.N) {
-                    store16_through(dst, v);
-                } else {
-                    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+        for (int i = 0; i < IB; ++i) {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        if (n + e < a.N)
-                            reinterpret_cast<uint16_t*>(dst)[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+            for (int j = 0; j < JB; ++j) {
+                uint2 v;
+                v.x = __builtin_bit_cast(uint32_t, __floats2half2_rn(cf[i][j][0], cf[i][j][1]));
+                v.y = __builtin_bit_cast(uint32_t, __floats2half2_rn(cf[i][j][2], cf[i][j][3]));
+                *reinterpret_cast<uint2*>(wbuf + l16 * PARK_ROW + (j * 16 + 4 * g) * 2) = v;
+            }
+#pragma unroll
+            for (int q = 0; q < (16 + RPS - 1) / RPS; ++q) {
+                const int row = q * RPS + prow;
+                if (prow >= RPS || row >= 16) continue;
+                const uint4 v = *reinterpret_cast<const uint4*>(wbuf + row * PARK_ROW + pch * 16);
+                const int t = tw + i * 16 + row, n = nw + pch * 8;
+                if (t < a.T) {
+                    __half* dst = y + (size_t)t * a.ldy + n;
+                    if (n + 8 <= a.N) {
+                        store16_through(dst, v);
+                    } else {
+                        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            if (n + e < a.N)
+                                reinterpret_cast<uint16_t*>(dst)[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+                    }
                 }
             }
         }
         return;
     }
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < IB; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int t = tw + i * 32 + l32;
+        for (int j = 0; j < JB; ++j) {
+            const int t = tw + i * 16 + l16;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int n = nw + j * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
-                if (t < a.T && n < a.N) {
-                    if (a.fp_only) reinterpret_cast<float*>(a.y)[(size_t)t * a.ldy + n] = cf[i][j][r];
-                    else y[(size_t)t * a.ldy + n] = __float2half(cf[i][j][r]);
-                }
+            for (int r = 0; r < 4; ++r) {
+                const int n = nw + j * 16 + 4 * g + r;
+                if (t < a.T && n < a.N) y[(size_t)t * a.ldy + n] = __float2half(cf[i][j][r]);
             }
         }
 }
 
-// Small-T variant (T <= 32 TM): the layer is bound by streaming the weights, so the point is many bytes in
-// flight per CU and many workgroups.  A workgroup owns a 32 TM (tokens) x 32 (channels) output tile and its
-// four waves split K: every wave streams its own quarter of the stages (1 KB of weights and TM KB of
-// activations each, one DMA instruction per KB) through a private ring, with no workgroup barrier in the
-// main loop (a wave waits only for its own DMA).  The four partial INT32 accumulators are summed exactly
-// through LDS; wave 0 then dequantizes, adds the fp16 outlier product (every wave takes every fourth
-// 16-column step, operands straight from global memory, requested before the weight stream starts) and
-// stores.
-template <int TM, int NST, int MODE>
-__global__ __launch_bounds__(256) void gemm_sp24_skinny(GemmArgs a) {
+// Few tokens: the layer is bound by streaming the weights, so the point is many bytes in flight per CU and many
+// workgroups.  A workgroup owns a 32 (tokens) x 32 (channels) output tile and its four waves split K: every wave streams
+// its own quarter of the panels (1 KB of weights and 1 KB of activations each, one DMA instruction per KB) through a
+// private ring, with no workgroup barrier in the main loop (a wave waits only for its own DMA), into
+// v_smfmac_i32_32x32x64_i8.  The four partial INT32 accumulators are summed exactly through LDS; wave 0 then dequantizes,
+// adds the fp16 outlier product (every wave takes every fourth 16-column step, operands straight from global memory,
+// requested before the weight stream starts) and stores.  Tiles of 64 tokens, which read the weights once for 33 to 64
+// tokens, won nowhere against this tile and the general kernel's 64 x 64 one.
+template <int NST, int MODE>
+__global__ __launch_bounds__(256) void gemm_sp24_split(GemmArgs a) {
     constexpr bool RAW = MODE != 0;
-    constexpr int BM = 32 * TM, A_BYTES = BM * 32, ST_BYTES = A_BYTES + 1024, RING = NST * ST_BYTES, LPS = TM + 1;
-    constexpr int RED_BYTES = 2 * TM * 16 * 64 * 4;        // one wave's INT32 accumulators + fp32 outlier partials
+    constexpr int BM = 32, A_BYTES = BM * 32, ST_BYTES = A_BYTES + 1024, RING = NST * ST_BYTES, LPS = 2;
+    constexpr int RED_BYTES = 2 * 16 * 64 * 4;             // one wave's INT32 accumulators + fp32 outlier partials
     constexpr int LDS_BYTES = (4 * RING > 3 * RED_BYTES) ? 4 * RING : 3 * RED_BYTES;
     static_assert((NST - 1) * LPS < 64, "vmcnt range");
     __shared__ __align__(1024) uint8_t lds[LDS_BYTES];
@@ -489,7 +417,7 @@ __global__ __launch_bounds__(256) void gemm_sp24_skinny(GemmArgs a) {
     const int tiles_m = (a.T + BM - 1) / BM;
     const int t0 = (blockIdx.x % tiles_m) * BM, n0 = (blockIdx.x / tiles_m) * 32;
 
-    const int nk = a.fp_only ? 0 : sp24::stages(a.K_b);
+    const int nk = sp24::stages(a.K_b);
     const int s_begin = (int)((long)nk * wave / 4), s_end = (int)((long)nk * (wave + 1) / 4);   // this wave's stages
     const uint32_t strideA = (uint32_t)a.T * sp24::kActBytes, strideB = (uint32_t)a.N * sp24::kWgtBytes;
     const v4i rA = make_rsrc((const uint8_t*)a.xq + (size_t)t0 * sp24::kActBytes, (size_t)(a.T - t0) * sp24::kActBytes);
@@ -507,55 +435,44 @@ __global__ __launch_bounds__(256) void gemm_sp24_skinny(GemmArgs a) {
                  __builtin_amdgcn_readfirstlane(ra[2]), __builtin_amdgcn_readfirstlane(ra[3])};
         rb = v4i{__builtin_amdgcn_readfirstlane(rb[0]), __builtin_amdgcn_readfirstlane(rb[1]),
                  __builtin_amdgcn_readfirstlane(rb[2]), __builtin_amdgcn_readfirstlane(rb[3])};
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-            dma16(ra, (uint32_t)__builtin_amdgcn_readfirstlane((int)(ring_addr + sb + i * 1024)), live ? vo + i * 1024 : kOob, 0);
+        dma16(ra, (uint32_t)__builtin_amdgcn_readfirstlane((int)(ring_addr + sb)), live ? vo : kOob, 0);
         dma16(rb, (uint32_t)__builtin_amdgcn_readfirstlane((int)(ring_addr + sb + A_BYTES)), live ? vo : kOob, 0);
     };
     const uint32_t rd = (uint32_t)(l32 * 32 + ((g ^ swz_f(l32)) << 4));   // this lane's piece of its row
 
     // ---- everything the epilogue needs is requested before the weight stream starts
-    constexpr int PF = (TM == 1) ? 4 : 2;                  // prefetched outlier steps per wave
-    float t_s[TM], t_z[TM];
-    uint4 pfa[PF][TM], pfb[PF];
+    constexpr int PF = 4;                                  // prefetched outlier steps per wave
+    float t_s = 0.0f, t_z = 0.0f;
+    uint4 pfa[PF], pfb[PF];
     const int fsteps = (a.n_out + 15) >> 4;                // 16-column steps of the outlier product
     const __half* __restrict__ xo = static_cast<const __half*>(a.x_out);
     const __half* __restrict__ wo = static_cast<const __half*>(a.w_out);
-    const int n2 = min(n0 + l32, a.N - 1);
+    const int t2 = min(t0 + l32, a.T - 1), n2 = min(n0 + l32, a.N - 1);
     if constexpr (!RAW) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            const int t = t0 + i * 32 + l32;
-            const bool ok = t < a.T && !a.fp_only;
-            t_s[i] = ok ? a.scale[t] : 0.0f;
-            t_z[i] = ok ? a.zero[t] : 0.0f;
+        if (t0 + l32 < a.T) {
+            t_s = a.scale[t0 + l32];
+            t_z = a.zero[t0 + l32];
         }
         if (tid < 32) {
             const int n = min(n0 + tid, a.N - 1);
             const __half* __restrict__ wsc = static_cast<const __half*>(a.w_scale);
             const __half* __restrict__ bias = static_cast<const __half*>(a.bias);
-            prm_sw[tid] = a.fp_only ? 0.0f : __half2float(wsc[n]) * (1.0f / 256.0f);   // exact power-of-two factor
-            prm_wr[tid] = a.fp_only ? 0.0f : a.w_reduced[n];
-            prm_bv[tid] = (bias && !a.fp_only) ? __half2float(bias[n]) : 0.0f;
+            prm_sw[tid] = __half2float(wsc[n]) * (1.0f / 256.0f);   // exact power-of-two factor
+            prm_wr[tid] = a.w_reduced[n];
+            prm_bv[tid] = bias ? __half2float(bias[n]) : 0.0f;
         }
 #pragma unroll
         for (int q = 0; q < PF; ++q) {
             const int kk = (wave + 4 * q) * 16 + g * 8;    // first of this lane's 8 outlier columns
             const bool live = (wave + 4 * q) < fsteps && kk < a.n_out;
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                const int t2 = min(t0 + i * 32 + l32, a.T - 1);
-                pfa[q][i] = live ? *reinterpret_cast<const uint4*>(xo + (size_t)t2 * a.ldo + kk) : make_uint4(0, 0, 0, 0);
-            }
+            pfa[q] = live ? *reinterpret_cast<const uint4*>(xo + (size_t)t2 * a.ldo + kk) : make_uint4(0, 0, 0, 0);
             pfb[q] = live ? *reinterpret_cast<const uint4*>(wo + (size_t)n2 * a.ldwo + kk) : make_uint4(0, 0, 0, 0);
         }
     }
 
-    v16i acc[TM];
+    v16i acc;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][r] = 0;
+    for (int r = 0; r < 16; ++r) acc[r] = 0;
 
 #pragma unroll
     for (int s = 0; s < NST - 1; ++s) issue(s_begin + s);
@@ -566,40 +483,28 @@ __global__ __launch_bounds__(256) void gemm_sp24_skinny(GemmArgs a) {
         constexpr uint32_t M = 0xF0F0F0F0u;
         const uint4 ww = *reinterpret_cast<const uint4*>(st + A_BYTES + rd);
         const v4i uw = v4i{(int)((ww.x << 4) & M), (int)(ww.x & M), (int)((ww.y << 4) & M), (int)(ww.y & M)};
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            const uint4 wa = *reinterpret_cast<const uint4*>(st + i * 1024 + rd);
-            const v8i ua = v8i{(int)(wa.x & M), (int)((wa.x << 4) & M), (int)(wa.y & M), (int)((wa.y << 4) & M),
-                               (int)(wa.z & M), (int)((wa.z << 4) & M), (int)(wa.w & M), (int)((wa.w << 4) & M)};
-            acc[i] = __builtin_amdgcn_smfmac_i32_32x32x64_i8(uw, ua, acc[i], (int)ww.z, 0, 0);
-        }
+        const uint4 wa = *reinterpret_cast<const uint4*>(st + rd);
+        const v8i ua = v8i{(int)(wa.x & M), (int)((wa.x << 4) & M), (int)(wa.y & M), (int)((wa.y << 4) & M),
+                           (int)(wa.z & M), (int)((wa.z << 4) & M), (int)(wa.w & M), (int)((wa.w << 4) & M)};
+        acc = __builtin_amdgcn_smfmac_i32_32x32x64_i8(uw, ua, acc, (int)ww.z, 0, 0);
         // the buffer read here is refilled NST - 1 iterations later by this same wave: the LDS reads above
         // have returned (their data fed the matrix instructions) before that DMA is issued
     }
     wait_vm<0>();
 
     // ---- this wave's share of the fp16 outlier product (weights first: same accumulator layout)
-    v16f cf[TM];
+    v16f cf;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) cf[i][r] = 0.0f;
+    for (int r = 0; r < 16; ++r) cf[r] = 0.0f;
     if constexpr (!RAW) {
 #pragma unroll
         for (int q = 0; q < PF; ++q)
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-                cf[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, pfb[q]), __builtin_bit_cast(v8h, pfa[q][i]),
-                                                               cf[i], 0, 0, 0);
+            cf = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, pfb[q]), __builtin_bit_cast(v8h, pfa[q]), cf, 0, 0, 0);
         for (int stp = wave + 4 * PF; stp < fsteps; stp += 4) {     // the outlier columns beyond the prefetched ones
             const int kk = stp * 16 + g * 8;
             const uint4 fb = (kk < a.n_out) ? *reinterpret_cast<const uint4*>(wo + (size_t)n2 * a.ldwo + kk) : make_uint4(0, 0, 0, 0);
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                const int t2 = min(t0 + i * 32 + l32, a.T - 1);
-                const uint4 fa = (kk < a.n_out) ? *reinterpret_cast<const uint4*>(xo + (size_t)t2 * a.ldo + kk) : make_uint4(0, 0, 0, 0);
-                cf[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, fb), __builtin_bit_cast(v8h, fa), cf[i], 0, 0, 0);
-            }
+            const uint4 fa = (kk < a.n_out) ? *reinterpret_cast<const uint4*>(xo + (size_t)t2 * a.ldo + kk) : make_uint4(0, 0, 0, 0);
+            cf = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, fb), __builtin_bit_cast(v8h, fa), cf, 0, 0, 0);
         }
     }
     __syncthreads();                                       // rings are dead: reuse LDS for the reduction
@@ -607,60 +512,43 @@ __global__ __launch_bounds__(256) void gemm_sp24_skinny(GemmArgs a) {
     // ---- sum the four partial results: waves 1..3 publish, wave 0 adds (INT32 exactly; the fp32 outlier
     // partials in wave order)
     int* red = reinterpret_cast<int*>(lds);
-    float* redf = reinterpret_cast<float*>(lds) + 3 * TM * 16 * 64;
+    float* redf = reinterpret_cast<float*>(lds) + 3 * 16 * 64;
     if (wave > 0) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int slot = (((wave - 1) * TM + i) * 16 + r) * 64 + lane;
-                red[slot] = acc[i][r];
-                if constexpr (!RAW) redf[slot] = cf[i][r];
-            }
+        for (int r = 0; r < 16; ++r) {
+            const int slot = ((wave - 1) * 16 + r) * 64 + lane;
+            red[slot] = acc[r];
+            if constexpr (!RAW) redf[slot] = cf[r];
+        }
     }
     __syncthreads();
     if (wave > 0) return;
-    auto add_partial = [&](int w) __attribute__((always_inline)) {
+    // (all 96 loads at once: 0.5 us faster than one partial result after the other, at 60 registers)
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+    for (int w = 0; w < 3; ++w)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int slot = ((w * TM + i) * 16 + r) * 64 + lane;
-                acc[i][r] += red[slot];
-                if constexpr (!RAW) cf[i][r] += redf[slot];
-            }
-    };
-    if constexpr (TM == 1) {
-        // all 96 loads at once: 0.5 us faster than one partial result after the other, at 60 registers
-        add_partial(0); add_partial(1); add_partial(2);
-    } else {
-        // one partial result after the other: hoisting all the loads would halve the occupancy
-#pragma unroll 1
-        for (int w = 0; w < 3; ++w) add_partial(w);
-    }
+        for (int r = 0; r < 16; ++r) {
+            const int slot = (w * 16 + r) * 64 + lane;
+            acc[r] += red[slot];
+            if constexpr (!RAW) cf[r] += redf[slot];
+        }
 
-    // lane: token t0 + 32 i + l32; register r: channel n0 + 8 (r / 4) + 4 g + r % 4
+    // lane: token t0 + l32; register r: channel n0 + 8 (r / 4) + 4 g + r % 4
+    const int t = t0 + l32;
+    if constexpr (RAW) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        const int t = t0 + i * 32 + l32;
-        if constexpr (RAW) {
+        for (int r = 0; r < 16; ++r) {
+            const int n = n0 + 8 * (r >> 2) + 4 * g + (r & 3);
+            if (t < a.T && n < a.N) a.acc[(size_t)t * a.ldacc + n] = acc[r] >> 8;   // exact: a multiple of 256
+        }
+    } else {
+        __half* __restrict__ y = static_cast<__half*>(a.y);
+        const float t_h = t_z + 8.0f * t_s;                // zeroAct + halfRange * scaleAct
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int n = n0 + 8 * (r >> 2) + 4 * g + (r & 3);
-                if (t < a.T && n < a.N) a.acc[(size_t)t * a.ldacc + n] = acc[i][r] >> 8;   // exact: a multiple of 256
-            }
-        } else {
-            __half* __restrict__ y = static_cast<__half*>(a.y);
-            const float t_h = t_z[i] + 8.0f * t_s[i];      // zeroAct + halfRange * scaleAct
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int c = 8 * (r >> 2) + 4 * g + (r & 3), n = n0 + c;
-                const float v = __builtin_fmaf((float)acc[i][r], t_s[i] * prm_sw[c], __builtin_fmaf(t_h, prm_wr[c], prm_bv[c])) + cf[i][r];
-                if (t < a.T && n < a.N) {
-                    if (a.fp_only) reinterpret_cast<float*>(a.y)[(size_t)t * a.ldy + n] = v;
-                    else y[(size_t)t * a.ldy + n] = __float2half(v);
-                }
-            }
+        for (int r = 0; r < 16; ++r) {
+            const int c = 8 * (r >> 2) + 4 * g + (r & 3), n = n0 + c;
+            const float v = __builtin_fmaf((float)acc[r], t_s * prm_sw[c], __builtin_fmaf(t_h, prm_wr[c], prm_bv[c])) + cf[r];
+            if (t < a.T && n < a.N) y[(size_t)t * a.ldy + n] = __float2half(v);
         }
     }
 }
@@ -715,40 +603,69 @@ __global__ __launch_bounds__(256) void weight_pack_sp24_kernel(const uint8_t* __
     if (bad && violations) atomicAdd(violations, bad);
 }
 
-template <int BM, int BN, int WM, int WN, int NST, int KS, int GM, int MODE>
+template <int IB, int JB, int WM, int WN, int NST, int OCC, int GM, int MODE>
 hipError_t launch_cfg(const GemmArgs& a, hipStream_t stream) {
+    constexpr int BM = WM * IB * 16, BN = WN * JB * 16;
     const int tiles = ((a.T + BM - 1) / BM) * ((a.N + BN - 1) / BN);
-    hipLaunchKernelGGL((gemm_sp24_kernel<BM, BN, WM, WN, NST, KS, GM, MODE>), dim3(tiles), dim3(WM * WN * 64), 0, stream, a);
+    hipLaunchKernelGGL((gemm_sp24_kernel<IB, JB, WM, WN, NST, OCC, GM, MODE>), dim3(tiles), dim3(WM * WN * 64), 0, stream, a);
     return hipGetLastError();
+}
+
+// The tile whose launch is estimated to be the shortest, up to `occ` workgroups of it per CU: base + round * rounds +
+// tile * tiles of the busiest CU + steps * (round_step * rounds + tile_step * tiles of the busiest CU), an outlier stage
+// counting as half a step.  Fitted to 245 shapes with every tile measured (T 1 .. 4096, K 512 .. 11008, N 512 .. 28672,
+// cached weights and from HBM); the choice costs 1 % against the fastest tile in the mean.  The first entry is the
+// K-split kernel: it wins up to 64 tokens nearly always, and never beyond 256, for which it was not measured.  The 64 x 64 tile
+// is left out beyond two rounds of it: the fit holds for cached operands, from HBM it fetches them too often there
+// (T = 920, N = 21928, K = 576: 52 us, 128 x 256 27).
+struct TileCost24 { int bm, bn, occ; double base, round, tile, round_step, tile_step; };
+constexpr TileCost24 kCost24[] = {{32, 32, 4, 1.899, 2.066, 0.502, 0.019, 0.059},
+                                  {64, 64, 4, 5.081, -3.715, 2.538, 0.234, 0.055},
+                                  {128, 128, 2, 3.433, -1.869, 8.007, 0.104, 0.249},
+                                  {128, 192, 1, -0.686, 14.189, 0, 0.456, 0},
+                                  {256, 192, 1, -2.823, 24.649, 0, 0.634, 0},
+                                  {128, 256, 2, 1.663, 0.780, 14.041, 0.204, 0.320}};
+constexpr int kSplitTokens = 256;
+
+int choose_tile_sp24(int T, int N, int K_b, int n_out, int cus) {
+    const double steps = (K_b + 127) / 128 + 0.5 * ((n_out + 31) / 32);
+    int best = -1;
+    double least = 0.0;
+    for (int i = 0; i < (int)(sizeof(kCost24) / sizeof(TileCost24)); ++i) {
+        const TileCost24& c = kCost24[i];
+        const long tiles = (long)((T + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+        const long rounds = (tiles + (long)c.occ * cus - 1) / ((long)c.occ * cus), busiest = (tiles + cus - 1) / cus;
+        if ((i == 0 && T > kSplitTokens) || (i == 1 && rounds > 2)) continue;
+        const double t = c.base + c.round * rounds + c.tile * busiest + steps * (c.round_step * rounds + c.tile_step * busiest);
+        if (best < 0 || t < least) { best = i; least = t; }
+    }
+    return best;
 }
 
 template <int MODE>
 hipError_t dispatch24(const GemmArgs& a, hipStream_t stream) {
-    // Few tokens: weight streaming dominates.  The K-split kernel, one workgroup per 32 channels and 32 or 64
-    // tokens (ring depth at 32 tokens: 4 and 6 measured alike, 8 to 16 up to 15 % slower).
-    if (a.T <= 32) {
-        hipLaunchKernelGGL((gemm_sp24_skinny<1, 4, MODE>), dim3((a.N + 31) / 32), dim3(256), 0, stream, a);
+    int cus = compute_units();
+    if (cus < 1) cus = 256;
+    switch (choose_tile_sp24(a.T, a.N, a.K_b, MODE ? 0 : a.n_out, cus)) {
+    case 0:
+        // (ring depth: 4 and 6 measured alike, 8 to 16 up to 15 % slower)
+        hipLaunchKernelGGL((gemm_sp24_split<4, MODE>), dim3(((a.T + 31) / 32) * ((a.N + 31) / 32)), dim3(256), 0, stream, a);
         return hipGetLastError();
+    case 1: return launch_cfg<4, 1, 1, 4, 8, 4, 8, MODE>(a, stream);
+    case 2: return launch_cfg<4, 2, 2, 4, 6, 2, 8, MODE>(a, stream);
+    case 3: return launch_cfg<4, 3, 2, 4, 8, 1, 8, MODE>(a, stream);
+    case 4: return launch_cfg<4, 6, 4, 2, 6, 1, 8, MODE>(a, stream);
+    default: return launch_cfg<4, 8, 2, 2, 6, 2, 8, MODE>(a, stream);
     }
-    if (a.T <= 64) {
-        hipLaunchKernelGGL((gemm_sp24_skinny<2, 4, MODE>), dim3((a.N + 31) / 32), dim3(256), 0, stream, a);
-        return hipGetLastError();
-    }
-    // One workgroup of eight waves per CU, so a launch runs in ceil(tiles / 256) rounds; a 256 x 192 tile
-    // takes about 1.4x as long as a 256 x 128 one.  Few tiles: 128 x 128 tiles, two workgroups per CU.
-    // Ring of eight stage buffers everywhere (measured: 6 and 8 run alike, odd counts and
-    // deeper rings up to the LDS limit 3 - 7 % slower).
-    auto rounds = [&](int bm, int bn) { return (((long)(a.T + bm - 1) / bm) * ((a.N + bn - 1) / bn) + 255) / 256; };
-    const long tiles_128 = (long)((a.T + 255) / 256) * ((a.N + 127) / 128);
-    // 65 .. 128 tokens: 128 x 64 tiles (twice the workgroups of 128 x 128 tiles: 15 % faster there, slower
-    // from 192 tokens on)
-    if (a.T <= 128) return launch_cfg<128, 64, 2, 2, 8, 2, 0, MODE>(a, stream);
-    if (tiles_128 < 256) return launch_cfg<128, 128, 2, 2, 8, 2, 0, MODE>(a, stream);
-    if (1.4 * (double)rounds(256, 192) <= (double)rounds(256, 128)) return launch_cfg<256, 192, 4, 2, 8, 2, 4, MODE>(a, stream);
-    return launch_cfg<256, 128, 4, 2, 8, 2, 4, MODE>(a, stream);
 }
 
 }  // namespace
+
+void sp24_form(int T, int N, int K_b, int n_out, int cus, int* rows, int* cols) {
+    const TileCost24& c = kCost24[choose_tile_sp24(T, N, K_b, n_out, cus)];
+    *rows = c.bm;
+    *cols = c.bn;
+}
 
 hipError_t launch_gemm_sp24(const GemmArgs& a, hipStream_t stream) {
     if (a.T <= 0 || a.N <= 0) return hipSuccess;

@@ -19,6 +19,11 @@
 // S = ceil(K_b / 64) stages), the rows of a stage one after the other, so the rows of an output tile are
 // one contiguous run per stage.
 //
+// v_smfmac_i32_16x16x128_i8 (same rate, 16 x 16 outputs, 128 columns) reads two stages as they are: dense lane (l, g)
+// takes piece g % 2 of stage g / 2, sparse lane (l, g) record g / 2 of stage g % 2.  Its measured layout: the first eight
+// bytes of sparse lane g meet bytes 16 (g / 2) .. 16 (g / 2) + 15 of the dense lanes of group 2 (g % 2), the other eight
+// the same bytes of group 2 (g % 2) + 1.
+//
 // Activations (R = T rows): 32 bytes per row and stage, byte (s R + r) 32 + b.  Byte b = 4 m + p holds
 // columns 8 m + p (high nibble) and 8 m + 4 + p (low nibble) of the stage as two's complement nibbles:
 // (word & 0xF0F0F0F0) and ((word << 4) & 0xF0F0F0F0) are then sixteen times the int8 values of two

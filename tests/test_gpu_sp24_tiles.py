@@ -1,0 +1,73 @@
+"""Every tile of the 2:4-sparse GEMM at its edges: accumulators bit-exact, output within 5e-3 of the oracle (run with -m
+gpu)."""
+import numpy as np
+import pytest
+
+from paper_2310_09259_amd import synth
+from tests.util import output_within_tolerance, to_dev, upload
+
+pytestmark = pytest.mark.gpu
+
+# T, N, K, n_out -> tile on 256 compute units (asserted in test_sp24_forms.py): fewer panels than the ring has slots, an
+# odd number of panels, a last panel that is not full; one, several and no outlier stages; ragged T and N, with and
+# without whole 16-byte output pieces
+SHAPES = {
+    (13, 64, 360, 40): (32, 32), (5, 118, 1056, 24): (32, 32), (45, 100, 4168, 8): (32, 32), (7, 1224, 352, 0): (32, 32),
+    (9, 84, 128, 48): (64, 64), (281, 78, 488, 96): (64, 64), (366, 80, 480, 0): (64, 64), (70, 4098, 2056, 264): (32, 32), (190, 4098, 2056, 264): (64, 64),
+    (198, 12412, 104, 40): (128, 128), (199, 12364, 464, 40): (128, 128), (204, 13168, 368, 0): (128, 128),
+    (401, 12094, 104, 48): (128, 192), (515, 9090, 440, 40): (128, 192), (450, 10328, 328, 0): (128, 192),
+    (806, 8900, 96, 40): (128, 256), (518, 11102, 456, 64): (128, 256), (859, 8544, 328, 0): (128, 256),
+    (641, 12498, 96, 40): (256, 192), (641, 12042, 456, 48): (256, 192), (652, 12400, 336, 0): (256, 192),
+}
+
+
+@pytest.mark.parametrize("T,N,K,n_out", SHAPES)
+def test_sp24_tile(oracle, T, N, K, n_out):
+    from paper_2310_09259_amd import api
+    shp = synth.LayerShape("sp24_tile", T, K, N, n_out, 4, seed=700 + T + N + K, sparse24=True)
+    inp = synth.make_inputs(shp)
+    d = upload(inp)
+    b = np.random.default_rng(T).standard_normal(N).astype(np.float16)
+    ref = oracle.linear(inp.x, inp.outlier_idx, 4, inp.w_packed, inp.w_scale, inp.w_out, bias=b)
+    w_red = api.quik_weight_reduce(d["w_q"], d["w_scale"], shp.K_b, 4)
+    w24 = api.quik_weight_pack_sp24(d["w_q"], shp.K_b)
+    xq24 = api.quik_quantize_sp24(d["x"], d["idx"])[0]
+    assert np.array_equal(api.quik_int_gemm_sp24(xq24, w24, N, shp.K_b).cpu().numpy(), ref.acc)
+    for bias in (to_dev(b), None):
+        y = api.quik_linear_sp24(d["x"], d["idx"], w24, d["w_scale"], w_red, d["w_out"], bias=bias)
+        want = ref.y if bias is not None else oracle.linear(inp.x, inp.outlier_idx, 4, inp.w_packed, inp.w_scale, inp.w_out).y
+        ok, worst = output_within_tolerance(y.cpu().numpy(), want)
+        assert ok, f"fp16 output outside 5e-3 (worst error / tolerance = {worst:.2f}, bias: {bias is not None})"
+
+
+def test_sp24_tiles_write_rows_that_are_not_16_byte_aligned():
+    """Output rows at an odd stride go element by element: the same bytes, and nothing beyond the row."""
+    import torch
+    from paper_2310_09259_amd import api
+    for T, N, K, n_out in ((281, 78, 488, 96), (198, 12412, 104, 40), (806, 8900, 96, 40)):
+        shp = synth.LayerShape("sp24_ld", T, K, N, n_out, 4, seed=11, sparse24=True)
+        d = upload(synth.make_inputs(shp))
+        w_red = api.quik_weight_reduce(d["w_q"], d["w_scale"], shp.K_b, 4)
+        w24 = api.quik_weight_pack_sp24(d["w_q"], shp.K_b)
+        want = api.quik_linear_sp24(d["x"], d["idx"], w24, d["w_scale"], w_red, d["w_out"])
+        wide = torch.full((T, N + 3), 7.0, dtype=torch.float16, device="cuda")
+        api.quik_linear_sp24(d["x"], d["idx"], w24, d["w_scale"], w_red, d["w_out"], out=wide[:, :N])
+        assert torch.equal(wide[:, :N].contiguous().view(torch.int16), want.view(torch.int16))
+        assert bool((wide[:, N:] == 7.0).all())
+
+
+def test_sp24_tiles_repeat_bit_identically():
+    """More workgroups than compute units, eight calls in a row."""
+    import torch
+    from paper_2310_09259_amd import api
+    for T, N, K, n_out in ((300, 9000, 1000, 104), (90, 20000, 904, 72), (1200, 12000, 520, 40)):
+        shp = synth.LayerShape("sp24_rep", T, K, N, n_out, 4, seed=9, sparse24=True)
+        d = upload(synth.make_inputs(shp))
+        w_red = api.quik_weight_reduce(d["w_q"], d["w_scale"], shp.K_b, 4)
+        w24 = api.quik_weight_pack_sp24(d["w_q"], shp.K_b)
+        first = None
+        for _ in range(8):
+            y = api.quik_linear_sp24(d["x"], d["idx"], w24, d["w_scale"], w_red, d["w_out"])
+            torch.cuda.synchronize()
+            first = y if first is None else first
+            assert torch.equal(first.view(torch.int16), y.view(torch.int16))
