@@ -5,14 +5,14 @@
 // representable in the 6-bit float format E3M2 (1 sign, 3 exponent bits with bias 3, 2 mantissa bits),
 // their products are integers of magnitude <= 64, and a dot product over K_b < 262144 columns stays
 // below 2^24, so an fp32 accumulator holds the integer result exactly.  gfx950 multiplies FP6 operands
-// at twice its int8 rate (v_mfma_f32_32x32x64_f8f6f4), and the operands need no widening in registers.
+// at twice its int8 rate (v_mfma_f32_16x16x128_f8f6f4), and the operands need no widening in registers.
 //
 // Operand layout ("panels").  The columns of a matrix with R rows are padded with zero codes to S
-// stages of 64 columns (one step of the matrix instruction), and the matrix is stored stage by stage:
+// stages of 64 columns (half a step of the matrix instruction), and the matrix is stored stage by stage:
 // stage s of row r is the 48-byte block at byte (s * R + r) * 48, so the rows of an output tile are one
 // contiguous run per stage (whole cache lines for the copy engine, and nothing to rearrange on the way
-// into LDS).  A stage holds two groups of 32 columns, g = 0, 1: the half of the wave's lanes that
-// consumes it.  A group is 32 x 6 bits = six dwords d0 .. d5, column j of the group in bits
+// into LDS).  A stage holds two groups of 32 columns, g = 0, 1, each consumed by one quarter of the wave's
+// lanes.  A group is 32 x 6 bits = six dwords d0 .. d5, column j of the group in bits
 // [6j, 6j + 6) of that 192-bit little-endian string: exactly the register image one lane hands to the
 // matrix instruction.  d0 .. d3 of group g sit at byte 16 g of the block, d4, d5 at byte 32 + 8 g.
 #pragma once
