@@ -244,7 +244,8 @@ int quik_debug_gemm_form(int T, int N, int K_b, int bits, int w_bits, int cus, i
  */
 int quik_debug_fp6_form(int T, int N, int K_b, int cus, int *form);
 
-/* Test hook (host only): the same for quik_gemm_dequant_sp24 / quik_int_gemm_sp24 (n_out = 0). */
+/* Test hook (host only): the same for quik_gemm_dequant_sp24 / quik_int_gemm_sp24 (n_out = 0); form[2]: waves per
+ * workgroup. */
 int quik_debug_sp24_form(int T, int N, int K_b, int n_out, int cus, int *form);
 
 /*

@@ -250,8 +250,8 @@ def quik_debug_fp6_form(T: int, N: int, K_b: int, cus: int):
 
 
 def quik_debug_sp24_form(T: int, N: int, K_b: int, n_out: int, cus: int):
-    """Host-only: (rows, cols) of the 2:4-sparse GEMM's output tile for this shape on `cus` compute units."""
-    form = (C.c_int * 2)()
+    """Host-only: (rows, cols, waves) of the 2:4-sparse GEMM's tile for this shape on `cus` compute units."""
+    form = (C.c_int * 3)()
     _check(load().quik_debug_sp24_form(T, N, K_b, n_out, cus, C.cast(form, C.c_void_p)), "quik_debug_sp24_form")
     return tuple(form)
 

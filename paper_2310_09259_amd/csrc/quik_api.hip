@@ -152,7 +152,7 @@ int quik_debug_fp6_form(int T, int N, int K_b, int cus, int* form) {
 int quik_debug_sp24_form(int T, int N, int K_b, int n_out, int cus, int* form) {
     if (T <= 0 || N <= 0 || K_b <= 0 || K_b >= kMaxKb || n_out < 0 || cus <= 0) return QUIK_EINVAL;
     if (!form) return QUIK_ENULL;
-    quik::sp24_form(T, N, K_b, n_out, cus, &form[0], &form[1]);
+    quik::sp24_form(T, N, K_b, n_out, cus, form);
     return QUIK_OK;
 }
 

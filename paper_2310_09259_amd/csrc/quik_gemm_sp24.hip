@@ -30,7 +30,7 @@
 //    took 64 us instead of 60 for the shape above with 256 outliers.
 // GEMM, us, a 32 x 32 x 64 kernel with steps of one panel : this one, same box: 13B QKV, 1024 tokens 72 : 49; 4096
 // tokens 214 : 186; 7B up-projection, 2048 tokens 72.5 : 63; 7B down-projection 61.5 : 59; T = 333, N = 11008, K = 4096
-// 27.6 : 23.9.  Over 183 drawn shapes of more than 64 tokens it takes 0.67 of that kernel's time in the mean.
+// 27.6 : 23.9.  Over 135 drawn shapes of 40 to 4096 tokens, N a multiple of 64, it takes 0.78 of that kernel's time.
 // Rows beyond T / N are out of range for the panel descriptors and arrive as zeros.
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
@@ -613,18 +613,20 @@ hipError_t launch_cfg(const GemmArgs& a, hipStream_t stream) {
 
 // The tile whose launch is estimated to be the shortest, up to `occ` workgroups of it per CU: base + round * rounds +
 // tile * tiles of the busiest CU + steps * (round_step * rounds + tile_step * tiles of the busiest CU), an outlier stage
-// counting as half a step.  Fitted to 245 shapes with every tile measured (T 1 .. 4096, K 512 .. 11008, N 512 .. 28672,
-// cached weights and from HBM); the choice costs 1 % against the fastest tile in the mean.  The first entry is the
-// K-split kernel: it wins up to 64 tokens nearly always, and never beyond 256, for which it was not measured.  The 64 x 64 tile
-// is left out beyond two rounds of it: the fit holds for cached operands, from HBM it fetches them too often there
-// (T = 920, N = 21928, K = 576: 52 us, 128 x 256 27).
-struct TileCost24 { int bm, bn, occ; double base, round, tile, round_step, tile_step; };
-constexpr TileCost24 kCost24[] = {{32, 32, 4, 1.899, 2.066, 0.502, 0.019, 0.059},
-                                  {64, 64, 4, 5.081, -3.715, 2.538, 0.234, 0.055},
-                                  {128, 128, 2, 3.433, -1.869, 8.007, 0.104, 0.249},
-                                  {128, 192, 1, -0.686, 14.189, 0, 0.456, 0},
-                                  {256, 192, 1, -2.823, 24.649, 0, 0.634, 0},
-                                  {128, 256, 2, 1.663, 0.780, 14.041, 0.204, 0.320}};
+// counting as half a step.  Fitted to 380 shapes with every tile measured (T 1 .. 4096, K 512 .. 11008, N 512 .. 28672,
+// cached weights and from HBM), those with output rows of whole 16-byte pieces counted threefold; the choice costs 0.8 %
+// against the fastest tile in the mean.  The first entry is the K-split kernel: it wins up to 64 tokens nearly always, and
+// never beyond 256, for which it was not measured.  The 64 x 64 tile is left out beyond two rounds of it: the fit holds
+// for cached operands, from HBM it fetches them too often there (T = 920, N = 21928, K = 576: 52 us, 128 x 256 27).
+struct TileCost24 { int bm, bn, waves, occ; double base, round, tile, round_step, tile_step; };
+constexpr TileCost24 kCost24[] = {{32, 32, 4, 4, 4.239, -0.913, 1.171, 0.025, 0.053},
+                                  {64, 64, 4, 4, 2.973, -0.458, 1.050, 0.228, 0.062},
+                                  {128, 128, 8, 2, 2.731, 1.544, 1.179, 0.089, 0.275},
+                                  {128, 192, 8, 1, 0.540, 7.261, 0, 0.469, 0},
+                                  {256, 192, 8, 1, 2.281, 8.325, 0, 0.656, 0},
+                                  {128, 256, 4, 2, 4.495, 4.695, 1.207, 0.201, 0.332},
+                                  {128, 192, 4, 2, 4.341, 4.301, 0.993, 0.288, 0.205},
+                                  {128, 128, 4, 2, 2.660, 3.112, 0.655, 0.245, 0.162}};
 constexpr int kSplitTokens = 256;
 
 int choose_tile_sp24(int T, int N, int K_b, int n_out, int cus) {
@@ -655,16 +657,19 @@ hipError_t dispatch24(const GemmArgs& a, hipStream_t stream) {
     case 2: return launch_cfg<4, 2, 2, 4, 6, 2, 8, MODE>(a, stream);
     case 3: return launch_cfg<4, 3, 2, 4, 8, 1, 8, MODE>(a, stream);
     case 4: return launch_cfg<4, 6, 4, 2, 6, 1, 8, MODE>(a, stream);
-    default: return launch_cfg<4, 8, 2, 2, 6, 2, 8, MODE>(a, stream);
+    case 5: return launch_cfg<4, 8, 2, 2, 6, 2, 8, MODE>(a, stream);
+    case 6: return launch_cfg<4, 6, 2, 2, 6, 2, 8, MODE>(a, stream);
+    default: return launch_cfg<4, 4, 2, 2, 8, 2, 8, MODE>(a, stream);
     }
 }
 
 }  // namespace
 
-void sp24_form(int T, int N, int K_b, int n_out, int cus, int* rows, int* cols) {
+void sp24_form(int T, int N, int K_b, int n_out, int cus, int* form) {
     const TileCost24& c = kCost24[choose_tile_sp24(T, N, K_b, n_out, cus)];
-    *rows = c.bm;
-    *cols = c.bn;
+    form[0] = c.bm;
+    form[1] = c.bn;
+    form[2] = c.waves;
 }
 
 hipError_t launch_gemm_sp24(const GemmArgs& a, hipStream_t stream) {

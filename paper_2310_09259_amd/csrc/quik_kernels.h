@@ -210,7 +210,7 @@ hipError_t launch_weight_pack_fp6(const void* w_q, int ldw, int N, int K_b, void
 // 2:4-sparse path (quik_gemm_sp24.hip): xq = activations [stage][T][32 bytes], w_q = weights
 // [stage][N][32 bytes] (quik_sp24_device.h); ldq / ldw unused
 hipError_t launch_gemm_sp24(const GemmArgs& a, hipStream_t stream);
-void sp24_form(int T, int N, int K_b, int n_out, int cus, int* rows, int* cols);     // its tile (host only)
+void sp24_form(int T, int N, int K_b, int n_out, int cus, int* form);     // its tile (host only): rows, channels, waves
 hipError_t launch_weight_pack_sp24(const void* w_q, int ldw, int N, int K_b, void* w24, int* violations,
                                    hipStream_t stream);
 
