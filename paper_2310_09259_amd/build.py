@@ -66,22 +66,22 @@ def _compile(src: str, extra_flags, verbose: bool):
     return src, obj, proc
 
 
-def build_call(verbose: bool = False, incremental: bool = False) -> str:
+def build_call(verbose: bool = False, incremental: bool = False, src: str = CALL_SRC, lib: str = CALL_LIB) -> str:
     """The Python binding's native marshalling (host code only, against the installed torch)."""
     import sysconfig
 
     import torch
-    if incremental and os.path.exists(CALL_LIB) and os.path.getmtime(CALL_LIB) > os.path.getmtime(CALL_SRC):
-        return CALL_LIB
+    if incremental and os.path.exists(lib) and os.path.getmtime(lib) > os.path.getmtime(src):
+        return lib
     t = os.path.dirname(torch.__file__)
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
            "-isystem", os.path.join(t, "include"), "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
-           "-isystem", sysconfig.get_paths()["include"], "-isystem", "/opt/rocm/include", CALL_SRC, "-o", CALL_LIB,
+           "-isystem", sysconfig.get_paths()["include"], "-isystem", "/opt/rocm/include", src, "-o", lib,
            "-L" + os.path.join(t, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
-    return CALL_LIB
+    return lib
 
 
 def build(verbose: bool = False, extra_flags=(), incremental: bool = False) -> str:

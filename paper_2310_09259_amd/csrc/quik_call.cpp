@@ -9,6 +9,7 @@
 
 #include <climits>
 #include <cstdint>
+#include <type_traits>
 
 namespace {
 
@@ -59,11 +60,14 @@ struct Arg {
 int count(const Arg& a) { return a.t ? (a.t->numel() <= INT_MAX ? (int)a.t->numel() : -1) : 0; }
 void* stream() { return (void*)c10::hip::getCurrentHIPStream().stream(); }
 
-PyObject* result(int rc) { return PyLong_FromLong(rc); }
-#define QUIK_CALL(expr)               \
-    int rc;                           \
-    Py_BEGIN_ALLOW_THREADS rc = expr; \
-    Py_END_ALLOW_THREADS return result(rc)
+// The library call, with the interpreter released for as long as it takes.  Pointers and sizes come as values: reading a
+// tensor may throw (a storage that refuses access) and must not run beside other Python threads.
+template <class... P>
+PyObject* call(int (*entry_point)(P...), std::common_type_t<P>... args) {
+    int rc;
+    Py_BEGIN_ALLOW_THREADS rc = entry_point(args...);
+    Py_END_ALLOW_THREADS return PyLong_FromLong(rc);
+}
 
 // linear(kind, x, outlier_idx, weights, w_scale, w_reduced, w_out, bias, out, workspace); kind: 4 or 8 (bits), 84 (4-bit
 // weights under 8-bit activations), 6 (FP6), 24 (2:4-sparse)
@@ -89,21 +93,21 @@ PyObject* linear(PyObject*, PyObject* const* o, Py_ssize_t n) {
         if (!w.matrix()) Py_RETURN_NONE;
         const int N = w.rows();
         if (kind == 84) {
-            QUIK_CALL(entry.linear_w4a8(px, T, K, x.ld(), pi, n_out, w.ptr(), w.ld(), sw.ptr(), pr, po, ldwo, bias.ptr(), N, y.ptr(),
-                                        y.ld(), ws.ptr(), (size_t)ws.t->numel(), st));
+            return call(entry.linear_w4a8, px, T, K, x.ld(), pi, n_out, w.ptr(), w.ld(), sw.ptr(), pr, po, ldwo, bias.ptr(),
+                        N, y.ptr(), y.ld(), ws.ptr(), (size_t)ws.t->numel(), st);
         }
-        QUIK_CALL(entry.linear(px, T, K, x.ld(), pi, n_out, (int)kind, w.ptr(), w.ld(), sw.ptr(), pr, po, ldwo, bias.ptr(), N, y.ptr(),
-                               y.ld(), ws.ptr(), ws.bytes(), st));
+        return call(entry.linear, px, T, K, x.ld(), pi, n_out, (int)kind, w.ptr(), w.ld(), sw.ptr(), pr, po, ldwo,
+                    bias.ptr(), N, y.ptr(), y.ld(), ws.ptr(), ws.bytes(), st);
     }
     if (kind != 6 && kind != 24) Py_RETURN_NONE;
     // panels [stages, rows, bytes]
     if (w.t->dim() != 3 || w.t->stride(2) != 1 || w.t->size(1) > INT_MAX || !sw.t || sw.t->numel() > INT_MAX) Py_RETURN_NONE;
     if (kind == 6) {
-        QUIK_CALL(entry.linear_fp6(px, T, K, x.ld(), pi, n_out, w.ptr(), sw.ptr(), pr, po, ldwo, bias.ptr(), (int)w.t->size(1), y.ptr(),
-                                   y.ld(), ws.ptr(), (size_t)ws.t->numel(), st));
+        return call(entry.linear_fp6, px, T, K, x.ld(), pi, n_out, w.ptr(), sw.ptr(), pr, po, ldwo, bias.ptr(),
+                    (int)w.t->size(1), y.ptr(), y.ld(), ws.ptr(), (size_t)ws.t->numel(), st);
     }
-    QUIK_CALL(entry.linear_sp24(px, T, K, x.ld(), pi, n_out, w.ptr(), sw.ptr(), pr, po, ldwo, bias.ptr(), (int)sw.t->numel(), y.ptr(),
-                                y.ld(), ws.ptr(), (size_t)ws.t->numel(), st));
+    return call(entry.linear_sp24, px, T, K, x.ld(), pi, n_out, w.ptr(), sw.ptr(), pr, po, ldwo, bias.ptr(),
+                (int)sw.t->numel(), y.ptr(), y.ld(), ws.ptr(), (size_t)ws.t->numel(), st);
 }
 
 // quantize(x, outlier_idx, bits, xq, scale, zero, x_out, workspace)
@@ -121,9 +125,10 @@ PyObject* quantize(PyObject*, PyObject* const* o, Py_ssize_t n) {
         (n_out && idx.t->dim() > 1) || n_out >= x.cols() || x.cols() >= 131072 || ((long)(x.cols() - n_out) * bits) % 8)
         Py_RETURN_NONE;
     void* const st = stream();
-    QUIK_CALL(entry.quantize(x.ptr(), x.rows(), x.cols(), x.ld(), n_out ? static_cast<const int32_t*>(idx.ptr()) : nullptr, n_out,
-                             (int)bits, xq.ptr(), xq.ld(), static_cast<float*>(sc.ptr()), static_cast<float*>(ze.ptr()),
-                             n_out ? xo.ptr() : nullptr, n_out ? xo.ld() : 0, ws.ptr(), ws.bytes(), st));
+    return call(entry.quantize, x.ptr(), x.rows(), x.cols(), x.ld(),
+                n_out ? static_cast<const int32_t*>(idx.ptr()) : nullptr, n_out, (int)bits, xq.ptr(), xq.ld(),
+                static_cast<float*>(sc.ptr()), static_cast<float*>(ze.ptr()), n_out ? xo.ptr() : nullptr,
+                n_out ? xo.ld() : 0, ws.ptr(), ws.bytes(), st);
 }
 
 // gemm_dequant(xq, scale, zero, x_out, K_b, bits, w_q, w_scale, w_reduced, w_out, bias, out, workspace)
@@ -142,10 +147,10 @@ PyObject* gemm_dequant(PyObject*, PyObject* const* o, Py_ssize_t n) {
     const int n_out = xo.t ? xo.cols() : 0;
     if (n_out && !wo.matrix()) Py_RETURN_NONE;
     void* const st = stream();
-    QUIK_CALL(entry.gemm_dequant(xq.ptr(), xq.ld(), static_cast<const float*>(sc.ptr()), static_cast<const float*>(ze.ptr()),
-                                 n_out ? xo.ptr() : nullptr, n_out ? xo.ld() : 0, xq.rows(), (int)K_b, n_out, (int)bits, w.ptr(),
-                                 w.ld(), sw.ptr(), static_cast<const float*>(wr.ptr()), n_out ? wo.ptr() : nullptr,
-                                 n_out ? wo.ld() : 0, bias.ptr(), w.rows(), y.ptr(), y.ld(), ws.ptr(), ws.bytes(), st));
+    return call(entry.gemm_dequant, xq.ptr(), xq.ld(), static_cast<const float*>(sc.ptr()),
+                static_cast<const float*>(ze.ptr()), n_out ? xo.ptr() : nullptr, n_out ? xo.ld() : 0, xq.rows(), (int)K_b,
+                n_out, (int)bits, w.ptr(), w.ld(), sw.ptr(), static_cast<const float*>(wr.ptr()), n_out ? wo.ptr() : nullptr,
+                n_out ? wo.ld() : 0, bias.ptr(), w.rows(), y.ptr(), y.ld(), ws.ptr(), ws.bytes(), st);
 }
 
 // bind(addresses of quik_linear, _w4a8, _fp6, _sp24, quik_quantize, quik_gemm_dequant)

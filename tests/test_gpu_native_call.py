@@ -90,3 +90,22 @@ def test_native_quantize_and_gemm_agree(layer):
     with pytest.raises(api.QuikError) as e:
         api.quik_gemm_dequant(*args, out=out)                                 # the 4-bit side data is missing
     assert e.value.status == -2
+
+
+def test_a_tensor_that_refuses_access_raises_as_through_ctypes(layer):
+    import torch
+    api, d, b, ws, forms = layer
+    out = torch.zeros((T, N), dtype=torch.float16, device="cuda")
+    for form, fn in forms.items():
+        want = fn(d["x"], d["idx"], bias=b)
+        for arg in ("x", "idx", "bias", "out", "workspace"):
+            a = {"x": d["x"], "idx": d["idx"], "bias": b, "out": out, "workspace": ws}
+            a[arg] = a[arg].clone()
+            torch._C._set_throw_on_mutable_data_ptr(a[arg])
+            for k in ({"out": a["out"], "workspace": a["workspace"]}, {"out": a["out"]}, {"workspace": a["workspace"]}):
+                if arg in ("x", "idx", "bias") or arg in k:
+                    with pytest.raises(RuntimeError) as e:
+                        fn(a["x"], a["idx"], bias=a["bias"], **k)
+                    assert not isinstance(e.value, api.QuikError), (form, arg)
+        got = fn(d["x"], d["idx"], bias=b, out=out, workspace=ws)                 # and the next call is served
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16)), form

@@ -44,3 +44,77 @@ def test_the_binding_still_raises_what_it_raised():
             fn()
     with pytest.raises(TypeError):
         api.quik_linear(None, None, 4, w, sw, wr, None, out=out, workspace=ws)
+
+
+# The marshalling compiled so that host tensors pass for device ones, over stub entry points that answer 0: what it serves,
+# refuses and raises, without a GPU.  In a process of its own: a mistake there can take the interpreter down.
+HOST_CALLS = r"""
+import ctypes as C, importlib.machinery, importlib.util, json, sys, torch
+loader = importlib.machinery.ExtensionFileLoader("_quik_call", sys.argv[1])
+call = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_quik_call", sys.argv[1], loader=loader))
+STUB = C.CFUNCTYPE(C.c_int)(lambda: 0)
+call.bind(*[C.cast(STUB, C.c_void_p).value] * 6)
+f16, u8, T, K, N, O = torch.float16, torch.uint8, 3, 72, 16, 8
+
+def linear(kind):
+    return {"kind": kind, "x": torch.zeros((T, K), dtype=f16), "idx": torch.zeros(O, dtype=torch.int32),
+            "w": torch.zeros((1, N, 48) if kind in (6, 24) else (N, 64), dtype=u8), "sw": torch.zeros(N, dtype=f16),
+            "wr": torch.zeros(2 * N), "wo": torch.zeros((N, O), dtype=f16), "bias": torch.zeros(N, dtype=f16),
+            "out": torch.zeros((T, N), dtype=f16), "ws": torch.zeros(4096, dtype=u8)}
+
+def quantize():
+    return {"x": torch.zeros((T, K), dtype=f16), "idx": torch.zeros(O, dtype=torch.int32), "bits": 4,
+            "xq": torch.zeros((T, 32), dtype=u8), "scale": torch.zeros(T), "zero": torch.zeros(T),
+            "x_out": torch.zeros((T, O), dtype=f16), "ws": torch.zeros(64, dtype=u8)}
+
+def gemm_dequant():
+    return {"xq": torch.zeros((T, 32), dtype=u8), "scale": torch.zeros(T), "zero": torch.zeros(T),
+            "x_out": torch.zeros((T, O), dtype=f16), "K_b": K - O, "bits": 4, "w": torch.zeros((N, 32), dtype=u8),
+            "sw": torch.zeros(N, dtype=f16), "wr": torch.zeros(2 * N), "wo": torch.zeros((N, O), dtype=f16),
+            "bias": torch.zeros(N, dtype=f16), "out": torch.zeros((T, N), dtype=f16), "ws": torch.zeros(64, dtype=u8)}
+
+def answer(fn, a):
+    try:
+        return fn(*a.values())
+    except RuntimeError as e:
+        return "RuntimeError"
+
+forms = {f"linear {k}": (call.linear, lambda k=k: linear(k)) for k in (4, 8, 84, 6, 24)}
+forms["quantize"], forms["gemm_dequant"] = (call.quantize, quantize), (call.gemm_dequant, gemm_dequant)
+got = {}
+for name, (fn, make) in forms.items():
+    got[name + ": plain"] = answer(fn, make())
+    for arg, value in make().items():
+        if isinstance(value, torch.Tensor):
+            a = make()
+            torch._C._set_throw_on_mutable_data_ptr(a[arg])
+            got[f"{name}: {arg} refuses access"] = answer(fn, a)
+print(json.dumps(got))
+"""
+
+
+@pytest.fixture(scope="module")
+def host_calls(tmp_path_factory):
+    import json
+    import subprocess
+    import sys
+
+    from paper_2310_09259_amd import build
+    d = tmp_path_factory.mktemp("host_call")
+    src = open(build.CALL_SRC).read()
+    for device, host in (("t->is_cuda()", "t->is_cpu()"),
+                         ("(void*)c10::hip::getCurrentHIPStream().stream()", "nullptr")):
+        assert src.count(device) == 1
+        src = src.replace(device, host)
+    (d / "call.cpp").write_text(src)
+    lib = build.build_call(src=str(d / "call.cpp"), lib=str(d / "_quik_call.so"))
+    run = subprocess.run([sys.executable, "-c", HOST_CALLS, lib], capture_output=True, text=True, timeout=300)
+    assert run.returncode == 0, (run.returncode, run.stderr[-2000:])
+    return json.loads(run.stdout)
+
+
+def test_a_tensor_that_refuses_access_raises(host_calls):
+    assert {v for k, v in host_calls.items() if k.endswith(": plain")} == {0}
+    refused = {k: v for k, v in host_calls.items() if k.endswith(" refuses access")}
+    assert len(refused) == 5 * 9 + 7 + 11
+    assert {k: v for k, v in refused.items() if v != "RuntimeError"} == {}
