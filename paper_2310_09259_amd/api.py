@@ -181,6 +181,24 @@ def _dev(t, dtype, name):
     return t
 
 
+def _layer_types(outlier_idx, w_scale, w_reduced, w_out, bias, y):
+    """The library takes these by address: elements of another size, or with gaps between them, would be misread."""
+    for name, t, dtype, size in (("outlier_idx", outlier_idx, torch.int32, 4), ("w_scale", w_scale, torch.float16, 2),
+                                 ("w_reduced", w_reduced, torch.float32, 4), ("bias", bias, torch.float16, 2)):
+        if t is None or t.dtype is dtype and t.is_contiguous() or t.numel() == 0:
+            continue
+        # (bytes that hold the values are taken, except where the number of elements says how many there are)
+        if t.element_size() > size or (t.element_size() < size and name == "outlier_idx"):
+            raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
+        if not t.is_contiguous():
+            raise ValueError(f"{name} must be contiguous")
+    if outlier_idx is None or outlier_idx.numel() == 0:
+        w_out = None                                   # not read
+    for name, t in (("w_out", w_out), ("out", y)):
+        if t is not None and t.dtype is not torch.float16 and t.element_size() != 2:
+            raise TypeError(f"{name} must be {torch.float16}, got {t.dtype}")
+
+
 def quik_version() -> int:
     return load().quik_version()
 
@@ -382,6 +400,7 @@ def _linear_buffers(x, outlier_idx, bits, w_q, out, workspace):
 
 
 def _linear_args(x, outlier_idx, bits, w_q, w_scale, w_reduced, w_out, bias, y, workspace):
+    _layer_types(outlier_idx, w_scale, w_reduced, w_out, bias, y)
     T, K = x.shape
     N = w_q.shape[0]
     n_out = 0 if outlier_idx is None else int(outlier_idx.numel())
@@ -468,6 +487,7 @@ def quik_linear_w4a8(x, outlier_idx, w_q, w_scale, w_reduced, w_out, bias=None, 
     if workspace is None:
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=x.device)
     y = out if out is not None else torch.empty((T, N), dtype=torch.float16, device=x.device)
+    _layer_types(outlier_idx, w_scale, w_reduced, w_out, bias, y)
     rc = load().quik_linear_w4a8(
         _ptr(x), T, K, x.stride(0), _ptr(outlier_idx) if n_out else None, n_out, _ptr(w_q), w_q.stride(0),
         _ptr(w_scale), _ptr(w_reduced), _ptr(w_out) if n_out else None, w_out.stride(0) if n_out else 0,
@@ -495,6 +515,7 @@ def prepare_linear_w4a8(x, outlier_idx, w_q, w_scale, w_reduced, w_out, bias=Non
     if workspace is None:
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=x.device)
     y = out if out is not None else torch.empty((T, N), dtype=torch.float16, device=x.device)
+    _layer_types(outlier_idx, w_scale, w_reduced, w_out, bias, y)
     args = (_ptr(x), T, K, x.stride(0), _ptr(outlier_idx) if n_out else None, n_out, _ptr(w_q), w_q.stride(0),
             _ptr(w_scale), _ptr(w_reduced), _ptr(w_out) if n_out else None, w_out.stride(0) if n_out else 0,
             _ptr(bias), N, _ptr(y), y.stride(0), _ptr(workspace), workspace.numel(), _stream())
@@ -615,6 +636,7 @@ def quik_int_gemm_fp6(xq6, w6, K_b: int):
 
 
 def _linear_fp6_args(x, outlier_idx, w6, w_scale, w_reduced, w_out, bias, y, workspace):
+    _layer_types(outlier_idx, w_scale, w_reduced, w_out, bias, y)
     T, K = x.shape
     N = w6.shape[1]
     n_out = 0 if outlier_idx is None else int(outlier_idx.numel())
@@ -763,6 +785,7 @@ def quik_int_gemm_sp24(xq24, w24, N: int, K_b: int):
 
 
 def _linear_sp24_args(x, outlier_idx, w24, w_scale, w_reduced, w_out, bias, y, workspace):
+    _layer_types(outlier_idx, w_scale, w_reduced, w_out, bias, y)
     T, K = x.shape
     N = int(w_scale.numel())
     n_out = 0 if outlier_idx is None else int(outlier_idx.numel())
@@ -820,6 +843,7 @@ def quik_linear_ablation(version: int, x, outlier_idx, bits: int, w_q, w_scale, 
     if workspace is None:
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=x.device)
     y = out if out is not None else torch.empty((T, N), dtype=torch.float16, device=x.device)
+    _layer_types(outlier_idx, w_scale, w_reduced, w_out, bias, y)
     rc = load().quik_linear_ablation(
         version, _ptr(x), T, K, x.stride(0), _ptr(outlier_idx) if n_out else None, n_out, bits,
         _ptr(w_q), w_q.stride(0), _ptr(w_scale), _ptr(w_reduced),

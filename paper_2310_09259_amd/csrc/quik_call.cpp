@@ -1,9 +1,9 @@
 // The marshalling of the layer calls, natively.  A call through ctypes with some twenty arguments, each looked up on a
 // tensor from Python, takes 10 us, more than a small layer takes on the GPU; here it takes under 1 us (16 tokens, 512 x
-// 512, 32 outliers, one call after another: 14.4 -> 8.2 us).  Only the ordinary call is served: plain strided device
-// tensors, the output and the workspace given.  Everything else -- missing buffers, other types or shapes, tensor
-// subclasses, transformed tensors -- is answered with None, and the Python binding (api.py) does what it always did,
-// errors included.
+// 512, 32 outliers, one call after another: 14.4 -> 8.2 us).  Only the ordinary call is served: plain device tensors of
+// the documented types and strides, the output and the workspace given.  Everything else -- missing buffers, other types
+// or strides, tensor subclasses, transformed tensors -- is answered with None, and the Python binding (api.py) does what
+// it does without this file, errors included.
 #include <torch/csrc/autograd/python_variable.h>
 #include <c10/hip/HIPStream.h>
 
@@ -51,6 +51,10 @@ struct Arg {
                t->stride(0) <= INT_MAX;
     }
     bool matrix(c10::ScalarType type) const { return matrix() && t->scalar_type() == type; }
+    // consecutive elements of a type
+    bool vector(c10::ScalarType type) const { return t && t->scalar_type() == type && t->is_contiguous(); }
+    bool vector_or_none(c10::ScalarType type) const { return !t || vector(type); }
+    bool buffer_or_none() const { return !t || t->is_contiguous(); }
     int rows() const { return (int)t->size(0); }
     int cols() const { return (int)t->size(1); }
     int ld() const { return (int)t->stride(0); }
@@ -81,7 +85,9 @@ PyObject* linear(PyObject*, PyObject* const* o, Py_ssize_t n) {
     const Arg x(o[1]), idx(o[2]), w(o[3]), sw(o[4]), wr(o[5]), wo(o[6]), bias(o[7]), y(o[8]), ws(o[9]);
     const int n_out = idx.ok ? count(idx) : -1;
     if (!(x.ok && idx.ok && w.ok && sw.ok && wr.ok && wo.ok && bias.ok && y.ok && ws.ok) || n_out < 0 || !ws.t ||
-        !x.matrix(at::kHalf) || !y.matrix() || (n_out && !wo.matrix()) || !w.t || w.t->scalar_type() != at::kByte)
+        !x.matrix(at::kHalf) || !y.matrix(at::kHalf) || !w.t || w.t->scalar_type() != at::kByte ||
+        (n_out && !(idx.vector(at::kInt) && wo.matrix(at::kHalf))) || !sw.vector(at::kHalf) || !wr.vector(at::kFloat) ||
+        !bias.vector_or_none(at::kHalf) || !ws.buffer_or_none())
         Py_RETURN_NONE;
     const int T = x.rows(), K = x.cols(), ldwo = n_out ? wo.ld() : 0;
     const void* px = x.ptr();
@@ -101,7 +107,7 @@ PyObject* linear(PyObject*, PyObject* const* o, Py_ssize_t n) {
     }
     if (kind != 6 && kind != 24) Py_RETURN_NONE;
     // panels [stages, rows, bytes]
-    if (w.t->dim() != 3 || w.t->stride(2) != 1 || w.t->size(1) > INT_MAX || !sw.t || sw.t->numel() > INT_MAX) Py_RETURN_NONE;
+    if (w.t->dim() != 3 || w.t->stride(2) != 1 || w.t->size(1) > INT_MAX || sw.t->numel() > INT_MAX) Py_RETURN_NONE;
     if (kind == 6) {
         return call(entry.linear_fp6, px, T, K, x.ld(), pi, n_out, w.ptr(), sw.ptr(), pr, po, ldwo, bias.ptr(),
                     (int)w.t->size(1), y.ptr(), y.ld(), ws.ptr(), (size_t)ws.t->numel(), st);
@@ -121,8 +127,8 @@ PyObject* quantize(PyObject*, PyObject* const* o, Py_ssize_t n) {
     const Arg x(o[0]), idx(o[1]), xq(o[3]), sc(o[4]), ze(o[5]), xo(o[6]), ws(o[7]);
     const int n_out = idx.ok ? count(idx) : -1;
     if (!(x.ok && idx.ok && xq.ok && sc.ok && ze.ok && xo.ok && ws.ok) || n_out < 0 || (bits != 4 && bits != 8) ||
-        !x.matrix(at::kHalf) || !xq.matrix() || (n_out && (!xo.matrix() || idx.t->scalar_type() != at::kInt)) ||
-        (n_out && idx.t->dim() > 1) || n_out >= x.cols() || x.cols() >= 131072 || ((long)(x.cols() - n_out) * bits) % 8)
+        !x.matrix(at::kHalf) || !xq.matrix(at::kByte) || !sc.vector(at::kFloat) || !ze.vector(at::kFloat) ||
+        (n_out && !(idx.vector(at::kInt) && xo.matrix(at::kHalf))) || !ws.buffer_or_none() || n_out >= x.cols() || x.cols() >= 131072 || ((long)(x.cols() - n_out) * bits) % 8)
         Py_RETURN_NONE;
     void* const st = stream();
     return call(entry.quantize, x.ptr(), x.rows(), x.cols(), x.ld(),
@@ -141,11 +147,13 @@ PyObject* gemm_dequant(PyObject*, PyObject* const* o, Py_ssize_t n) {
     }
     const Arg xq(o[0]), sc(o[1]), ze(o[2]), xo(o[3]), w(o[6]), sw(o[7]), wr(o[8]), wo(o[9]), bias(o[10]), y(o[11]), ws(o[12]);
     if (!(xq.ok && sc.ok && ze.ok && xo.ok && w.ok && sw.ok && wr.ok && wo.ok && bias.ok && y.ok && ws.ok) ||
-        !xq.matrix(at::kByte) || !w.matrix(at::kByte) || !y.matrix() || (xo.t && !xo.matrix()) || K_b < INT_MIN || K_b > INT_MAX ||
-        bits < INT_MIN || bits > INT_MAX)
+        !xq.matrix(at::kByte) || !w.matrix(at::kByte) || !y.matrix(at::kHalf) || (xo.t && !xo.matrix(at::kHalf)) ||
+        !sc.vector(at::kFloat) || !ze.vector(at::kFloat) || !sw.vector(at::kHalf) || !wr.vector(at::kFloat) ||
+        !bias.vector_or_none(at::kHalf) || !ws.buffer_or_none() || K_b < INT_MIN || K_b > INT_MAX || bits < INT_MIN ||
+        bits > INT_MAX)
         Py_RETURN_NONE;
     const int n_out = xo.t ? xo.cols() : 0;
-    if (n_out && !wo.matrix()) Py_RETURN_NONE;
+    if (n_out && !wo.matrix(at::kHalf)) Py_RETURN_NONE;
     void* const st = stream();
     return call(entry.gemm_dequant, xq.ptr(), xq.ld(), static_cast<const float*>(sc.ptr()),
                 static_cast<const float*>(ze.ptr()), n_out ? xo.ptr() : nullptr, n_out ? xo.ld() : 0, xq.rows(), (int)K_b,

@@ -109,3 +109,26 @@ def test_a_tensor_that_refuses_access_raises_as_through_ctypes(layer):
                     assert not isinstance(e.value, api.QuikError), (form, arg)
         got = fn(d["x"], d["idx"], bias=b, out=out, workspace=ws)                 # and the next call is served
         assert torch.equal(got.view(torch.int16), want.view(torch.int16)), form
+
+
+def test_misread_arguments_are_refused_and_ordinary_ones_without_outliers_served(layer):
+    import torch
+    api, d, b, ws, forms = layer
+    out = torch.zeros((T, N), dtype=torch.float16, device="cuda")
+    for form, fn in forms.items():
+        for idx, kw in ((d["idx"].long(), {}), (d["idx"], {"bias": b.float()}), (d["idx"], {"out": out.float()})):
+            with pytest.raises(TypeError, match="must be torch"):
+                fn(d["x"], idx, **{"out": out, "workspace": ws, **kw})
+        gaps = torch.stack((d["idx"], d["idx"]), 1)[:, 0]
+        with pytest.raises(ValueError, match="outlier_idx must be contiguous"):
+            fn(d["x"], gaps, out=out, workspace=ws)
+    shp = synth.LayerShape("plain", T, 1024, N, 0, 4, seed=5, sparse24=True)
+    p = upload(synth.make_inputs(shp))
+    red = api.quik_weight_reduce(p["w_q"], p["w_scale"], shp.K_b, 4)
+    w6, w24 = api.quik_weight_pack_fp6(p["w_q"], shp.K_b), api.quik_weight_pack_sp24(p["w_q"], shp.K_b)
+    for name, call in (("int4", lambda **k: api.quik_linear(p["x"], None, 4, p["w_q"], p["w_scale"], red, None, **k)),
+                       ("w4a8", lambda **k: api.quik_linear_w4a8(p["x"], None, p["w_q"], p["w_scale"], red, None, **k)),
+                       ("fp6", lambda **k: api.quik_linear_fp6(p["x"], None, w6, p["w_scale"], red, None, **k)),
+                       ("sp24", lambda **k: api.quik_linear_sp24(p["x"], None, w24, p["w_scale"], red, None, **k))):
+        want = call()
+        assert torch.equal(call(out=out, workspace=ws).view(torch.int16), want.view(torch.int16)), name

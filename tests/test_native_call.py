@@ -89,6 +89,17 @@ for name, (fn, make) in forms.items():
             a = make()
             torch._C._set_throw_on_mutable_data_ptr(a[arg])
             got[f"{name}: {arg} refuses access"] = answer(fn, a)
+            if arg in ("w", "ws") and name != "gemm_dequant":
+                continue                                        # bytes
+            for dtype in (torch.float64, torch.int64, torch.uint8, torch.float16, torch.int32):
+                if dtype != value.dtype and arg not in ("w", "ws", "xq"):
+                    got[f"{name}: {arg} of another type, {dtype}"] = answer(fn, {**make(), arg: value.to(dtype)})
+            wide = torch.zeros((*value.shape, 2), dtype=value.dtype)[..., 0]       # every other element
+            got[f"{name}: {arg} with gaps"] = answer(fn, {**make(), arg: wide})
+    a = make()
+    for arg in ("idx", "bias"):
+        if arg in a:
+            got[f"{name}: without {arg}"] = answer(fn, {**a, arg: None, **({"wo": None} if "wo" in a and arg == "idx" else {})})
 print(json.dumps(got))
 """
 
@@ -118,3 +129,30 @@ def test_a_tensor_that_refuses_access_raises(host_calls):
     refused = {k: v for k, v in host_calls.items() if k.endswith(" refuses access")}
     assert len(refused) == 5 * 9 + 7 + 11
     assert {k: v for k, v in refused.items() if v != "RuntimeError"} == {}
+
+
+def test_types_and_strides_that_would_be_misread_go_to_python(host_calls):
+    other = {k: v for k, v in host_calls.items() if " of another type" in k or k.endswith(" with gaps")}
+    assert len(other) > 150 and {k: v for k, v in other.items() if v is not None} == {}
+    without = {k: v for k, v in host_calls.items() if ": without " in k}
+    assert len(without) == 5 * 2 + 1 + 1 and set(without.values()) == {0}
+
+
+def test_the_binding_refuses_what_would_be_misread():
+    """The ctypes path, before anything is enqueued (host tensors: the message tells the check that was reached)."""
+    half, f32 = torch.zeros(8, dtype=torch.float16), torch.zeros(16)
+    good = {"outlier_idx": torch.zeros(8, dtype=torch.int32), "w_scale": half, "w_reduced": f32,
+            "w_out": torch.zeros((8, 8), dtype=torch.float16), "bias": half, "out": torch.zeros((2, 8), dtype=torch.float16)}
+    api._layer_types(*good.values())
+    api._layer_types(None, half, f32, None, None, good["out"])
+    for nothing in (None, torch.zeros(0, dtype=torch.int64)):                                  # w_out is not read
+        api._layer_types(*{**good, "outlier_idx": nothing, "w_out": torch.zeros((8, 8))}.values())
+    api._layer_types(*{**good, "w_reduced": torch.zeros(64, dtype=torch.uint8)}.values())      # the raw bytes
+    for arg, bad in (("outlier_idx", torch.zeros(8, dtype=torch.int64)), ("w_scale", torch.zeros(8)),
+                     ("w_reduced", torch.zeros(16, dtype=torch.float64)), ("w_out", torch.zeros((8, 8))),
+                     ("bias", torch.zeros(8)), ("out", torch.zeros((2, 8))), ("out", torch.zeros((2, 8), dtype=torch.uint8))):
+        with pytest.raises(TypeError, match=f"{arg} must be "):
+            api._layer_types(*{**good, arg: bad}.values())
+    for arg, n in (("outlier_idx", 16), ("w_scale", 16), ("w_reduced", 32), ("bias", 16)):
+        with pytest.raises(ValueError, match=f"{arg} must be contiguous"):
+            api._layer_types(*{**good, arg: torch.zeros(n, dtype=good[arg].dtype)[::2]}.values())
