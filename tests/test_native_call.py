@@ -156,3 +156,30 @@ def test_the_binding_refuses_what_would_be_misread():
     for arg, n in (("outlier_idx", 16), ("w_scale", 16), ("w_reduced", 32), ("bias", 16)):
         with pytest.raises(ValueError, match=f"{arg} must be contiguous"):
             api._layer_types(*{**good, arg: torch.zeros(n, dtype=good[arg].dtype)[::2]}.values())
+
+
+def test_without_the_native_marshalling_calls_go_through_ctypes(monkeypatch, tmp_path):
+    api.load()
+    monkeypatch.setattr(api, "CALL_PATH", str(tmp_path / "none.so"))
+    monkeypatch.setattr(api, "_call", None)
+    monkeypatch.setattr(api, "_lib", None)
+    with pytest.warns(RuntimeWarning, match="go through ctypes"):
+        assert api.quik_version() == 1                                       # the library itself is served
+    test_the_binding_still_raises_what_it_raised()
+
+
+def test_the_library_is_built_where_the_marshalling_cannot_be(monkeypatch, tmp_path, capsys):
+    from paper_2310_09259_amd import build
+    ran = []
+
+    def run(cmd, **kw):
+        ran.append(cmd[0])
+        if cmd[0] == "g++":
+            raise FileNotFoundError("g++")
+    monkeypatch.setattr(build.subprocess, "run", run)
+    monkeypatch.setattr(build, "SOURCES", [])
+    stale = tmp_path / "_quik_call.so"
+    stale.write_bytes(b"")
+    monkeypatch.setattr(build, "build_call", lambda *a, _real=build.build_call: _real(*a, lib=str(stale)))
+    assert build.build() == build.LIB and ran == [build.HIPCC, "g++"]
+    assert "go through ctypes" in capsys.readouterr().err and not stale.exists()
