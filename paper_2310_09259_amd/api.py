@@ -131,7 +131,7 @@ def load() -> C.CDLL:
 
 
 class _ThroughCtypes:
-    """In the place of the native marshalling where there is none: serves no call."""
+    """In the place of the native marshalling where there is none for this interpreter: serves no call."""
 
     @staticmethod
     def linear(*_):
@@ -141,20 +141,24 @@ class _ThroughCtypes:
 
 
 def _load_call(lib):
-    """The native marshalling, if it is there.  Every call can go through ctypes, so
+    """The native marshalling, if one built for this torch and this Python is there.  Every call can go through ctypes, so
     its absence costs host time only (about 8 us a call): a warning, no error."""
     global _call
     import importlib.machinery
     import importlib.util
+
+    from . import build
     try:
         loader = importlib.machinery.ExtensionFileLoader("_quik_call", CALL_PATH)
         call = importlib.util.module_from_spec(
             importlib.util.spec_from_file_location("_quik_call", CALL_PATH, loader=loader))
+        if call.BUILT_FOR != build.call_build_stamp():
+            raise ImportError(f"{CALL_PATH} was built for {call.BUILT_FOR}")
         call.bind(*(C.cast(fn, C.c_void_p).value
                     for fn in (lib.quik_linear, lib.quik_linear_w4a8, lib.quik_linear_fp6, lib.quik_linear_sp24,
                                lib.quik_quantize, lib.quik_gemm_dequant)))
         _call = call
-    except ImportError as e:
+    except (ImportError, AttributeError) as e:
         import warnings
         warnings.warn(f"layer calls go through ctypes ({e}): build the native marshalling with "
                       "`python -m paper_2310_09259_amd.build`", RuntimeWarning, stacklevel=3)

@@ -66,15 +66,25 @@ def _compile(src: str, extra_flags, verbose: bool):
     return src, obj, proc
 
 
+def call_build_stamp() -> str:
+    """What the marshalling is compiled for; it carries this text."""
+    import torch
+    return f"torch {torch.__version__}, Python {sys.version_info.major}.{sys.version_info.minor}"
+
+
 def build_call(verbose: bool = False, incremental: bool = False, src: str = CALL_SRC, lib: str = CALL_LIB) -> str:
     """The Python binding's native marshalling (host code only, against the installed torch)."""
     import sysconfig
 
     import torch
+    stamp = call_build_stamp()
     if incremental and os.path.exists(lib) and os.path.getmtime(lib) > os.path.getmtime(src):
-        return lib
+        with open(lib, "rb") as f:
+            if stamp.encode() + b"\0" in f.read():
+                return lib
     t = os.path.dirname(torch.__file__)
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           f'-DQUIK_BUILT_FOR="{stamp}"',
            "-isystem", os.path.join(t, "include"), "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
            "-isystem", sysconfig.get_paths()["include"], "-isystem", "/opt/rocm/include", src, "-o", lib,
            "-L" + os.path.join(t, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]

@@ -196,4 +196,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_quik_call", nullptr, -1, methods,
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__quik_call() { return PyModule_Create(&module); }
+// BUILT_FOR: the torch and Python this was compiled for (the binding uses it with these only)
+PyMODINIT_FUNC PyInit__quik_call() {
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "BUILT_FOR", QUIK_BUILT_FOR) < 0) Py_CLEAR(m);
+    return m;
+}

@@ -183,3 +183,20 @@ def test_the_library_is_built_where_the_marshalling_cannot_be(monkeypatch, tmp_p
     monkeypatch.setattr(build, "build_call", lambda *a, _real=build.build_call: _real(*a, lib=str(stale)))
     assert build.build() == build.LIB and ran == [build.HIPCC, "g++"]
     assert "go through ctypes" in capsys.readouterr().err and not stale.exists()
+
+
+def test_a_marshalling_for_another_torch_is_neither_used_nor_kept(monkeypatch):
+    from paper_2310_09259_amd import build
+    api.load()
+    assert api._call.BUILT_FOR == build.call_build_stamp()
+    ran = []
+    monkeypatch.setattr(build.subprocess, "run", lambda cmd, **kw: ran.append(cmd))
+    build.build_call(incremental=True)
+    assert ran == []                                                         # up to date
+    monkeypatch.setattr(build, "call_build_stamp", lambda: "torch 0.0.0, Python 3.0")
+    monkeypatch.setattr(api, "_call", None)
+    with pytest.warns(RuntimeWarning, match="was built for torch"):
+        api._load_call(api._lib)
+    assert api._call is api._ThroughCtypes
+    build.build_call(incremental=True)
+    assert len(ran) == 1 and ran[0][0] == "g++"
