@@ -394,18 +394,22 @@ __global__ __launch_bounds__(WM * WN * 64, OCC * WM * WN / 4) void gemm_sp24_ker
 }
 
 // Few tokens: the layer is bound by streaming the weights, so the point is many bytes in flight per CU and many
-// workgroups.  A workgroup owns a 32 (tokens) x 32 (channels) output tile and its four waves split K: every wave streams
-// its own quarter of the panels (1 KB of weights and 1 KB of activations each, one DMA instruction per KB) through a
-// private ring, with no workgroup barrier in the main loop (a wave waits only for its own DMA), into
+// workgroups.  A workgroup owns a 32 TM (tokens) x 32 (channels) output tile and its four waves split K: every wave
+// streams its own quarter of the panels (1 KB of weights and TM KB of activations each, one DMA instruction per KB)
+// through a private ring, with no workgroup barrier in the main loop (a wave waits only for its own DMA), into
 // v_smfmac_i32_32x32x64_i8.  The four partial INT32 accumulators are summed exactly through LDS; wave 0 then dequantizes,
 // adds the fp16 outlier product (every wave takes every fourth 16-column step, operands straight from global memory,
-// requested before the weight stream starts) and stores.  Tiles of 64 tokens, which read the weights once for 33 to 64
-// tokens, won nowhere against this tile and the general kernel's 64 x 64 one.
-template <int NST, int MODE>
+// requested before the weight stream starts) and stores.
+// TM = 2 reads the weights once for 33 to 64 tokens.  It is ahead of 32 x 32 and of the general kernel's 64 x 64 tiles
+// where its launch gives every CU more than one workgroup but not three, and K is deep.  GEMM, us, cached / from HBM,
+// 32 x 32 : 64 x 64 : this: T=50 K=5600 N=15968 20.1/20.2 : 17.6/17.8 : 14.7/16.8;  T=44 K=8320 N=10104 19.0/19.2 :
+// 23.5/23.7 : 16.6/17.0;  T=39 K=5856 N=10616 16.4/16.5 : 18.3/18.4 : 15.0/15.8;  with fewer workgroups 32 x 32 is ahead
+// (T=34 K=8640 N=7616 15.2 : 23.5 : 15.3), with more 64 x 64 (T=60 K=4544 N=29936 28.3 : 17.4 : 25.6).
+template <int TM, int NST, int MODE>
 __global__ __launch_bounds__(256) void gemm_sp24_split(GemmArgs a) {
     constexpr bool RAW = MODE != 0;
-    constexpr int BM = 32, A_BYTES = BM * 32, ST_BYTES = A_BYTES + 1024, RING = NST * ST_BYTES, LPS = 2;
-    constexpr int RED_BYTES = 2 * 16 * 64 * 4;             // one wave's INT32 accumulators + fp32 outlier partials
+    constexpr int BM = 32 * TM, A_BYTES = BM * 32, ST_BYTES = A_BYTES + 1024, RING = NST * ST_BYTES, LPS = TM + 1;
+    constexpr int RED_BYTES = 2 * TM * 16 * 64 * 4;        // one wave's INT32 accumulators + fp32 outlier partials
     constexpr int LDS_BYTES = (4 * RING > 3 * RED_BYTES) ? 4 * RING : 3 * RED_BYTES;
     static_assert((NST - 1) * LPS < 64, "vmcnt range");
     __shared__ __align__(1024) uint8_t lds[LDS_BYTES];
@@ -435,23 +439,35 @@ __global__ __launch_bounds__(256) void gemm_sp24_split(GemmArgs a) {
                  __builtin_amdgcn_readfirstlane(ra[2]), __builtin_amdgcn_readfirstlane(ra[3])};
         rb = v4i{__builtin_amdgcn_readfirstlane(rb[0]), __builtin_amdgcn_readfirstlane(rb[1]),
                  __builtin_amdgcn_readfirstlane(rb[2]), __builtin_amdgcn_readfirstlane(rb[3])};
-        dma16(ra, (uint32_t)__builtin_amdgcn_readfirstlane((int)(ring_addr + sb)), live ? vo : kOob, 0);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+            dma16(ra, (uint32_t)__builtin_amdgcn_readfirstlane((int)(ring_addr + sb + i * 1024)), live ? vo + i * 1024 : kOob, 0);
         dma16(rb, (uint32_t)__builtin_amdgcn_readfirstlane((int)(ring_addr + sb + A_BYTES)), live ? vo : kOob, 0);
     };
     const uint32_t rd = (uint32_t)(l32 * 32 + ((g ^ swz_f(l32)) << 4));   // this lane's piece of its row
 
     // ---- everything the epilogue needs is requested before the weight stream starts
-    constexpr int PF = 4;                                  // prefetched outlier steps per wave
-    float t_s = 0.0f, t_z = 0.0f;
-    uint4 pfa[PF], pfb[PF];
+    constexpr int PF = TM == 1 ? 4 : 2;                    // prefetched outlier steps per wave
+    float t_s[TM], t_z[TM];
+    uint4 pfa[PF][TM], pfb[PF];
     const int fsteps = (a.n_out + 15) >> 4;                // 16-column steps of the outlier product
     const __half* __restrict__ xo = static_cast<const __half*>(a.x_out);
     const __half* __restrict__ wo = static_cast<const __half*>(a.w_out);
-    const int t2 = min(t0 + l32, a.T - 1), n2 = min(n0 + l32, a.N - 1);
+    const int n2 = min(n0 + l32, a.N - 1);
+    // this lane's 8 outlier columns from kk on, of its channel and of its token in block i
+    auto wgt8 = [&](int kk, bool live) __attribute__((always_inline)) {
+        return live ? *reinterpret_cast<const uint4*>(wo + (size_t)n2 * a.ldwo + kk) : make_uint4(0, 0, 0, 0);
+    };
+    auto act8 = [&](int i, int kk, bool live) __attribute__((always_inline)) {
+        const int t2 = min(t0 + i * 32 + l32, a.T - 1);
+        return live ? *reinterpret_cast<const uint4*>(xo + (size_t)t2 * a.ldo + kk) : make_uint4(0, 0, 0, 0);
+    };
     if constexpr (!RAW) {
-        if (t0 + l32 < a.T) {
-            t_s = a.scale[t0 + l32];
-            t_z = a.zero[t0 + l32];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int t = t0 + i * 32 + l32;
+            t_s[i] = t < a.T ? a.scale[t] : 0.0f;
+            t_z[i] = t < a.T ? a.zero[t] : 0.0f;
         }
         if (tid < 32) {
             const int n = min(n0 + tid, a.N - 1);
@@ -465,14 +481,17 @@ __global__ __launch_bounds__(256) void gemm_sp24_split(GemmArgs a) {
         for (int q = 0; q < PF; ++q) {
             const int kk = (wave + 4 * q) * 16 + g * 8;    // first of this lane's 8 outlier columns
             const bool live = (wave + 4 * q) < fsteps && kk < a.n_out;
-            pfa[q] = live ? *reinterpret_cast<const uint4*>(xo + (size_t)t2 * a.ldo + kk) : make_uint4(0, 0, 0, 0);
-            pfb[q] = live ? *reinterpret_cast<const uint4*>(wo + (size_t)n2 * a.ldwo + kk) : make_uint4(0, 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < TM; ++i) pfa[q][i] = act8(i, kk, live);
+            pfb[q] = wgt8(kk, live);
         }
     }
 
-    v16i acc;
+    v16i acc[TM];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0;
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][r] = 0;
 
 #pragma unroll
     for (int s = 0; s < NST - 1; ++s) issue(s_begin + s);
@@ -483,28 +502,37 @@ __global__ __launch_bounds__(256) void gemm_sp24_split(GemmArgs a) {
         constexpr uint32_t M = 0xF0F0F0F0u;
         const uint4 ww = *reinterpret_cast<const uint4*>(st + A_BYTES + rd);
         const v4i uw = v4i{(int)((ww.x << 4) & M), (int)(ww.x & M), (int)((ww.y << 4) & M), (int)(ww.y & M)};
-        const uint4 wa = *reinterpret_cast<const uint4*>(st + rd);
-        const v8i ua = v8i{(int)(wa.x & M), (int)((wa.x << 4) & M), (int)(wa.y & M), (int)((wa.y << 4) & M),
-                           (int)(wa.z & M), (int)((wa.z << 4) & M), (int)(wa.w & M), (int)((wa.w << 4) & M)};
-        acc = __builtin_amdgcn_smfmac_i32_32x32x64_i8(uw, ua, acc, (int)ww.z, 0, 0);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const uint4 wa = *reinterpret_cast<const uint4*>(st + i * 1024 + rd);
+            const v8i ua = v8i{(int)(wa.x & M), (int)((wa.x << 4) & M), (int)(wa.y & M), (int)((wa.y << 4) & M),
+                               (int)(wa.z & M), (int)((wa.z << 4) & M), (int)(wa.w & M), (int)((wa.w << 4) & M)};
+            acc[i] = __builtin_amdgcn_smfmac_i32_32x32x64_i8(uw, ua, acc[i], (int)ww.z, 0, 0);
+        }
         // the buffer read here is refilled NST - 1 iterations later by this same wave: the LDS reads above
         // have returned (their data fed the matrix instructions) before that DMA is issued
     }
     wait_vm<0>();
 
     // ---- this wave's share of the fp16 outlier product (weights first: same accumulator layout)
-    v16f cf;
+    v16f cf[TM];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) cf[r] = 0.0f;
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) cf[i][r] = 0.0f;
     if constexpr (!RAW) {
+        auto fp_step = [&](uint4 fb, uint4 fa, int i) __attribute__((always_inline)) {
+            cf[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, fb), __builtin_bit_cast(v8h, fa), cf[i], 0, 0, 0);
+        };
 #pragma unroll
         for (int q = 0; q < PF; ++q)
-            cf = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, pfb[q]), __builtin_bit_cast(v8h, pfa[q]), cf, 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < TM; ++i) fp_step(pfb[q], pfa[q][i], i);
         for (int stp = wave + 4 * PF; stp < fsteps; stp += 4) {     // the outlier columns beyond the prefetched ones
             const int kk = stp * 16 + g * 8;
-            const uint4 fb = (kk < a.n_out) ? *reinterpret_cast<const uint4*>(wo + (size_t)n2 * a.ldwo + kk) : make_uint4(0, 0, 0, 0);
-            const uint4 fa = (kk < a.n_out) ? *reinterpret_cast<const uint4*>(xo + (size_t)t2 * a.ldo + kk) : make_uint4(0, 0, 0, 0);
-            cf = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, fb), __builtin_bit_cast(v8h, fa), cf, 0, 0, 0);
+            const uint4 fb = wgt8(kk, kk < a.n_out);
+#pragma unroll
+            for (int i = 0; i < TM; ++i) fp_step(fb, act8(i, kk, kk < a.n_out), i);
         }
     }
     __syncthreads();                                       // rings are dead: reuse LDS for the reduction
@@ -512,43 +540,52 @@ __global__ __launch_bounds__(256) void gemm_sp24_split(GemmArgs a) {
     // ---- sum the four partial results: waves 1..3 publish, wave 0 adds (INT32 exactly; the fp32 outlier
     // partials in wave order)
     int* red = reinterpret_cast<int*>(lds);
-    float* redf = reinterpret_cast<float*>(lds) + 3 * 16 * 64;
+    float* redf = reinterpret_cast<float*>(lds) + 3 * TM * 16 * 64;
     if (wave > 0) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int slot = ((wave - 1) * 16 + r) * 64 + lane;
-            red[slot] = acc[r];
-            if constexpr (!RAW) redf[slot] = cf[r];
-        }
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int slot = (((wave - 1) * TM + i) * 16 + r) * 64 + lane;
+                red[slot] = acc[i][r];
+                if constexpr (!RAW) redf[slot] = cf[i][r];
+            }
     }
     __syncthreads();
     if (wave > 0) return;
-    // (all 96 loads at once: 0.5 us faster than one partial result after the other, at 60 registers)
-#pragma unroll
+    // one block: all 96 loads at once, 0.5 us faster than one partial result after the other, at 60 registers; two blocks:
+    // one after the other, all at once would halve the occupancy
+    constexpr int AT_ONCE = TM == 1 ? 3 : 1;
+#pragma unroll AT_ONCE
     for (int w = 0; w < 3; ++w)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int slot = (w * 16 + r) * 64 + lane;
-            acc[r] += red[slot];
-            if constexpr (!RAW) cf[r] += redf[slot];
-        }
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int slot = ((w * TM + i) * 16 + r) * 64 + lane;
+                acc[i][r] += red[slot];
+                if constexpr (!RAW) cf[i][r] += redf[slot];
+            }
 
-    // lane: token t0 + l32; register r: channel n0 + 8 (r / 4) + 4 g + r % 4
-    const int t = t0 + l32;
-    if constexpr (RAW) {
+    // lane: token t0 + 32 i + l32; register r: channel n0 + 8 (r / 4) + 4 g + r % 4
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int n = n0 + 8 * (r >> 2) + 4 * g + (r & 3);
-            if (t < a.T && n < a.N) a.acc[(size_t)t * a.ldacc + n] = acc[r] >> 8;   // exact: a multiple of 256
-        }
-    } else {
-        __half* __restrict__ y = static_cast<__half*>(a.y);
-        const float t_h = t_z + 8.0f * t_s;                // zeroAct + halfRange * scaleAct
+    for (int i = 0; i < TM; ++i) {
+        const int t = t0 + i * 32 + l32;
+        if constexpr (RAW) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int c = 8 * (r >> 2) + 4 * g + (r & 3), n = n0 + c;
-            const float v = __builtin_fmaf((float)acc[r], t_s * prm_sw[c], __builtin_fmaf(t_h, prm_wr[c], prm_bv[c])) + cf[r];
-            if (t < a.T && n < a.N) y[(size_t)t * a.ldy + n] = __float2half(v);
+            for (int r = 0; r < 16; ++r) {
+                const int n = n0 + 8 * (r >> 2) + 4 * g + (r & 3);
+                if (t < a.T && n < a.N) a.acc[(size_t)t * a.ldacc + n] = acc[i][r] >> 8;   // exact: a multiple of 256
+            }
+        } else {
+            __half* __restrict__ y = static_cast<__half*>(a.y);
+            const float t_h = t_z[i] + 8.0f * t_s[i];      // zeroAct + halfRange * scaleAct
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int c = 8 * (r >> 2) + 4 * g + (r & 3), n = n0 + c;
+                const float v = __builtin_fmaf((float)acc[i][r], t_s[i] * prm_sw[c], __builtin_fmaf(t_h, prm_wr[c], prm_bv[c])) + cf[i][r];
+                if (t < a.T && n < a.N) y[(size_t)t * a.ldy + n] = __float2half(v);
+            }
         }
     }
 }
@@ -616,7 +653,8 @@ hipError_t launch_cfg(const GemmArgs& a, hipStream_t stream) {
 // counting as half a step.  Fitted to 380 shapes with every tile measured (T 1 .. 4096, K 512 .. 11008, N 512 .. 28672,
 // cached weights and from HBM), those with output rows of whole 16-byte pieces counted threefold; the choice costs 0.8 %
 // against the fastest tile in the mean.  The first entry is the K-split kernel: it wins up to 64 tokens nearly always, and
-// never beyond 256, for which it was not measured.  The 64 x 64 tile is left out beyond two rounds of it: the fit holds
+// never beyond 256, for which it was not measured; the last one is its 64-token form (added from 171 shapes
+// of 33 to 64 tokens), for the tokens that it reads the weights once for.  The 64 x 64 tile is left out beyond two rounds of it: the fit holds
 // for cached operands, from HBM it fetches them too often there (T = 920, N = 21928, K = 576: 52 us, 128 x 256 27).
 struct TileCost24 { int bm, bn, waves, occ; double base, round, tile, round_step, tile_step; };
 constexpr TileCost24 kCost24[] = {{32, 32, 4, 4, 4.239, -0.913, 1.171, 0.025, 0.053},
@@ -626,7 +664,8 @@ constexpr TileCost24 kCost24[] = {{32, 32, 4, 4, 4.239, -0.913, 1.171, 0.025, 0.
                                   {256, 192, 8, 1, 2.281, 8.325, 0, 0.656, 0},
                                   {128, 256, 4, 2, 4.495, 4.695, 1.207, 0.201, 0.332},
                                   {128, 192, 4, 2, 4.341, 4.301, 0.993, 0.288, 0.205},
-                                  {128, 128, 4, 2, 2.660, 3.112, 0.655, 0.245, 0.162}};
+                                  {128, 128, 4, 2, 2.660, 3.112, 0.655, 0.245, 0.162},
+                                  {64, 32, 4, 2, 7.596, -0.837, 1.086, 0.083, 0.026}};
 constexpr int kSplitTokens = 256;
 
 int choose_tile_sp24(int T, int N, int K_b, int n_out, int cus) {
@@ -637,7 +676,7 @@ int choose_tile_sp24(int T, int N, int K_b, int n_out, int cus) {
         const TileCost24& c = kCost24[i];
         const long tiles = (long)((T + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
         const long rounds = (tiles + (long)c.occ * cus - 1) / ((long)c.occ * cus), busiest = (tiles + cus - 1) / cus;
-        if ((i == 0 && T > kSplitTokens) || (i == 1 && rounds > 2)) continue;
+        if ((i == 0 && T > kSplitTokens) || (i == 1 && rounds > 2) || (i == 8 && (T <= 32 || T > 64))) continue;
         const double t = c.base + c.round * rounds + c.tile * busiest + steps * (c.round_step * rounds + c.tile_step * busiest);
         if (best < 0 || t < least) { best = i; least = t; }
     }
@@ -651,7 +690,7 @@ hipError_t dispatch24(const GemmArgs& a, hipStream_t stream) {
     switch (choose_tile_sp24(a.T, a.N, a.K_b, MODE ? 0 : a.n_out, cus)) {
     case 0:
         // (ring depth: 4 and 6 measured alike, 8 to 16 up to 15 % slower)
-        hipLaunchKernelGGL((gemm_sp24_split<4, MODE>), dim3(((a.T + 31) / 32) * ((a.N + 31) / 32)), dim3(256), 0, stream, a);
+        hipLaunchKernelGGL((gemm_sp24_split<1, 4, MODE>), dim3(((a.T + 31) / 32) * ((a.N + 31) / 32)), dim3(256), 0, stream, a);
         return hipGetLastError();
     case 1: return launch_cfg<4, 1, 1, 4, 8, 4, 8, MODE>(a, stream);
     case 2: return launch_cfg<4, 2, 2, 4, 6, 2, 8, MODE>(a, stream);
@@ -659,7 +698,10 @@ hipError_t dispatch24(const GemmArgs& a, hipStream_t stream) {
     case 4: return launch_cfg<4, 6, 4, 2, 6, 1, 8, MODE>(a, stream);
     case 5: return launch_cfg<4, 8, 2, 2, 6, 2, 8, MODE>(a, stream);
     case 6: return launch_cfg<4, 6, 2, 2, 6, 2, 8, MODE>(a, stream);
-    default: return launch_cfg<4, 4, 2, 2, 8, 2, 8, MODE>(a, stream);
+    case 7: return launch_cfg<4, 4, 2, 2, 8, 2, 8, MODE>(a, stream);
+    default:
+        hipLaunchKernelGGL((gemm_sp24_split<2, 4, MODE>), dim3(((a.T + 63) / 64) * ((a.N + 31) / 32)), dim3(256), 0, stream, a);
+        return hipGetLastError();
     }
 }
 

@@ -20,6 +20,8 @@ SHAPES = {
     (257, 13292, 736, 80): (128, 192, 8), (336, 11712, 976, 0): (128, 192, 8),
     (899, 13338, 200, 40): (128, 256, 4), (900, 12292, 432, 40): (128, 256, 4),
     (515, 13810, 304, 40): (256, 192, 8), (529, 13246, 440, 40): (256, 192, 8), (527, 13784, 472, 0): (256, 192, 8),
+    (33, 8234, 8456, 264): (64, 32, 4), (64, 8248, 8200, 72): (64, 32, 4), (45, 15362, 5192, 16): (64, 32, 4),
+    (44, 15402, 7256, 0): (64, 32, 4),
     (45, 100, 4168, 8): (32, 32, 4), (190, 4098, 2056, 264): (64, 64, 4),
 }
 
