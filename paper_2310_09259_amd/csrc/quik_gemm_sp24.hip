@@ -401,7 +401,7 @@ __global__ __launch_bounds__(WM * WN * 64, OCC * WM * WN / 4) void gemm_sp24_ker
 // adds the fp16 outlier product (every wave takes every fourth 16-column step, operands straight from global memory,
 // requested before the weight stream starts) and stores.
 // TM = 2 reads the weights once for 33 to 64 tokens.  It is ahead of 32 x 32 and of the general kernel's 64 x 64 tiles
-// where its launch gives every CU more than one workgroup but not three, and K is deep.  GEMM, us, cached / from HBM,
+// where its launch gives the busiest CU two workgroups, or three, and K is deep.  GEMM, us, cached / from HBM,
 // 32 x 32 : 64 x 64 : this: T=50 K=5600 N=15968 20.1/20.2 : 17.6/17.8 : 14.7/16.8;  T=44 K=8320 N=10104 19.0/19.2 :
 // 23.5/23.7 : 16.6/17.0;  T=39 K=5856 N=10616 16.4/16.5 : 18.3/18.4 : 15.0/15.8;  with fewer workgroups 32 x 32 is ahead
 // (T=34 K=8640 N=7616 15.2 : 23.5 : 15.3), with more 64 x 64 (T=60 K=4544 N=29936 28.3 : 17.4 : 25.6).
@@ -650,22 +650,27 @@ hipError_t launch_cfg(const GemmArgs& a, hipStream_t stream) {
 
 // The tile whose launch is estimated to be the shortest, up to `occ` workgroups of it per CU: base + round * rounds +
 // tile * tiles of the busiest CU + steps * (round_step * rounds + tile_step * tiles of the busiest CU), an outlier stage
-// counting as half a step.  Fitted to 380 shapes with every tile measured (T 1 .. 4096, K 512 .. 11008, N 512 .. 28672,
-// cached weights and from HBM), those with output rows of whole 16-byte pieces counted threefold; the choice costs 0.8 %
-// against the fastest tile in the mean.  The first entry is the K-split kernel: it wins up to 64 tokens nearly always, and
-// never beyond 256, for which it was not measured; the last one is its 64-token form (added from 171 shapes
-// of 33 to 64 tokens), for the tokens that it reads the weights once for.  The 64 x 64 tile is left out beyond two rounds of it: the fit holds
-// for cached operands, from HBM it fetches them too often there (T = 920, N = 21928, K = 576: 52 us, 128 x 256 27).
+// counting as half a step.  Fitted to 976 shapes with all or most tiles measured (T 1 .. 4096, K 512 .. 11008, N 512 ..
+// 28672, cached weights and from HBM, mean of both), those with output rows of whole 16-byte pieces counted threefold; the
+// choice costs 0.3 % against the fastest tile in the mean.  A fit to fewer shapes of few tokens gave them 64 x 64 tiles
+// where the K-split kernel is ahead (us, cached / from HBM: T=8 K=1376 N=8720 7.4/7.7, now 6.2/6.6; T=48 K=3296 N=8448
+// 11.9/12.3, now 9.0/10.7), and took 256 x 192 tiles for T=2048 K=4096 N=11008 (68.1/70.7, now 128 x 256 with 64.9/68.8) and
+// 128 x 128 ones for T=2048 K=11008 N=4096 (65.6/65.1, now 60.7/63.3).
+// The first entry is the K-split kernel: it wins up to 64 tokens nearly always; beyond 256 its line does not hold.  The
+// last one is its 64-token form, for the tokens that it reads the weights once for and two or three workgroups on the
+// busiest CU: with one 32 x 32 is ahead, with more 64 x 64 (T=60 K=13312 N=26626 40.9/44.6 with 64 x 64, 46.8/64.2 with it).
+// The 64 x 64 tile is left out beyond two rounds of it: the fit holds for cached operands, from HBM it fetches them too
+// often there (T = 920, N = 21928, K = 576: 52 us, 128 x 256 27).
 struct TileCost24 { int bm, bn, waves, occ; double base, round, tile, round_step, tile_step; };
-constexpr TileCost24 kCost24[] = {{32, 32, 4, 4, 4.239, -0.913, 1.171, 0.025, 0.053},
-                                  {64, 64, 4, 4, 2.973, -0.458, 1.050, 0.228, 0.062},
-                                  {128, 128, 8, 2, 2.731, 1.544, 1.179, 0.089, 0.275},
-                                  {128, 192, 8, 1, 0.540, 7.261, 0, 0.469, 0},
-                                  {256, 192, 8, 1, 2.281, 8.325, 0, 0.656, 0},
-                                  {128, 256, 4, 2, 4.495, 4.695, 1.207, 0.201, 0.332},
-                                  {128, 192, 4, 2, 4.341, 4.301, 0.993, 0.288, 0.205},
-                                  {128, 128, 4, 2, 2.660, 3.112, 0.655, 0.245, 0.162},
-                                  {64, 32, 4, 2, 7.596, -0.837, 1.086, 0.083, 0.026}};
+constexpr TileCost24 kCost24[] = {{32, 32, 4, 3, 2.727, 1.520, 0.415, 0.024, 0.061},
+                                  {64, 64, 4, 4, 3.614, -0.131, 0.752, 0.235, 0.060},
+                                  {128, 128, 8, 2, 2.775, 1.632, 1.210, 0.091, 0.282},
+                                  {128, 192, 8, 1, 0.530, 7.213, 0, 0.468, 0},
+                                  {256, 192, 8, 1, 2.246, 8.223, 0, 0.671, 0},
+                                  {128, 256, 4, 2, 4.382, 4.385, 1.162, 0.196, 0.324},
+                                  {128, 192, 4, 2, 4.342, 4.285, 0.973, 0.288, 0.228},
+                                  {128, 128, 4, 2, 2.660, 3.109, 0.655, 0.235, 0.161},
+                                  {64, 32, 4, 3, 0.1, 0, 4.3, -0.011, 0.072}};
 constexpr int kSplitTokens = 256;
 
 int choose_tile_sp24(int T, int N, int K_b, int n_out, int cus) {
@@ -676,7 +681,8 @@ int choose_tile_sp24(int T, int N, int K_b, int n_out, int cus) {
         const TileCost24& c = kCost24[i];
         const long tiles = (long)((T + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
         const long rounds = (tiles + (long)c.occ * cus - 1) / ((long)c.occ * cus), busiest = (tiles + cus - 1) / cus;
-        if ((i == 0 && T > kSplitTokens) || (i == 1 && rounds > 2) || (i == 8 && (T <= 32 || T > 64))) continue;
+        if ((i == 0 && T > kSplitTokens) || (i == 1 && rounds > 2)) continue;
+        if (i == 8 && (T <= 32 || T > 64 || busiest < 2 || busiest > 3)) continue;
         const double t = c.base + c.round * rounds + c.tile * busiest + steps * (c.round_step * rounds + c.tile_step * busiest);
         if (best < 0 || t < least) { best = i; least = t; }
     }

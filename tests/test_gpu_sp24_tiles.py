@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 # without whole 16-byte output pieces
 SHAPES = {
     (7, 474, 360, 72): (32, 32, 4), (7, 68, 720, 40): (32, 32, 4), (3, 176, 1112, 0): (32, 32, 4),
-    (4, 76, 184, 56): (64, 64, 4), (273, 68, 496, 80): (64, 64, 4), (46, 112, 456, 0): (64, 64, 4),
+    (4, 76, 184, 56): (64, 64, 4), (273, 68, 496, 80): (64, 64, 4), (46, 112, 456, 0): (32, 32, 4),
+    (150, 4100, 328, 0): (64, 64, 4),
     (260, 13778, 592, 72): (128, 128, 4), (269, 13640, 864, 0): (128, 128, 4),
     (157, 11164, 96, 40): (128, 128, 8), (132, 10924, 488, 96): (128, 128, 8), (152, 11416, 328, 0): (128, 128, 8),
     (878, 13956, 144, 56): (128, 192, 4), (789, 12388, 448, 48): (128, 192, 4), (811, 12336, 584, 0): (128, 192, 4),
