@@ -243,6 +243,8 @@ int quik_debug_gemm_form(int T, int N, int K_b, int bits, int w_bits, int cus, i
  * QUIK_EINVAL / QUIK_ENULL on invalid input.
  */
 int quik_debug_fp6_form(int T, int N, int K_b, int cus, int *form);
+/* the ring slots of that tile (> 0), or QUIK_EINVAL */
+int quik_debug_fp6_slots(int T, int N, int K_b, int cus);
 
 /* Test hook (host only): the same for quik_gemm_dequant_sp24 / quik_int_gemm_sp24 (n_out = 0); form[2]: waves per
  * workgroup. */

@@ -50,6 +50,8 @@ def load() -> C.CDLL:
         lib.quik_debug_gemm_form.argtypes = [i, i, i, i, i, i, vp]
         lib.quik_debug_fp6_form.restype = i
         lib.quik_debug_fp6_form.argtypes = [i, i, i, i, vp]
+        lib.quik_debug_fp6_slots.restype = i
+        lib.quik_debug_fp6_slots.argtypes = [i, i, i, i]
         lib.quik_debug_sp24_form.restype = i
         lib.quik_debug_sp24_form.argtypes = [i, i, i, i, i, vp]
         lib.quik_debug_gemm_tile.restype = i
@@ -284,6 +286,14 @@ def quik_debug_fp6_form(T: int, N: int, K_b: int, cus: int):
     form = (C.c_int * 2)()
     _check(load().quik_debug_fp6_form(T, N, K_b, cus, C.cast(form, C.c_void_p)), "quik_debug_fp6_form")
     return tuple(form)
+
+
+def quik_debug_fp6_slots(T: int, N: int, K_b: int, cus: int) -> int:
+    """Host-only: the ring slots of that tile."""
+    slots = load().quik_debug_fp6_slots(T, N, K_b, cus)
+    if slots < 0:
+        _check(slots, "quik_debug_fp6_slots")
+    return slots
 
 
 def quik_debug_sp24_form(T: int, N: int, K_b: int, n_out: int, cus: int):

@@ -145,8 +145,16 @@ int quik_debug_gemm_form(int T, int N, int K_b, int bits, int w_bits, int cus, i
 int quik_debug_fp6_form(int T, int N, int K_b, int cus, int* form) {
     if (T <= 0 || N <= 0 || K_b <= 0 || K_b >= kMaxKb || cus <= 0) return QUIK_EINVAL;
     if (!form) return QUIK_ENULL;
-    quik::fp6_form(T, N, K_b, cus, &form[0], &form[1]);
+    int slots;
+    quik::fp6_form(T, N, K_b, cus, &form[0], &form[1], &slots);
     return QUIK_OK;
+}
+
+int quik_debug_fp6_slots(int T, int N, int K_b, int cus) {
+    if (T <= 0 || N <= 0 || K_b <= 0 || K_b >= kMaxKb || cus <= 0) return QUIK_EINVAL;
+    int rows, cols, slots;
+    quik::fp6_form(T, N, K_b, cus, &rows, &cols, &slots);
+    return slots;
 }
 
 int quik_debug_sp24_form(int T, int N, int K_b, int n_out, int cus, int* form) {

@@ -427,18 +427,25 @@ hipError_t launch_cfg(const GemmArgs& a, hipStream_t stream) {
 
 // The tile whose launch is estimated to be the shortest, up to `occ` workgroups of it per CU: base + round * rounds +
 // tile * tiles of the busiest CU + stages (of 128 columns) * (round_stage * rounds + tile_stage * tiles of the busiest CU).
-// Fitted to 175 shapes with every tile measured (T 1 .. 4096, K 512 .. 11008, N 512 .. 28672, cached weights and from
-// HBM); good to 5 - 10 %, and the choice costs 0.5 % against the fastest tile in the mean.  The 256 x 256 tile needs a
-// third fewer operand bytes per operation than 256 x 128 and wins wherever it fills the chip: K = 5120, N = 15360,
+// Fitted to 765 shapes with every tile measured (T 1 .. 4096, K 512 .. 11008, N 512 .. 28672, cached weights and from
+// HBM, mean of both); good to 5 - 10 %, and the choice costs 0.2 % against the fastest tile in the mean.  The 256 x 256 tile
+// needs a third fewer operand bytes per operation than 256 x 128 and wins wherever it fills the chip: K = 5120, N = 15360,
 // T = 1024 in one round 49 us (256 x 192 in two 73, 128 x 128 64; the former kernel's 256 x 128 73).
+// The last line is the 64 x 128 tile with eight ring slots instead of six, for up to 64 tokens: weights from HBM want more
+// bytes in flight (us, cached / from HBM, six : eight: T=21 K=7200 N=19600 21.4/29.0 : 22.1/24.5, T=25 K=10272 N=23456
+// 29.6/40.6 : 30.7/34.4; the former kernel 27.5/28.1 and 38.6/40.0), smaller layers and cached ones do not.  With more
+// tokens it was ahead nowhere.  65 to 128 tokens of such layers run 128 x 128 tiles, whose rings have no room for
+// more: from HBM up to 8 % behind the former kernel, cached as much ahead (T=76 K=5152 N=20360 22.7/23.7 there, 21.0/25.8).
 struct TileCost6 { int bm, bn, occ; double base, round, tile, round_stage, tile_stage; };
 constexpr TileCost6 kCost6[] = {{64, 64, 4, 1.495, 1.495, 1.396, 0.160, 0.092},
-                                {64, 128, 2, 2.020, 1.115, 2.378, 0.137, 0.153},
-                                {128, 128, 2, 1.548, 1.632, 4.020, 0.099, 0.250},
+                                {64, 128, 2, 2.120, 1.115, 2.468, 0.137, 0.153},
+                                {128, 128, 2, 1.548, 1.636, 4.019, 0.099, 0.250},
                                 {128, 192, 1, -2.250, 9.384, 0, 0.409, 0},
                                 {128, 256, 1, -4.435, 12.559, 0, 0.481, 0},
-                                {256, 192, 1, -6.067, 18.828, 0, 0.558, 0},
-                                {256, 256, 1, -6.037, 20.272, 0, 0.670, 0}};
+                                {256, 192, 1, -6.078, 17.534, 0, 0.558, 0},
+                                {256, 256, 1, -6.037, 20.272, 0, 0.670, 0},
+                                {64, 128, 2, 0.848, 0.849, 4.383, -0.014, 0.291}};
+constexpr int kDeepRing = 7;             // the line of the eight-slot 64 x 128 tile
 
 int choose_tile_fp6(int T, int N, int K_b, int cus) {
     const int stages = (K_b + 127) / 128;
@@ -446,6 +453,7 @@ int choose_tile_fp6(int T, int N, int K_b, int cus) {
     double least = 0.0;
     for (int i = 0; i < (int)(sizeof(kCost6) / sizeof(TileCost6)); ++i) {
         const TileCost6& c = kCost6[i];
+        if (i == kDeepRing && T > 64) continue;
         const long tiles = (long)((T + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
         const double rounds = (double)((tiles + (long)c.occ * cus - 1) / ((long)c.occ * cus)), busiest = (double)((tiles + cus - 1) / cus);
         const double t = c.base + c.round * rounds + c.tile * busiest + stages * (c.round_stage * rounds + c.tile_stage * busiest);
@@ -454,7 +462,7 @@ int choose_tile_fp6(int T, int N, int K_b, int cus) {
     return best;
 }
 
-// Six ring slots everywhere: a seventh under 256 x 192 cost 3 %, 256 x 256 has room for no more.
+// Six ring slots but for that line: a seventh under 256 x 192 cost 3 %, 128 x 128 and 256 x 256 have room for no more.
 template <int MODE>
 hipError_t dispatch6(const GemmArgs& a, hipStream_t stream) {
     int cus = compute_units();
@@ -466,16 +474,19 @@ hipError_t dispatch6(const GemmArgs& a, hipStream_t stream) {
     case 3: return launch_cfg<4, 3, 2, 4, 6, 1, 8, MODE>(a, stream);
     case 4: return launch_cfg<4, 4, 2, 4, 6, 1, 8, MODE>(a, stream);
     case 5: return launch_cfg<4, 6, 4, 2, 6, 1, 4, MODE>(a, stream);
-    default: return launch_cfg<8, 4, 2, 4, 6, 1, 8, MODE>(a, stream);
+    case 6: return launch_cfg<8, 4, 2, 4, 6, 1, 8, MODE>(a, stream);
+    default: return launch_cfg<4, 2, 1, 4, 8, 2, 8, MODE>(a, stream);
     }
 }
 
 }  // namespace
 
-void fp6_form(int T, int N, int K_b, int cus, int* rows, int* cols) {
-    const TileCost6& c = kCost6[choose_tile_fp6(T, N, K_b, cus)];
+void fp6_form(int T, int N, int K_b, int cus, int* rows, int* cols, int* slots) {
+    const int i = choose_tile_fp6(T, N, K_b, cus);
+    const TileCost6& c = kCost6[i];
     *rows = c.bm;
     *cols = c.bn;
+    *slots = i == kDeepRing ? 8 : 6;
 }
 
 hipError_t launch_gemm_fp6(const GemmArgs& a, hipStream_t stream) {

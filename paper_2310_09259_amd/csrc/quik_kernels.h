@@ -205,7 +205,7 @@ void set_gemm_path(int mode);                                           // test 
 hipError_t launch_gemm_stream(const GemmArgs& a, const StreamPlan& p, hipStream_t stream);
 // FP6 path (quik_gemm_fp6.hip): xq / w_q of GemmArgs are panel buffers [stage][row][48 bytes]; ldq / ldw unused
 hipError_t launch_gemm_fp6(const GemmArgs& a, hipStream_t stream);
-void fp6_form(int T, int N, int K_b, int cus, int* rows, int* cols);     // its tile (host only)
+void fp6_form(int T, int N, int K_b, int cus, int* rows, int* cols, int* slots);     // its tile and ring (host only)
 hipError_t launch_weight_pack_fp6(const void* w_q, int ldw, int N, int K_b, void* w6, hipStream_t stream);
 // 2:4-sparse path (quik_gemm_sp24.hip): xq = activations [stage][T][32 bytes], w_q = weights
 // [stage][N][32 bytes] (quik_sp24_device.h); ldq / ldw unused

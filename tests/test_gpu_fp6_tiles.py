@@ -22,7 +22,12 @@ SHAPES = {
 }
 
 
-@pytest.mark.parametrize("T,N,K,n_out", SHAPES)
+# the 64 x 128 tile with eight ring slots (asserted there too): odd and even numbers of panels, none, one and more outlier
+# stages than its ring holds
+DEEP_RING = [(20, 20098, 4200, 264), (64, 22018, 4104, 8), (33, 19204, 3720, 0)]
+
+
+@pytest.mark.parametrize("T,N,K,n_out", [*SHAPES, *DEEP_RING])
 def test_fp6_tile(oracle, T, N, K, n_out):
     from paper_2310_09259_amd import api
     shp = synth.LayerShape("fp6_tile", T, K, N, n_out, 4, seed=600 + T + N + K)
