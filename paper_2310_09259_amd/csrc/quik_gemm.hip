@@ -615,7 +615,7 @@ int basic_tile_4bit(int T, int N, int K_b, int cus) {
 // (pair_fixed > 0): up to one per CU they take the same line; when some CUs hold two, pair_fixed + (pair_per_stage +
 // pair_more * share of CUs that do) * stages, the launch lasting as long as such a CU but slowed by how many there
 // are; every further two per CU that again, and a remainder `rest` of what it would take by itself, as the CUs have
-// drifted apart by then.
+// drifted apart by then.  (pair_more of a tile of eight waves: see kCost4; 0 here.)
 // Measured lines behind it (us; integer stages; both from HBM unless said otherwise, N = 4096 .. 28672):
 //   integer stages              4      6     14     30     84
 //   W8A8  64 x 32             5.5    5.8    7.0   10.2   18.5 - 22.8
@@ -667,7 +667,7 @@ constexpr TileCost kCost8w4[] = {{kTile64x32, 64, 32, 6.12, 0.118, 0, 0, 0, 0},
 
 double launch_cost(const TileCost& t, long tiles, int cus, int stages) {
     const double alone = t.fixed + t.per_stage * stages;
-    if (t.pair_fixed == 0) return (double)((tiles + cus - 1) / cus) * alone;
+    if (t.pair_fixed == 0) return (double)((tiles + cus - 1) / cus) * alone + t.pair_more * stages * (double)tiles / cus;
     auto up_to_two = [&](long n) {
         return n <= cus ? alone : t.pair_fixed + (t.pair_per_stage + t.pair_more * (double)(n - cus) / cus) * stages;
     };
@@ -676,23 +676,25 @@ double launch_cost(const TileCost& t, long tiles, int cus, int stages) {
     return (double)full * up_to_two(2L * cus) + (left ? t.rest * up_to_two(left) : 0.0);
 }
 
-// 4-bit operands beyond the smallest tiles: the same estimate, a stage being 256 k, fitted to 139 shapes with every tile
-// measured (T 65 .. 4096, K 2048 .. 11008, N 1024 .. 28672, cached weights and from HBM).  It predicts a tile's time to
-// 7 - 9 %, so the tile of basic_tile_4bit is left only for one that is estimated 7 % shorter; over those shapes that
-// makes the launch 5.5 % shorter in the mean, none more than 3 % longer except two (6 %, 5 %).  GEMM, us, before : now,
-// cached and from HBM alike:
+// 4-bit operands beyond the smallest tiles: the same estimate, a stage being 256 k, fitted to 469 shapes with every tile
+// measured (T 33 .. 4096, K 1808 .. 11008, N 512 .. 28672, cached weights and from HBM, mean of both).  A round of one
+// workgroup per CU takes pair_more * stages longer when it is full than when it is empty: with rounds of one length 256 x
+// 128 tiles were preferred to 128 x 128 for one nearly full round (T=905 K=8320 N=7384, 232 : 464 tiles, 58.0 : 54.8 us;
+// T=1204 K=7712 N=6136 57.4 : 53.9).  It predicts a tile's time to 6 - 9 %, so the tile of basic_tile_4bit is left only
+// for one that is estimated 7 % shorter; over those shapes that makes the launch 8 % shorter in the mean, on two of them
+// 4 - 5 % longer.  GEMM, us, before : now, cached and from HBM alike:
 //   T=333 K=4096 N=11008, 258 tiles of 128 x 128 on 256 CUs, now 460 of 96 x 96, two per CU          28.8 : 23.4
 //   T=92 K=7552 N=18626 (128 x 64) 35.8 : 28.4;  T=143 K=9984 N=20644 56.0 : 43.2;  T=1360 K=7040 N=1628 29.8 : 25.0
 //   T=512 K=4096 N=11008, 344 tiles, now 232 of 128 x 192                                              29.4 : 26.7
 //   T=2325 K=5344 N=2444 39.2 : 33.4;  T=1365 K=8368 N=5514, 174 tiles of 256 x 192, now 484 of 128 x 128  73.9 : 59.5
 constexpr TileCost kCost4[] = {{kTile128x64Pair32, 128, 64, 0.975, 0.777, 6.956, 0.769, 0.195, 0.891},
-                               {kTile128x128Pair32, 128, 128, 8.275, 0.768, 10.375, 1.193, 0.324, 0.829},
+                               {kTile128x128Pair32, 128, 128, 8.110, 0.753, 10.168, 1.169, 0.318, 0.829},
                                {kTile96x96Pair, 96, 96, 7.771, 0.604, 8.613, 0.979, -0.039, 0.823},
                                {kTile96x128Pair, 96, 128, 8.225, 0.725, 9.431, 1.103, 0.128, 0.765},
-                               {kTile128x192, 128, 192, 9.532, 1.065, 0, 0, 0, 0},
-                               {kTile256x128, 256, 128, 11.229, 1.282, 0, 0, 0, 0},
-                               {kTile256x192, 256, 192, 13.517, 1.635, 0, 0, 0, 0},
-                               {kTile192x256, 192, 256, 13.336, 1.637, 0, 0, 0, 0}};
+                               {kTile128x192, 128, 192, 8.920, 0.926, 0, 0, 0.244, 0},
+                               {kTile256x128, 256, 128, 9.991, 1.101, 0, 0, 0.328, 0},
+                               {kTile256x192, 256, 192, 12.301, 1.329, 0, 0, 0.702, 0},
+                               {kTile192x256, 192, 256, 12.180, 1.343, 0, 0, 0.657, 0}};
 constexpr int kModelK4 = 1792;        // below, the fixed parts decide and the measurements behind basic_tile_4bit hold
 constexpr double kModelGain4 = 0.93;
 
