@@ -6,7 +6,7 @@ from tests import test_gpu_fp6_tiles
 
 
 def test_shapes_of_the_gpu_test_run_the_tiles_they_name():
-    for (T, N, K, n_out), want in test_gpu_fp6_tiles.SHAPES.items():
+    for (T, N, K, n_out), want in {**test_gpu_fp6_tiles.SHAPES, **test_gpu_fp6_tiles.OUTLIER_RING}.items():
         assert api.quik_debug_fp6_form(T, N, K - n_out, 256) == want, (T, N, K, n_out)
 
 

@@ -27,7 +27,15 @@ SHAPES = {
 DEEP_RING = [(20, 20098, 4200, 264), (64, 22018, 4104, 8), (33, 19204, 3720, 0)]
 
 
-@pytest.mark.parametrize("T,N,K,n_out", [*SHAPES, *DEEP_RING])
+# every other tile with nine outlier stages, the last one not full, more than its ring holds at a time
+OUTLIER_RING = {
+    (40, 2142, 328, 264): (64, 64), (130, 5454, 336, 264): (64, 128), (130, 11072, 408, 264): (128, 128),
+    (130, 10986, 328, 264): (128, 192), (400, 12582, 328, 264): (128, 256), (515, 13154, 328, 264): (256, 192),
+    (800, 12686, 328, 264): (256, 256),
+}
+
+
+@pytest.mark.parametrize("T,N,K,n_out", [*SHAPES, *OUTLIER_RING, *DEEP_RING])
 def test_fp6_tile(oracle, T, N, K, n_out):
     from paper_2310_09259_amd import api
     shp = synth.LayerShape("fp6_tile", T, K, N, n_out, 4, seed=600 + T + N + K)

@@ -143,10 +143,10 @@ LINEAR_SHAPES = [_sparse(s) for s in [
     synth.LayerShape("n_out_24", 40, 528, 136, 24, 4, seed=34),
     synth.LayerShape("odd_n", 70, 1024, 131, 64, 4, seed=36),
     synth.LayerShape("one_token", 1, 4096, 512, 256, 4, seed=35),
-    # eight-wave 256 x 192 tiles (>= 128 of them), ragged T and N, K_b not a multiple of 64
+    # hundreds of tiles, ragged T and N, K_b not a multiple of 64
     synth.LayerShape("big_tiles_ragged", 520, 512, 11000, 32, 4, seed=38),
     synth.LayerShape("big_tiles_k", 700, 1320, 5001, 40, 4, seed=51),
-    # 256 x 128 tiles (the 1.5x-area tile would not save a round here), ragged T and N
+    # several hundred tiles of two K steps, ragged T and N
     synth.LayerShape("tiles_256x128", 1030, 256, 15300, 24, 4, seed=53),
 ]]
 
@@ -157,11 +157,11 @@ LINEAR_SHAPES += [_sparse(s) for s in [
     synth.LayerShape("one_by_one", 1, 16, 1, 8, 4, seed=61),
     synth.LayerShape("two_groups", 3, 24, 5, 16, 4, seed=62),
     synth.LayerShape("stage_plus_two_groups", 33, 80, 65, 8, 4, seed=63),
-    # ring shorter than / equal to / one longer than the number of stages (eight buffers)
+    # seven, eight and nine stages of 64 columns: K in parts that do not come out even, and an odd number of panels
     synth.LayerShape("seven_stages", 130, 448 + 16, 200, 16, 4, seed=64),
     synth.LayerShape("eight_stages", 130, 512 + 16, 200, 16, 4, seed=65),
     synth.LayerShape("nine_stages", 300, 576 + 16, 400, 16, 4, seed=66),
-    # 65 .. 128 tokens: 128 x 64 tiles (two matrix instructions per wave and stage), ragged T and N
+    # 65 .. 128 tokens and few channels, ragged T and N
     synth.LayerShape("tiles_128x64", 97, 1096, 150, 72, 4, seed=68),
     synth.LayerShape("tiles_128x64_full", 128, 2048 + 128, 192, 128, 4, seed=69),
     # odd number of integer stages followed by an odd number of outlier stages
@@ -179,12 +179,13 @@ def test_linear_sp24_with_bias(api, oracle):
 
 
 @pytest.mark.parametrize("shp", [_sparse(synth.LayerShape("acc_small", 100, 1024, 160, 64, 4, seed=42)),
-                                 # the K-split kernel for up to 32 tokens: ragged T and N, stage counts that do not
+                                 # the K-split kernel: ragged T and N, stage counts that do not
                                  # divide by four, fewer stages than waves, more than 256 outlier columns
                                  _sparse(synth.LayerShape("acc_skinny", 19, 1160, 75, 72, 4, seed=55)),
                                  _sparse(synth.LayerShape("acc_skinny_32", 32, 4096 + 320, 200, 320, 4, seed=56)),
                                  _sparse(synth.LayerShape("acc_skinny_short", 5, 136, 40, 8, 4, seed=57)),
-                                 # its 64-token form: ragged second token fragment, N not a multiple of 32
+                                 # two token tiles of it, the second one ragged, N not a multiple of 32 (its 64-token form:
+                                 # tests/test_gpu_sp24_tiles.py)
                                  _sparse(synth.LayerShape("acc_skinny_64", 57, 2304 + 64, 101, 64, 4, seed=58)),
                                  _sparse(synth.LayerShape("acc_skinny_64_full", 64, 640 + 8, 64, 8, 4, seed=59)),
                                  _sparse(synth.LayerShape("acc_skinny_64_outliers", 40, 1024 + 264, 70, 264, 4, seed=60)),

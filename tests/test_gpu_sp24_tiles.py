@@ -27,7 +27,18 @@ SHAPES = {
 }
 
 
-@pytest.mark.parametrize("T,N,K,n_out", SHAPES)
+# every tile of the general kernel with nine outlier stages, the last one not full: more than its ring holds at a time, so
+# that freed slots are refilled with stages that exist
+OUTLIER_RING = {
+    (33, 4170, 328, 264): (64, 64, 4), (130, 11128, 328, 264): (128, 128, 8), (400, 12308, 528, 264): (128, 128, 4),
+    (260, 13062, 1168, 264): (128, 192, 8), (800, 13976, 336, 264): (128, 192, 4), (900, 12298, 328, 264): (128, 256, 4),
+    (600, 13096, 528, 264): (256, 192, 8),
+}
+# the accumulator hook knows no outlier columns and takes another tile for these
+OTHER_RAW_TILE = {(257, 13292, 736, 80), (515, 13810, 304, 40)}
+
+
+@pytest.mark.parametrize("T,N,K,n_out", [*SHAPES, *OUTLIER_RING])
 def test_sp24_tile(oracle, T, N, K, n_out):
     from paper_2310_09259_amd import api
     shp = synth.LayerShape("sp24_tile", T, K, N, n_out, 4, seed=700 + T + N + K, sparse24=True)
@@ -77,3 +88,24 @@ def test_sp24_tiles_repeat_bit_identically():
             torch.cuda.synchronize()
             first = y if first is None else first
             assert torch.equal(first.view(torch.int16), y.view(torch.int16))
+
+
+@pytest.mark.parametrize("T,N,K,n_out", [(9, 1030, 1112, 40), (150, 4100, 328, 72), (157, 11164, 96, 40), (900, 12292, 432, 40)])
+def test_sp24_parameters_start_at_any_element(T, N, K, n_out):
+    """w_scale and bias at an odd half, scale, zero and w_reduced at an odd float: the same bytes."""
+    import torch
+    from paper_2310_09259_amd import api
+    shp = synth.LayerShape("sp24_odd", T, K, N, n_out, 4, seed=17, sparse24=True)
+    d = upload(synth.make_inputs(shp))
+    w_red = api.quik_weight_reduce(d["w_q"], d["w_scale"], shp.K_b, 4)
+    w24 = api.quik_weight_pack_sp24(d["w_q"], shp.K_b)
+    xq, scale, zero, x_out = api.quik_quantize_sp24(d["x"], d["idx"])
+    bias = torch.randn(N, device="cuda").half()
+
+    def odd(t):
+        out = torch.full((t.numel() + 3,), 9.0, dtype=t.dtype, device="cuda")[1:1 + t.numel()]
+        return out.copy_(t)
+    want = api.quik_gemm_dequant_sp24(xq, scale, zero, x_out, shp.K_b, w24, d["w_scale"], w_red, d["w_out"], bias=bias)
+    got = api.quik_gemm_dequant_sp24(xq, odd(scale), odd(zero), x_out, shp.K_b, w24, odd(d["w_scale"]), odd(w_red), d["w_out"],
+                                     bias=odd(bias))
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))

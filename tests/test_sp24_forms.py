@@ -6,8 +6,10 @@ from tests import test_gpu_sp24_tiles
 
 
 def test_shapes_of_the_gpu_test_run_the_tiles_they_name():
-    for (T, N, K, n_out), want in test_gpu_sp24_tiles.SHAPES.items():
+    for (T, N, K, n_out), want in {**test_gpu_sp24_tiles.SHAPES, **test_gpu_sp24_tiles.OUTLIER_RING}.items():
         assert api.quik_debug_sp24_form(T, N, K - n_out, n_out, 256) == want, (T, N, K, n_out)
+        raw = api.quik_debug_sp24_form(T, N, K - n_out, 0, 256)                  # the accumulator hook's tile
+        assert (raw == want) == ((T, N, K, n_out) not in test_gpu_sp24_tiles.OTHER_RAW_TILE), (T, N, K, n_out, raw)
     assert len(set(test_gpu_sp24_tiles.SHAPES.values())) == 9
 
 
