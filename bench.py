@@ -32,7 +32,7 @@ PEAK_HBM_GBS = 8000.0
 TRAFFIC_BYTES = {"llama7b_up": int((46193 * 2.0 + 44032) * 1024)}
 TRAFFIC_BYTES_TILES = {"llama7b_up": int((47796 * 2.0 + 44033) * 1024)}
 # profiles/gemm_sp24_kernel_llama7b_up.md: the sparse GEMM, same factors
-TRAFFIC_BYTES_SP24 = {"llama7b_up": int((55044 * 2.0 + 44032) * 1024)}
+TRAFFIC_BYTES_SP24 = {"llama7b_up": int((47823 * 2.0 + 44032) * 1024)}
 
 
 PREHEAT_MS = 150.0           # continuous load before any timing (the clocks need ~40-100 ms to settle)

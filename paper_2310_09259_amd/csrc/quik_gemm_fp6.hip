@@ -20,9 +20,10 @@
 //    of a step sits there, frees the step's own slots and leaves all slots but four flying.  With the barrier at the
 //    step's start (two slots landed but not yet read) 70B took 668 us instead of 580.
 // The 16 x 16 x 128 instruction sustains 7.1 POP/s on operands like these, the 32 x 32 x 64 one 6.4 (the chip lowers its
-// clock).  GEMM, us, 32 x 32 x 64 kernel with a step of one panel : this one, same box: 7B up-projection, 2048 tokens
-// 81.5 : 70;  70B, 4096 tokens 656 : 525;  13B QKV, 1024 tokens 75 : 49;  7B down-projection 66.6 : 59;  T = 333,
-// N = 11008, K = 4096 27.9 : 21;  T = 16, K = N = 4096 16.8 : 11.9.
+// clock).  GEMM, us, 32 x 32 x 64 kernel with a step of one panel : this one, one box, weights cached: 7B up-projection,
+// 2048 tokens 83.2 : 75.4;  70B, 4096 tokens 671 : 542;  13B QKV, 1024 tokens 77.8 : 53.3;  7B down-projection 68.9 : 66.6;
+// T = 333, N = 11008, K = 4096 29.1 : 22.8;  T = 16, K = N = 4096 21.7 : 12.3.  Over 100 drawn shapes it takes 0.65 of
+// that kernel's time with cached weights, 0.68 from HBM.
 //
 // The fp16 outlier columns run as stages of 32 columns (64-byte rows) through slots of their own over the same
 // memory, copied while the tile is dequantized, with the dequantized integer part as the C operand of

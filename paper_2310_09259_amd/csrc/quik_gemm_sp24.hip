@@ -28,9 +28,10 @@
 //    as the C operand of v_mfma_f32_16x16x32_f16 (weights first, so the accumulator layout is the same).  With
 //    parameters loaded to registers and an outlier ring that starts when the loop has ended 128 x 128 tiles
 //    took 64 us instead of 60 for the shape above with 256 outliers.
-// GEMM, us, a 32 x 32 x 64 kernel with steps of one panel : this one, same box: 13B QKV, 1024 tokens 72 : 49; 4096
-// tokens 214 : 186; 7B up-projection, 2048 tokens 72.5 : 63; 7B down-projection 61.5 : 59; T = 333, N = 11008, K = 4096
-// 27.6 : 23.9.  Over 135 drawn shapes of 40 to 4096 tokens, N a multiple of 64, it takes 0.78 of that kernel's time.
+// GEMM, us, a 32 x 32 x 64 kernel with steps of one panel : this one with the tiles that the estimate below takes, one box,
+// weights cached: 13B QKV, 1024 tokens 78.6 : 56.5; 4096 tokens 237 : 206; 7B up-projection, 2048 tokens 83.7 : 70.2; 7B
+// down-projection 64.8 : 63.9; 70B, 4096 tokens 635 : 543; T = 333, N = 11008, K = 4096 28.7 : 24.6.  Over 150 drawn shapes
+// of 1 to 4096 tokens it takes 0.74 of that kernel's time.
 // Rows beyond T / N are out of range for the panel descriptors and arrive as zeros.
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
