@@ -185,18 +185,25 @@ def test_the_library_is_built_where_the_marshalling_cannot_be(monkeypatch, tmp_p
     assert "go through ctypes" in capsys.readouterr().err and not stale.exists()
 
 
-def test_a_marshalling_for_another_torch_is_neither_used_nor_kept(monkeypatch):
+def test_a_marshalling_for_another_torch_is_neither_used_nor_kept(monkeypatch, tmp_path):
+    import os
+    import shutil
+
     from paper_2310_09259_amd import build
     api.load()
+    src, lib = str(tmp_path / "quik_call.cpp"), str(tmp_path / "_quik_call.so")
+    shutil.copy(build.CALL_SRC, src)
+    shutil.copy(build.CALL_LIB, lib)
+    os.utime(src, (1e9, 1e9))                                                # older than the built one
     assert api._call.BUILT_FOR == build.call_build_stamp()
     ran = []
     monkeypatch.setattr(build.subprocess, "run", lambda cmd, **kw: ran.append(cmd))
-    build.build_call(incremental=True)
+    build.build_call(incremental=True, src=src, lib=lib)
     assert ran == []                                                         # up to date
     monkeypatch.setattr(build, "call_build_stamp", lambda: "torch 0.0.0, Python 3.0")
     monkeypatch.setattr(api, "_call", None)
     with pytest.warns(RuntimeWarning, match="was built for torch"):
         api._load_call(api._lib)
     assert api._call is api._ThroughCtypes
-    build.build_call(incremental=True)
+    build.build_call(incremental=True, src=src, lib=lib)
     assert len(ran) == 1 and ran[0][0] == "g++"
